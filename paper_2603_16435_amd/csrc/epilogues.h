@@ -1,7 +1,7 @@
 // epilogues.h - what each contraction does with its accumulators while they are in registers.
 //
 // Orientation.  The logits contraction is run "vocab-major": A = W (rows = vocab entries),
-// B = X (rows = tokens), so that in the MFMA accumulator layouts (see Layout32 / Layout16) a lane
+// B = X (rows = tokens), so that in the MFMA accumulator layout (see Layout16) a lane
 // owns ONE token column per block and several vocab rows of it.  The softmax reductions over the
 // vocabulary are then mostly in-register; the only cross-lane steps are between the lane groups
 // that hold other rows of the same column (one or two shuffles), and the only cross-wavefront
@@ -293,8 +293,8 @@ struct EpiDS {
 
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims& d, const Pre&) const {
-    if constexpr (L::kBlk == 16 && sizeof(T) == 2) {
-      static_assert(MB == 8 && NB == 8, "the relabelling is written for 128x128 wavefront sub-tiles");
+    if constexpr (AGPR) {                                  // hot kernel
+      static_assert(MB == 8 && NB == 8 && sizeof(T) == 2, "the relabelling is written for 128x128 wavefront sub-tiles");
       const int g = c.lane >> 4, cc = c.lane & 15;
       int y[NB]; float lse[NB], lse_l2e[NB], ct[NB];
 #pragma unroll
@@ -381,9 +381,26 @@ struct EpiDX {
   const int* row_map;   // compact row -> original row
   T* dX; int64_t ldx; int H;
   const float* row_scale;   // optional [chunk row]: factor applied to the whole row
+  float* split_part;        // K slices: [slice][ceil(M / BM) * BM][H] partial tiles, added up by splitk_reduce_kernel
 
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims& d, const Pre&) const {
+    if (c.slices > 1) {
+      float* p = split_part + (int64_t)c.slice * ((c.Mv + BM - 1) / BM * BM) * H;
+#pragma unroll
+      for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+        for (int i = 0; i < L::kRegs; ++i) {
+          const int m = c.m0 + L::row(bi, i, c.lane);
+          if (m >= c.Mv) continue;
+#pragma unroll
+          for (int bj = 0; bj < NB; ++bj) {
+            const int n = c.n0 + L::col(bj, c.lane);
+            if (n < H) p[(int64_t)m * H + n] = acc_read<AGPR>(acc[bi][bj], i);
+          }
+        }
+      return;
+    }
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
@@ -400,6 +417,29 @@ struct EpiDX {
       }
   }
 };
+
+// The slices of a split dX contraction added up in order, scaled and scattered to the original rows (four columns per
+// thread, H % 4 == 0).  Works the number of slices out like the contraction itself; returns at once if there was one.
+template <class T>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDims d, EpiDX<T> e, int bm, int bn, int bk) {
+  int M, N, K;
+  if (!resolve_dims(d, M, N, K)) return;
+  const int tiles_m = (M + bm - 1) / bm;
+  const SplitK sk = split_k(tiles_m * ((d.N + bn - 1) / bn), (K + bk - 1) / bk, d.split_slots);
+  if (sk.slices == 1) return;
+  const int64_t stride = (int64_t)tiles_m * bm * e.H;
+  const int h4 = e.H / 4;
+  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < (int64_t)M * h4; q += (int64_t)gridDim.x * 256) {
+    const int m = (int)(q / h4), n = (int)(q - (int64_t)m * h4) * 4;
+    const float* p = e.split_part + (int64_t)m * e.H + n;
+    floatx4 s = *reinterpret_cast<const floatx4*>(p);
+    for (int k = 1; k < sk.slices; ++k) s += *reinterpret_cast<const floatx4*>(p + k * stride);
+    const float f = e.row_scale ? e.row_scale[m] : 1.f;
+    T* o = e.dX + (int64_t)e.row_map[d.chunk_start + m] * e.ldx + n;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = (T)(f * s[i]);
+  }
+}
 
 // ---- backward, stage 3: dW tile, f32, overwritten by the first chunk and accumulated after.
 //      When accumulating, the old values of a whole block row are fetched first (32 loads in flight)

@@ -21,8 +21,8 @@
 //    sched_barrier, so the interleaving in the source is the interleaving issued.  A light
 //    software prefetch (one 4-byte load per 128-byte line, two slabs ahead, shared between the
 //    workgroups of an XCD; off for dX) pulls the next panels into that XCD's L2.
-//  * gemm_nt_kernel       - generic fallback (f32 inputs, or K not a multiple of 128): eight
-//    wavefronts of 128x64, 32x32 MFMA blocks, register-staged loads with a K-tail predicate.
+//  * gemm_nt_kernel       - general kernel (f32 inputs, K not a multiple of 128, unaligned operands): tile size as
+//    a parameter, 16x16 MFMA blocks, register-staged loads with a K-tail predicate.
 //
 // LDS rows are 128 B = eight 16-byte chunks; chunk c of row r sits at slot c ^ ((r>>1)&7),
 // which spreads both the 16-byte row-wise stores and the column-wise fragment loads over all
@@ -37,7 +37,6 @@ typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -58,9 +57,11 @@ struct GemmDims {
   const int* chunk;       // if set, device pair {first compacted row, rows} of this chunk; replaces n_real / chunk_start,
                           // and the gather tables are then indexed from the chunk's first row
   int a_tiled, b_tiled;   // hot kernel only: operand stored slab-tiled (see tiled_index) instead of row-major; K is then its full K extent
-  int dyn;                // which extent is min(rows left in the chunk, bound): 0 none, 1 M, 2 N, 3 K (rounded up to 256)
+  int dyn;                // which extent is min(rows left in the chunk, bound): 0 none, 1 M, 2 N, 3 K (rounded up to k_round)
+  int k_round;            // dyn == 3: rows beyond the chunk's last that the producers of both operands have zeroed, a power of two
   int zero_if_empty;      // dyn == 3 only: an empty chunk still runs the epilogue (with K = 0) instead of returning
   int group_m;            // tile-order parameter: M-tiles per band
+  int split_slots;        // > 0: the contraction may be cut along K (see split_k); workgroups the chip runs at a time
 };
 
 // Slab-tiled operand layout of the library's own bf16 work buffers: [row / 256][k / 64][256 rows][64 k].
@@ -91,8 +92,44 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
     if (d.dyn == 3 && d.zero_if_empty) K = 0; else return false;
   } else if (d.dyn == 1) M = left < M ? left : M;
   else if (d.dyn == 2) N = left < N ? left : N;
-  else { const int k = (left + 255) & ~255; K = k < K ? k : K; }
+  else { const int k = (left + d.k_round - 1) & ~(d.k_round - 1); K = k < K ? k : K; }
   return true;
+}
+
+// Cutting a contraction along K.  dX = dS W has K = V and only (tokens / tile) x (H / tile) tiles: a few hundred tokens
+// leave most of the chip idle behind a serial chain of thousands of slabs.  It is then cut into S slices of `per` slabs,
+// each slice's tile goes to a partial buffer in f32 and splitk_reduce_kernel adds the slices in order.  S minimises the
+// time in slabs: rounds of `slots` workgroups times (slabs per slice + what a workgroup spends outside its main loop);
+// a partial tile costs more there (it is written and read again in f32), and no more than 2 slots workgroups are made,
+// which bounds the partial buffer.  The number of tokens is only known on the
+// device, so every workgroup works S out for itself: lane s of a wavefront prices s + 1 slices.
+constexpr int kMaxSplit = 64, kSplitMinSlabs = 4;
+struct SplitK { int slices, per; };
+__device__ __host__ inline int64_t split_cost(int tiles, int nk, int want, int slots, SplitK& k) {
+  if ((int64_t)tiles * want > 2 * slots) want = 1;
+  int per = (nk + want - 1) / want;
+  if (per < kSplitMinSlabs) per = nk < kSplitMinSlabs ? (nk > 0 ? nk : 1) : kSplitMinSlabs;
+  k.per = per;
+  k.slices = nk > 0 ? (nk + per - 1) / per : 1;
+  const int64_t rounds = ((int64_t)tiles * k.slices + slots - 1) / slots;
+  return rounds * (per + (k.slices > 1 ? 6 : 2));
+}
+inline SplitK split_k_host(int tiles, int nk, int slots) {             // the same on the host
+  SplitK best{1, nk}, k;
+  int64_t c0 = split_cost(tiles, nk, 1, slots, best);
+  for (int s = 2; s <= kMaxSplit; ++s) {
+    const int64_t c = split_cost(tiles, nk, s, slots, k);
+    if (c < c0) { c0 = c; best = k; }
+  }
+  return best;
+}
+__device__ inline SplitK split_k(int tiles, int nk, int slots) {            // every lane of the wavefront must call it
+  SplitK k;
+  const int64_t c = split_cost(tiles, nk, (int)(threadIdx.x & 63) + 1, slots, k);
+  int64_t m = (c << 8) | (threadIdx.x & 63);
+  for (int o = 32; o > 0; o >>= 1) { const int64_t x = __shfl_xor(m, o); m = x < m ? x : m; }
+  split_cost(tiles, nk, __builtin_amdgcn_readfirstlane((int)(m & 63)) + 1, slots, k);
+  return k;
 }
 
 // Workgroup -> tile.  Workgroups are dealt to the 8 XCDs round-robin (workgroup id % 8), and each XCD has
@@ -139,23 +176,27 @@ __device__ __host__ inline bool tile_of_block(int pid, int tiles_m, int tiles_n,
   return true;
 }
 
+// Equal runs of `total` work items, one run per XCD: item of workgroup pid, or false.  (Any launch of at least `total`
+// workgroups rounded up to a multiple of the XCD count covers them all.)
+__device__ __host__ inline bool run_of_block(int pid, int total, int& t) {
+  const int xcd = pid % kXcds, q = pid / kXcds, per = total / kXcds, rem = total % kXcds;
+  if (q >= per + (xcd < rem ? 1 : 0)) return false;
+  t = xcd * per + (xcd < rem ? xcd : rem) + q;
+  return true;
+}
+
 __device__ inline int lds_off(int row, int chunk) {           // byte offset inside one operand slab
   return row * kSlabBytes + ((chunk ^ ((row >> 1) & 7)) << 4);
 }
 
+// 16x16 block of one 16-byte k-chunk per lane: lane l holds row l%16 of the operand, chunk l/16 of four
 template <class T>
-__device__ inline void mma_step(const uint4& a, const uint4& b, floatx16& acc);
+__device__ inline void mma_step(const uint4& a, const uint4& b, floatx4& acc);
 
+__device__ inline float f32_at(const uint4& v, int e) { return __builtin_bit_cast(float, e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w); }
 template <>
-__device__ inline void mma_step<bf16_t>(const uint4& a, const uint4& b, floatx16& acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-template <>
-__device__ inline void mma_step<float>(const uint4& a, const uint4& b, floatx16& acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.x), __builtin_bit_cast(float, b.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.y), __builtin_bit_cast(float, b.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.z), __builtin_bit_cast(float, b.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a.w), __builtin_bit_cast(float, b.w), acc, 0, 0, 0);
+__device__ inline void mma_step<bf16_t>(const uint4& a, const uint4& b, floatx4& acc) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
 
 // Coordinates handed to an epilogue: everything it needs to map acc[bi][bj][i] to (m,n).
@@ -165,19 +206,12 @@ struct TileCtx {
   int lane, wm, wn;  // lane id, wavefront coordinates inside the workgroup
   int tile_m, tile_n;// workgroup tile indices
   int tid;
+  int slice, slices; // K slice of this workgroup and how many there are (1: the tile is complete)
 };
-template <int> struct Int {};
 struct NoPre {};      // epilogue with nothing to fetch ahead of the main loop
 
-// Accumulator layouts: where register i of block (bi, bj) of a lane sits inside the wavefront's
+// Accumulator layout: where register i of block (bi, bj) of a lane sits inside the wavefront's
 // sub-tile.  Registers come in runs of four consecutive rows of one column.
-struct Layout32 {   // 32x32 MFMA blocks, 16 registers per block: row = 8*(i/4) + 4*(l/32) + i%4, col = l%32
-  typedef floatx16 acc_t;
-  static constexpr int kBlk = 32, kRegs = 16;
-  __device__ static int row(int bi, int i, int lane) { return bi * 32 + ((i >> 2) << 3) + ((lane >> 5) << 2) + (i & 3); }
-  __device__ static int col(int bj, int lane) { return bj * 32 + (lane & 31); }
-  __device__ static bool owns(int r, int lane) { return ((r >> 2) & 1) == (lane >> 5); }   // does this lane hold row r of its columns?
-};
 struct Layout16 {   // 16x16 MFMA blocks, 4 registers per block: row = 4*(l/16) + i, col = l%16
   typedef floatx4 acc_t;
   static constexpr int kBlk = 16, kRegs = 4;
@@ -202,28 +236,40 @@ __device__ inline float acc_read(const V& v, int i) {
   }
 }
 
+// General kernel: BM x BN tile, WAVES_M x WAVES_N wavefronts.  A slab is 128 bytes of K, staged global -> registers ->
+// LDS (any alignment, K tail zeroed) into two LDS stages; one barrier per slab.
 template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64)
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, 2)
 void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, Epi epi) {
   constexpr int NT = WAVES_M * WAVES_N * 64;
   constexpr int BK = Elem<T>::kBK;
   constexpr int EPC = Elem<T>::kPerChunk;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  constexpr int MB = WM / 32, NB = WN / 32;
+  constexpr int MB = WM / 16, NB = WN / 16;
   constexpr int ROWS_PER_PASS = NT / 8;
-  constexpr int PA = BM / ROWS_PER_PASS, PB = BN / ROWS_PER_PASS;
-  static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "tile vs threads");
+  constexpr int PA = BM / ROWS_PER_PASS, PB = (BN + ROWS_PER_PASS - 1) / ROWS_PER_PASS;
+  static_assert(BM % ROWS_PER_PASS == 0 && (BN % ROWS_PER_PASS == 0 || BN < ROWS_PER_PASS), "tile vs threads");
   constexpr int A_BYTES = BM * kSlabBytes, B_BYTES = BN * kSlabBytes;
 
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * (A_BYTES + B_BYTES)];
 
   int M, N, K;
   if (!resolve_dims(d, M, N, K)) return;
+  int nk = (K + BK - 1) / BK, tm, tn, k_begin = 0, slice = 0, slices = 1;
   // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
   const bool by_share = d.dyn == 1;
   const int tiles_m = ((by_share ? M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
-  int tm, tn;
-  if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, d.group_m, by_share, tm, tn)) return;
+  if (d.split_slots > 0) {
+    const SplitK sk = split_k(tiles_m * tiles_n, nk, d.split_slots);
+    slices = sk.slices;
+    int t;
+    if (!run_of_block(blockIdx.x, tiles_m * tiles_n * slices, t)) return;      // slice after slice, M fastest inside one
+    slice = t / (tiles_m * tiles_n);
+    t -= slice * (tiles_m * tiles_n);
+    tn = t / tiles_m; tm = t - tn * tiles_m;
+    k_begin = slice * sk.per;
+    nk = nk - k_begin < sk.per ? nk - k_begin : sk.per;
+  } else if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, d.group_m, by_share, tm, tn)) return;
   if (tm * BM >= M || tn * BN >= N) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -248,51 +294,63 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
     bp[p] = B + (int64_t)r * d.ldb + lchunk * EPC;
   }
   uint4 ra[PA], rb[PB];
-  auto gload = [&](int k0) {
+  auto gload = [&](int k0) __attribute__((always_inline)) {
     const bool ok = (k0 + lchunk * EPC) < K;
 #pragma unroll
     for (int p = 0; p < PA; ++p) ra[p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int p = 0; p < PB; ++p) rb[p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
   };
-  auto lstore = [&](int buf) {
+  auto lstore = [&](int buf) __attribute__((always_inline)) {
     unsigned char* as = smem + buf * (A_BYTES + B_BYTES);
     unsigned char* bs = as + A_BYTES;
 #pragma unroll
     for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = ra[p];
 #pragma unroll
-    for (int p = 0; p < PB; ++p) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = rb[p];
+    for (int p = 0; p < PB; ++p)
+      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = rb[p];
   };
 
-  floatx16 acc[MB][NB];
+  floatx4 acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
-  const int nk = (K + BK - 1) / BK;
-  gload(0);
-  lstore(0);
+  if (nk > 0) {
+    gload(k_begin * BK);
+    lstore(0);
+  }
   __syncthreads();
-  const int frow = lane & 31, fhalf = lane >> 5;
+  const int frow = lane & 15, fq = lane >> 4;
   for (int kt = 0; kt < nk; ++kt) {
     const int cur = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * BK);
+    if (kt + 1 < nk) gload((k_begin + kt + 1) * BK);
     const unsigned char* as = smem + cur * (A_BYTES + B_BYTES);
     const unsigned char* bs = as + A_BYTES;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {                  // four 32-byte k-steps per slab
+    for (int s = 0; s < 2; ++s) {                  // two 64-byte k-steps per slab
       uint4 af[MB], bf[NB];
 #pragma unroll
-      for (int i = 0; i < MB; ++i) af[i] = *reinterpret_cast<const uint4*>(as + lds_off(wm * WM + i * 32 + frow, s * 2 + fhalf));
+      for (int i = 0; i < MB; ++i) af[i] = *reinterpret_cast<const uint4*>(as + lds_off(wm * WM + i * 16 + frow, s * 4 + fq));
 #pragma unroll
-      for (int j = 0; j < NB; ++j) bf[j] = *reinterpret_cast<const uint4*>(bs + lds_off(wn * WN + j * 32 + frow, s * 2 + fhalf));
+      for (int j = 0; j < NB; ++j) bf[j] = *reinterpret_cast<const uint4*>(bs + lds_off(wn * WN + j * 16 + frow, s * 4 + fq));
+      if constexpr (sizeof(T) == 4) {              // element e of the chunks: four k of the block's sixteen; blocks in turn, so
+#pragma unroll                                     // that consecutive MFMAs do not wait for each other's accumulators
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+          for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma_step<T>(af[i], bf[j], acc[i][j]);
+            for (int j = 0; j < NB; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f32_at(af[i], e), f32_at(bf[j], e), acc[i][j], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) mma_step<T>(af[i], bf[j], acc[i][j]);
+      }
     }
     if (kt + 1 < nk) lstore(cur ^ 1);
     __syncthreads();
@@ -301,8 +359,9 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   TileCtx c;
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
-  const typename Epi::Pre pre = epi.template preload<Layout32>(c, d);
-  epi.template run<Layout32, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
+  c.slice = slice; c.slices = slices;
+  const typename Epi::Pre pre = epi.template preload<Layout16>(c, d);
+  epi.template run<Layout16, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
 }
 
 // ------------------------------------------------------------------ bf16 hot kernel
@@ -493,6 +552,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   TileCtx c;
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
+  c.slice = 0; c.slices = 1;
   // what the epilogue needs from memory per column or row (a few registers): fetched now, used after the main loop
   const typename Epi::Pre pre = epi.template preload<Layout16>(c, d);
 

@@ -31,9 +31,10 @@ namespace rlk {
 
 constexpr int kDefaultChunkRows = 32768;        // recompute mode: 128 x 14 dX tiles = 7 full rounds of 256 CUs on the 7B shape
 constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step time is flat (+-0.7 %) from 24576 to 65536 rows
-constexpr int kBM = 256, kBN = 256, kWavesM = 2, kWavesN = 4;
-constexpr int kGemmThreads = kWavesM * kWavesN * 64;
-constexpr int kGemmSmem = 2 * (kBM + kBN) * kSlabBytes;   // 128 KiB of the 160 KiB per CU
+constexpr int kBM = 256, kBN = 256;
+// General kernel in f32: tiles of 256 x 64 (four wavefronts of 64 x 64, two workgroups per CU), or 256 x 16 where the large
+// ones would leave CUs without work.
+constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 // Per-contraction tuning of the hot kernel, from sweeps on the 7B-shaped workload:
 // tile-order band height (M-tiles per band), L2 prefetch distance in slabs (0 = off), where in a
 // phase of 32 MFMAs the slab loads are issued (after MFMA kVmo, kVmo + kVmg, ...) and how many of a slab's 16 loads
@@ -336,7 +337,7 @@ __global__ void target_logit_kernel(const bf16_t* X, const bf16_t* W, int H, con
 constexpr int kSumSlices = 16;
 __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* part, int ldp, int tiles_v, const float* zy_c, const float* ref_l2e,
                                const int32_t* row_map, const ChunkDesc* desc, const int32_t* ycol_c, Ctrl* ctrl, rl_stats* stats,
-                               float* lse_c, float* logp_c, float* zsum_c, float* lse_out, float* logp_out, float* ent_out,
+                               float* lse_c, double* logp_c, float* zsum_c, float* lse_out, float* logp_out, float* ent_out,
                                float* zy_out, int32_t* ycol_out) {
   __shared__ double ss[kSumSlices][64], su[kSumSlices][64];
   const int left = desc->rows, chunk_start = desc->row_start;
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* 
     const int g = chunk_start + n;
     const double lse_d = (double)ref_l2e[g] * 0.6931471805599453 + log(S);
     const float lse = (float)lse_d;
-    const float lp = zy_c[g] - lse;
+    const double lp = (double)zy_c[g] - lse_d;             // the loss takes it unrounded: its sums over a sequence cancel
     lse_c[g] = lse; logp_c[g] = lp; zsum_c[g] = (float)S;
     // Z_t = exp(lse_t - ref_t) is of order one when the old log-prob is anywhere near the current one.  A row whose
     // sum left [1e-30, 1e30] (or is not a number) had stored probabilities outside the staging precision's range:
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* 
     if (!(S >= 1e-30 && S <= 1e30)) { atomicAdd(&ctrl->overflow, 1); if (stats) atomicAdd(&stats->n_overflow_rows, 1); }
     const int r = row_map[g];
     if (lse_out) lse_out[r] = lse;
-    if (logp_out) logp_out[r] = lp;
+    if (logp_out) logp_out[r] = (float)lp;
     if (ent_out) ent_out[r] = (float)fmax(lse_d - U / S, 0.0);
     if (zy_out) zy_out[r] = zy_c[g];
     if (ycol_out) ycol_out[r] = ycol_c[g];
@@ -393,7 +394,7 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 // along the rows, then the four slices are merged through LDS in a fixed order.
 __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
                                    const int32_t* row_map, const Ctrl* ctrl, int chunk_start, int chunk_rows, const int32_t* ycol_c,
-                                   float* lse_c, float* logp_c, float* lse_out, float* logp_out, float* ent_out,
+                                   float* lse_c, double* logp_c, float* lse_out, float* logp_out, float* ent_out,
                                    float* zy_out, int32_t* ycol_out) {
   __shared__ float sm[4][64], ss[4][64], su[4][64];
   int left = ctrl->n_real - chunk_start;
@@ -429,11 +430,11 @@ __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, con
     const double lse_d = (double)M + log(S);
     const float lse = (float)lse_d;
     const int g = chunk_start + n;
-    const float lp = zy_c[g] - lse;
+    const double lp = (double)zy_c[g] - lse_d;             // the loss takes it unrounded: its sums over a sequence cancel
     lse_c[g] = lse; logp_c[g] = lp;
     const int r = row_map[g];
     if (lse_out) lse_out[r] = lse;
-    if (logp_out) logp_out[r] = lp;
+    if (logp_out) logp_out[r] = (float)lp;
     if (ent_out) ent_out[r] = (float)fmax(lse_d - U / S, 0.0);     // H = lse - sum_v p_v z_v
     if (zy_out) zy_out[r] = zy_c[g];
     if (ycol_out) ycol_out[r] = ycol_c[g];
@@ -450,7 +451,7 @@ struct LossOpts {
 };
 
 // One workgroup per sequence over its compact rows [cstart[i], cstart[i+1]).
-__global__ void seq_loss_kernel(int objective, const float* logp_c, const float* old_lp, const float* ref_lp,
+__global__ void seq_loss_kernel(int objective, const double* logp_c, const float* old_lp, const float* ref_lp,
                                 const int32_t* row_map, const int32_t* cstart, const float* adv,
                                 const int32_t* group_idx, const float* log_z, int B, LossOpts o, const Ctrl* ctrl,
                                 float* seq_loss, float* gterm, float* c_c, float* coeff_out, rl_stats* stats,
@@ -479,7 +480,7 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
       // per-token terms in f64: e^d - d - 1 cancels to ~d^2/2 and would lose digits in f32
-      const double lp = (double)logp_c[k];
+      const double lp = logp_c[k];
       const double rho = exp(lp - (double)old_lp[r]);
       const double dd = (double)ref_lp[r] - lp;
       const double ed = exp(dd);
@@ -508,7 +509,7 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
     double s_old = 0.0, s_kl = 0.0;
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
-      const double lp = (double)logp_c[k];
+      const double lp = logp_c[k];
       const double dd = (double)ref_lp[r] - lp;
       s_old += lp - (double)old_lp[r];
       s_kl += exp(dd) - dd - 1.0;
@@ -522,7 +523,7 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
     const double ds = (chi || clo) ? 0.0 : -Ad * sr;               // d(-surrogate)/d(mean log-ratio)
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
-      const double dd = (double)ref_lp[r] - (double)logp_c[k];
+      const double dd = (double)ref_lp[r] - logp_c[k];
       const float ct = (float)((ds + (double)o.kl_coef * (1.0 - exp(dd))) * inv_bn);
       c_c[k] = ct;
       if (coeff_out) coeff_out[r] = ct;
@@ -535,9 +536,9 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
     double s_ref = 0.0, s_old = 0.0;
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
-      const float lp = logp_c[k];
-      s_ref += (double)(lp - ref_lp[r]);
-      s_old += (double)(lp - old_lp[r]);
+      const double lp = logp_c[k];
+      s_ref += lp - (double)ref_lp[r];
+      s_old += lp - (double)old_lp[r];
     }
     const double t_ref = block_sum(s_ref, sh);
     double t_old = block_sum(s_old, sh);
@@ -726,11 +727,28 @@ struct Plan {
   int n_desc, max_len;   // stash: number of chunk records, promised bound on rows per sequence
   float inv_tau;         // 1 / temperature
   size_t off_ctrl, off_seq_len, off_cstart, off_row_map, off_ids_c, off_cpos, off_zy, off_lse_c, off_logp_c,
-      off_c_c, off_adv, off_seq_loss, off_gterm, off_part, off_wt, off_xt, off_ds, off_dst,
+      off_c_c, off_adv, off_seq_loss, off_gterm, off_part, off_wt, off_xt, off_ds, off_dst, off_split,
       off_desc, off_ref, off_zsum, off_scale, off_ycol, total;
 };
 
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Width of the f32 tiles of an M x N contraction over K.  (Bounds: the real extents may be smaller.)
+static int f32_tile_n(int M, int N, int K, bool split) {
+  const int64_t big = (int64_t)((M + kBM - 1) / kBM) * ((N + kF32BN - 1) / kF32BN);
+  const int nk = (K + 31) / 32, most = split ? (nk / kSplitMinSlabs < kMaxSplit ? nk / kSplitMinSlabs : kMaxSplit) : 1;
+  return big * (most > 1 ? most : 1) < kF32Slots ? kF32SmallBN : kF32BN;
+}
+
+// Bytes of the partial buffer of a contraction that may be split (at most 2 slots workgroups, at most kMaxSplit slices).
+static size_t split_bytes(int M, int N, int K, int bn, int bk, int slots) {
+  const int64_t tm = (M + kBM - 1) / kBM, tn = (N + bn - 1) / bn;
+  int64_t slices = (K + bk - 1) / bk / kSplitMinSlabs;
+  if (slices > kMaxSplit) slices = kMaxSplit;
+  int64_t rows = tm * slices;                        // slices x tile rows ...
+  if (rows > 2 * slots / tn) rows = 2 * slots / tn;  // ... of which at most this many exist when there is more than one slice
+  return (size_t)rows * kBM * (size_t)N * 4;
+}
 
 static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Plan& p) {
   if (!b) return RL_ERR_NULL;
@@ -780,17 +798,21 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.off_seq_len = take(sizeof(int32_t) * (size_t)b->B);
   p.off_cstart = take(sizeof(int32_t) * ((size_t)b->B + 1));
   p.off_row_map = take(4 * Rp); p.off_ids_c = take(4 * Rp); p.off_cpos = take(4 * Rp);
-  p.off_zy = take(4 * Rp); p.off_lse_c = take(4 * Rp); p.off_logp_c = take(4 * Rp); p.off_c_c = take(4 * Rp);
+  p.off_zy = take(4 * Rp); p.off_lse_c = take(4 * Rp); p.off_logp_c = take(8 * Rp);
+  p.off_c_c = bwd ? take(4 * Rp) : p.off_cpos;       // (positions are only looked up by the backward, coefficients written after them)
   p.off_ycol = take(4 * Rp);
   p.off_adv = take(4 * (size_t)b->B); p.off_seq_loss = take(4 * (size_t)b->B); p.off_gterm = take(4 * (size_t)b->B);
   p.off_part = take(sizeof(float4) * (size_t)p.tiles_v * (size_t)tc);
-  p.off_wt = p.off_xt = p.off_ds = p.off_dst = 0;
+  p.off_wt = p.off_xt = p.off_ds = p.off_dst = p.off_split = 0;
   if (bwd) {
     const size_t Hp = ((size_t)b->H + 255) & ~(size_t)255;   // tiled layouts come in blocks of 256 rows
     p.off_wt = take(p.esz * Hp * (size_t)p.Vp);
     p.off_xt = take(p.esz * Hp * (size_t)tc);
     p.off_ds = take(p.esz * (size_t)tc * (size_t)p.Vp);
-    if (b->dtype == RL_F32) p.off_dst = take(p.esz * (size_t)p.Vp * (size_t)tc);   // bf16: dW reads dS / E itself
+    if (b->dtype == RL_F32) {
+      p.off_dst = take(p.esz * (size_t)p.Vp * (size_t)tc);   // bf16: dW reads dS / E itself
+      p.off_split = take(split_bytes(tc, b->H, p.Vp, f32_tile_n(tc, b->H, p.Vp, true), 32, kF32Slots));
+    }
   }
   p.off_desc = p.off_ref = p.off_zsum = p.off_scale = 0;
   if (p.stash) {
@@ -803,13 +825,15 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
 
 // The bf16 hot kernel needs an even number of whole 64-element slabs and 16-byte aligned rows; anything else (f32
 // inputs, ragged K) takes the generic kernel.
-template <class T, class Epi>
-static void launch_generic(const T* A, const T* B, const GemmDims& d, const Epi& epi, int tiles, hipStream_t s) {
-  auto kern = gemm_nt_kernel<T, Epi, kBM, kBN, kWavesM, kWavesN>;
-  // 128 KiB of dynamic LDS needs the opt-in on every device the caller may be on: set on each launch (a host-side table
-  // update, no device work) rather than remembered in a flag that is neither per device nor thread-safe
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kGemmSmem);
-  kern<<<tiles, kGemmThreads, kGemmSmem, s>>>(A, B, d, epi);
+template <class Epi>
+static void launch_generic(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Epi& epi, int tiles, hipStream_t s) {
+  gemm_nt_kernel<bf16_t, Epi, kBM, kBN, 2, 4><<<tiles, 512, 0, s>>>(A, B, d, epi);
+}
+
+// Workgroups of a launch that may be split.
+static int split_launch(int tiles_m, int tiles_n, int slots) {
+  const int64_t t = launch_tiles(tiles_m, tiles_n);
+  return (int)(t > 2 * slots ? t : 2 * slots);
 }
 
 template <class Tune, class Epi>
@@ -818,14 +842,17 @@ static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, con
   const bool fast = (d.K % 128 == 0) && (d.lda % 8 == 0) && (d.ldb % 8 == 0) &&
                     ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0) &&
                     !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB;     // (how the hot kernel addresses its operands)
-  if (!fast) { launch_generic<bf16_t, Epi>(A, B, d, epi, tiles, s); return; }
+  if (!fast) { launch_generic(A, B, d, epi, tiles, s); return; }
   gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
 template <class Tune, class Epi>
 static void launch_gemm(const float* A, const float* B, const GemmDims& d, const Epi& epi, hipStream_t s) {
-  const int tiles = launch_tiles((d.M + kBM - 1) / kBM, (d.N + kBN - 1) / kBN);
-  launch_generic<float, Epi>(A, B, d, epi, tiles, s);
+  const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);
+  const int tm = (d.M + kBM - 1) / kBM, tn = (d.N + bn - 1) / bn;
+  const int tiles = d.split_slots > 0 ? split_launch(tm, tn, d.split_slots) : launch_tiles(tm, tn);
+  if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  else gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
 // Weight-gradient contraction of the recompute mode: bf16 reads dS (K-major A operand), f32 its stored transpose.
@@ -839,8 +866,8 @@ static void launch_dw(const float*, const float* dST, const float* XT, const Gem
 
 struct Ptrs {
   Ctrl* ctrl; int32_t *seq_len, *cstart, *row_map, *ids_c, *cpos;
-  float *zy, *lse_c, *logp_c, *c_c, *adv, *seq_loss, *gterm; float4* part;
-  void *wt, *xt, *ds, *dst;
+  float *zy, *lse_c, *c_c, *adv, *seq_loss, *gterm; double* logp_c; float4* part;
+  void *wt, *xt, *ds, *dst; float* split;
   ChunkDesc* desc; float *ref, *zsum, *scale;
   int32_t* ycol;
 };
@@ -850,11 +877,12 @@ static Ptrs carve(void* ws, const Plan& p) {
   Ptrs q;
   q.ctrl = (Ctrl*)(w + p.off_ctrl); q.seq_len = (int32_t*)(w + p.off_seq_len); q.cstart = (int32_t*)(w + p.off_cstart);
   q.row_map = (int32_t*)(w + p.off_row_map); q.ids_c = (int32_t*)(w + p.off_ids_c); q.cpos = (int32_t*)(w + p.off_cpos);
-  q.zy = (float*)(w + p.off_zy); q.lse_c = (float*)(w + p.off_lse_c); q.logp_c = (float*)(w + p.off_logp_c);
+  q.zy = (float*)(w + p.off_zy); q.lse_c = (float*)(w + p.off_lse_c); q.logp_c = (double*)(w + p.off_logp_c);
   q.c_c = (float*)(w + p.off_c_c); q.adv = (float*)(w + p.off_adv); q.seq_loss = (float*)(w + p.off_seq_loss);
   q.gterm = (float*)(w + p.off_gterm); q.part = (float4*)(w + p.off_part);
   q.wt = w + p.off_wt; q.xt = w + p.off_xt; q.ds = w + p.off_ds;
   q.dst = p.off_dst ? w + p.off_dst : nullptr;          // f32 inputs only
+  q.split = (float*)(w + p.off_split);
   q.desc = (ChunkDesc*)(w + p.off_desc); q.ref = (float*)(w + p.off_ref); q.zsum = (float*)(w + p.off_zsum);
   q.scale = (float*)(w + p.off_scale);
   q.ycol = (int32_t*)(w + p.off_ycol);
@@ -935,15 +963,17 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       GemmDims d{};
       d.M = p.Tc; d.N = p.H; d.K = p.Vp; d.lda = p.Vp; d.ldb = p.Vp;
       d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 1; d.group_m = TuneDX::kBand; d.a_tiled = d.b_tiled = p.tiled;
-      EpiDX<T> e{q.row_map, dX, p.H, p.H, nullptr};
+      if (!p.tiled) d.split_slots = kF32Slots;
+      EpiDX<T> e{q.row_map, dX, p.H, p.H, nullptr, q.split};
       ProfScope ps(RL_PROF_GEMM_DX, s);
       launch_gemm<TuneDX>(dS, WT, d, e, s);
+      if (d.split_slots) splitk_reduce_kernel<T><<<512, 256, 0, s>>>(d, e, kBM, f32_tile_n(d.M, d.N, d.K, true), 32);
     }
     {  // dW (+)= dS^T X : B = X^T [H][Tc]; A = dS^T, for bf16 read out of dS itself as a K-major operand
        // (K = Tc is a multiple of 256 and the workspace is aligned: always the hot kernel), for f32 the stored copy [Vp][Tc]
       GemmDims d{};
       d.M = p.V; d.N = p.H; d.K = p.Tc; d.lda = p.tiled ? p.Vp : p.Tc; d.ldb = p.Tc;
-      d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 3; d.group_m = TuneDW::kBand; d.a_tiled = d.b_tiled = p.tiled;
+      d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 3; d.k_round = p.tiled ? 256 : kF32SmallBN; d.group_m = TuneDW::kBand; d.a_tiled = d.b_tiled = p.tiled;
       d.zero_if_empty = (ch == 0);
       EpiDW e{d_weight, p.H, p.V, p.H, ch > 0 ? 1 : 0};
       ProfScope ps(RL_PROF_GEMM_DW, s);
@@ -1025,10 +1055,10 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
       GemmDims dx{};
       dx.M = p.Tc; dx.N = p.H; dx.K = p.Vp; dx.lda = p.Vp; dx.ldb = p.Vp;
       dx.chunk = chunk; dx.dyn = 1; dx.group_m = TuneDX::kBand; dx.a_tiled = dx.b_tiled = 1;
-      EpiDX<T> ex{q.row_map, dX, p.H, p.H, q.scale};
+      EpiDX<T> ex{q.row_map, dX, p.H, p.H, q.scale, nullptr};
       GemmDims dw{};
       dw.M = p.V; dw.N = p.H; dw.K = p.Tc; dw.lda = p.Vp; dw.ldb = p.Tc;
-      dw.chunk = chunk; dw.dyn = 3; dw.zero_if_empty = (k == 0); dw.group_m = TuneDW::kBand; dw.a_tiled = dw.b_tiled = 1;
+      dw.chunk = chunk; dw.dyn = 3; dw.k_round = 256; dw.zero_if_empty = (k == 0); dw.group_m = TuneDW::kBand; dw.a_tiled = dw.b_tiled = 1;
       EpiDW ew{out->d_weight, p.H, p.V, p.H, k > 0 ? 1 : 0};
       const int tn = (p.H + kBN - 1) / kBN;
       const int n1 = launch_tiles((p.Tc + kBM - 1) / kBM, tn);
@@ -1131,6 +1161,14 @@ rl_status rl_debug_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t group_m,
     if (!tile_of_block(w, tiles_m, tiles_n, group_m, by_share != 0, tm, tn)) tm = tn = -1;
     tile[2 * w] = tm; tile[2 * w + 1] = tn;
   }
+  return RL_OK;
+}
+
+rl_status rl_debug_split_k(int32_t tiles, int32_t slabs, int32_t slots, int32_t* slices, int32_t* per) {
+  if (!slices || !per) return RL_ERR_NULL;
+  if (tiles < 1 || slabs < 0 || slots < 1) return RL_ERR_SHAPE;
+  const SplitK k = split_k_host(tiles, slabs, slots);
+  *slices = k.slices; *per = k.per;
   return RL_OK;
 }
 
