@@ -278,7 +278,7 @@ def time_mode(a, b, batch, objective: str, backward: str, steps: int, warmup: in
     binding.rl_profile_enable(False)
 
     # launches per step that have rows to work on (the library launches a fixed upper bound of chunks; the rest return at once)
-    stash = prof["gemm_bwd"][1] > 0
+    stash = prof["gemm_bwd"][1] > 0 and prof["gemm_ds"][1] == 0          # (recomputed logits have a class of their own)
     default_tc = binding.lib().rl_default_chunk_rows_single_pass() if stash else binding.lib().rl_default_chunk_rows()
     tc = a.chunk_rows or default_tc
     if stash:                                  # sequence-aligned chunks: greedy packing of whole sequences

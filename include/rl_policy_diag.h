@@ -55,9 +55,12 @@ rl_status rl_measure_mfma_peak(int32_t millis, void* scratch, size_t scratch_byt
 rl_status rl_debug_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t group_m, int32_t by_share,
                               int32_t* workgroups, int32_t* tile);
 
-/* Diagnostic (host only): into how many slices of how many slabs of K a contraction of `tiles` tiles and `slabs` slabs is
- * cut when the chip runs `slots` workgroups at a time (the device works the same out from the number of tokens it finds). */
-rl_status rl_debug_split_k(int32_t tiles, int32_t slabs, int32_t slots, int32_t* slices, int32_t* per);
+/* Diagnostic (host only): into how many slices of how many steps of K a contraction of tiles_m x tiles_n tiles and `steps`
+ * steps is cut when the chip runs `slots` workgroups at a time and `fill` steps of another contraction fill the launch (the
+ * device works the same out from the number of tokens it finds), and the tile rows (slices x M-tiles) the partial buffer has
+ * when tiles_m is the most there can be. */
+rl_status rl_debug_split_k(int32_t tiles_m, int32_t tiles_n, int32_t steps, int32_t slots, int64_t fill, int32_t* slices, int32_t* per,
+                           int32_t* tile_rows);
 
 /* rl_rvq_encode that also counts, in the device word *n_exact (added to, not cleared; may be NULL), the decisions whose
  * float32 lead was within the rounding margin and that were therefore settled in float64 among the entries that came

@@ -1,7 +1,7 @@
 // epilogues.h - what each contraction does with its accumulators while they are in registers.
 //
 // Orientation.  The logits contraction is run "vocab-major": A = W (rows = vocab entries),
-// B = X (rows = tokens), so that in the MFMA accumulator layout (see Layout16) a lane
+// B = X (rows = tokens), so that in the MFMA accumulator layouts (see Layout32 / Layout16) a lane
 // owns ONE token column per block and several vocab rows of it.  The softmax reductions over the
 // vocabulary are then mostly in-register; the only cross-lane steps are between the lane groups
 // that hold other rows of the same column (one or two shuffles), and the only cross-wavefront
@@ -38,6 +38,7 @@ template <class T>
 struct EpiFwd {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSplit = false;
   static constexpr bool kPermute = false;
   static constexpr bool kGatherB = true;      // the B rows come through a row map (GemmDims::b_rows)
   __device__ void keep_alive() const { zy_c[0] = 0.f; }
@@ -166,6 +167,7 @@ struct EpiFwdStash {
     }
     return p;
   }
+  static constexpr bool kSplit = false;
   static constexpr bool kPermute = true;
   static constexpr bool kGatherB = true;      // the B rows come through a row map (GemmDims::b_rows)
   __device__ void keep_alive() const { E[0] = (T)0.f; }
@@ -281,6 +283,7 @@ template <class T>
 struct EpiDS {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSplit = false;
   static constexpr bool kPermute = true;
   static constexpr bool kGatherB = true;      // the B rows come through a row map (GemmDims::b_rows)
   __device__ void keep_alive() const { dS[0] = (T)0.f; }
@@ -375,6 +378,7 @@ template <class T>
 struct EpiDX {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSplit = true;       // may be cut along K (split_k)
   static constexpr bool kPermute = false;
   static constexpr bool kGatherB = false;      // the B rows come through a row map (GemmDims::b_rows)
   __device__ void keep_alive() const { dX[0] = (T)0.f; }
@@ -386,7 +390,7 @@ struct EpiDX {
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims& d, const Pre&) const {
     if (c.slices > 1) {
-      float* p = split_part + (int64_t)c.slice * ((c.Mv + BM - 1) / BM * BM) * H;
+      float* p = split_part + (int64_t)c.slice * ((c.Mv + BM - 1) / BM * BM) * H;     // (H % 4 == 0)
 #pragma unroll
       for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
@@ -419,13 +423,13 @@ struct EpiDX {
 };
 
 // The slices of a split dX contraction added up in order, scaled and scattered to the original rows (four columns per
-// thread, H % 4 == 0).  Works the number of slices out like the contraction itself; returns at once if there was one.
+// thread, H % 4 == 0; `step`: elements of K per step of the cut).  Works the number of slices out like the contraction itself; returns at once if there was one.
 template <class T>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDims d, EpiDX<T> e, int bm, int bn, int bk) {
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDims d, EpiDX<T> e, int bm, int bn, int step) {
   int M, N, K;
   if (!resolve_dims(d, M, N, K)) return;
   const int tiles_m = (M + bm - 1) / bm;
-  const SplitK sk = split_k(tiles_m * ((d.N + bn - 1) / bn), (K + bk - 1) / bk, d.split_slots);
+  const SplitK sk = split_k(tiles_m * ((d.N + bn - 1) / bn), (K + step - 1) / step, d.split_slots, fill_steps(d, M));
   if (sk.slices == 1) return;
   const int64_t stride = (int64_t)tiles_m * bm * e.H;
   const int h4 = e.H / 4;
@@ -448,6 +452,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDims d, EpiDX<T>
 struct EpiDW {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSplit = false;
   static constexpr bool kPermute = false;
   static constexpr bool kGatherB = false;      // the B rows come through a row map (GemmDims::b_rows)
   __device__ void keep_alive() const { dW[0] = 0.f; }

@@ -22,7 +22,7 @@
 //    software prefetch (one 4-byte load per 128-byte line, two slabs ahead, shared between the
 //    workgroups of an XCD; off for dX) pulls the next panels into that XCD's L2.
 //  * gemm_nt_kernel       - general kernel (f32 inputs, K not a multiple of 128, unaligned operands): tile size as
-//    a parameter, 16x16 MFMA blocks, register-staged loads with a K-tail predicate.
+//    a parameter, register-staged loads with a K-tail predicate.
 //
 // LDS rows are 128 B = eight 16-byte chunks; chunk c of row r sits at slot c ^ ((r>>1)&7),
 // which spreads both the 16-byte row-wise stores and the column-wise fragment loads over all
@@ -38,7 +38,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kSlabBytes = 128;   // bytes of K per LDS row
 constexpr int kXcds = 8;          // MI355X: 8 accelerator dies, workgroups dealt round-robin
@@ -46,6 +48,10 @@ constexpr int kXcds = 8;          // MI355X: 8 accelerator dies, workgroups deal
 template <class T> struct Elem;
 template <> struct Elem<bf16_t> { static constexpr int kPerChunk = 8; static constexpr int kBK = 64; };
 template <> struct Elem<float>  { static constexpr int kPerChunk = 4; static constexpr int kBK = 32; };
+struct Layout32;
+struct Layout16;
+template <bool SMALL> struct GeneralLayout { typedef Layout32 L; typedef u32x4_t F; };       // general kernel: MFMA blocks, fragment of a k-step
+template <> struct GeneralLayout<true> { typedef Layout16 L; typedef u32x2_t F; };
 
 struct GemmDims {
   int M, N, K;            // upper bounds (static); the dynamic extent trims one of them
@@ -62,6 +68,7 @@ struct GemmDims {
   int zero_if_empty;      // dyn == 3 only: an empty chunk still runs the epilogue (with K = 0) instead of returning
   int group_m;            // tile-order parameter: M-tiles per band
   int split_slots;        // > 0: the contraction may be cut along K (see split_k); workgroups the chip runs at a time
+  int fill_tiles;         // tiles of another contraction over K = M in the same launch, which fill the CUs this one leaves
 };
 
 // Slab-tiled operand layout of the library's own bf16 work buffers: [row / 256][k / 64][256 rows][64 k].
@@ -97,40 +104,46 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
 }
 
 // Cutting a contraction along K.  dX = dS W has K = V and only (tokens / tile) x (H / tile) tiles: a few hundred tokens
-// leave most of the chip idle behind a serial chain of thousands of slabs.  It is then cut into S slices of `per` slabs,
-// each slice's tile goes to a partial buffer in f32 and splitk_reduce_kernel adds the slices in order.  S minimises the
-// time in slabs: rounds of `slots` workgroups times (slabs per slice + what a workgroup spends outside its main loop);
-// a partial tile costs more there (it is written and read again in f32), and no more than 2 slots workgroups are made,
-// which bounds the partial buffer.  The number of tokens is only known on the
-// device, so every workgroup works S out for itself: lane s of a wavefront prices s + 1 slices.
-constexpr int kMaxSplit = 64, kSplitMinSlabs = 4;
+// leave most of the chip idle behind a serial chain of thousands of slabs.  It is then cut into slices of `per` steps
+// (a step is one slab, two in the hot kernel), each slice's tile goes to a partial buffer in f32 and splitk_reduce_kernel
+// adds the slices in order.  The number of slices minimises the time in steps, for `slots` workgroups at a time: the
+// rounds of workgroups times (steps per slice + what a workgroup spends outside its main loop), but no less than all
+// the work, `fill` steps of the other contraction of the launch included, spread over the slots.  A partial tile costs
+// more outside the loop (it is written and read again in f32), and no more than 2 slots workgroups are made, which bounds
+// the partial buffer.  The number of tokens is only known on the device, so every workgroup works the cut out for itself:
+// lane s of a wavefront prices s + 1 slices.
+constexpr int kMaxSplit = 64, kSplitMinSteps = 4;
 struct SplitK { int slices, per; };
-__device__ __host__ inline int64_t split_cost(int tiles, int nk, int want, int slots, SplitK& k) {
+__device__ __host__ inline int64_t split_cost(int tiles, int nk, int want, int slots, int64_t fill, SplitK& k) {
   if ((int64_t)tiles * want > 2 * slots) want = 1;
   int per = (nk + want - 1) / want;
-  if (per < kSplitMinSlabs) per = nk < kSplitMinSlabs ? (nk > 0 ? nk : 1) : kSplitMinSlabs;
+  if (per < kSplitMinSteps) per = nk < kSplitMinSteps ? (nk > 0 ? nk : 1) : kSplitMinSteps;
   k.per = per;
   k.slices = nk > 0 ? (nk + per - 1) / per : 1;
-  const int64_t rounds = ((int64_t)tiles * k.slices + slots - 1) / slots;
-  return rounds * (per + (k.slices > 1 ? 6 : 2));
+  const int64_t each = per + (k.slices > 1 ? 6 : 2), n = (int64_t)tiles * k.slices;
+  const int64_t rounds = (n + slots - 1) / slots * each, spread = (n * each + fill) / slots;
+  return rounds > spread ? rounds : spread;
 }
-inline SplitK split_k_host(int tiles, int nk, int slots) {             // the same on the host
+inline SplitK split_k_host(int tiles, int nk, int slots, int64_t fill) {       // the same on the host
   SplitK best{1, nk}, k;
-  int64_t c0 = split_cost(tiles, nk, 1, slots, best);
+  int64_t c0 = split_cost(tiles, nk, 1, slots, fill, best);
   for (int s = 2; s <= kMaxSplit; ++s) {
-    const int64_t c = split_cost(tiles, nk, s, slots, k);
+    const int64_t c = split_cost(tiles, nk, s, slots, fill, k);
     if (c < c0) { c0 = c; best = k; }
   }
   return best;
 }
-__device__ inline SplitK split_k(int tiles, int nk, int slots) {            // every lane of the wavefront must call it
+__device__ inline SplitK split_k(int tiles, int nk, int slots, int64_t fill) {       // every lane of the wavefront must call it
   SplitK k;
-  const int64_t c = split_cost(tiles, nk, (int)(threadIdx.x & 63) + 1, slots, k);
+  const int64_t c = split_cost(tiles, nk, (int)(threadIdx.x & 63) + 1, slots, fill, k);
   int64_t m = (c << 8) | (threadIdx.x & 63);
   for (int o = 32; o > 0; o >>= 1) { const int64_t x = __shfl_xor(m, o); m = x < m ? x : m; }
-  split_cost(tiles, nk, __builtin_amdgcn_readfirstlane((int)(m & 63)) + 1, slots, k);
+  split_cost(tiles, nk, __builtin_amdgcn_readfirstlane((int)(m & 63)) + 1, slots, fill, k);
+  k.slices = __builtin_amdgcn_readfirstlane(k.slices); k.per = __builtin_amdgcn_readfirstlane(k.per);     // (uniform, and known to be)
   return k;
 }
+// steps of the filling contraction of the hot kernel (two slabs each): its K is the M rows here, rounded up to 256; 3 per tile for its epilogue
+__device__ inline int64_t fill_steps(const GemmDims& d, int M) { return (int64_t)d.fill_tiles * ((M + 255) / 256 * 2 + 3); }
 
 // Workgroup -> tile.  Workgroups are dealt to the 8 XCDs round-robin (workgroup id % 8), and each XCD has
 // its own L2.  Tiles are walked in bands of group_m M-tiles by all N-tiles, M fastest inside a band column,
@@ -189,16 +202,6 @@ __device__ inline int lds_off(int row, int chunk) {           // byte offset ins
   return row * kSlabBytes + ((chunk ^ ((row >> 1) & 7)) << 4);
 }
 
-// 16x16 block of one 16-byte k-chunk per lane: lane l holds row l%16 of the operand, chunk l/16 of four
-template <class T>
-__device__ inline void mma_step(const uint4& a, const uint4& b, floatx4& acc);
-
-__device__ inline float f32_at(const uint4& v, int e) { return __builtin_bit_cast(float, e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w); }
-template <>
-__device__ inline void mma_step<bf16_t>(const uint4& a, const uint4& b, floatx4& acc) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-
 // Coordinates handed to an epilogue: everything it needs to map acc[bi][bj][i] to (m,n).
 struct TileCtx {
   int m0, n0;        // first row / col of this wavefront's sub-tile
@@ -210,8 +213,15 @@ struct TileCtx {
 };
 struct NoPre {};      // epilogue with nothing to fetch ahead of the main loop
 
-// Accumulator layout: where register i of block (bi, bj) of a lane sits inside the wavefront's
+// Accumulator layouts: where register i of block (bi, bj) of a lane sits inside the wavefront's
 // sub-tile.  Registers come in runs of four consecutive rows of one column.
+struct Layout32 {   // 32x32 MFMA blocks, 16 registers per block: row = 8*(i/4) + 4*(l/32) + i%4, col = l%32
+  typedef floatx16 acc_t;
+  static constexpr int kBlk = 32, kRegs = 16;
+  __device__ static int row(int bi, int i, int lane) { return bi * 32 + ((i >> 2) << 3) + ((lane >> 5) << 2) + (i & 3); }
+  __device__ static int col(int bj, int lane) { return bj * 32 + (lane & 31); }
+  __device__ static bool owns(int r, int lane) { return ((r >> 2) & 1) == (lane >> 5); }   // does this lane hold row r of its columns?
+};
 struct Layout16 {   // 16x16 MFMA blocks, 4 registers per block: row = 4*(l/16) + i, col = l%16
   typedef floatx4 acc_t;
   static constexpr int kBlk = 16, kRegs = 4;
@@ -238,6 +248,10 @@ __device__ inline float acc_read(const V& v, int i) {
 
 // General kernel: BM x BN tile, WAVES_M x WAVES_N wavefronts.  A slab is 128 bytes of K, staged global -> registers ->
 // LDS (any alignment, K tail zeroed) into two LDS stages; one barrier per slab.
+// Blocks of 32x32 (f32: v_mfma_f32_32x32x2), or of 16x16 where the tile is narrower than 32 (f32 only, 16x16x4).  Both add the k of an
+// eight-wide step in the order 0 4 1 5 2 6 3 7, so that an f32 logit does not depend on the tile it came from: in the
+// 16x16 form lane group g supplies element g/2, then g/2 + 2, of chunk g%2 - one 8-byte read, the chunks being stored in the
+// order 0 2 1 3 for it.
 template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64, 2)
 void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, Epi epi) {
@@ -245,7 +259,10 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   constexpr int BK = Elem<T>::kBK;
   constexpr int EPC = Elem<T>::kPerChunk;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  constexpr int MB = WM / 16, NB = WN / 16;
+  constexpr bool SMALL = WN < 32;
+  static_assert(!SMALL || sizeof(T) == 4, "16x16 blocks: f32 only");
+  typedef typename GeneralLayout<SMALL>::L L;
+  constexpr int MB = WM / L::kBlk, NB = WN / L::kBlk;
   constexpr int ROWS_PER_PASS = NT / 8;
   constexpr int PA = BM / ROWS_PER_PASS, PB = (BN + ROWS_PER_PASS - 1) / ROWS_PER_PASS;
   static_assert(BM % ROWS_PER_PASS == 0 && (BN % ROWS_PER_PASS == 0 || BN < ROWS_PER_PASS), "tile vs threads");
@@ -260,7 +277,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   const bool by_share = d.dyn == 1;
   const int tiles_m = ((by_share ? M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   if (d.split_slots > 0) {
-    const SplitK sk = split_k(tiles_m * tiles_n, nk, d.split_slots);
+    const SplitK sk = split_k(tiles_m * tiles_n, nk, d.split_slots, 0);
     slices = sk.slices;
     int t;
     if (!run_of_block(blockIdx.x, tiles_m * tiles_n * slices, t)) return;      // slice after slice, M fastest inside one
@@ -295,62 +312,72 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   }
   uint4 ra[PA], rb[PB];
   auto gload = [&](int k0) __attribute__((always_inline)) {
-    const bool ok = (k0 + lchunk * EPC) < K;
+    if (k0 + BK <= K) {                              // a whole slab
 #pragma unroll
-    for (int p = 0; p < PA; ++p) ra[p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
+      for (int p = 0; p < PA; ++p) ra[p] = *reinterpret_cast<const uint4*>(ap[p] + k0);
 #pragma unroll
-    for (int p = 0; p < PB; ++p) rb[p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
+      for (int p = 0; p < PB; ++p) rb[p] = *reinterpret_cast<const uint4*>(bp[p] + k0);
+    } else {
+      const bool ok = (k0 + lchunk * EPC) < K;
+#pragma unroll
+      for (int p = 0; p < PA; ++p) ra[p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < PB; ++p) rb[p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
+    }
   };
+  auto stored = [](const uint4& v) __attribute__((always_inline)) { return SMALL ? make_uint4(v.x, v.z, v.y, v.w) : v; };
   auto lstore = [&](int buf) __attribute__((always_inline)) {
     unsigned char* as = smem + buf * (A_BYTES + B_BYTES);
     unsigned char* bs = as + A_BYTES;
 #pragma unroll
-    for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = ra[p];
+    for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(ra[p]);
 #pragma unroll
     for (int p = 0; p < PB; ++p)
-      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = rb[p];
+      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(rb[p]);
   };
 
-  floatx4 acc[MB][NB];
+  typename L::acc_t acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < L::kRegs; ++e) acc[i][j][e] = 0.f;
 
   if (nk > 0) {
     gload(k_begin * BK);
     lstore(0);
   }
   __syncthreads();
-  const int frow = lane & 15, fq = lane >> 4;
+  const int frow = lane & (L::kBlk - 1), fq = lane / L::kBlk;
   for (int kt = 0; kt < nk; ++kt) {
     const int cur = kt & 1;
     if (kt + 1 < nk) gload((k_begin + kt + 1) * BK);
     const unsigned char* as = smem + cur * (A_BYTES + B_BYTES);
     const unsigned char* bs = as + A_BYTES;
+    typedef typename GeneralLayout<SMALL>::F F;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {                  // two 64-byte k-steps per slab
-      uint4 af[MB], bf[NB];
+    for (int s = 0; s < 4; ++s) {                  // four 32-byte k-steps per slab; in a step the blocks take turns, so that
+      F a[MB], b[NB];                              // consecutive MFMAs do not wait for each other's accumulators
 #pragma unroll
-      for (int i = 0; i < MB; ++i) af[i] = *reinterpret_cast<const uint4*>(as + lds_off(wm * WM + i * 16 + frow, s * 4 + fq));
+      for (int i = 0; i < MB; ++i)
+        a[i] = *reinterpret_cast<const F*>(as + lds_off(wm * WM + i * L::kBlk + frow, s * 2 + (fq & 1)) + (fq >> 1) * 8);
 #pragma unroll
-      for (int j = 0; j < NB; ++j) bf[j] = *reinterpret_cast<const uint4*>(bs + lds_off(wn * WN + j * 16 + frow, s * 4 + fq));
-      if constexpr (sizeof(T) == 4) {              // element e of the chunks: four k of the block's sixteen; blocks in turn, so
-#pragma unroll                                     // that consecutive MFMAs do not wait for each other's accumulators
-        for (int e = 0; e < 4; ++e)
+      for (int j = 0; j < NB; ++j)
+        b[j] = *reinterpret_cast<const F*>(bs + lds_off(wn * WN + j * L::kBlk + frow, s * 2 + (fq & 1)) + (fq >> 1) * 8);
 #pragma unroll
-          for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f32_at(af[i], e), f32_at(bf[j], e), acc[i][j], 0, 0, 0);
-      } else {
+      for (int e = 0; e < (sizeof(T) == 2 ? 1 : SMALL ? 2 : 4); ++e)
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
-          for (int j = 0; j < NB; ++j) mma_step<T>(af[i], bf[j], acc[i][j]);
-      }
+          for (int j = 0; j < NB; ++j) {
+            if constexpr (SMALL)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i][e]), __uint_as_float(b[j][e]), acc[i][j], 0, 0, 0);
+            else if constexpr (sizeof(T) == 4)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[i][e]), __uint_as_float(b[j][e]), acc[i][j], 0, 0, 0);
+            else
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
+          }
     }
     if (kt + 1 < nk) lstore(cur ^ 1);
     __syncthreads();
@@ -360,8 +387,8 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
   c.slice = slice; c.slices = slices;
-  const typename Epi::Pre pre = epi.template preload<Layout16>(c, d);
-  epi.template run<Layout16, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
+  const typename Epi::Pre pre = epi.template preload<L>(c, d);
+  epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
 }
 
 // ------------------------------------------------------------------ bf16 hot kernel
@@ -385,6 +412,13 @@ __device__ __attribute__((always_inline)) inline void load16_to_lds_lanes(const 
 
 __device__ inline void load16_to_lds(const void* g, void* l) {   // 64 lanes x 16 B -> 1 KiB of LDS at l
   __builtin_amdgcn_global_load_lds((glb_ptr_t)g, (lds_ptr_t)l, 16, 0, 0);
+}
+
+// A wavefront-uniform pointer the compiler may have computed in vector registers, in scalar ones.
+template <class P> __device__ inline P* uniform_ptr(P* p) {
+  const uint64_t v = (uint64_t)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+  return (P*)(((uint64_t)hi << 32) | lo);
 }
 
 // Optional relabelling of the tile's rows and columns in the hot kernel (epilogues with kPermute).
@@ -418,7 +452,6 @@ constexpr int kHotStageBytes = (256 + 256) * kSlabBytes;      // one LDS stage o
 // value j%4 of the piece fetched by lane 4e + j/4.  With lanes 4e..4e+3 pointing at sixteen consecutive m of
 // k-row e, lane j ends up with (m = j, k = 0..3): an MFMA operand read out of a K-major slab.
 typedef short tr16x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 __device__ __attribute__((always_inline)) inline u32x2_t lds_read_tr16(const unsigned char* p) {
   typedef __attribute__((address_space(3))) tr16x4_t* lds_ptr;
   return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p)));
@@ -447,15 +480,32 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
                 "the slab loads of the fullest phase must fit into its 32 MFMAs");
   static_assert(STAGE == kHotStageBytes, "stage size");
   static_assert(!ATR || !Epi::kPermute, "the K-major A path loads rows in natural order");
+  static_assert(!Epi::kSplit || (!ATR && PFD == 0 && !Epi::kGatherB), "a slice starts at a slab offset of both row-wise operands");
 
   int M, N, K;
   if (!resolve_dims(d, M, N, K)) return;
-  const int nk = K / BK;
+  int nk = K / BK;
   // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
   const bool by_share = d.dyn == 1;
   const int tiles_m = ((by_share ? M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
-  int tm, tn;
-  if (!tile_of_block(pid, tiles_m, tiles_n, d.group_m, by_share, tm, tn)) return;
+  int tm, tn, slice = 0, slices = 1, k_first = 0;                 // first slab
+  if constexpr (Epi::kSplit) {
+    const SplitK sk = split_k(tiles_m * tiles_n, nk / 2, d.split_slots, fill_steps(d, M));
+    slices = sk.slices;
+    if (slices > 1) {                                             // slice after slice, M fastest inside one: an XCD works on few
+      int t;                                                      // slices, whose panels of both operands its L2 then holds
+      if (!run_of_block(pid, tiles_m * tiles_n * slices, t)) return;
+      slice = t / (tiles_m * tiles_n);
+      t -= slice * (tiles_m * tiles_n);
+      tn = t / tiles_m; tm = t - tn * tiles_m;
+      k_first = slice * sk.per * 2;
+      nk = nk - k_first < sk.per * 2 ? nk - k_first : sk.per * 2;
+    }
+  }
+  if (slices == 1 && !tile_of_block(pid, tiles_m, tiles_n, d.group_m, by_share, tm, tn)) return;
+  if constexpr (Epi::kSplit) {                                    // (all uniform; said so, because the slab loads want scalar addresses)
+    nk = __builtin_amdgcn_readfirstlane(nk); tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
+  }
   if (tm * BM >= M || tn * BN >= N) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -473,9 +523,9 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   const bf16_t* ap[8];
   const bf16_t* bp[8];
   unsigned aoff[8], boff[8];
-  const bf16_t* const abase = ATR ? A + tiled_index(0, tm * BM, d.lda)
+  const bf16_t* abase = ATR ? A + tiled_index(0, tm * BM, d.lda)
                                   : A + (d.a_tiled ? tiled_index(tm * BM, 0, d.K) : (int64_t)(tm * BM) * d.lda);
-  const bf16_t* const bbase = B + (d.b_tiled ? tiled_index(tn * BN, 0, d.K) : (int64_t)(tn * BN) * d.ldb);
+  const bf16_t* bbase = B + (d.b_tiled ? tiled_index(tn * BN, 0, d.K) : (int64_t)(tn * BN) * d.ldb);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int lr = wave * 64 + j * 8 + (lane >> 3);
@@ -499,6 +549,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     boff[j] = GB ? 0u : (unsigned)(bp[j] - bbase) * 2u;
   }
   const int a_ks = d.a_tiled ? 16384 : BK, b_ks = d.b_tiled ? 16384 : BK;     // elements from one slab to the next
+  if constexpr (Epi::kSplit) { abase = uniform_ptr(abase + (int64_t)k_first * a_ks); bbase = uniform_ptr(bbase + (int64_t)k_first * b_ks); }
   // K-major A: slab s is k-rows [64 s, 64 s + 64), i.e. quarter s%4 of row block s/4 of the tiled layout
   auto a_slab = [&](int slab) __attribute__((always_inline)) -> int64_t {
     return ATR ? (int64_t)(slab >> 2) * (d.lda * 256) + (slab & 3) * 4096 : (int64_t)slab * a_ks;
@@ -552,7 +603,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   TileCtx c;
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
-  c.slice = 0; c.slices = 1;
+  c.slice = slice; c.slices = slices;
   // what the epilogue needs from memory per column or row (a few registers): fetched now, used after the main loop
   const typename Epi::Pre pre = epi.template preload<Layout16>(c, d);
 

@@ -32,9 +32,10 @@ namespace rlk {
 constexpr int kDefaultChunkRows = 32768;        // recompute mode: 128 x 14 dX tiles = 7 full rounds of 256 CUs on the 7B shape
 constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step time is flat (+-0.7 %) from 24576 to 65536 rows
 constexpr int kBM = 256, kBN = 256;
-// General kernel in f32: tiles of 256 x 64 (four wavefronts of 64 x 64, two workgroups per CU), or 256 x 16 where the large
+// General kernel in f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU), or 256 x 16 where the large
 // ones would leave CUs without work.
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
+constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup per CU, a step of a K cut is two slabs
 // Per-contraction tuning of the hot kernel, from sweeps on the 7B-shaped workload:
 // tile-order band height (M-tiles per band), L2 prefetch distance in slabs (0 = off), where in a
 // phase of 32 MFMAs the slab loads are issued (after MFMA kVmo, kVmo + kVmg, ...) and how many of a slab's 16 loads
@@ -337,7 +338,7 @@ __global__ void target_logit_kernel(const bf16_t* X, const bf16_t* W, int H, con
 constexpr int kSumSlices = 16;
 __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* part, int ldp, int tiles_v, const float* zy_c, const float* ref_l2e,
                                const int32_t* row_map, const ChunkDesc* desc, const int32_t* ycol_c, Ctrl* ctrl, rl_stats* stats,
-                               float* lse_c, double* logp_c, float* zsum_c, float* lse_out, float* logp_out, float* ent_out,
+                               float* lse_c, float* logp_c, float* zsum_c, float* lse_out, float* logp_out, float* ent_out,
                                float* zy_out, int32_t* ycol_out) {
   __shared__ double ss[kSumSlices][64], su[kSumSlices][64];
   const int left = desc->rows, chunk_start = desc->row_start;
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* 
     const int g = chunk_start + n;
     const double lse_d = (double)ref_l2e[g] * 0.6931471805599453 + log(S);
     const float lse = (float)lse_d;
-    const double lp = (double)zy_c[g] - lse_d;             // the loss takes it unrounded: its sums over a sequence cancel
+    const float lp = zy_c[g] - lse;
     lse_c[g] = lse; logp_c[g] = lp; zsum_c[g] = (float)S;
     // Z_t = exp(lse_t - ref_t) is of order one when the old log-prob is anywhere near the current one.  A row whose
     // sum left [1e-30, 1e30] (or is not a number) had stored probabilities outside the staging precision's range:
@@ -363,7 +364,7 @@ __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* 
     if (!(S >= 1e-30 && S <= 1e30)) { atomicAdd(&ctrl->overflow, 1); if (stats) atomicAdd(&stats->n_overflow_rows, 1); }
     const int r = row_map[g];
     if (lse_out) lse_out[r] = lse;
-    if (logp_out) logp_out[r] = (float)lp;
+    if (logp_out) logp_out[r] = lp;
     if (ent_out) ent_out[r] = (float)fmax(lse_d - U / S, 0.0);
     if (zy_out) zy_out[r] = zy_c[g];
     if (ycol_out) ycol_out[r] = ycol_c[g];
@@ -394,7 +395,7 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 // along the rows, then the four slices are merged through LDS in a fixed order.
 __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
                                    const int32_t* row_map, const Ctrl* ctrl, int chunk_start, int chunk_rows, const int32_t* ycol_c,
-                                   float* lse_c, double* logp_c, float* lse_out, float* logp_out, float* ent_out,
+                                   float* lse_c, float* logp_c, float* lse_out, float* logp_out, float* ent_out,
                                    float* zy_out, int32_t* ycol_out) {
   __shared__ float sm[4][64], ss[4][64], su[4][64];
   int left = ctrl->n_real - chunk_start;
@@ -430,11 +431,11 @@ __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, con
     const double lse_d = (double)M + log(S);
     const float lse = (float)lse_d;
     const int g = chunk_start + n;
-    const double lp = (double)zy_c[g] - lse_d;             // the loss takes it unrounded: its sums over a sequence cancel
+    const float lp = zy_c[g] - lse;
     lse_c[g] = lse; logp_c[g] = lp;
     const int r = row_map[g];
     if (lse_out) lse_out[r] = lse;
-    if (logp_out) logp_out[r] = (float)lp;
+    if (logp_out) logp_out[r] = lp;
     if (ent_out) ent_out[r] = (float)fmax(lse_d - U / S, 0.0);     // H = lse - sum_v p_v z_v
     if (zy_out) zy_out[r] = zy_c[g];
     if (ycol_out) ycol_out[r] = ycol_c[g];
@@ -451,7 +452,7 @@ struct LossOpts {
 };
 
 // One workgroup per sequence over its compact rows [cstart[i], cstart[i+1]).
-__global__ void seq_loss_kernel(int objective, const double* logp_c, const float* old_lp, const float* ref_lp,
+__global__ void seq_loss_kernel(int objective, const float* logp_c, const float* old_lp, const float* ref_lp,
                                 const int32_t* row_map, const int32_t* cstart, const float* adv,
                                 const int32_t* group_idx, const float* log_z, int B, LossOpts o, const Ctrl* ctrl,
                                 float* seq_loss, float* gterm, float* c_c, float* coeff_out, rl_stats* stats,
@@ -480,7 +481,7 @@ __global__ void seq_loss_kernel(int objective, const double* logp_c, const float
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
       // per-token terms in f64: e^d - d - 1 cancels to ~d^2/2 and would lose digits in f32
-      const double lp = logp_c[k];
+      const double lp = (double)logp_c[k];
       const double rho = exp(lp - (double)old_lp[r]);
       const double dd = (double)ref_lp[r] - lp;
       const double ed = exp(dd);
@@ -509,7 +510,7 @@ __global__ void seq_loss_kernel(int objective, const double* logp_c, const float
     double s_old = 0.0, s_kl = 0.0;
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
-      const double lp = logp_c[k];
+      const double lp = (double)logp_c[k];
       const double dd = (double)ref_lp[r] - lp;
       s_old += lp - (double)old_lp[r];
       s_kl += exp(dd) - dd - 1.0;
@@ -523,7 +524,7 @@ __global__ void seq_loss_kernel(int objective, const double* logp_c, const float
     const double ds = (chi || clo) ? 0.0 : -Ad * sr;               // d(-surrogate)/d(mean log-ratio)
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
-      const double dd = (double)ref_lp[r] - logp_c[k];
+      const double dd = (double)ref_lp[r] - (double)logp_c[k];
       const float ct = (float)((ds + (double)o.kl_coef * (1.0 - exp(dd))) * inv_bn);
       c_c[k] = ct;
       if (coeff_out) coeff_out[r] = ct;
@@ -536,9 +537,9 @@ __global__ void seq_loss_kernel(int objective, const double* logp_c, const float
     double s_ref = 0.0, s_old = 0.0;
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
-      const double lp = logp_c[k];
-      s_ref += lp - (double)ref_lp[r];
-      s_old += lp - (double)old_lp[r];
+      const float lp = logp_c[k];
+      s_ref += (double)(lp - ref_lp[r]);
+      s_old += (double)(lp - old_lp[r]);
     }
     const double t_ref = block_sum(s_ref, sh);
     double t_old = block_sum(s_old, sh);
@@ -736,18 +737,20 @@ static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Width of the f32 tiles of an M x N contraction over K.  (Bounds: the real extents may be smaller.)
 static int f32_tile_n(int M, int N, int K, bool split) {
   const int64_t big = (int64_t)((M + kBM - 1) / kBM) * ((N + kF32BN - 1) / kF32BN);
-  const int nk = (K + 31) / 32, most = split ? (nk / kSplitMinSlabs < kMaxSplit ? nk / kSplitMinSlabs : kMaxSplit) : 1;
+  const int nk = (K + 31) / 32, most = split ? (nk / kSplitMinSteps < kMaxSplit ? nk / kSplitMinSteps : kMaxSplit) : 1;
   return big * (most > 1 ? most : 1) < kF32Slots ? kF32SmallBN : kF32BN;
 }
 
-// Bytes of the partial buffer of a contraction that may be split (at most 2 slots workgroups, at most kMaxSplit slices).
-static size_t split_bytes(int M, int N, int K, int bn, int bk, int slots) {
-  const int64_t tm = (M + kBM - 1) / kBM, tn = (N + bn - 1) / bn;
-  int64_t slices = (K + bk - 1) / bk / kSplitMinSlabs;
+// Tile rows (slices x M-tiles) of the partial buffer of a contraction of at most tm x tn tiles and `steps` steps of K that may be cut:
+// at most kMaxSplit slices of at least kSplitMinSteps steps, at most 2 slots workgroups.
+static int64_t split_tile_rows(int tm, int tn, int steps, int slots) {
+  int64_t slices = (steps + kSplitMinSteps - 1) / kSplitMinSteps;
   if (slices > kMaxSplit) slices = kMaxSplit;
-  int64_t rows = tm * slices;                        // slices x tile rows ...
-  if (rows > 2 * slots / tn) rows = 2 * slots / tn;  // ... of which at most this many exist when there is more than one slice
-  return (size_t)rows * kBM * (size_t)N * 4;
+  const int64_t rows = tm * slices, most = 2 * slots / tn;
+  return rows < most ? rows : most;
+}
+static size_t split_bytes(int M, int N, int K, int bn, int step, int slots) {
+  return (size_t)split_tile_rows((M + kBM - 1) / kBM, (N + bn - 1) / bn, (K + step - 1) / step, slots) * kBM * (size_t)N * 4;
 }
 
 static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Plan& p) {
@@ -786,7 +789,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len
-  p.n_desc = 2 * p.n_chunks + 1;
+  // (a batch of no more rows than a chunk holds is one chunk)
+  p.n_desc = p.n_chunks == 1 ? 1 : 2 * p.n_chunks + 1;
   if (p.stash && p.max_len < tc) {
     const int64_t alt = (b->R + (tc - p.max_len)) / (tc - p.max_len + 1) + 1;
     if (alt < p.n_desc) p.n_desc = (int)alt;
@@ -798,8 +802,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.off_seq_len = take(sizeof(int32_t) * (size_t)b->B);
   p.off_cstart = take(sizeof(int32_t) * ((size_t)b->B + 1));
   p.off_row_map = take(4 * Rp); p.off_ids_c = take(4 * Rp); p.off_cpos = take(4 * Rp);
-  p.off_zy = take(4 * Rp); p.off_lse_c = take(4 * Rp); p.off_logp_c = take(8 * Rp);
-  p.off_c_c = bwd ? take(4 * Rp) : p.off_cpos;       // (positions are only looked up by the backward, coefficients written after them)
+  p.off_zy = take(4 * Rp); p.off_lse_c = take(4 * Rp); p.off_logp_c = take(4 * Rp); p.off_c_c = take(4 * Rp);
   p.off_ycol = take(4 * Rp);
   p.off_adv = take(4 * (size_t)b->B); p.off_seq_loss = take(4 * (size_t)b->B); p.off_gterm = take(4 * (size_t)b->B);
   p.off_part = take(sizeof(float4) * (size_t)p.tiles_v * (size_t)tc);
@@ -812,6 +815,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
     if (b->dtype == RL_F32) {
       p.off_dst = take(p.esz * (size_t)p.Vp * (size_t)tc);   // bf16: dW reads dS / E itself
       p.off_split = take(split_bytes(tc, b->H, p.Vp, f32_tile_n(tc, b->H, p.Vp, true), 32, kF32Slots));
+    } else {
+      p.off_split = take(split_bytes(tc, b->H, p.Vp, kBN, kHotStep, kHotSlots));
     }
   }
   p.off_desc = p.off_ref = p.off_zsum = p.off_scale = 0;
@@ -851,22 +856,26 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
   const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);
   const int tm = (d.M + kBM - 1) / kBM, tn = (d.N + bn - 1) / bn;
   const int tiles = d.split_slots > 0 ? split_launch(tm, tn, d.split_slots) : launch_tiles(tm, tn);
-  if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 2, 2><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
-// Weight-gradient contraction of the recompute mode: bf16 reads dS (K-major A operand), f32 its stored transpose.
-static void launch_dw(const bf16_t* dS, const bf16_t*, const bf16_t* XT, const GemmDims& d, const EpiDW& epi, hipStream_t s) {
-  const int tiles = launch_tiles((d.M + kBM - 1) / kBM, (d.N + kBN - 1) / kBN);
-  gemm_nt_bf16_kernel<EpiDW, TuneDW, true><<<tiles, 256, 0, s>>>(dS, XT, d, epi);
-}
-static void launch_dw(const float*, const float* dST, const float* XT, const GemmDims& d, const EpiDW& epi, hipStream_t s) {
-  launch_gemm<TuneDW>(dST, XT, d, epi, s);
+// dX = diag(f) dS W  (A = dS or E' [Tc][Vp], B = W^T [H][Vp]) and dW (+)= dS^T (diag(f) X)  (A = the same array read as a K-major
+// operand, B = X^T [H][Tc]) of a bf16 chunk in one launch: dX alone has few (long) tiles, whose last round would leave CUs
+// idle; the dW tiles fill them.  dX is cut along K where its tiles are fewer still.
+static void launch_dx_dw(const bf16_t* E, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, const GemmDims& dw, const EpiDW& ew,
+                         hipStream_t s) {
+  const int tn = (dx.N + kBN - 1) / kBN;
+  dx.split_slots = kHotSlots; dx.fill_tiles = (dw.M + kBM - 1) / kBM * tn;
+  const int n1 = split_launch((dx.M + kBM - 1) / kBM, tn, kHotSlots);
+  const int n2 = launch_tiles((dw.M + kBM - 1) / kBM, tn);
+  gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
+  splitk_reduce_kernel<bf16_t><<<512, 256, 0, s>>>(dx, ex, kBM, kBN, kHotStep);
 }
 
 struct Ptrs {
   Ctrl* ctrl; int32_t *seq_len, *cstart, *row_map, *ids_c, *cpos;
-  float *zy, *lse_c, *c_c, *adv, *seq_loss, *gterm; double* logp_c; float4* part;
+  float *zy, *lse_c, *logp_c, *c_c, *adv, *seq_loss, *gterm; float4* part;
   void *wt, *xt, *ds, *dst; float* split;
   ChunkDesc* desc; float *ref, *zsum, *scale;
   int32_t* ycol;
@@ -877,7 +886,7 @@ static Ptrs carve(void* ws, const Plan& p) {
   Ptrs q;
   q.ctrl = (Ctrl*)(w + p.off_ctrl); q.seq_len = (int32_t*)(w + p.off_seq_len); q.cstart = (int32_t*)(w + p.off_cstart);
   q.row_map = (int32_t*)(w + p.off_row_map); q.ids_c = (int32_t*)(w + p.off_ids_c); q.cpos = (int32_t*)(w + p.off_cpos);
-  q.zy = (float*)(w + p.off_zy); q.lse_c = (float*)(w + p.off_lse_c); q.logp_c = (double*)(w + p.off_logp_c);
+  q.zy = (float*)(w + p.off_zy); q.lse_c = (float*)(w + p.off_lse_c); q.logp_c = (float*)(w + p.off_logp_c);
   q.c_c = (float*)(w + p.off_c_c); q.adv = (float*)(w + p.off_adv); q.seq_loss = (float*)(w + p.off_seq_loss);
   q.gterm = (float*)(w + p.off_gterm); q.part = (float4*)(w + p.off_part);
   q.wt = w + p.off_wt; q.xt = w + p.off_xt; q.ds = w + p.off_ds;
@@ -959,25 +968,31 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       ProfScope ps(RL_PROF_GEMM_DS, s);
       launch_gemm<TuneLogits>(W, X, d, e, s);
     }
-    {  // dX = dS W  : A = dS [Tc][Vp], B = W^T [H][Vp]
-      GemmDims d{};
-      d.M = p.Tc; d.N = p.H; d.K = p.Vp; d.lda = p.Vp; d.ldb = p.Vp;
-      d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 1; d.group_m = TuneDX::kBand; d.a_tiled = d.b_tiled = p.tiled;
-      if (!p.tiled) d.split_slots = kF32Slots;
-      EpiDX<T> e{q.row_map, dX, p.H, p.H, nullptr, q.split};
-      ProfScope ps(RL_PROF_GEMM_DX, s);
-      launch_gemm<TuneDX>(dS, WT, d, e, s);
-      if (d.split_slots) splitk_reduce_kernel<T><<<512, 256, 0, s>>>(d, e, kBM, f32_tile_n(d.M, d.N, d.K, true), 32);
-    }
-    {  // dW (+)= dS^T X : B = X^T [H][Tc]; A = dS^T, for bf16 read out of dS itself as a K-major operand
-       // (K = Tc is a multiple of 256 and the workspace is aligned: always the hot kernel), for f32 the stored copy [Vp][Tc]
-      GemmDims d{};
-      d.M = p.V; d.N = p.H; d.K = p.Tc; d.lda = p.tiled ? p.Vp : p.Tc; d.ldb = p.Tc;
-      d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 3; d.k_round = p.tiled ? 256 : kF32SmallBN; d.group_m = TuneDW::kBand; d.a_tiled = d.b_tiled = p.tiled;
-      d.zero_if_empty = (ch == 0);
-      EpiDW e{d_weight, p.H, p.V, p.H, ch > 0 ? 1 : 0};
+    // dX = dS W: A = dS [Tc][Vp], B = W^T [H][Vp]
+    GemmDims dx{};
+    dx.M = p.Tc; dx.N = p.H; dx.K = p.Vp; dx.lda = p.Vp; dx.ldb = p.Vp;
+    dx.n_real = &q.ctrl->n_real; dx.chunk_start = c0; dx.dyn = 1; dx.group_m = TuneDX::kBand; dx.a_tiled = dx.b_tiled = p.tiled;
+    EpiDX<T> ex{q.row_map, dX, p.H, p.H, nullptr, q.split};
+    // dW (+)= dS^T X: B = X^T [H][Tc]; A = dS^T, for bf16 read out of dS itself as a K-major operand (K = Tc is a multiple of 256
+    // and the workspace is aligned: always the hot kernel), for f32 the stored copy [Vp][Tc]
+    GemmDims dw{};
+    dw.M = p.V; dw.N = p.H; dw.K = p.Tc; dw.lda = p.tiled ? p.Vp : p.Tc; dw.ldb = p.Tc;
+    dw.n_real = &q.ctrl->n_real; dw.chunk_start = c0; dw.dyn = 3; dw.k_round = p.tiled ? 256 : kF32SmallBN; dw.group_m = TuneDW::kBand;
+    dw.a_tiled = dw.b_tiled = p.tiled;
+    dw.zero_if_empty = (ch == 0);
+    EpiDW ew{d_weight, p.H, p.V, p.H, ch > 0 ? 1 : 0};
+    if constexpr (sizeof(T) == 2) {
+      ProfScope ps(RL_PROF_GEMM_BWD, s);
+      launch_dx_dw(dS, WT, dx, ex, XT, dw, ew, s);
+    } else {
+      {
+        ProfScope ps(RL_PROF_GEMM_DX, s);
+        dx.split_slots = kF32Slots;
+        launch_gemm<TuneDX>(dS, WT, dx, ex, s);
+        splitk_reduce_kernel<T><<<512, 256, 0, s>>>(dx, ex, kBM, f32_tile_n(dx.M, dx.N, dx.K, true), 32);
+      }
       ProfScope ps(RL_PROF_GEMM_DW, s);
-      launch_dw(dS, dST, XT, d, e, s);
+      launch_gemm<TuneDW>(dST, XT, dw, ew, s);
     }
   }
 }
@@ -1049,23 +1064,17 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
       dim3 g((p.Tc + 63) / 64, (p.H + 63) / 64);
       launch_transpose<T>(g, s, X, p.H, p.Tc, p.H, q.row_map, q.ctrl, 0, 1, dk, q.scale, XT, p.Tc, p.Tc, true);
     }
-    {  // dX = diag(-c/Z) E' W  (A = E' [Tc][Vp], B = W^T [H][Vp]) and dW (+)= E'^T (diag(-c/Z) X)  (A = E'^T, read out
-       // of E' itself as a K-major operand; B = scaled X^T [H][Tc]) in one launch: dX alone has too few (long) tiles
-       // to fill its last round of CUs
+    {  // dX = diag(-c/Z) E' W and dW (+)= E'^T (diag(-c/Z) X)
       GemmDims dx{};
       dx.M = p.Tc; dx.N = p.H; dx.K = p.Vp; dx.lda = p.Vp; dx.ldb = p.Vp;
       dx.chunk = chunk; dx.dyn = 1; dx.group_m = TuneDX::kBand; dx.a_tiled = dx.b_tiled = 1;
-      EpiDX<T> ex{q.row_map, dX, p.H, p.H, q.scale, nullptr};
+      EpiDX<T> ex{q.row_map, dX, p.H, p.H, q.scale, q.split};
       GemmDims dw{};
       dw.M = p.V; dw.N = p.H; dw.K = p.Tc; dw.lda = p.Vp; dw.ldb = p.Tc;
       dw.chunk = chunk; dw.dyn = 3; dw.k_round = 256; dw.zero_if_empty = (k == 0); dw.group_m = TuneDW::kBand; dw.a_tiled = dw.b_tiled = 1;
       EpiDW ew{out->d_weight, p.H, p.V, p.H, k > 0 ? 1 : 0};
-      const int tn = (p.H + kBN - 1) / kBN;
-      const int n1 = launch_tiles((p.Tc + kBM - 1) / kBM, tn);
-      const int n2 = launch_tiles((p.V + kBM - 1) / kBM, tn);
       ProfScope ps(RL_PROF_GEMM_BWD, s);
-      gemm_nt_bf16_pair_kernel<EpiDX<T>, TuneDX, EpiDW, TuneDW, true>
-          <<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
+      launch_dx_dw(E, WT, dx, ex, XT, dw, ew, s);
     }
   }
   ProfScope ps(RL_PROF_LOSS, s);
@@ -1164,11 +1173,13 @@ rl_status rl_debug_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t group_m,
   return RL_OK;
 }
 
-rl_status rl_debug_split_k(int32_t tiles, int32_t slabs, int32_t slots, int32_t* slices, int32_t* per) {
-  if (!slices || !per) return RL_ERR_NULL;
-  if (tiles < 1 || slabs < 0 || slots < 1) return RL_ERR_SHAPE;
-  const SplitK k = split_k_host(tiles, slabs, slots);
+rl_status rl_debug_split_k(int32_t tiles_m, int32_t tiles_n, int32_t steps, int32_t slots, int64_t fill, int32_t* slices, int32_t* per,
+                           int32_t* tile_rows) {
+  if (!slices || !per || !tile_rows) return RL_ERR_NULL;
+  if (tiles_m < 1 || tiles_n < 1 || (int64_t)tiles_m * tiles_n > (1 << 24) || steps < 0 || slots < 1 || fill < 0) return RL_ERR_SHAPE;
+  const SplitK k = split_k_host(tiles_m * tiles_n, steps, slots, fill);
   *slices = k.slices; *per = k.per;
+  *tile_rows = (int32_t)split_tile_rows(tiles_m, tiles_n, steps, slots);
   return RL_OK;
 }
 
