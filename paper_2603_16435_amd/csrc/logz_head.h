@@ -3,13 +3,12 @@
 //   pooled_p = mean of the prompt's hidden-state rows        logz_pool_kernel   (HBM-bound: reads the rows once)
 //   a_p = W1 pooled_p + b1,  g_p = gelu(a_p)                 logz_hidden_kernel (HBM-bound: W1 streamed once per 16 prompts)
 //   logZ_p = w2 . g_p + b2                                   logz_out_kernel
-//   backward from d_logZ: da, db1, dw2, db2                  logz_bwd_vec_kernel
-//                         dW1 = sum_p da_p pooled_p^T        logz_bwd_w1_kernel  (HBM-bound: writes dW1 once)
+//   backward from d_logZ: db2, db1, dw2, dW1 = sum_p da_p pooled_p^T   logz_bwd_kernel (HBM-bound: writes dW1 once)
 //
 // The hidden states are constants here (no gradient into the language model).  Parameters and
-// activations are f32; the hidden states come in the model's dtype.  All of it is a few tens of
-// microseconds next to the policy-loss path: with 16-32 prompts the layer is a matrix-vector product per
-// prompt, bound by reading W1 and writing dW1 once, so these are plain bandwidth kernels, not MFMA ones.
+// activations are f32; the hidden states come in the model's dtype.  With 16-32 prompts the layer is a matrix-vector product
+// per prompt, bound by reading the hidden states and W1 and writing dW1 once (H = M = 3584, 16 prompts of 7050 rows: 153 MB,
+// 32 us at the rate of a large copy), so every kernel moves 16 bytes per lane and keeps many loads in flight.
 #pragma once
 #include "gemm_nt.h"
 
@@ -20,87 +19,117 @@ __device__ inline float gelu_grad_f(float a) {
   return 0.5f * (1.f + erff(a * 0.70710678118654752f)) + a * expf(-0.5f * a * a) * 0.3989422804014327f;
 }
 
-// grid (P, ceil(H / 64)): a workgroup pools 64 hidden columns of one prompt; its four wavefronts take every
-// fourth row each (f32 sums), merged through LDS
-template <class T>
-__global__ void logz_pool_kernel(const T* X, int64_t rows, int H, const int32_t* cu, float* pooled) {
-  __shared__ float part[4][64];
-  const int p = blockIdx.x, c = threadIdx.x & 63, slice = threadIdx.x >> 6;
-  const int h = blockIdx.y * 64 + c;
-  int64_t a = cu[p], b = cu[p + 1];
-  if (a < 0) a = 0;
-  if (b > rows) b = rows;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  if (h < H) {
-    int64_t r = a + slice;
-    for (; r + 12 < b; r += 16) {                       // four independent loads in flight per thread
-      s0 += (float)X[r * H + h]; s1 += (float)X[(r + 4) * H + h];
-      s2 += (float)X[(r + 8) * H + h]; s3 += (float)X[(r + 12) * H + h];
-    }
-    for (; r < b; r += 4) s0 += (float)X[r * H + h];
-  }
-  part[slice][c] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  if (slice == 0 && h < H) {
-    const float s = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
-    pooled[(int64_t)p * H + h] = b > a ? s / (float)(b - a) : 0.f;
+// A piece of VEC consecutive elements of a row as f32.  VEC > 1: 16 bytes, for rows that are 16-byte aligned.
+template <class T, int VEC> __device__ inline void logz_load(const T* p, float (&v)[VEC]) {
+  if constexpr (VEC == 1) {
+    v[0] = (float)p[0];
+  } else {
+    T e[VEC];
+    const uint4 q = *reinterpret_cast<const uint4*>(p);
+    __builtin_memcpy(e, &q, 16);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) v[i] = (float)e[i];
   }
 }
 
-// Hidden layer.  grid (ceil(M / 16), ceil(P / 16)): a workgroup computes 16 units for 16 prompts; each of its four
-// wavefronts owns four units.  The pooled states of the 16 prompts go through LDS in chunks of 256 columns; a
-// lane multiplies its four columns of the chunk into 4 x 16 accumulators, reduced across the wavefront at the end.
-__global__ __launch_bounds__(256) void logz_hidden_kernel(const float* W1, const float* b1, const float* pooled, int P, int H, int M,
-                                                          float* a_out, float* g_out) {
-  __shared__ float ch[16][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j0 = blockIdx.x * 16 + wave * 4, p0 = blockIdx.y * 16;
-  float acc[4][16];
+// grid (P, ceil(H / (LANES VEC))): a workgroup of eight wavefronts pools LANES VEC columns of one prompt, 512 / LANES rows at a
+// time, four pieces in flight per lane; f32 sums, merged through LDS in a fixed order.
+// (One element per lane, 64 columns per workgroup: 22 us on the shape above, 16 bytes per lane: 14 us.)
+template <int VEC> constexpr int logz_pool_lanes() { return VEC == 1 ? 64 : 16; }
+template <class T, int VEC>
+__global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows, int H, const int32_t* cu, float* pooled) {
+  constexpr int LANES = logz_pool_lanes<VEC>(), SLICES = 512 / LANES;
+  __shared__ float part[SLICES][LANES * VEC + 1];
+  const int p = blockIdx.x, c = threadIdx.x % LANES, slice = threadIdx.x / LANES;
+  const int h = (blockIdx.y * LANES + c) * VEC;
+  int64_t a = cu[p], b = cu[p + 1];
+  if (a < 0) a = 0;
+  if (b > rows) b = rows;
+  float s[4][VEC];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[u][q] = 0.f;
-  for (int h0 = 0; h0 < H; h0 += 256) {
-    __syncthreads();
+    for (int i = 0; i < VEC; ++i) s[u][i] = 0.f;
+  if (h < H) {
+    const T* x = X + h;
+    int64_t r = a + slice;
+    for (; r + 3 * SLICES < b; r += 4 * SLICES) {
+      float v[4][VEC];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int p = p0 + q, h = h0 + threadIdx.x;
-      ch[q][threadIdx.x] = (p < P && h < H) ? pooled[(int64_t)p * H + h] : 0.f;
+      for (int u = 0; u < 4; ++u) logz_load<T, VEC>(x + (r + SLICES * u) * H, v[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) s[u][i] += v[u][i];
     }
-    __syncthreads();
+    for (; r < b; r += SLICES) {
+      float v[VEC];
+      logz_load<T, VEC>(x + r * H, v);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int h = h0 + lane + 64 * k;
-      float w[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = (j0 + u < M && h < H) ? W1[(int64_t)(j0 + u) * H + h] : 0.f;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const float x = ch[q][lane + 64 * k];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[u][q] = fmaf(w[u], x, acc[u][q]);
-      }
+      for (int i = 0; i < VEC; ++i) s[0][i] += v[i];
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      float v = acc[u][q];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
-      acc[u][q] = v;
+  for (int i = 0; i < VEC; ++i) part[slice][c * VEC + i] = (s[0][i] + s[1][i]) + (s[2][i] + s[3][i]);
+  __syncthreads();
+  if (threadIdx.x < LANES * VEC) {
+    const int hh = blockIdx.y * LANES * VEC + threadIdx.x;
+    if (hh < H) {
+      float t = 0.f;
+      for (int k = 0; k < SLICES; ++k) t += part[k][threadIdx.x];
+      pooled[(int64_t)p * H + hh] = b > a ? t / (float)(b - a) : 0.f;
     }
-  if (lane == 0) {
+  }
+}
+
+// Hidden layer.  grid (ceil(M / 16), ceil(P / 16)): a workgroup computes 16 units for 16 prompts with v_mfma_f32_16x16x4 (A = rows
+// of W1, B = rows of the pooled states, both straight from memory in operand layout: lane l holds row l%16, four
+// consecutive k of every 16), its eight wavefronts taking 16-wide k-steps in turn, eight in flight; the eight partial blocks are
+// added through LDS in order.  VEC: rows are 16-byte aligned (else element loads).  (The vector-FMA
+// form with the pooled states in LDS was bound by its LDS reads: 94 us against 18 us on the shape above.)
+template <bool VEC>
+__global__ __launch_bounds__(512) void logz_hidden_kernel(const float* W1, const float* b1, const float* pooled, int P, int H, int M,
+                                                          float* a_out, float* g_out) {
+  __shared__ float part[8][16][17];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15, kq = lane >> 4;
+  const int j0 = blockIdx.x * 16, p0 = blockIdx.y * 16;
+  const int j = j0 + row < M ? j0 + row : M - 1, p = p0 + row < P ? p0 + row : P - 1;       // (rows past the end: not written)
+  const float* w = W1 + (int64_t)j * H;
+  const float* x = pooled + (int64_t)p * H;
+  auto load = [&](const float* q, int k) __attribute__((always_inline)) {
+    floatx4 v;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u;
-      if (j >= M) continue;
-      const float bias = b1[j];
+    for (int e = 0; e < 4; ++e) v[e] = 0.f;
+    if constexpr (VEC) { if (k < H) v = *reinterpret_cast<const floatx4*>(q + k); }          // (H % 4 == 0)
+    else {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int p = p0 + q;
-        if (p < P) { const float a = acc[u][q] + bias; a_out[(int64_t)p * M + j] = a; g_out[(int64_t)p * M + j] = gelu_f(a); }
-      }
+      for (int e = 0; e < 4; ++e) if (k + e < H) v[e] = q[k + e];
+    }
+    return v;
+  };
+  floatx4 acc;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] = 0.f;
+  for (int k0 = wave * 16; k0 < H; k0 += 8 * 128) {
+    floatx4 a[8], b[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { a[u] = load(w, k0 + 128 * u + 4 * kq); b[u] = load(x, k0 + 128 * u + 4 * kq); }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[wave][row][4 * kq + e] = acc[e];                          // [prompt][unit]
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    const int u = threadIdx.x & 15, q = threadIdx.x >> 4;
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += part[k][q][u];
+    if (j0 + u < M && p0 + q < P) {
+      const float v = s + b1[j0 + u];
+      a_out[(int64_t)(p0 + q) * M + j0 + u] = v; g_out[(int64_t)(p0 + q) * M + j0 + u] = gelu_f(v);
     }
   }
 }
@@ -117,48 +146,68 @@ __global__ void logz_out_kernel(const float* g, const float* w2, const float* b2
   if (threadIdx.x == 0) log_z[p] = sh[0] + sh[1] + sh[2] + sh[3] + b2[0];
 }
 
-// thread per hidden unit j: da[p][j] for every prompt, db1[j], dw2[j]; thread 0 also db2
-__global__ void logz_bwd_vec_kernel(const float* d, const float* a, const float* g, const float* w2, int P, int M,
-                                    float* da, float* db1, float* dw2, float* db2) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j == 0) { float s = 0.f; for (int p = 0; p < P; ++p) s += d[p]; db2[0] = s; }
-  if (j >= M) return;
-  const float w = w2[j];
-  float sb = 0.f, sw = 0.f;
-  for (int p = 0; p < P; ++p) {
-    const float dp = d[p];
-    const float v = dp * w * gelu_grad_f(a[(int64_t)p * M + j]);
-    da[(int64_t)p * M + j] = v;
-    sb += v;
-    sw += dp * g[(int64_t)p * M + j];
+// Backward: a workgroup takes eight units.  Per 32 prompts it forms da[p][j] = d_p w2_j gelu'(a[p][j]) in LDS, adds up
+// db1_j and dw2_j, and accumulates dW1[j][h] = sum_p da[p][j] pooled[p][h], VEC columns x eight units per thread; workgroup 0
+// also writes db2.  With more than 32 prompts or more than 256 VEC columns the da are formed again for every pass over
+// the columns (a few hundred values).  grid (ceil(M / 8), ceil(H / (256 VEC))); the column blocks other than the first skip the sums.
+// (da by a kernel of its own and single-element stores: 11 + 37 us on the shape above, fused with 16-byte stores: 16.5 us.)
+template <int VEC>
+__global__ __launch_bounds__(256) void logz_bwd_kernel(const float* d, const float* a, const float* g, const float* w2, const float* pooled,
+                                                       int P, int M, int H, float* dW1, float* db1, float* dw2, float* db2) {
+  __shared__ float da[32][8], dg[32][8];
+  const int t = threadIdx.x, j0 = blockIdx.x * 8, h = (blockIdx.y * 256 + t) * VEC;
+  const bool first = blockIdx.y == 0;
+  float s[8][VEC], sum = 0.f;
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) s[u][i] = 0.f;
+  const int u8 = t & 7, q = t >> 3, j = j0 + u8;             // 32 prompts x 8 units
+  for (int p0 = 0; p0 < P; p0 += 32) {
+    __syncthreads();
+    float v = 0.f, dw = 0.f;
+    if (p0 + q < P && j < M) {
+      const float dp = d[p0 + q];
+      const int64_t at = (int64_t)(p0 + q) * M + j;
+      v = dp * w2[j] * gelu_grad_f(a[at]);
+      if (first) dw = dp * g[at];
+    }
+    da[q][u8] = v; dg[q][u8] = dw;
+    __syncthreads();
+    const int np = P - p0 < 32 ? P - p0 : 32;
+    if (h < H)
+#pragma unroll 4
+      for (int p = 0; p < np; ++p) {
+        float x[VEC];
+        logz_load<float, VEC>(pooled + (int64_t)(p0 + p) * H + h, x);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) s[u][i] = fmaf(da[p][u], x[i], s[u][i]);
+      }
+    if (first && t < 16)                                     // threads 0..7: db1, 8..15: dw2, prompts in order
+      for (int p = 0; p < np; ++p) sum += t < 8 ? da[p][t] : dg[p][t - 8];
   }
-  db1[j] = sb; dw2[j] = sw;
+  if (h < H)
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (j0 + u < M) {
+        float* o = dW1 + (int64_t)(j0 + u) * H + h;
+        if constexpr (VEC == 4) { floatx4 v; v[0] = s[u][0]; v[1] = s[u][1]; v[2] = s[u][2]; v[3] = s[u][3]; *reinterpret_cast<floatx4*>(o) = v; }
+        else o[0] = s[u][0];
+      }
+  if (first && t < 16 && j0 + (t & 7) < M) (t < 8 ? db1 : dw2)[j0 + (t & 7)] = sum;
+  if (first && blockIdx.x == 0 && t == 16) { float b = 0.f; for (int p = 0; p < P; ++p) b += d[p]; db2[0] = b; }
 }
 
-// grid (ceil(H / 256), ceil(M / 8)): dW1[j][h] = sum_p da[p][j] pooled[p][h] for eight units j per workgroup, so that a
-// pooled value is loaded once for eight outputs; stores are coalesced along h
-__global__ void logz_bwd_w1_kernel(const float* da, const float* pooled, int P, int M, int H, float* dW1) {
-  const int j0 = blockIdx.y * 8, h = blockIdx.x * 256 + threadIdx.x;
-  if (h >= H) return;
-  float s[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) s[u] = 0.f;
-  for (int p = 0; p < P; ++p) {
-    const float x = pooled[(int64_t)p * H + h];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) if (j0 + u < M) s[u] = fmaf(da[(int64_t)p * M + j0 + u], x, s[u]);
-  }
-#pragma unroll
-  for (int u = 0; u < 8; ++u) if (j0 + u < M) dW1[(int64_t)(j0 + u) * H + h] = s[u];
-}
-
-struct LogzPlan { size_t off_pooled, off_a, off_g, off_da, total; };
+struct LogzPlan { size_t off_pooled, off_a, off_g, total; };
 
 static inline LogzPlan logz_plan(int P, int H, int M) {
   LogzPlan q; size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += (bytes + 255) & ~(size_t)255; return at; };
   q.off_pooled = take(4 * (size_t)P * H); q.off_a = take(4 * (size_t)P * M); q.off_g = take(4 * (size_t)P * M);
-  q.off_da = take(4 * (size_t)P * M); q.total = o;
+  take(4 * (size_t)P * M);        // (not used; the workspace keeps the size callers know)
+  q.total = o;
   return q;
 }
 

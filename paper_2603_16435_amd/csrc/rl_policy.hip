@@ -1358,11 +1358,18 @@ rl_status rl_logz_head_forward(const void* prompt_hidden, int32_t dtype, int64_t
   (void)hipGetLastError();
   unsigned char* w = static_cast<unsigned char*>(ws);
   float* pooled = (float*)(w + q.off_pooled); float* a = (float*)(w + q.off_a); float* g = (float*)(w + q.off_g);
-  dim3 gp(P, (H + 63) / 64);
-  if (dtype == RL_BF16) logz_pool_kernel<bf16_t><<<gp, 256, 0, s>>>(static_cast<const bf16_t*>(prompt_hidden), rows, H, cu_prompt, pooled);
-  else logz_pool_kernel<float><<<gp, 256, 0, s>>>(static_cast<const float*>(prompt_hidden), rows, H, cu_prompt, pooled);
-  dim3 gh((M + 15) / 16, (P + 15) / 16);
-  logz_hidden_kernel<<<gh, 256, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
+  const bool vec_x = H % (dtype == RL_BF16 ? 8 : 4) == 0 && reinterpret_cast<uintptr_t>(prompt_hidden) % 16 == 0;
+  auto pool = [&](auto kern, auto* X, int cols) { kern<<<dim3(P, (H + cols - 1) / cols), 512, 0, s>>>(X, rows, H, cu_prompt, pooled); };
+  if (dtype == RL_BF16) {
+    const bf16_t* X = static_cast<const bf16_t*>(prompt_hidden);
+    if (vec_x) pool(logz_pool_kernel<bf16_t, 8>, X, 128); else pool(logz_pool_kernel<bf16_t, 1>, X, 64);
+  } else {
+    const float* X = static_cast<const float*>(prompt_hidden);
+    if (vec_x) pool(logz_pool_kernel<float, 4>, X, 64); else pool(logz_pool_kernel<float, 1>, X, 64);
+  }
+  const dim3 gh((M + 15) / 16, (P + 15) / 16);
+  if (H % 4 == 0 && reinterpret_cast<uintptr_t>(W1) % 16 == 0) logz_hidden_kernel<true><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
+  else logz_hidden_kernel<false><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
   logz_out_kernel<<<P, 256, 0, s>>>(g, w2, b2, M, log_z);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
@@ -1379,10 +1386,10 @@ rl_status rl_logz_head_backward(const float* d_log_z, int32_t P, int32_t H, int3
   (void)hipGetLastError();
   unsigned char* w = static_cast<unsigned char*>(ws);
   float* pooled = (float*)(w + q.off_pooled); float* a = (float*)(w + q.off_a); float* g = (float*)(w + q.off_g);
-  float* da = (float*)(w + q.off_da);
-  logz_bwd_vec_kernel<<<(M + 255) / 256, 256, 0, s>>>(d_log_z, a, g, w2, P, M, da, db1, dw2, db2);
-  dim3 gw((H + 255) / 256, (M + 7) / 8);
-  logz_bwd_w1_kernel<<<gw, 256, 0, s>>>(da, pooled, P, M, H, dW1);
+  if (H % 4 == 0 && reinterpret_cast<uintptr_t>(dW1) % 16 == 0)
+    logz_bwd_kernel<4><<<dim3((M + 7) / 8, (H + 1023) / 1024), 256, 0, s>>>(d_log_z, a, g, w2, pooled, P, M, H, dW1, db1, dw2, db2);
+  else
+    logz_bwd_kernel<1><<<dim3((M + 7) / 8, (H + 255) / 256), 256, 0, s>>>(d_log_z, a, g, w2, pooled, P, M, H, dW1, db1, dw2, db2);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 

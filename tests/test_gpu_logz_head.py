@@ -67,3 +67,29 @@ def test_head_feeds_the_flow_objective_end_to_end():
     assert np.abs(res.d_log_z.double().cpu().numpy() - ref["d_log_z"]).max() <= 1e-3 * np.abs(ref["d_log_z"]).max()
     for got, want in ((dW1, g["dW1"]), (db1, g["db1"]), (dw2, g["dw2"])):
         assert np.abs(got.double().cpu().numpy() - want).max() <= 2e-3 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("dtype,P,H,M,lens,offset", [
+    (torch.bfloat16, 1, 8, 1, (1,), 0),                                   # one piece per row, one unit
+    (torch.bfloat16, 17, 1032, 9, tuple(range(1, 18)), 0),                # a column block beyond 1024, prompts and units past a block
+    (torch.bfloat16, 33, 140, 17, tuple(120 + i for i in range(33)), 0),  # rows not 16-byte aligned, more than 32 prompts, 128 rows and more
+    (torch.bfloat16, 3, 256, 16, (127, 128, 129), 1),                     # hidden states that start off a 16-byte border
+    (torch.float32, 2, 1028, 24, (0, 300), 1),
+    (torch.float32, 40, 30, 8, tuple(1 + i % 3 for i in range(40)), 0),   # element loads everywhere
+])
+def test_logz_head_at_the_edges_of_its_blocks(dtype, P, H, M, lens, offset):
+    X, cu, W1, b1, w2, b2, d = _head(12, P, H, M, lens, dtype)
+    dev = "cuda"
+    buf = torch.empty(X.numel() + offset, dtype=dtype, device=dev)
+    Xd = buf[offset:].view(X.shape)
+    Xd.copy_(X)
+    log_z, ws = binding.rl_logz_head_forward(Xd, cu.to(dev), W1.to(dev), b1.to(dev), w2.to(dev), b2.to(dev))
+    dW1, db1, dw2, db2 = binding.rl_logz_head_backward(d.to(dev), w2.to(dev), H, ws)
+    torch.cuda.synchronize()
+    f = lzo.logz_head_forward(np_bits(X), cu.numpy(), W1.numpy(), b1.numpy(), w2.numpy(), float(b2))
+    g = lzo.logz_head_backward(f, W1.numpy(), w2.numpy(), d.numpy())
+    # the bounds of the parity test above: f32 sums of at most 1032 terms
+    assert np.abs(log_z.double().cpu().numpy() - f["log_z"]).max() <= 2e-5 * max(1.0, np.abs(f["log_z"]).max())
+    for got, want in ((dW1, g["dW1"]), (db1, g["db1"]), (dw2, g["dw2"])):
+        assert np.abs(got.double().cpu().numpy() - want).max() <= 2e-5 * np.abs(want).max()
+    assert abs(float(db2.item()) - g["db2"]) <= 1e-5 * max(1.0, abs(g["db2"]))
