@@ -1,0 +1,216 @@
+// rvq_few.h - residual-VQ encode of a few vectors per codebook group (a decode step: one vector per sequence of the batch).
+//
+// The codes are those of rvq_encode.h (the float64 arg-min of the definition, lowest index on ties, bf16 residual between the
+// stages); with up to 32 vectors of a group the work is reading the codebooks once (256 groups x 16 stages x 512 entries:
+// 547 MB, 115 us at the rate of a large copy), and the kernel written for 256 and more vectors spends its time scoring copies
+// of the few there are (313 us).  Here a workgroup takes 16 NV vectors of one group:
+//  * Four scoring wavefronts share the entries of a stage (blocks of 16 in turn).  They read the codebook straight from memory
+//    in MFMA operand layout (A = 16 entries, B = 16 vectors, -|c|^2/2 as the start of the accumulator), 64 entries each at a time,
+//    and always have the next 64 on their way, also across the end of a stage: the codebook does not depend on the codes.
+//  * The scores of a stage stay in LDS.  When all are there, every lane compares its own with the vector's largest and lists the
+//    entries within the margin (twice the bound on a float32 score's error, see rvq_encode.h); only those can be the exact arg-min.
+//  * A fifth wavefront settles the stage: one entry listed is the code; several are evaluated in float64 from the stored values,
+//    and if more were listed than the list holds, all entries are.  It also fetches the chosen entries for the
+//    residual update.  It is a wavefront of its own because a wait for these loads would wait for all loads issued
+//    before them too: the scoring wavefronts' loads of the next stage stay in flight meanwhile.
+// Three workgroup barriers per stage, written out (lgkmcnt only) so that they do not wait for loads in flight.
+#pragma once
+#include "rvq_encode.h"
+
+namespace rlk {
+
+constexpr int kRvqFewScoreBytes = 128 * 1024;                     // scores of one stage: 64 NV bytes per entry
+constexpr int kRvqFewList = 32;
+__host__ __device__ constexpr int rvq_few_max_entries(int nv) { return kRvqFewScoreBytes / (64 * nv); }
+
+__device__ __attribute__((always_inline)) inline void rvq_few_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// grid as for rvq_encode_kernel with 16 NV vectors per workgroup; S % 64 == 0, S <= rvq_few_max_entries(NV)
+template <int NV>
+__global__ __launch_bounds__(320, 1)
+void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb, const float* __restrict__ cn,
+                    int G, int L, int N, int S, int32_t* __restrict__ codes, bf16_t* __restrict__ residual, int32_t* __restrict__ stats) {
+  constexpr int VECS = 16 * NV, U = 4;                            // U: blocks per scoring wavefront and round (64 entries)
+  __shared__ floatx4 score[kRvqFewScoreBytes / 16];               // [round][block of the wavefront][vector block][wavefront, lane]
+  __shared__ u32x4_t bits[VECS][kRvqD / 8], rows[VECS][kRvqD / 8]; // the vectors as stored; the chosen entries
+  __shared__ float top[4][VECS], cmx[4];
+  __shared__ int count[VECS], cand[VECS][kRvqFewList];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int e16 = lane & 15, kq = lane >> 4;
+  const int w = blockIdx.x, gx = (L + VECS - 1) / VECS;
+  const int g = 8 * ((w >> 3) / gx) + (w & 7);
+  if (g >= G) return;                                             // (the whole workgroup)
+  const int v0 = ((w >> 3) % gx) * VECS;
+  x += (int64_t)g * L * kRvqD; codes += (int64_t)g * L * N;
+  cb += (int64_t)g * N * S * kRvqD; cn += (int64_t)g * N * S;
+  if (residual) residual += (int64_t)g * L * kRvqD;
+
+  const int nblk = S / 16, rounds = (nblk + 4 * U - 1) / (4 * U), total = N * rounds;
+  const bool scoring = wave < 4;
+  u32x4_t ra[NV][4];                                              // [vector block][k-step]: vector l%16, k = 32 ks + 8 (l/16) .. +7
+  float rn2[NV];
+  u32x4_t nx[U][4];                                               // the next round's entries and squared norms
+  floatx4 nn[U];
+  // round t of the whole walk: block 16 r + 4 u + wave of stage t / rounds (past the stage's end: its last block, not used)
+  auto fetch = [&](int stage, int r) __attribute__((always_inline)) {
+    const bf16_t* scb = cb + (int64_t)stage * S * kRvqD;
+    const float* scn = cn + (int64_t)stage * S;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int blk = r * 4 * U + u * 4 + wave; blk = blk < nblk ? blk : nblk - 1;
+      const bf16_t* ent = scb + (int64_t)(blk * 16 + e16) * kRvqD + kq * 8;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) nx[u][ks] = *reinterpret_cast<const u32x4_t*>(ent + ks * 32);
+      nn[u] = *reinterpret_cast<const floatx4*>(scn + blk * 16 + 4 * kq);
+    }
+  };
+  if (scoring) {
+    fetch(0, 0);
+#pragma unroll
+    for (int b = 0; b < NV; ++b) {
+      int v = v0 + b * 16 + e16; v = v < L ? v : L - 1;
+      float a = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        ra[b][ks] = *reinterpret_cast<const u32x4_t*>(x + (int64_t)v * kRvqD + ks * 32 + kq * 8);
+        a = rvq_sumsq(ra[b][ks], a);
+        if (wave == 0) bits[b * 16 + e16][ks * 4 + kq] = ra[b][ks];
+      }
+      rn2[b] = rvq_sum4(a);
+    }
+  }
+  if (tid < VECS) count[tid] = 0;                                 // (the first append comes after the first barrier)
+
+  const float NEG = -__builtin_inff();
+  for (int stage = 0; stage < N; ++stage) {
+    if (scoring) {
+      float mx[NV], cm = 0.f;
+#pragma unroll
+      for (int b = 0; b < NV; ++b) mx[b] = NEG;
+      for (int r = 0; r < rounds; ++r) {
+        floatx4 acc[U][NV];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          floatx4 h;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { cm = fmaxf(cm, nn[u][e]); h[e] = -0.5f * nn[u][e]; }
+#pragma unroll
+          for (int b = 0; b < NV; ++b) {
+            acc[u][b] = h;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+              acc[u][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, nx[u][ks]), __builtin_bit_cast(bf16x8, ra[b][ks]), acc[u][b], 0, 0, 0);
+          }
+        }
+        {                                                         // the next round, perhaps of the next stage, into the same registers
+          const int t = stage * rounds + r + 1;
+          if (t < total) fetch(r + 1 < rounds ? stage : stage + 1, r + 1 < rounds ? r + 1 : 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (r * 4 * U + u * 4 + wave < nblk) {                  // (uniform)
+#pragma unroll
+            for (int b = 0; b < NV; ++b) {
+              score[((r * U + u) * NV + b) * 256 + tid] = acc[u][b];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) mx[b] = fmaxf(mx[b], acc[u][b][e]);
+            }
+          }
+      }
+#pragma unroll
+      for (int b = 0; b < NV; ++b) {
+        const float m = rvq_max4(mx[b]);
+        if (kq == 0) top[wave][b * 16 + e16] = m;
+      }
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) cm = fmaxf(cm, __shfl_xor(cm, o));
+      if (lane == 0) cmx[wave] = cm;
+    }
+    rvq_few_barrier();
+    if (scoring) {                                                // list the entries that come within the margin of the largest score
+      const float cm = fmaxf(fmaxf(cmx[0], cmx[1]), fmaxf(cmx[2], cmx[3]));
+#pragma unroll
+      for (int b = 0; b < NV; ++b) {
+        const int v = b * 16 + e16;
+        const float best = fmaxf(fmaxf(top[0][v], top[1][v]), fmaxf(top[2][v], top[3][v]));
+        const float margin = kRvqGamma2 * (sqrtf(rn2[b] * 1.02f * cm) + 0.5f * cm);     // (1.02: rn2 is known to one part in 2^7)
+        for (int q = 0; q < rounds * U; ++q) {
+          const int blk = q * 4 + wave;
+          if (blk >= nblk) break;
+          const floatx4 s = score[(q * NV + b) * 256 + tid];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (!(best - s[e] > margin)) {
+              const int pos = atomicAdd(&count[v], 1);
+              if (pos < kRvqFewList) cand[v][pos] = blk * 16 + 4 * kq + e;
+            }
+        }
+      }
+    }
+    rvq_few_barrier();
+    if (!scoring) {                                               // settle the stage: lane v answers for vector v
+      const bf16_t* stage_cb = cb + (int64_t)stage * S * kRvqD;
+      const int v = lane < VECS ? lane : VECS - 1;
+      const int n = count[v];
+      int z = n > 0 ? cand[v][0] : 0;                             // (no entry listed: no score of the stage was a number)
+      unsigned long long open = __ballot(lane < VECS && v0 + lane < L && n != 1);
+      if (stats && lane == 0 && open) atomicAdd(stats, __builtin_popcountll(open));
+      while (open) {
+        const int q = __builtin_ctzll(open);
+        open &= open - 1;
+        const int listed = count[q], m = listed > kRvqFewList ? S : listed;
+        double dmin = __builtin_inf();
+        int imin = 0x7fffffff;
+        for (int i = 0; i < m; i += 4) {                          // four entries at a time, one per 16 lanes
+          int ent = -1;
+          if (i + kq < m) ent = listed > kRvqFewList ? i + kq : cand[q][i + kq];
+          const double d = rvq_exact_distance16(&bits[q][0], stage_cb, ent, e16);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const double dk = __shfl(d, 16 * k);
+            const int ek = __shfl(ent, 16 * k);
+            if (ek >= 0 && (dk < dmin || (dk == dmin && ek < imin))) { dmin = dk; imin = ek; }
+          }
+        }
+        if (imin < S && lane == q) z = imin;
+      }
+      if (lane < VECS) {
+        count[lane] = 0;
+        if (v0 + lane < L) codes[(int64_t)(v0 + lane) * N + stage] = z;
+      }
+      u32x4_t c[VECS / 4];                                        // a quarter of the wavefront per entry
+#pragma unroll
+      for (int i = 0; i < VECS / 4; ++i) {
+        const int zi = __shfl(z, 4 * i + kq);
+        c[i] = *reinterpret_cast<const u32x4_t*>(stage_cb + (int64_t)zi * kRvqD + 8 * e16);
+      }
+#pragma unroll
+      for (int i = 0; i < VECS / 4; ++i) rows[4 * i + kq][e16] = c[i];
+    }
+    rvq_few_barrier();
+    if (scoring) {
+#pragma unroll
+      for (int b = 0; b < NV; ++b) {
+        float a = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          ra[b][ks] = rvq_sub_bf16(ra[b][ks], rows[b * 16 + e16][ks * 4 + kq], a);
+          if (wave == 0) bits[b * 16 + e16][ks * 4 + kq] = ra[b][ks];       // (read again after two more barriers)
+        }
+        rn2[b] = rvq_sum4(a);
+      }
+    }
+  }
+  if (residual && wave == 0) {
+#pragma unroll
+    for (int b = 0; b < NV; ++b) {
+      const int v = v0 + b * 16 + e16;
+      if (v < L) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) *reinterpret_cast<u32x4_t*>(residual + (int64_t)v * kRvqD + ks * 32 + kq * 8) = ra[b][ks];
+      }
+    }
+  }
+}
+
+}  // namespace rlk

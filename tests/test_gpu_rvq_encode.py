@@ -128,3 +128,49 @@ def test_rvq_encode_exact_path_is_rare_on_ordinary_inputs():
     n = int(n_exact.item())
     print("decisions re-evaluated exactly:", n, "of", G * L * N)
     assert n <= 0.01 * G * L * N
+
+
+@pytest.mark.parametrize("G,L,N,S", [
+    (1, 1, 2, 64),            # one vector, one block per wavefront
+    (9, 12, 16, 512),         # a decode step; 9 groups (the grid covers 16)
+    (2, 16, 3, 320),          # a full vector block, a second round of which only one block per wavefront exists
+    (1, 16, 2, 2048),         # the largest codebook of the 16-vector form
+    (1, 16, 2, 2112),         # ... and one beyond it
+    (2, 17, 3, 192),          # 32-vector form, one vector in the second block
+    (1, 64, 2, 1024),         # two workgroups of a group, the largest codebook of that form
+    (1, 33, 2, 1088),         # ... and one beyond it
+    (2, 65, 2, 128),          # three workgroups of each of two groups
+    (130, 33, 1, 64),         # more workgroups than fit the chip
+    (88, 65, 1, 64),          # three workgroups of each of eleven groups per die: one more than that form takes
+    (1, 1024, 2, 64),         # 32 workgroups on one die ...
+    (1, 1025, 2, 64),         # ... and one more
+])
+def test_rvq_encode_of_few_vectors(G, L, N, S):
+    x, cb = synth.make_rvq_case(G, L, N, S, device="cuda", seed=0x5EED0300)
+    for want_residual in (True, False):
+        codes, res = binding.rl_rvq_encode(x, cb, want_residual=want_residual)
+        torch.cuda.synchronize()
+        if want_residual:
+            print(_compare(x, cb, codes, res))
+            first = codes
+    np.testing.assert_array_equal(codes.cpu().numpy(), first.cpu().numpy())
+
+
+@pytest.mark.parametrize("L", [5, 30])
+def test_rvq_encode_of_few_vectors_settles_near_and_equal_entries_exactly(L):
+    """Stage 0: pairs 2^-20 apart, which float32 cannot order; stage 1: 200 equal entries among 256, more than a list of
+    candidates holds; stage 2: every entry the same (code 0)."""
+    x, cb = synth.make_rvq_case(1, L, 3, 256, seed=0x5EED0400, device="cuda")
+    cb = cb.clone()
+    cb[:, 0, 0::2, 0] = 0
+    cb[:, 0, 1::2, :] = cb[:, 0, 0::2, :]
+    cb[:, 0, 1::2, 0] = 2.0 ** -20
+    cb[:, 1, 40:240] = 0
+    cb[:, 2] = cb[:, 2, :1]
+    n_exact = torch.zeros(1, dtype=torch.int32, device="cuda")
+    codes, res = binding.rl_rvq_encode(x, cb, count_exact=n_exact)
+    torch.cuda.synchronize()
+    want, want_res = rvq.rvq_encode(_bits(x[0]), _bits(cb[0]))
+    np.testing.assert_array_equal(codes[0].cpu().numpy(), want)
+    np.testing.assert_array_equal(_bits(res[0]), want_res)
+    assert bool((codes[0, :, 2] == 0).all()) and int(n_exact.item()) >= 2 * L
