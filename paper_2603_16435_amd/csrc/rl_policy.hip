@@ -96,21 +96,6 @@ __device__ inline int wave_prefix_count(bool flag, int lane, int& total) {
   return __popcll(b & ((1ull << lane) - 1ull));
 }
 
-template <class V>
-__global__ void fill_kernel(V* p, int64_t n, V v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-  for (; i < n; i += step) p[i] = v;
-}
-
-template <class V>
-static void fill(V* p, int64_t n, V v, hipStream_t s) {
-  if (!p || n <= 0) return;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  fill_kernel<V><<<(int)blocks, 256, 0, s>>>(p, n, v);
-}
-
 __device__ inline double block_sum(double v, double* sh) {   // blockDim.x multiple of 64, <= 1024
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -124,35 +109,87 @@ __device__ inline double block_sum(double v, double* sh) {   // blockDim.x multi
 }
 
 // ------------------------------------------------------------------ prep
-// Inclusive running maximum of the sequence offsets, hi[i] = max(cu[0..i]) for i < B (single workgroup of 1024).
-// A sequence keeps its rows only if its first offset is not below any earlier offset: the kept row ranges are then
-// pairwise disjoint whatever the offsets are, so no row can count twice and the compacted rows never exceed R.
-__global__ void cu_running_max_kernel(const int32_t* cu, int B, int32_t* hi) {
-  __shared__ int wmax[16];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = INT32_MIN;
-  __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int base = 0; base < B; base += 1024) {
-    const int i = base + threadIdx.x;
-    int x = i < B ? cu[i] : INT32_MIN;
-    for (int o = 1; o < 64; o <<= 1) { const int y = __shfl_up(x, o); if (lane >= o) x = max(x, y); }
-    if (lane == 63) wmax[w] = x;
-    __syncthreads();
-    int m = carry;
-    for (int k = 0; k < w; ++k) m = max(m, wmax[k]);
-    x = max(x, m);
-    if (i < B) hi[i] = x;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry = x;
-    __syncthreads();
+// Everything the call needs cleared or worked out before the rows are looked at, in one launch (a call on a few hundred tokens is
+// bound by its launches: nine fills, the advantages and the running maximum were 11 of 27).
+//   workgroup 0:     inclusive running maximum of the sequence offsets, hi[i] = max(cu[0..i]) for i < B.  A sequence keeps its rows
+//                    only if its first offset is not below any earlier offset: the kept row ranges are then pairwise disjoint
+//                    whatever the offsets are, so no row can count twice and the compacted rows never exceed R.
+//   the next adv.blocks:  group advantages
+//   the rest:        row outputs to zero / -1
+struct RowFill { int32_t* p[8]; int v[8]; };       // arrays of R words and the value of each (NULL: skipped)
+struct AdvJob {
+  int blocks; const float* rewards; const int32_t* group_idx; int P; float adv_eps; int ddof;
+  float* adv; float* adv_out; int32_t* group_count;
+};
+constexpr int kInitThreads = 256;
+
+// Thread per prompt p: mean and std of the rewards of its members, then A_i for each member (prompt indices and rewards
+// pass through LDS, members in order).  Sequences that name no prompt get 0.
+__device__ inline void advantages_of_block(int blk, int B, const AdvJob& a, int* sh_g, float* sh_r) {
+  const int t = threadIdx.x, p = blk * kInitThreads + t;
+  int n = 0; double s = 0.0, q = 0.0, mu = 0.0, inv = 0.0;
+  for (int pass = 0; pass < 3; ++pass) {
+    if (pass == 1) mu = n ? s / n : 0.0;
+    if (pass == 2 && n - a.ddof > 0) inv = 1.0 / (sqrt(q / (n - a.ddof)) + (double)a.adv_eps);
+    for (int base = 0; base < B; base += kInitThreads) {
+      __syncthreads();
+      if (base + t < B) {
+        const int g = a.group_idx[base + t];
+        sh_g[t] = g; sh_r[t] = a.rewards[base + t];
+        if (pass == 0 && blk == 0 && (g < 0 || g >= a.P)) { a.adv[base + t] = 0.f; if (a.adv_out) a.adv_out[base + t] = 0.f; }
+      }
+      __syncthreads();
+      const int m = B - base < kInitThreads ? B - base : kInitThreads;
+      for (int i = 0; i < m; ++i)
+        if (sh_g[i] == p) {
+          const double r = (double)sh_r[i];
+          if (pass == 0) { ++n; s += r; }
+          else if (pass == 1) q += (r - mu) * (r - mu);
+          else if (p < a.P) {
+            const float A = (float)((r - mu) * inv);
+            a.adv[base + i] = A;
+            if (a.adv_out) a.adv_out[base + i] = A;
+          }
+        }
+    }
+  }
+  if (p < a.P && a.group_count) a.group_count[p] = n;
+}
+
+__global__ __launch_bounds__(kInitThreads) void prep_init_kernel(const int32_t* cu, int B, int64_t R, int32_t* hi, RowFill f, AdvJob adv, rl_stats* stats) {
+  __shared__ int sh_i[kInitThreads];
+  __shared__ float sh_f[kInitThreads];
+  const int t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    if (stats && t < (int)(sizeof(rl_stats) / 4)) reinterpret_cast<int32_t*>(stats)[t] = 0;
+    const int lane = t & 63, w = t >> 6;
+    int carry = INT32_MIN;
+    for (int base = 0; base < B; base += kInitThreads) {
+      const int i = base + t;
+      int x = i < B ? cu[i] : INT32_MIN;
+      for (int o = 1; o < 64; o <<= 1) { const int y = __shfl_up(x, o); if (lane >= o) x = max(x, y); }
+      if (lane == 63) sh_i[w] = x;
+      __syncthreads();
+      int all = carry;
+      for (int k = 0; k < kInitThreads / 64; ++k) { if (k < w) x = max(x, sh_i[k]); all = max(all, sh_i[k]); }
+      if (i < B) hi[i] = max(x, carry);
+      carry = all;
+      __syncthreads();
+    }
+  } else if ((int)blockIdx.x <= adv.blocks) {
+    advantages_of_block(blockIdx.x - 1, B, adv, sh_i, sh_f);
+  } else {
+    const int64_t step = (int64_t)(gridDim.x - 1 - adv.blocks) * kInitThreads;
+    for (int64_t r = (int64_t)(blockIdx.x - 1 - adv.blocks) * kInitThreads + t; r < R; r += step)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) if (f.p[k]) f.p[k][r] = f.v[k];
   }
 }
 
 // One workgroup per sequence: validate its row range and group index, count rows that count.
 __global__ void seq_count_kernel(const uint8_t* mask, const int32_t* ids, const int32_t* cu, const int32_t* cu_hi,
                                  const int32_t* group_idx, int64_t R, int V, int P,
-                                 int32_t* seq_len, rl_stats* stats) {
+                                 int32_t* seq_len, int32_t* seq_len_out, rl_stats* stats) {
   const int i = blockIdx.x;
   __shared__ int sh_cnt, sh_bad;
   if (threadIdx.x == 0) { sh_cnt = 0; sh_bad = 0; }
@@ -174,6 +211,7 @@ __global__ void seq_count_kernel(const uint8_t* mask, const int32_t* ids, const 
   __syncthreads();
   if (threadIdx.x == 0) {
     seq_len[i] = sh_cnt;
+    if (seq_len_out) seq_len_out[i] = sh_cnt;
     if (stats) {
       if (sh_bad) atomicAdd(&stats->n_bad_token, sh_bad);
       if (!seq_ok) atomicAdd(&stats->n_bad_seq, 1);
@@ -182,8 +220,10 @@ __global__ void seq_count_kernel(const uint8_t* mask, const int32_t* ids, const 
   }
 }
 
-// Exclusive scan of seq_len over sequences (single workgroup of 1024), total -> ctrl.
-__global__ void seq_scan_kernel(const int32_t* seq_len, int B, int32_t* cstart, Ctrl* ctrl, rl_stats* stats) {
+// Exclusive scan of seq_len over sequences (single workgroup of 1024).  Up to kScanInline sequences every workgroup of the
+// compaction adds up the lengths before its own instead, which saves a launch.
+constexpr int kScanInline = 1024;
+__global__ void seq_scan_kernel(const int32_t* seq_len, int B, int32_t* cstart) {
   __shared__ int wsum[16];
   __shared__ int carry;
   if (threadIdx.x == 0) carry = 0;
@@ -203,25 +243,73 @@ __global__ void seq_scan_kernel(const int32_t* seq_len, int B, int32_t* cstart, 
     if (threadIdx.x == 1023) carry += woff + x;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    cstart[B] = carry;
-    ctrl->n_real = carry;
-    ctrl->too_long = 0;
-    ctrl->overflow = 0;
-    if (stats) stats->n_tokens = carry;
+  if (threadIdx.x == 0) cstart[B] = carry;
+}
+
+// sum of seq_len[0 .. n) (n <= kScanInline = blockDim.x), the same in every thread
+__device__ inline int block_count(const int32_t* seq_len, int n, int* wsum) {
+  int x = (int)threadIdx.x < n ? seq_len[threadIdx.x] : 0;
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = x;
+  __syncthreads();
+  x = 0;
+  for (int k = 0; k < (int)(blockDim.x >> 6); ++k) x += wsum[k];
+  __syncthreads();
+  return x;
+}
+
+// Single-pass backward: greedy packing of whole sequences into chunks of at most Tc compacted rows (one thread; the lengths pass
+// through LDS).  Two consecutive chunks together hold more than Tc rows, so n_desc = 2 ceil(R / Tc) + 1 records
+// always suffice; unused records are empty.  A sequence longer than max_len (<= Tc) raises the flag.
+struct ChunkJob { ChunkDesc* desc; int n_desc, Tc, max_len; };
+__device__ inline void build_chunks(const int32_t* seq_len, int B, const ChunkJob& c, Ctrl* ctrl, rl_stats* stats, int* sh) {
+  ChunkDesc* desc = c.desc;
+  int k = 0, start = 0, rows = 0, sb = 0, bad = 0;
+  for (int base = 0; base < B; base += blockDim.x) {
+    __syncthreads();
+    if (base + (int)threadIdx.x < B) sh[threadIdx.x] = seq_len[base + threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x != 0) continue;
+    const int m = B - base < (int)blockDim.x ? B - base : (int)blockDim.x;
+    for (int i = 0; i < m; ++i) {
+      const int n = sh[i];
+      if (n > c.max_len) ++bad;
+      if (rows > 0 && rows + n > c.Tc && k < c.n_desc - 1) {
+        desc[k].row_start = start; desc[k].rows = rows; desc[k].seq_begin = sb; desc[k].seq_end = base + i;
+        ++k; start += rows; rows = 0; sb = base + i;
+      }
+      rows += n;
+    }
   }
+  if (threadIdx.x != 0) return;
+  desc[k].row_start = start; desc[k].rows = rows; desc[k].seq_begin = sb; desc[k].seq_end = B;
+  for (int j = k + 1; j < c.n_desc; ++j) { desc[j].row_start = start + rows; desc[j].rows = 0; desc[j].seq_begin = B; desc[j].seq_end = B; }
+  ctrl->too_long = bad ? 1 : 0;
+  if (bad && stats) stats->n_seq_too_long = bad;
 }
 
 // Ordered compaction, one workgroup per sequence: the k-th counting row of sequence i becomes
-// compact row cstart[i]+k.  cpos[r] = compact position of original row r (left at -1 otherwise).
-__global__ void compact_kernel(const uint8_t* mask, const int32_t* ids, const int32_t* cu,
-                               const int32_t* seq_len, const int32_t* cstart, int V,
-                               int32_t* row_map, int32_t* ids_c, int32_t* cpos, int32_t* row_map_out) {
+// compact row cstart[i]+k.  cpos[r] = compact position of original row r (left at -1 otherwise).  One workgroup more writes the
+// control block (number of rows, flags) and the chunk records.
+__global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* mask, const int32_t* ids, const int32_t* cu, const int32_t* seq_len, int B,
+                               int32_t* cstart, bool scanned, int V, int32_t* row_map, int32_t* ids_c, int32_t* cpos, int32_t* row_map_out,
+                               Ctrl* ctrl, ChunkJob chunks, rl_stats* stats) {
   const int i = blockIdx.x;
-  if (seq_len[i] == 0) return;
   __shared__ int wsum[16];
   __shared__ int carry;
-  if (threadIdx.x == 0) carry = cstart[i];
+  __shared__ int sh_len[1024];
+  const int first = scanned ? cstart[i] : block_count(seq_len, i, wsum);        // (cstart[B] = all rows)
+  if (i == B) {
+    if (threadIdx.x == 0) {
+      cstart[B] = first;
+      ctrl->n_real = first; ctrl->too_long = 0; ctrl->overflow = 0;
+      if (stats) stats->n_tokens = first;
+    }
+    if (chunks.desc) build_chunks(seq_len, B, chunks, ctrl, stats, sh_len);
+    return;
+  }
+  if (threadIdx.x == 0) { cstart[i] = first; carry = first; }
+  if (seq_len[i] == 0) return;
   __syncthreads();
   const int64_t a = cu[i], b = cu[i + 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -258,58 +346,23 @@ __global__ void zero_masked_rows_kernel(const int32_t* cpos, T* dX, int64_t R, i
   for (int k = lane; k < n16; k += 64) p[k] = make_uint4(0, 0, 0, 0);
 }
 
-// ------------------------------------------------------------------ advantage
-// Thread per prompt p: mean and std of the rewards of its members, then A_i for each member.
-__global__ void advantage_kernel(const float* rewards, const int32_t* group_idx, int B, int P,
-                                 float adv_eps, int ddof, float* adv, int32_t* group_count) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= P) return;
-  int n = 0; double s = 0.0;
-  for (int i = 0; i < B; ++i) if (group_idx[i] == p) { ++n; s += (double)rewards[i]; }
-  if (group_count) group_count[p] = n;
-  if (n == 0) return;
-  const double mu = s / n;
-  double inv = 0.0;
-  if (n - ddof > 0) {
-    double q = 0.0;
-    for (int i = 0; i < B; ++i) if (group_idx[i] == p) { const double e = (double)rewards[i] - mu; q += e * e; }
-    inv = 1.0 / (sqrt(q / (n - ddof)) + (double)adv_eps);
-  }
-  for (int i = 0; i < B; ++i) if (group_idx[i] == p) adv[i] = (float)(((double)rewards[i] - mu) * inv);
-}
-
-// ------------------------------------------------------------------ single-pass backward: chunking and references
-// Greedy packing of whole sequences into chunks of at most Tc compacted rows (one thread: B is small).
-// Two consecutive chunks together hold more than Tc rows, so n_desc = 2 ceil(R / Tc) + 1 records
-// always suffice; unused records are empty.  A sequence longer than max_len (<= Tc) raises the flag.
-__global__ void chunk_build_kernel(const int32_t* seq_len, const int32_t* cstart, int B, int Tc, int max_len,
-                                   ChunkDesc* desc, int n_desc, Ctrl* ctrl, rl_stats* stats) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int k = 0, start = 0, rows = 0, sb = 0, bad = 0;
-  for (int i = 0; i < B; ++i) {
-    const int n = seq_len[i];
-    if (n > max_len) ++bad;
-    if (rows > 0 && rows + n > Tc && k < n_desc - 1) {
-      desc[k].row_start = start; desc[k].rows = rows; desc[k].seq_begin = sb; desc[k].seq_end = i;
-      ++k; start += rows; rows = 0; sb = i;
-    }
-    rows += n;
-  }
-  desc[k].row_start = start; desc[k].rows = rows; desc[k].seq_begin = sb; desc[k].seq_end = B;
-  for (int j = k + 1; j < n_desc; ++j) { desc[j].row_start = start + rows; desc[j].rows = 0; desc[j].seq_begin = B; desc[j].seq_end = B; }
-  if (bad) { ctrl->too_long = 1; if (stats) stats->n_seq_too_long = bad; }
-}
-
-// One wavefront per compacted row t: target logit zy_t = x_t . W[y_t] (f32 accumulation of bf16 products)
+// ------------------------------------------------------------------ single-pass backward: references
+// Single-pass backward, one wavefront per original row: a row that does not count has its dX row zeroed; for one that does, at
+// compact position t, the target logit zy_t = x_t . W[y_t] (f32 accumulation of bf16 products)
 // (times the inverse temperature) and the reference of the stored probabilities, ref_t = zy_t - old_t, which is
 // the logsumexp of the row up to the (small) drift between the old and the current policy (NaN-free for any finite old_t).
-__global__ void target_logit_kernel(const bf16_t* X, const bf16_t* W, int H, const int32_t* row_map, const int32_t* ids_c,
-                                    const float* old_lp, const Ctrl* ctrl, float inv_tau, float* zy, float* ref_l2e, int32_t* ycol) {
-  const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (t >= ctrl->n_real) return;
+__global__ void target_logit_kernel(const bf16_t* X, const bf16_t* W, int64_t R, int H, const int32_t* cpos, const int32_t* ids_c,
+                                    const float* old_lp, float inv_tau, bf16_t* dX, float* zy, float* ref_l2e, int32_t* ycol) {
+  const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (r >= R) return;
   const int lane = threadIdx.x & 63;
-  const int r = row_map[t];
-  const uint4* x = reinterpret_cast<const uint4*>(X + (int64_t)r * H);
+  const int t = cpos[r];
+  if (t < 0) {
+    uint4* p = reinterpret_cast<uint4*>(dX + r * H);
+    for (int k = lane; k < H / 8; k += 64) p[k] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  const uint4* x = reinterpret_cast<const uint4*>(X + r * H);
   const int y = ids_c[t];
   const uint4* w = reinterpret_cast<const uint4*>(W + (int64_t)y * H);
   float acc = 0.f;
@@ -348,7 +401,13 @@ __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* 
   const int n = blockIdx.x * 64 + col;
   double s = 0.0, u = 0.0;
   if (n < left)
-    for (int t = slice; t < tiles_v; t += kSumSlices) { const float2 v = part[(int64_t)t * ldp + n]; s += (double)v.x; u += (double)v.y; }
+    for (int t0 = slice; t0 < tiles_v; t0 += 8 * kSumSlices) {       // eight loads in flight, added in order
+      float2 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) { const int t = t0 + k * kSumSlices; v[k] = t < tiles_v ? part[(int64_t)t * ldp + n] : make_float2(0.f, 0.f); }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) { s += (double)v[k].x; u += (double)v[k].y; }
+    }
   ss[slice][col] = s; su[slice][col] = u;
   __syncthreads();
   if (slice == 0 && n < left) {
@@ -407,15 +466,22 @@ __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, con
   const float NEG = -__builtin_inff();
   float m = NEG, s = 0.f, u = 0.f;
   if (n < left) {
-    for (int t = slice; t < tiles_v; t += 4) {
-      const float4 v = part[(int64_t)t * ldp + n];
-      const float mm = fmaxf(m, v.x);
-      if (mm != NEG) {
-        const float f1 = expf(m - mm), f2 = expf(v.x - mm);
-        s = s * f1 + v.y * f2;
-        u = u * f1 + v.z * f2;
+    for (int t0 = slice; t0 < tiles_v; t0 += 32) {             // eight loads in flight, folded in order
+      float4 q[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) if (t0 + 4 * k < tiles_v) q[k] = part[(int64_t)(t0 + 4 * k) * ldp + n];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (t0 + 4 * k >= tiles_v) break;
+        const float4 v = q[k];
+        const float mm = fmaxf(m, v.x);
+        if (mm != NEG) {
+          const float f1 = expf(m - mm), f2 = expf(v.x - mm);
+          s = s * f1 + v.y * f2;
+          u = u * f1 + v.z * f2;
+        }
+        m = mm;
       }
-      m = mm;
     }
   }
   sm[slice][col] = m; ss[slice][col] = s; su[slice][col] = u;
@@ -899,22 +965,23 @@ static Ptrs carve(void* ws, const Plan& p) {
   return q;
 }
 
-// prep: counts, scan, compaction; zero the per-row outputs so masked rows read 0
-static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, int32_t* seq_len_out, rl_stats* stats,
-                     const int32_t* group_idx, float* logp_out, float* lse_out, float* coeff_out, int32_t* row_map_out,
+// prep: row outputs cleared (rows that do not count read 0 / -1), advantages, counts, compaction, chunk records
+static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int32_t* group_idx, const rl_outputs& out, const AdvJob& adv,
                      hipStream_t s) {
   ProfScope ps(RL_PROF_PREP, s);
-  if (stats) fill<int32_t>(reinterpret_cast<int32_t*>(stats), sizeof(rl_stats) / 4, 0, s);
-  fill<int32_t>(q.cpos, p.R, -1, s);
-  fill<int32_t>(row_map_out, p.R, -1, s);
-  fill<float>(logp_out, p.R, 0.f, s); fill<float>(lse_out, p.R, 0.f, s); fill<float>(coeff_out, p.R, 0.f, s);
-  // the running maximum of the offsets borrows cstart until the scan below overwrites it with the compacted starts
-  cu_running_max_kernel<<<1, 1024, 0, s>>>(b->cu_seqlens, p.B, q.cstart);
-  seq_count_kernel<<<p.B, 256, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.cstart, group_idx, p.R, p.V, p.P, q.seq_len, stats);
-  seq_scan_kernel<<<1, 1024, 0, s>>>(q.seq_len, p.B, q.cstart, q.ctrl, stats);
-  compact_kernel<<<p.B, 1024, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.seq_len, q.cstart, p.V, q.row_map, q.ids_c, q.cpos,
-                                      row_map_out);
-  if (seq_len_out) (void)hipMemcpyAsync(seq_len_out, q.seq_len, 4 * (size_t)p.B, hipMemcpyDeviceToDevice, s);
+  RowFill f{};
+  int nf = 0;
+  auto clear = [&](void* a, int v) { f.p[nf] = static_cast<int32_t*>(a); f.v[nf++] = v; };
+  clear(q.cpos, -1); clear(out.row_map, -1); clear(out.target_col, -1);
+  clear(out.logprob, 0); clear(out.lse, 0); clear(out.coeff, 0); clear(out.entropy, 0); clear(out.target_logit, 0);
+  const int64_t fill = (p.R + kInitThreads - 1) / kInitThreads;
+  // the running maximum of the offsets borrows cstart until the compaction overwrites it with the compacted starts
+  prep_init_kernel<<<1 + adv.blocks + (int)(fill < 2048 ? fill : 2048), kInitThreads, 0, s>>>(b->cu_seqlens, p.B, p.R, q.cstart, f, adv, out.stats);
+  seq_count_kernel<<<p.B, 256, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.cstart, group_idx, p.R, p.V, p.P, q.seq_len, out.seq_len, out.stats);
+  const bool scan = p.B > kScanInline;
+  if (scan) seq_scan_kernel<<<1, 1024, 0, s>>>(q.seq_len, p.B, q.cstart);
+  compact_kernel<<<p.B + 1, 1024, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.seq_len, p.B, q.cstart, scan, p.V, q.row_map, q.ids_c, q.cpos,
+                                          out.row_map, q.ctrl, ChunkJob{p.stash ? q.desc : nullptr, p.n_desc, p.Tc, p.max_len}, out.stats);
 }
 
 template <class T>
@@ -1024,15 +1091,12 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
   T* dX = static_cast<T*>(out->d_hidden);
   {
     ProfScope ps(RL_PROF_TRANSPOSE, s);
-    const int rows_per_block = 4;
-    zero_masked_rows_kernel<T><<<(unsigned)((p.R + rows_per_block - 1) / rows_per_block), 256, 0, s>>>(q.cpos, dX, p.R, p.H);
     dim3 g((p.Vp + 63) / 64, (p.H + 63) / 64);
     launch_transpose<T>(g, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
   }
   {
     ProfScope ps(RL_PROF_PREP, s);
-    chunk_build_kernel<<<1, 64, 0, s>>>(q.seq_len, q.cstart, p.B, p.Tc, p.max_len, q.desc, p.n_desc, q.ctrl, out->stats);
-    target_logit_kernel<<<(unsigned)((p.R + 3) / 4), 256, 0, s>>>(X, W, p.H, q.row_map, q.ids_c, b->old_logprob, q.ctrl, p.inv_tau, q.zy, q.ref, q.ycol);
+    target_logit_kernel<<<(unsigned)((p.R + 3) / 4), 256, 0, s>>>(X, W, p.R, p.H, q.cpos, q.ids_c, b->old_logprob, p.inv_tau, dX, q.zy, q.ref, q.ycol);
   }
   float2* part = reinterpret_cast<float2*>(q.part);
   for (int k = 0; k < p.n_desc; ++k) {
@@ -1212,7 +1276,9 @@ rl_status rl_token_logprob_tempered(const rl_batch* b, float temperature, float*
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   Ptrs q = carve(ws, p);
-  run_prep(b, p, q, nullptr, nullptr, nullptr, logprob, lse, nullptr, nullptr, s);
+  rl_outputs out{};
+  out.logprob = logprob; out.lse = lse;
+  run_prep(b, p, q, nullptr, out, AdvJob{}, s);
   if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
   else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
@@ -1246,16 +1312,9 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   (void)hipGetLastError();
   Ptrs q = carve(ws, p);
 
-  run_prep(b, p, q, out->seq_len, out->stats, b->group_idx, out->logprob, out->lse, out->coeff, out->row_map, s);
-  fill<float>(out->entropy, p.R, 0.f, s);
-  fill<float>(out->target_logit, p.R, 0.f, s);
-  fill<int32_t>(out->target_col, p.R, -1, s);
-  {
-  ProfScope ps(RL_PROF_LOSS, s);
-  fill<float>(q.adv, p.B, 0.f, s);
-  advantage_kernel<<<(p.P + 127) / 128, 128, 0, s>>>(b->rewards, b->group_idx, p.B, p.P, prm->adv_eps, prm->adv_std_ddof, q.adv, out->group_count);
-  if (out->advantages) (void)hipMemcpyAsync(out->advantages, q.adv, 4 * (size_t)p.B, hipMemcpyDeviceToDevice, s);
-  }
+  const AdvJob adv{(p.P + kInitThreads - 1) / kInitThreads, b->rewards, b->group_idx, p.P, prm->adv_eps, prm->adv_std_ddof, q.adv, out->advantages,
+                   out->group_count};
+  run_prep(b, p, q, b->group_idx, *out, adv, s);
 
   if (p.stash) {
     run_fused(b, prm, objective, p, q, out, s);
@@ -1324,7 +1383,9 @@ rl_status rl_token_logprob_static(const rl_batch* b, float temperature, float* l
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   Ptrs q = carve(ws, p);
-  run_prep(b, p, q, nullptr, nullptr, nullptr, logprob, lse, nullptr, nullptr, s);
+  rl_outputs out{};
+  out.logprob = logprob; out.lse = lse;
+  run_prep(b, p, q, nullptr, out, AdvJob{}, s);
   if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
   else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
