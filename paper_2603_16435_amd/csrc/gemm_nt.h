@@ -68,6 +68,7 @@ struct GemmDims {
   int zero_if_empty;      // dyn == 3 only: an empty chunk still runs the epilogue (with K = 0) instead of returning
   int group_m;            // tile-order parameter: M-tiles per band
   int split_slots;        // > 0: the contraction may be cut along K (see split_k); workgroups the chip runs at a time
+  int b_k_rows;           // hot kernel, B operand given K-major: its rows (K is their number rounded up, with zeros in the other operand)
   int fill_tiles;         // tiles of another contraction over K = M in the same launch, which fill the CUs this one leaves
 };
 
@@ -467,7 +468,17 @@ __device__ __attribute__((always_inline)) inline u32x2_t lds_read_tr16(const uns
 // 64 k-rows of 256 m (512 bytes a row, 32-byte pieces XOR-swizzled by a function of the row such that the eight
 // rows a half-wavefront's transposing read touches fall into different banks) and its fragments come from two
 // transposing reads each.
-template <class Epi, int PFD, int VMG, int VMO, bool ATR = false, int LDA = 6, int LDB = 5>
+//
+// BTR: the B operand is given K-major and row-major, element (n, k) at B[k * d.ldb + n] with d.b_k_rows rows (dX contracts dS with W
+// as it is stored, without a W^T in memory); same slab layout and reads as ATR.  Rows past the last are read as the last
+// one: the A operand has zeros there.
+//
+// KT: K need not be a multiple of 128 (only of 8): 16-byte chunks past the end of a row are fetched from a zero block.
+//
+// Both have slabs whose load addresses are not those of the plain loop, at the end of K; the last six slabs run in a copy of the
+// loop body that works them out per lane (TAIL), so that the main loop stays free of vector operations.
+__device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
+template <class Epi, int PFD, int VMG, int VMO, bool ATR = false, int LDA = 6, int LDB = 5, bool BTR = false, bool KT = false>
 __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d,
                                                                         const Epi& epi, int pid, unsigned char* stage0, unsigned char* stage1) {
   constexpr int BM = 256, BN = 256, BK = 64, WAVES_M = 2, WAVES_N = 2;
@@ -480,11 +491,13 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
                 "the slab loads of the fullest phase must fit into its 32 MFMAs");
   static_assert(STAGE == kHotStageBytes, "stage size");
   static_assert(!ATR || !Epi::kPermute, "the K-major A path loads rows in natural order");
+  static_assert(!BTR || (!ATR && !KT && !Epi::kGatherB && PFD == 0), "K-major B: dX");
+  static_assert(!KT || !ATR, "K tail: row-wise operands");
   static_assert(!Epi::kSplit || (!ATR && PFD == 0 && !Epi::kGatherB), "a slice starts at a slab offset of both row-wise operands");
 
   int M, N, K;
   if (!resolve_dims(d, M, N, K)) return;
-  int nk = K / BK;
+  int nk = KT ? (K + 127) / 128 * 2 : K / BK;
   // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
   const bool by_share = d.dyn == 1;
   const int tiles_m = ((by_share ? M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
@@ -525,7 +538,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   unsigned aoff[8], boff[8];
   const bf16_t* abase = ATR ? A + tiled_index(0, tm * BM, d.lda)
                                   : A + (d.a_tiled ? tiled_index(tm * BM, 0, d.K) : (int64_t)(tm * BM) * d.lda);
-  const bf16_t* bbase = B + (d.b_tiled ? tiled_index(tn * BN, 0, d.K) : (int64_t)(tn * BN) * d.ldb);
+  const bf16_t* bbase = BTR ? B + tn * BN : B + (d.b_tiled ? tiled_index(tn * BN, 0, d.K) : (int64_t)(tn * BN) * d.ldb);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int lr = wave * 64 + j * 8 + (lane >> 3);
@@ -542,26 +555,45 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       if (d.a_rows) r = d.a_rows[r];
       ap[j] = A + (d.a_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.lda) + c * 8;
     }
-    r = tn * BN + (Epi::kPermute ? perm_lds_row_b(lr) : lr); r = r < N ? r : N - 1;
-    if (d.b_rows) r = d.b_rows[r];
-    bp[j] = B + (d.b_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.ldb) + c * 8;
+    if constexpr (BTR) {
+      const int p = (wave * 8 + j) * 64 + lane;
+      const int row = p >> 5, u = p & 31;
+      const int f = (row & 3) | (((row >> 3) & 1) << 2);
+      int n = tn * BN + (((u >> 1) ^ f) << 4) + ((u & 1) << 3); n = n < N ? n : N - 8;       // (N % 8 == 0)
+      bp[j] = B + (int64_t)row * d.ldb + n;
+    } else {
+      r = tn * BN + (Epi::kPermute ? perm_lds_row_b(lr) : lr); r = r < N ? r : N - 1;
+      if (d.b_rows) r = d.b_rows[r];
+      bp[j] = B + (d.b_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.ldb) + c * 8;
+    }
     aoff[j] = (unsigned)(ap[j] - abase) * 2u;                   // in bytes
     boff[j] = GB ? 0u : (unsigned)(bp[j] - bbase) * 2u;
   }
-  const int a_ks = d.a_tiled ? 16384 : BK, b_ks = d.b_tiled ? 16384 : BK;     // elements from one slab to the next
+  const int a_ks = d.a_tiled ? 16384 : BK;                                    // elements from one slab to the next
+  const int64_t b_ks = BTR ? (int64_t)BK * d.ldb : d.b_tiled ? 16384 : BK;
   if constexpr (Epi::kSplit) { abase = uniform_ptr(abase + (int64_t)k_first * a_ks); bbase = uniform_ptr(bbase + (int64_t)k_first * b_ks); }
   // K-major A: slab s is k-rows [64 s, 64 s + 64), i.e. quarter s%4 of row block s/4 of the tiled layout
   auto a_slab = [&](int slab) __attribute__((always_inline)) -> int64_t {
     return ATR ? (int64_t)(slab >> 2) * (d.lda * 256) + (slab & 3) * 4096 : (int64_t)slab * a_ks;
   };
   // load j of the 16 per slab (0..7 = A rows, 8..15 = B rows)
-  auto issue1 = [&](int slab, unsigned char* stage, int j) __attribute__((always_inline)) {
+  auto issue1 = [&](bool tail, int slab, unsigned char* stage, int j) __attribute__((always_inline)) {
     unsigned char* as = stage + wave * 64 * kSlabBytes;
-    if (j < 8) {
-      load16_to_lds_uniform(abase + a_slab(slab), aoff[j], as + j * 8 * kSlabBytes);   // (the hot kernel is not launched with gathered A rows)
+    unsigned char* dst = j < 8 ? as + j * 8 * kSlabBytes : as + A_BYTES + (j - 8) * 8 * kSlabBytes;
+    if (KT && tail) {
+      const int c = (lane & 7) ^ ((4 * j + (lane >> 4)) & 7);         // the lane's chunk of the slab (row lr = 64 wave + 8 j + lane/8)
+      const bf16_t* g = j < 8 ? ap[j & 7] + a_slab(slab) : bp[j & 7] + (int64_t)slab * b_ks;
+      load16_to_lds_lanes(slab * BK + c * 8 < K ? (const void*)g : (const void*)&kZeroChunk, dst);
+    } else if (j < 8) {
+      load16_to_lds_uniform(abase + a_slab(slab), aoff[j], dst);      // (the hot kernel is not launched with gathered A rows)
+    } else if (BTR && tail) {
+      const int last = (d.b_k_rows - 1) >> 6, s_abs = k_first + slab, sc = s_abs < last ? s_abs : last;       // a slab that has rows
+      const int row = ((wave * 8 + j - 8) * 64 + lane) >> 5, left = d.b_k_rows - 1 - sc * BK;
+      load16_to_lds_lanes(bp[j - 8] + (int64_t)(sc * BK + (row < left ? row : left) - row) * d.ldb, dst);
+    } else if constexpr (GB) {
+      load16_to_lds_lanes(bp[j - 8] + (int64_t)slab * b_ks, dst);
     } else {
-      if constexpr (GB) load16_to_lds_lanes(bp[j - 8] + (int64_t)slab * b_ks, as + A_BYTES + (j - 8) * 8 * kSlabBytes);
-      else load16_to_lds_uniform(bbase + (int64_t)slab * b_ks, boff[j - 8], as + A_BYTES + (j - 8) * 8 * kSlabBytes);
+      load16_to_lds_uniform(bbase + (int64_t)slab * b_ks, boff[j - 8], dst);
     }
   };
 
@@ -586,7 +618,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     int r = tn * BN + 32 * (tm & 7) + (lane & 31); r = r < N ? r : N - 1;
     if (d.b_rows) r = d.b_rows[r];
     pf_ptr = reinterpret_cast<const unsigned char*>(B + (d.b_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.ldb));
-    pf_stride = b_ks * 2;
+    pf_stride = (int)b_ks * 2;
   } else {
     pf_ptr = reinterpret_cast<const unsigned char*>(A);
     pf_stride = 0;
@@ -595,7 +627,8 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   auto prefetch = [&](unsigned& slot, int kt) __attribute__((always_inline)) {
     if (PFD > 0) {
       pf_sink ^= slot;                                   // fetched two slabs ago: long since back
-      const int k = kt + PFD < nk ? kt + PFD : nk - 1;
+      const int last = KT ? (K - 1) / BK : nk - 1;       // (a row has no lines past its end)
+      const int k = kt + PFD < last ? kt + PFD : last;
       slot = *reinterpret_cast<const unsigned*>(pf_ptr + (int64_t)k * pf_stride + (pf_atr ? a_slab(k) * 2 : 0));
     }
   };
@@ -631,6 +664,16 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
 #pragma unroll
     for (int i = 0; i < MB; ++i) atr_base[i] = (8 * fq + (frow >> 2)) * 512 + (((wm * 8 + i) ^ f) << 5) + ((frow & 3) << 3);
   }
+  int btr_base[NB];                                // the same for a K-major B
+  if constexpr (BTR) {
+    const int f = ((frow >> 2) & 3) | ((fq & 1) << 2);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) btr_base[i] = A_BYTES + (8 * fq + (frow >> 2)) * 512 + (((wn * 8 + i) ^ f) << 5) + ((frow & 3) << 3);
+  }
+  auto read_b_tr = [&](u32x4_t& dst, const unsigned char* fstage, int i, int fs, int h) __attribute__((always_inline)) {
+    const u32x2_t v = lds_read_tr16(fstage + btr_base[i] + (32 * fs + 4 * h) * 512);
+    dst[2 * h] = v[0]; dst[2 * h + 1] = v[1];
+  };
   // half h (k = 0..3 or 4..7 of the lane's eight) of A block i of k-step fs
   auto read_a_tr = [&](u32x4_t& dst, const unsigned char* fstage, int i, int fs, int h) __attribute__((always_inline)) {
     const u32x2_t v = lds_read_tr16(fstage + atr_base[i] + (32 * fs + 4 * h) * 512);
@@ -643,7 +686,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   //    k-step fs in fstage; kind 12: fa[aset^1], fb[bset^1] <- A blocks 0..7 and B blocks 0..3 of k-step fs
   //  * slab loads lo .. lo+nvm-1 of the slab at k0 into wstage.
   // Every MFMA (with what follows it) is fenced off, so the order below is the order issued.
-  auto phase = [&](int aset, int bset, int half, int kind, const unsigned char* fstage, int fs,
+  auto phase = [&](bool tail, int aset, int bset, int half, int kind, const unsigned char* fstage, int fs,
                    int k0, unsigned char* wstage, int lo, int nvm) __attribute__((always_inline)) {
     const int slot = ((fs * 4 + fq) ^ swz) << 4;
 #pragma unroll
@@ -652,13 +695,21 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       if (ATR && kind == 12) {                          // sixteen half-reads of A, one per MFMA, then the four of B
         if (q < 16) read_a_tr(fa[aset ^ 1][q >> 1], fstage, q >> 1, fs, q & 1);
         else if (q % DSG == 0 && q < 24) fb[bset ^ 1][(q - 16) / DSG] = *reinterpret_cast<const u32x4_t*>(fstage + brow + ((q - 16) / DSG) * 16 * kSlabBytes + slot);
+      } else if (BTR) {                                 // B blocks in two half-reads each: eight for half of B, after the eight of A
+        if (kind == 12 && q < 16) {
+          if (q % DSG == 0) fa[aset ^ 1][q / DSG] = *reinterpret_cast<const u32x4_t*>(fstage + arow + (q / DSG) * 16 * kSlabBytes + slot);
+        } else if (kind == 12 && q < 24) {
+          read_b_tr(fb[bset ^ 1][(q - 16) >> 1], fstage, (q - 16) >> 1, fs, q & 1);
+        } else if (kind == 4 && q < 8) {
+          read_b_tr(fb[bset ^ 1][q >> 1], fstage, 4 + (q >> 1), fs, q & 1);
+        }
       } else if (q % DSG == 0 && q / DSG < kind) {
         const int f = q / DSG;
         if (kind == 4) fb[bset ^ 1][f] = *reinterpret_cast<const u32x4_t*>(fstage + brow + (4 + f) * 16 * kSlabBytes + slot);
         else if (f < 8) fa[aset ^ 1][f] = *reinterpret_cast<const u32x4_t*>(fstage + arow + f * 16 * kSlabBytes + slot);
         else fb[bset ^ 1][f - 8] = *reinterpret_cast<const u32x4_t*>(fstage + brow + (f - 8) * 16 * kSlabBytes + slot);
       }
-      if (q % VMG == VMO && q / VMG < nvm) issue1(k0, wstage, lo + q / VMG);
+      if (q % VMG == VMO && q / VMG < nvm) issue1(tail, k0, wstage, lo + q / VMG);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -666,23 +717,23 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // Slab kt sits in `cur`.  On entry fa[0] / fb[0] hold its k-step 0 (A all, B blocks 0..3) and loads
   // 0..LDA-1 of slab kt+1 are in flight towards `nxt`.  The last phase runs from registers after the
   // workgroup barrier, so it covers the first fragment reads of slab kt+1 and the first loads of kt+2.
-  auto slab = [&](unsigned char* cur, unsigned char* nxt, int kt, unsigned& pfslot) __attribute__((always_inline)) {
+  auto slab = [&](bool tail, unsigned char* cur, unsigned char* nxt, int kt, unsigned& pfslot) __attribute__((always_inline)) {
     prefetch(pfslot, kt);
-    phase(0, 0, 0, 4, cur, 0, kof(kt + 1), nxt, LDA, LDB);
-    phase(0, 1, 1, 12, cur, 1, kof(kt + 1), nxt, LDA + LDB, LDC);
-    phase(1, 0, 0, 4, cur, 1, 0, nxt, 0, 0);
+    phase(tail, 0, 0, 0, 4, cur, 0, kof(kt + 1), nxt, LDA, LDB);
+    phase(tail, 0, 1, 1, 12, cur, 1, kof(kt + 1), nxt, LDA + LDB, LDC);
+    phase(tail, 1, 0, 0, 4, cur, 1, 0, nxt, 0, 0);
     __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0): own loads have landed, own fragment reads are done
     __syncthreads();                        // ... and so have everybody else's: `nxt` is complete, `cur` is free
-    phase(1, 1, 1, 12, nxt, 0, kof(kt + 2), cur, 0, LDA);
+    phase(tail, 1, 1, 1, 12, nxt, 0, kof(kt + 2), cur, 0, LDA);
   };
 
   if (nk > 0) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) issue1(0, stage0, j);
+    for (int j = 0; j < 16; ++j) issue1(true, 0, stage0, j);
     __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < LDA; ++j) issue1(kof(1), stage1, j);
+    for (int j = 0; j < LDA; ++j) issue1(true, kof(1), stage1, j);
     {
       const int slot = (fq ^ swz) << 4;
 #pragma unroll
@@ -691,12 +742,25 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
         else fa[0][i] = *reinterpret_cast<const u32x4_t*>(stage0 + arow + i * 16 * kSlabBytes + slot);
       }
 #pragma unroll
-      for (int j = 0; j < NB / 2; ++j) fb[0][j] = *reinterpret_cast<const u32x4_t*>(stage0 + brow + j * 16 * kSlabBytes + slot);
+      for (int j = 0; j < NB / 2; ++j) {
+        if constexpr (BTR) { read_b_tr(fb[0][j], stage0, j, 0, 0); read_b_tr(fb[0][j], stage0, j, 0, 1); }
+        else fb[0][j] = *reinterpret_cast<const u32x4_t*>(stage0 + brow + j * 16 * kSlabBytes + slot);
+      }
     }
-    for (int kt = 0; kt < nk; kt += 2) {    // nk is even (K % 128 == 0 is a launch condition)
-      slab(stage0, stage1, kt, pf0);
-      slab(stage1, stage0, kt + 1, pf1);
+    // nk is even (K is a multiple of 128, or rounded up to one).  Slabs that reach past the end of an operand are among the
+    // last four (b_k_rows) or two (KT), and loads run up to two slabs ahead: the last six slabs.
+    const bool has_tail = KT || (BTR && (k_first + nk) * BK > d.b_k_rows);
+    const int plain = !has_tail ? nk : nk > 6 ? nk - 6 : 0;
+    int kt = 0;
+    for (; kt < plain; kt += 2) {
+      slab(false, stage0, stage1, kt, pf0);
+      slab(false, stage1, stage0, kt + 1, pf1);
     }
+    if constexpr (KT || BTR)
+      for (; kt < nk; kt += 2) {
+        slab(true, stage0, stage1, kt, pf0);
+        slab(true, stage1, stage0, kt + 1, pf1);
+      }
   }
   __builtin_amdgcn_s_waitcnt(0x0070);       // trailing re-loads must land before the epilogue reuses LDS
   __syncthreads();
@@ -706,28 +770,28 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   if (PFD > 0 && (pf_sink ^ pf0 ^ pf1) == 0x9E3779B9u && K < 0) epi.keep_alive();   // never true: keeps the prefetch loads
 }
 
-template <class Epi, class Tune, bool ATR = false>
+template <class Epi, class Tune, bool KT = false>
 __global__ __launch_bounds__(256)
 void gemm_nt_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, Epi epi) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage0[kHotStageBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char stage1[kHotStageBytes];
-  gemm_nt_bf16_tile<Epi, Tune::kPfd, Tune::kVmg, Tune::kVmo, ATR, Tune::kLdA, Tune::kLdB>(A, B, d, epi, blockIdx.x, stage0, stage1);
+  gemm_nt_bf16_tile<Epi, Tune::kPfd, Tune::kVmg, Tune::kVmo, false, Tune::kLdA, Tune::kLdB, false, KT>(A, B, d, epi, blockIdx.x, stage0, stage1);
 }
 
 // Two independent contractions in one launch: workgroups [0, n1) work on the first, the rest on the
 // second.  Used where one of them alone has too few tiles to fill the last round of the 256 CUs: the
 // other's workgroups then fill the tail.  n1 = launch_tiles() of the first (a multiple of the XCD count).
-// ATR2: the second contraction's A operand is given K-major (see gemm_nt_bf16_tile).
-template <class Epi1, class Tune1, class Epi2, class Tune2, bool ATR2 = false>
+// BTR1: the first contraction's B operand is given K-major, the second's A operand always is (see gemm_nt_bf16_tile).
+template <class Epi1, class Tune1, class Epi2, class Tune2, bool BTR1>
 __global__ __launch_bounds__(256)
 void gemm_nt_bf16_pair_kernel(const bf16_t* __restrict__ A1, const bf16_t* __restrict__ B1, GemmDims d1, Epi1 epi1, int n1,
                               const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2, GemmDims d2, Epi2 epi2) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage0[kHotStageBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char stage1[kHotStageBytes];
   if ((int)blockIdx.x < n1)
-    gemm_nt_bf16_tile<Epi1, Tune1::kPfd, Tune1::kVmg, Tune1::kVmo, false, Tune1::kLdA, Tune1::kLdB>(A1, B1, d1, epi1, blockIdx.x, stage0, stage1);
+    gemm_nt_bf16_tile<Epi1, Tune1::kPfd, Tune1::kVmg, Tune1::kVmo, false, Tune1::kLdA, Tune1::kLdB, BTR1>(A1, B1, d1, epi1, blockIdx.x, stage0, stage1);
   else
-    gemm_nt_bf16_tile<Epi2, Tune2::kPfd, Tune2::kVmg, Tune2::kVmo, ATR2, Tune2::kLdA, Tune2::kLdB>(A2, B2, d2, epi2, (int)blockIdx.x - n1, stage0, stage1);
+    gemm_nt_bf16_tile<Epi2, Tune2::kPfd, Tune2::kVmg, Tune2::kVmo, true, Tune2::kLdA, Tune2::kLdB>(A2, B2, d2, epi2, (int)blockIdx.x - n1, stage0, stage1);
 }
 
 }  // namespace rlk

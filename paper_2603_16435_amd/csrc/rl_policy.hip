@@ -35,6 +35,11 @@ constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step ti
 constexpr int kBM = 256, kBN = 256;
 // General kernel in f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU), or 256 x 16 where the large
 // ones would leave CUs without work.
+// Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
+// The copy costs 2 x 2 V H bytes a call (7B head: 410 us, and 1.1 GB of workspace); its contiguous slabs save up to 1 % of the two
+// contractions.  747 tokens at the 7B head: 3274 us with the copy, 2860 without; 11.5 k tokens (16 k rows): 38.65 / 38.37 ms; 67 k tokens
+// (131 k rows): 163.5 / 163.4; 36 k tokens at H 2048, V 32000 (65 k rows): 11.39 / 11.47.
+constexpr int64_t kKMajorRows = 32768;
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup per CU, a step of a K cut is two slabs
 // Per-contraction tuning of the hot kernel, from sweeps on the 7B-shaped workload:
@@ -791,6 +796,7 @@ struct Plan {
   int Tc, Vp, tiles_v, n_chunks;
   bool bwd;
   bool tiled;            // bf16: the work buffers dS/E, W^T, X^T are slab-tiled (hot kernel operands)
+  bool k_major_w;        // dX reads W as it is stored: no W^T in the workspace
   bool stash;            // single-pass backward (forward keeps each chunk's unnormalised probabilities)
   int n_desc, max_len;   // stash: number of chunk records, promised bound on rows per sequence
   float inv_tau;         // 1 / temperature
@@ -853,6 +859,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.n_chunks = (int)((b->R + tc - 1) / tc);
   p.bwd = bwd;
   p.tiled = (b->dtype == RL_BF16);
+  p.k_major_w = p.tiled && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len
@@ -876,7 +883,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.off_wt = p.off_xt = p.off_ds = p.off_dst = p.off_split = 0;
   if (bwd) {
     const size_t Hp = ((size_t)b->H + 255) & ~(size_t)255;   // tiled layouts come in blocks of 256 rows
-    p.off_wt = take(p.esz * Hp * (size_t)p.Vp);
+    if (!p.k_major_w) p.off_wt = take(p.esz * Hp * (size_t)p.Vp);
     p.off_xt = take(p.esz * Hp * (size_t)tc);
     p.off_ds = take(p.esz * (size_t)tc * (size_t)p.Vp);
     if (b->dtype == RL_F32) {
@@ -911,11 +918,12 @@ static int split_launch(int tiles_m, int tiles_n, int slots) {
 template <class Tune, class Epi>
 static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Epi& epi, hipStream_t s) {
   const int tiles = launch_tiles((d.M + kBM - 1) / kBM, (d.N + kBN - 1) / kBN);
-  const bool fast = (d.K % 128 == 0) && (d.lda % 8 == 0) && (d.ldb % 8 == 0) &&
+  const bool fast = (d.lda % 8 == 0) && (d.ldb % 8 == 0) && (d.K % 8 == 0) &&
                     ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0) &&
                     !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB;     // (how the hot kernel addresses its operands)
-  if (!fast) { launch_generic(A, B, d, epi, tiles, s); return; }
-  gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  if (!fast) launch_generic(A, B, d, epi, tiles, s);
+  else if (d.K % 128) gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  else gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
 template <class Tune, class Epi>
@@ -930,13 +938,18 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
 // dX = diag(f) dS W  (A = dS or E' [Tc][Vp], B = W^T [H][Vp]) and dW (+)= dS^T (diag(f) X)  (A = the same array read as a K-major
 // operand, B = X^T [H][Tc]) of a bf16 chunk in one launch: dX alone has few (long) tiles, whose last round would leave CUs
 // idle; the dW tiles fill them.  dX is cut along K where its tiles are fewer still.
-static void launch_dx_dw(const bf16_t* E, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, const GemmDims& dw, const EpiDW& ew,
-                         hipStream_t s) {
+static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, const GemmDims& dw,
+                         const EpiDW& ew, hipStream_t s) {
   const int tn = (dx.N + kBN - 1) / kBN;
   dx.split_slots = kHotSlots; dx.fill_tiles = (dw.M + kBM - 1) / kBM * tn;
   const int n1 = split_launch((dx.M + kBM - 1) / kBM, tn, kHotSlots);
   const int n2 = launch_tiles((dw.M + kBM - 1) / kBM, tn);
-  gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
+  if (WT) {
+    gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
+  } else {
+    dx.ldb = dx.N; dx.b_tiled = 0; dx.b_k_rows = dw.M;
+    gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, W, dx, ex, n1, E, XT, dw, ew);
+  }
   splitk_reduce_kernel<bf16_t><<<512, 256, 0, s>>>(dx, ex, kBM, kBN, kHotStep);
 }
 
@@ -1016,7 +1029,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     zero_masked_rows_kernel<T><<<(unsigned)((p.R + rows_per_block - 1) / rows_per_block), 256, 0, s>>>(q.cpos, dX, p.R, p.H);
   }
   // W^T [H][Vp] with zero padding columns, once per call
-  {
+  if (!p.k_major_w) {
     ProfScope ps(RL_PROF_TRANSPOSE, s);
     dim3 g((p.Vp + 63) / 64, (p.H + 63) / 64);
     launch_transpose<T>(g, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
@@ -1051,7 +1064,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     EpiDW ew{d_weight, p.H, p.V, p.H, ch > 0 ? 1 : 0};
     if constexpr (sizeof(T) == 2) {
       ProfScope ps(RL_PROF_GEMM_BWD, s);
-      launch_dx_dw(dS, WT, dx, ex, XT, dw, ew, s);
+      launch_dx_dw(dS, W, p.k_major_w ? nullptr : WT, dx, ex, XT, dw, ew, s);
     } else {
       {
         ProfScope ps(RL_PROF_GEMM_DX, s);
@@ -1089,7 +1102,7 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
   T* WT = static_cast<T*>(q.wt); T* XT = static_cast<T*>(q.xt);
   T* E = static_cast<T*>(q.ds);
   T* dX = static_cast<T*>(out->d_hidden);
-  {
+  if (!p.k_major_w) {
     ProfScope ps(RL_PROF_TRANSPOSE, s);
     dim3 g((p.Vp + 63) / 64, (p.H + 63) / 64);
     launch_transpose<T>(g, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
@@ -1139,7 +1152,7 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
       dw.chunk = chunk; dw.dyn = 3; dw.k_round = 256; dw.zero_if_empty = (k == 0); dw.group_m = TuneDW::kBand; dw.a_tiled = dw.b_tiled = 1;
       EpiDW ew{out->d_weight, p.H, p.V, p.H, k > 0 ? 1 : 0};
       ProfScope ps(RL_PROF_GEMM_BWD, s);
-      launch_dx_dw(E, WT, dx, ex, XT, dw, ew, s);
+      launch_dx_dw(E, W, p.k_major_w ? nullptr : WT, dx, ex, XT, dw, ew, s);
     }
   }
   ProfScope ps(RL_PROF_LOSS, s);

@@ -67,3 +67,34 @@ def test_bf16_dx_in_slices(H, V, lengths, modes):
         for mode in modes:
             for chunk in (0, 512):
                 print(objective, mode, chunk, compare_all(b, run_gpu(b, objective, chunk_rows=chunk, mode=mode), ref, **BF16_TOL), flush=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,V,lengths", [
+    (8, 257, [3, 0, 1, 2]),             # one 16-byte chunk of K, one row past a vocabulary tile
+    (120, 512, [40, 1, 0, 30]),         # the only slab pair ends inside its second slab
+    (136, 300, [100, 100, 57, 3]),      # two slab pairs, the last chunk alone in the second
+    (264, 1000, [5, 300, 0, 9]),        # three pairs: all of them in the tail loop
+    (520, 769, [64, 64, 64, 64]),       # five pairs: plain loop and tail loop
+    (1160, 2000, [31, 2, 200, 1]),
+])
+def test_bf16_hidden_sizes_off_the_slab_grid(H, V, lengths):
+    cfg = synth.RolloutConfig("edge", 2, 2, 1, 64, H, V, "bf16", 0.5, seed=33)
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=lengths)
+    for objective in ("grpo", "flow"):
+        ref = run_oracle(b, objective)
+        print(objective, compare_all(b, run_gpu(b, objective), ref, **BF16_TOL), flush=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V", [512, 513, 575, 576, 577, 767, 1024 + 129])      # rows of W past the last slab: none, one, all but one, a whole slab, ...
+def test_dx_reads_w_to_its_last_row_and_no_further(V):
+    cfg = synth.RolloutConfig("edge", 2, 2, 1, 64, 384, V, "bf16", 0.5, seed=34)
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[20, 3, 0, 40])
+    # W in front of a block of NaN: whatever is read past its last row shows
+    buf = torch.full((V + 300, 384), float("nan"), dtype=torch.bfloat16, device="cuda")
+    buf[:V] = b.weight
+    b.weight = buf[:V]
+    ref = run_oracle(b, "grpo")
+    for mode in ("recompute", "stash"):
+        print(mode, compare_all(b, run_gpu(b, "grpo", mode=mode), ref, **BF16_TOL), flush=True)
