@@ -38,6 +38,7 @@ template <class T>
 struct EpiFwd {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSwap = false;
   static constexpr bool kSplit = false;
   static constexpr bool kPermute = false;
   static constexpr bool kGatherB = true;      // the B rows come through a row map (GemmDims::b_rows)
@@ -167,6 +168,7 @@ struct EpiFwdStash {
     }
     return p;
   }
+  static constexpr bool kSwap = false;
   static constexpr bool kSplit = false;
   static constexpr bool kPermute = true;
   static constexpr bool kGatherB = true;      // the B rows come through a row map (GemmDims::b_rows)
@@ -283,6 +285,7 @@ template <class T>
 struct EpiDS {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSwap = false;
   static constexpr bool kSplit = false;
   static constexpr bool kPermute = true;
   static constexpr bool kGatherB = true;      // the B rows come through a row map (GemmDims::b_rows)
@@ -378,6 +381,7 @@ template <class T>
 struct EpiDX {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSwap = true;        // hot kernel: blocks transposed, a lane holds four consecutive columns of one row
   static constexpr bool kSplit = true;       // may be cut along K (split_k)
   static constexpr bool kPermute = false;
   static constexpr bool kGatherB = false;      // the B rows come through a row map (GemmDims::b_rows)
@@ -387,8 +391,42 @@ struct EpiDX {
   const float* row_scale;   // optional [chunk row]: factor applied to the whole row
   float* split_part;        // K slices: [slice][ceil(M / BM) * BM][H] partial tiles, added up by splitk_reduce_kernel
 
+  // Hot kernel: lane (g, r) = (l / 16, l % 16) holds row 16 bi + r, columns 16 bj + 4 g .. + 3 of the sub-tile.  PART: to the partial
+  // buffer in f32; EDGE: the sub-tile reaches past the last row or column (H is a multiple of 8: never inside a lane's four).
+  template <int MB, int NB, bool PART, bool EDGE>
+  __device__ __attribute__((always_inline)) void rows(floatx4 (&acc)[MB][NB], const TileCtx& c, const GemmDims& d, float* part) const {
+    const int r = c.lane & 15, n = c.n0 + (c.lane >> 4) * 4;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi) {
+      const int m = c.m0 + bi * 16 + r;
+      if (EDGE && m >= c.Mv) continue;
+      const float f = !PART && row_scale ? row_scale[m] : 1.f;
+      float* p = PART ? part + (int64_t)m * H + n : nullptr;
+      T* o = PART ? nullptr : dX + (int64_t)row_map[d.chunk_start + m] * ldx + n;
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj) {
+        floatx4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = f * acc_read<true>(acc[bi][bj], e);
+        if (EDGE && n + bj * 16 >= H) continue;
+        if constexpr (PART) *reinterpret_cast<floatx4*>(p + bj * 16) = v;
+        else Pack4<T>::store(o + bj * 16, v[0], v[1], v[2], v[3]);
+      }
+    }
+  }
+
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims& d, const Pre&) const {
+    if constexpr (AGPR) {
+      const bool edge = c.m0 + MB * 16 > c.Mv || c.n0 + NB * 16 > H;
+      if (c.slices > 1) {
+        float* part = split_part + (int64_t)c.slice * ((c.Mv + BM - 1) / BM * BM) * H;
+        if (edge) rows<MB, NB, true, true>(acc, c, d, part); else rows<MB, NB, true, false>(acc, c, d, part);
+      } else {
+        if (edge) rows<MB, NB, false, true>(acc, c, d, nullptr); else rows<MB, NB, false, false>(acc, c, d, nullptr);
+      }
+      return;
+    }
     if (c.slices > 1) {
       float* p = split_part + (int64_t)c.slice * ((c.Mv + BM - 1) / BM * BM) * H;     // (H % 4 == 0)
 #pragma unroll
@@ -446,20 +484,57 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDims d, EpiDX<T>
 }
 
 // ---- backward, stage 3: dW tile, f32, overwritten by the first chunk and accumulated after.
-//      When accumulating, the old values of a whole block row are fetched first (32 loads in flight)
+//      When accumulating, the old values of several blocks are fetched first (many loads in flight)
 //      and only then added and stored: a load-add-store per element would pay the memory latency
-//      256 times per tile.
+//      256 times per tile.  Hot kernel: 16 bytes per lane, bounds looked at once per tile.
 struct EpiDW {
   typedef NoPre Pre;
   template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  static constexpr bool kSwap = true;        // hot kernel: blocks transposed, a lane holds four consecutive columns of one row
   static constexpr bool kSplit = false;
   static constexpr bool kPermute = false;
   static constexpr bool kGatherB = false;      // the B rows come through a row map (GemmDims::b_rows)
   __device__ void keep_alive() const { dW[0] = 0.f; }
   float* dW; int64_t ldw; int V, H; int accumulate;
 
+  template <int MB, int NB, bool ACC, bool EDGE>
+  __device__ __attribute__((always_inline)) void rows(floatx4 (&acc)[MB][NB], const TileCtx& c) const {
+    const int r = c.lane & 15, n = c.n0 + (c.lane >> 4) * 4;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi) {
+      const int m = c.m0 + bi * 16 + r;
+      if (EDGE && m >= V) continue;
+      float* p = dW + (int64_t)m * ldw + n;
+      floatx4 old[NB];
+      if (ACC) {
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj) if (!EDGE || n + bj * 16 < H) old[bj] = *reinterpret_cast<const floatx4*>(p + bj * 16);
+      }
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj) {
+        floatx4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc_read<true>(acc[bi][bj], e);
+        if (ACC) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = old[bj][e] + v[e];
+        }
+        if (!EDGE || n + bj * 16 < H) *reinterpret_cast<floatx4*>(p + bj * 16) = v;
+      }
+    }
+  }
+
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims&, const Pre&) const {
+    if constexpr (AGPR) {
+      const bool edge = c.m0 + MB * 16 > V || c.n0 + NB * 16 > H;
+      if (accumulate) {
+        if (edge) rows<MB, NB, true, true>(acc, c); else rows<MB, NB, true, false>(acc, c);
+      } else {
+        if (edge) rows<MB, NB, false, true>(acc, c); else rows<MB, NB, false, false>(acc, c);
+      }
+      return;
+    }
     constexpr int RUN = L::kRegs < 4 ? L::kRegs : 4;      // registers handled per round: 4 rows x NB columns
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)

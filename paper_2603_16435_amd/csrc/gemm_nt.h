@@ -691,7 +691,9 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     const int slot = ((fs * 4 + fq) ^ swz) << 4;
 #pragma unroll
     for (int q = 0; q < 32; ++q) {
-      mfma16(acc[q >> 2][half * 4 + (q & 3)], fa[aset][q >> 2], fb[bset][q & 3]);
+      // (the operands' layouts are alike: exchanged, they give the transposed block with the same sums)
+      if constexpr (Epi::kSwap) mfma16(acc[q >> 2][half * 4 + (q & 3)], fb[bset][q & 3], fa[aset][q >> 2]);
+      else mfma16(acc[q >> 2][half * 4 + (q & 3)], fa[aset][q >> 2], fb[bset][q & 3]);
       if (ATR && kind == 12) {                          // sixteen half-reads of A, one per MFMA, then the four of B
         if (q < 16) read_a_tr(fa[aset ^ 1][q >> 1], fstage, q >> 1, fs, q & 1);
         else if (q % DSG == 0 && q < 24) fb[bset ^ 1][(q - 16) / DSG] = *reinterpret_cast<const u32x4_t*>(fstage + brow + ((q - 16) / DSG) * 16 * kSlabBytes + slot);
