@@ -30,14 +30,32 @@ template <> __device__ inline float exp_shifted<bf16_t>(float z, float, float m_
 }
 template <> __device__ inline float exp_shifted<float>(float z, float m, float, float zs, float) { return expf(z * zs - m); }
 
+// A lane's value and that of the lane OFF (16 or 32) away, lower lane first: the same pair in both lanes.
+template <int OFF>
+__device__ __attribute__((always_inline)) inline void lane_pair(float v, float& lo, float& hi) {
+  const unsigned u = __float_as_uint(v);
+  if constexpr (OFF == 16) { const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false); lo = __uint_as_float(r[0]); hi = __uint_as_float(r[1]); }
+  else { const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false); lo = __uint_as_float(r[0]); hi = __uint_as_float(r[1]); }
+}
+
 // ---- forward: per-token partial (max m, s = sum exp(z-m), u = sum exp(z-m) z) over this tile's vocab
 //      range + target gather; z_t[y_t] is written by the single lane that holds vocab row y_t of token t.
 //      u feeds the entropy H_t = lse_t - u/s of the full distribution at no extra pass.
 //      z is the tempered logit zs * (W x_t), zs = 1 / temperature; everything written is in tempered units.
 template <class T>
 struct EpiFwd {
-  typedef NoPre Pre;
-  template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  // sampled tokens of the lane's columns, fetched ahead of the main loop (one after the other in the epilogue they cost a memory
+  // latency per column block: 7 us of a tile)
+  struct Pre { int y[8]; };
+  template <class L> __device__ Pre preload(const TileCtx& c, const GemmDims& d) const {
+    Pre p;
+#pragma unroll
+    for (int bj = 0; bj < 8; ++bj) {
+      const int n = c.n0 + L::col(bj, c.lane);
+      p.y[bj] = n < c.Nv ? ids_c[d.chunk_start + n] : -1;
+    }
+    return p;
+  }
   static constexpr bool kSwap = false;
   static constexpr bool kSplit = false;
   static constexpr bool kPermute = false;
@@ -83,18 +101,35 @@ struct EpiFwd {
     mx *= zs; su *= zs;
   }
 
+  template <int OFF, int NB>
+  __device__ __attribute__((always_inline)) void merge_lanes(float (&mx)[NB], float (&sm)[NB], float (&su)[NB]) const {
+    const float NEG = -__builtin_inff();
+#pragma unroll
+    for (int bj = 0; bj < NB; ++bj) {
+      float m1, m2, s1, s2, u1, u2;
+      lane_pair<OFF>(mx[bj], m1, m2); lane_pair<OFF>(sm[bj], s1, s2); lane_pair<OFF>(su[bj], u1, u2);
+      const float mm = fmaxf(m1, m2);
+      const float mms = (mm == NEG) ? 0.f : mm;
+      const float f1 = fast_exp<T>(m1 - mms), f2 = fast_exp<T>(m2 - mms);
+      sm[bj] = s1 * f1 + s2 * f2;
+      su[bj] = u1 * f1 + u2 * f2;
+      mx[bj] = mm;
+    }
+  }
+
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char* smem, const GemmDims& d, const Pre& pre) const {
     float4* red = reinterpret_cast<float4*>(smem);              // [WAVES_M][BN]
     const float NEG = -__builtin_inff();
     const int vleft = V - c.m0;                                 // rows of this sub-tile below vleft are real vocabulary
     const bool pad = vleft < MB * L::kBlk;                      // wavefront-uniform
+    static_assert(NB <= 8, "Pre holds eight columns");
+    float mx[NB], sm[NB], su[NB];
 #pragma unroll
     for (int bj = 0; bj < NB; ++bj) {
       const int n = c.n0 + L::col(bj, c.lane);
-      const bool valid = n < c.Nv;
       // target gather: at most one lane of the whole grid holds row y of column n, so this branch is almost never taken
-      const int yrel = valid ? ids_c[d.chunk_start + n] - c.m0 : -1;
+      const int yrel = pre.y[bj] >= 0 ? pre.y[bj] - c.m0 : -1;
       if (yrel >= 0 && yrel < MB * L::kBlk && L::owns(yrel, c.lane)) {
         float zy = 0.f;
         int got = -1;
@@ -108,22 +143,16 @@ struct EpiFwd {
         zy_c[d.chunk_start + n] = zy * zs;
         ycol_c[d.chunk_start + n] = got;
       }
-      float mx, sm, su;
-      if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, mx, sm, su);
-      else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, mx, sm, su);
-      // merge with the lane groups that hold the other rows of this column
-#pragma unroll
-      for (int off = L::kBlk; off < 64; off <<= 1) {
-        const float mx2 = __shfl_xor(mx, off), sm2 = __shfl_xor(sm, off), su2 = __shfl_xor(su, off);
-        const float mm = fmaxf(mx, mx2);
-        const float mms = (mm == NEG) ? 0.f : mm;
-        const float f1 = fast_exp<T>(mx - mms), f2 = fast_exp<T>(mx2 - mms);
-        sm = sm * f1 + sm2 * f2;
-        su = su * f1 + su2 * f2;
-        mx = mm;
-      }
-      if (c.lane < L::kBlk) red[c.wm * BN + (n - c.tile_n * BN)] = make_float4(mx, sm, su, 0.f);
+      if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
+      else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
     }
+    // merge with the lane groups that hold the other rows of these columns (row swaps at vector speed; the pair comes lower
+    // lane first, which is the order the lanes whose result is kept add in)
+    merge_lanes<L::kBlk, NB>(mx, sm, su);
+    if constexpr (L::kBlk == 16) merge_lanes<32, NB>(mx, sm, su);
+#pragma unroll
+    for (int bj = 0; bj < NB; ++bj)
+      if (c.lane < L::kBlk) red[c.wm * BN + (c.n0 + L::col(bj, c.lane) - c.tile_n * BN)] = make_float4(mx[bj], sm[bj], su[bj], 0.f);
     __syncthreads();
     if (c.tid < BN) {
       const int n = c.tile_n * BN + c.tid;
@@ -283,8 +312,21 @@ template <> struct Pack4<float> {
 //      vocabulary entries of a token: the copy leaves in 16-byte stores with no staging through LDS.
 template <class T>
 struct EpiDS {
-  typedef NoPre Pre;
-  template <class L> __device__ Pre preload(const TileCtx&, const GemmDims&) const { return Pre(); }
+  struct Pre { int y[8]; float lse[8], ct[8]; };          // hot kernel: the lane's eight token columns, fetched ahead of the main loop
+  template <class L> __device__ Pre preload(const TileCtx& c, const GemmDims& d) const {
+    Pre p;
+    if constexpr (sizeof(T) == 2 && L::kBlk == 16) {
+#pragma unroll
+      for (int bj = 0; bj < 8; ++bj) {
+        const int n = c.n0 + perm_col(bj, c.lane & 15), t = d.chunk_start + n;
+        const bool valid = n < c.Nv;
+        p.y[bj] = valid ? ids_c[t] : -1;
+        p.lse[bj] = valid ? lse_c[t] : 3.0e38f;           // invalid token: p = exp(z - huge) = 0 and
+        p.ct[bj] = valid ? c_c[t] : 0.f;                  // c = 0, so every dS entry becomes 0
+      }
+    }
+    return p;
+  }
   static constexpr bool kSwap = false;
   static constexpr bool kSplit = false;
   static constexpr bool kPermute = true;
@@ -298,19 +340,16 @@ struct EpiDS {
   float zs;                 // inverse temperature
 
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
-  __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims& d, const Pre&) const {
+  __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims& d, const Pre& pre) const {
     if constexpr (AGPR) {                                  // hot kernel
       static_assert(MB == 8 && NB == 8 && sizeof(T) == 2, "the relabelling is written for 128x128 wavefront sub-tiles");
       const int g = c.lane >> 4, cc = c.lane & 15;
       int y[NB]; float lse[NB], lse_l2e[NB], ct[NB];
 #pragma unroll
       for (int bj = 0; bj < NB; ++bj) {
-        const int n = c.n0 + perm_col(bj, cc);
-        const bool valid = n < c.Nv;
-        const int t = d.chunk_start + n;
-        y[bj] = valid ? ids_c[t] - c.m0 : -1;             // relative to the sub-tile; -1 never matches
-        lse[bj] = valid ? lse_c[t] : 3.0e38f;             // invalid token: p = exp(z - huge) = 0 and
-        ct[bj] = valid ? c_c[t] * zs : 0.f;               // c = 0, so every dS entry becomes 0
+        y[bj] = pre.y[bj] >= 0 ? pre.y[bj] - c.m0 : -1;   // relative to the sub-tile; -1 never matches
+        lse[bj] = pre.lse[bj];
+        ct[bj] = pre.ct[bj] * zs;
         lse_l2e[bj] = lse[bj] * kLog2e;
       }
       const float zs_l2e = zs * kLog2e;
