@@ -340,15 +340,18 @@ __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* mask, cons
   }
 }
 
+// one wavefront per row; rows that count are left alone (the dX epilogue writes them)
 template <class T>
-__global__ void zero_masked_rows_kernel(const int32_t* cpos, T* dX, int64_t R, int H) {
-  // one wavefront per row; rows that count are left alone (the dX epilogue writes them)
-  const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+__device__ inline void zero_masked_row(int64_t r, const int32_t* cpos, T* dX, int64_t R, int H) {
   if (r >= R || cpos[r] >= 0) return;
   const int lane = threadIdx.x & 63;
   uint4* p = reinterpret_cast<uint4*>(dX + r * H);
   const int n16 = H * (int)sizeof(T) / 16;
   for (int k = lane; k < n16; k += 64) p[k] = make_uint4(0, 0, 0, 0);
+}
+template <class T>
+__global__ void zero_masked_rows_kernel(const int32_t* cpos, T* dX, int64_t R, int H) {
+  zero_masked_row((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), cpos, dX, R, H);
 }
 
 // ------------------------------------------------------------------ single-pass backward: references
@@ -659,35 +662,55 @@ __global__ void finalize_kernel(const float* seq_loss, const float* gterm, const
 // ------------------------------------------------------------------ transposes (K-contiguous operands)
 // dst[c][r] = src[row_of(r)][c] for r < rows_valid, 0 for rows_valid <= r < ld_dst rows covered by the grid.
 template <class T>
-__global__ void transpose_kernel(const T* src, int64_t ld_src, int rows, int cols, const int32_t* row_idx,
-                                 const Ctrl* ctrl, int chunk_start, int dyn_rows, const ChunkDesc* desc, const float* row_scale,
-                                 T* dst, int64_t ld_dst, int rows_padded, bool dst_tiled) {
-  __shared__ T tile[64][65];
-  int rv = rows;
-  if (dyn_rows) {
+struct TransposeJob {
+  const T* src; int64_t ld_src; int rows, cols; const int32_t* row_idx;
+  const Ctrl* ctrl; int chunk_start, dyn_rows; const ChunkDesc* desc; const float* row_scale;
+  T* dst; int64_t ld_dst; int rows_padded; bool dst_tiled;
+};
+template <class T>
+__device__ inline void transpose_block(const TransposeJob<T>& j, int bx, int by, T (&tile)[64][65]) {
+  int rv = j.rows, chunk_start = j.chunk_start;
+  if (j.dyn_rows) {
     int left;
-    if (desc) { chunk_start = desc->row_start; left = desc->rows; } else left = ctrl->n_real - chunk_start;
+    if (j.desc) { chunk_start = j.desc->row_start; left = j.desc->rows; } else left = j.ctrl->n_real - chunk_start;
     if (left <= 0) return;
-    rv = left < rows ? left : rows;
+    rv = left < j.rows ? left : j.rows;
   }
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  if (dyn_rows && r0 >= ((rv + 255) & ~255)) return;
+  const int r0 = bx * 64, c0 = by * 64;
+  if (j.dyn_rows && r0 >= ((rv + 255) & ~255)) return;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;        // 256 threads: 4 rows per pass
+#pragma unroll 4
   for (int k = ty; k < 64; k += 4) {
     const int r = r0 + k, c = c0 + tx;
     T v = (T)0.f;
-    if (r < rv && c < cols) {
-      const int64_t sr = row_idx ? (int64_t)row_idx[chunk_start + r] : (int64_t)r;
-      v = src[sr * ld_src + c];
-      if (row_scale) v = (T)((float)v * row_scale[r]);
+    if (r < rv && c < j.cols) {
+      const int64_t sr = j.row_idx ? (int64_t)j.row_idx[chunk_start + r] : (int64_t)r;
+      v = j.src[sr * j.ld_src + c];
+      if (j.row_scale) v = (T)((float)v * j.row_scale[r]);
     }
     tile[k][tx] = v;
   }
   __syncthreads();
   for (int k = ty; k < 64; k += 4) {
     const int c = c0 + k, r = r0 + tx;
-    if (c < cols && r < rows_padded) dst[operand_index(dst_tiled, c, r, ld_dst)] = tile[tx][k];
+    if (c < j.cols && r < j.rows_padded) j.dst[operand_index(j.dst_tiled, c, r, j.ld_dst)] = tile[tx][k];
   }
+}
+template <class T>
+__global__ void transpose_kernel(TransposeJob<T> j) {
+  __shared__ T tile[64][65];
+  transpose_block(j, blockIdx.x, blockIdx.y, tile);
+}
+// W^T, X^T of the only chunk and the zeroing of the rows that do not count in one launch (f32: a small call is bound by its
+// launches): workgroups [0, nw) and [nw, nw + nx) transpose, the rest zero four rows each.
+__global__ __launch_bounds__(256) void backward_prep_kernel(TransposeJob<float> w, int wx, int nw, TransposeJob<float> x, int xx, int nx,
+                                                            const int32_t* cpos, float* dX, int64_t R, int H) {
+  __shared__ float tile[64][65];
+  int b = blockIdx.x;
+  if (b < nw) { transpose_block(w, b % wx, b / wx, tile); return; }
+  b -= nw;
+  if (b < nx) { transpose_block(x, b % xx, b / xx, tile); return; }
+  zero_masked_row((int64_t)(b - nx) * 4 + (threadIdx.x >> 6), cpos, dX, R, H);
 }
 
 // The same for bf16 with 16-byte accesses on both sides (cols % 8 == 0, 16-byte aligned rows; rows_padded % 8 == 0, tiled
@@ -752,8 +775,8 @@ static void launch_transpose(dim3 grid, hipStream_t s, const T* src, int64_t ld_
       return;
     }
   }
-  transpose_kernel<T><<<grid, 256, 0, s>>>(src, ld_src, rows, cols, row_idx, ctrl, chunk_start, dyn_rows, desc, row_scale,
-                                           dst, ld_dst, rows_padded, dst_tiled);
+  transpose_kernel<T><<<grid, 256, 0, s>>>(TransposeJob<T>{src, ld_src, rows, cols, row_idx, ctrl, chunk_start, dyn_rows, desc, row_scale,
+                                                           dst, ld_dst, rows_padded, dst_tiled});
 }
 
 // ------------------------------------------------------------------ MFMA ceiling probe (benchmark aid)
@@ -1022,24 +1045,30 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
   T* WT = static_cast<T*>(q.wt); T* XT = static_cast<T*>(q.xt);
   T* dS = static_cast<T*>(q.ds); T* dST = static_cast<T*>(q.dst);
   T* dX = static_cast<T*>(d_hidden);
-  // masked rows of dX are zero; rows that count are written by the dX epilogue
-  {
-    ProfScope ps(RL_PROF_TRANSPOSE, s);
-    const int rows_per_block = 4;
-    zero_masked_rows_kernel<T><<<(unsigned)((p.R + rows_per_block - 1) / rows_per_block), 256, 0, s>>>(q.cpos, dX, p.R, p.H);
+  // masked rows of dX are zero; rows that count are written by the dX epilogue.  W^T [H][Vp] with zero padding columns, once per
+  // call (bf16: unless dX reads W as it is).  With one chunk the f32 path does both, and X^T, in one launch.
+  const dim3 gw((p.Vp + 63) / 64, (p.H + 63) / 64), gx((p.Tc + 63) / 64, (p.H + 63) / 64);
+  bool xt_done = false;
+  if constexpr (sizeof(T) == 4) {
+    const int64_t nw = (int64_t)gw.x * gw.y, nx = (int64_t)gx.x * gx.y, n = nw + nx + (p.R + 3) / 4;
+    xt_done = p.n_chunks == 1 && n < (1 << 30);
+    if (xt_done) {
+      ProfScope ps(RL_PROF_TRANSPOSE, s);
+      backward_prep_kernel<<<(unsigned)n, 256, 0, s>>>(
+          TransposeJob<T>{W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, false}, (int)gw.x, (int)nw,
+          TransposeJob<T>{X, p.H, p.Tc, p.H, q.row_map, q.ctrl, 0, 1, nullptr, nullptr, XT, p.Tc, p.Tc, false}, (int)gx.x, (int)nx, q.cpos, dX, p.R, p.H);
+    }
   }
-  // W^T [H][Vp] with zero padding columns, once per call
-  if (!p.k_major_w) {
+  if (!xt_done) {
     ProfScope ps(RL_PROF_TRANSPOSE, s);
-    dim3 g((p.Vp + 63) / 64, (p.H + 63) / 64);
-    launch_transpose<T>(g, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
+    zero_masked_rows_kernel<T><<<(unsigned)((p.R + 3) / 4), 256, 0, s>>>(q.cpos, dX, p.R, p.H);
+    if (!p.k_major_w) launch_transpose<T>(gw, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
   }
   for (int ch = 0; ch < p.n_chunks; ++ch) {
     const int c0 = ch * p.Tc;
-    {  // X^T chunk [H][Tc], gathered through row_map, zero beyond the valid rows
+    if (!xt_done) {  // X^T chunk [H][Tc], gathered through row_map, zero beyond the valid rows
       ProfScope ps(RL_PROF_TRANSPOSE, s);
-      dim3 g((p.Tc + 63) / 64, (p.H + 63) / 64);
-      launch_transpose<T>(g, s, X, p.H, p.Tc, p.H, q.row_map, q.ctrl, c0, 1, nullptr, nullptr, XT, p.Tc, p.Tc, p.tiled);
+      launch_transpose<T>(gx, s, X, p.H, p.Tc, p.H, q.row_map, q.ctrl, c0, 1, nullptr, nullptr, XT, p.Tc, p.Tc, p.tiled);
     }
     {  // recompute logits, form dS (and dS^T for f32 inputs)
       GemmDims d{};
