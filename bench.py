@@ -312,14 +312,14 @@ def time_mode(a, b, batch, objective: str, backward: str, steps: int, warmup: in
     R, Hh, Vv = b.R, cfg.H, cfg.V
     class_bytes = {
         # mask + ids read, three zero-filled row outputs + compaction index, compacted ids / row map written;
-        # single pass also reads each token's x row and W[y] row for the target logit
-        "prep": R * (1 + 4 + 12 + 4) + T * 8 + (T * 2 * Hh * esz if stash else 0),
+        # single pass also reads each token's x row and W[y] row for the target logit and zeroes the dX rows of the others
+        "prep": R * (1 + 4 + 12 + 4) + T * 8 + ((T * 2 + R - T) * Hh * esz if stash else 0),
         # per-tile partials (float2 single pass, float4 recompute) in, lse / logp / entropy out
         "combine": tiles_v * T * (8 if stash else 16) + T * 24,
         # logp, old, ref, row map in; c_t twice out; single pass: the per-row patch and factor as well
         "loss": T * 24 + (T * 26 if stash else 0),
-        # W -> W^T and the X chunks -> X^T (read + write), masked dX rows zeroed
-        "transpose": 2 * Vv * Hh * esz + 2 * T * Hh * esz + (R - T) * Hh * esz,
+        # W -> W^T (bf16: beyond 32768 rows) and the X chunks -> X^T (read + write); recompute: masked dX rows zeroed
+        "transpose": (2 * Vv * Hh * esz if esz == 4 or R > 32768 else 0) + 2 * T * Hh * esz + (0 if stash else (R - T) * Hh * esz),
     }
     hbm = {}
     for k, nbytes in class_bytes.items():

@@ -5,11 +5,11 @@
 // Every contraction of the path is brought into this form (K contiguous in both operands)
 // so that one MFMA main loop serves the forward logits, the recomputed logits, dX and dW;
 // what differs is the epilogue functor that consumes the accumulators in registers.  One
-// exception: the hot kernel can also take its A operand K-major (the stored array is A^T, rows = k),
-// read through transposing LDS loads; dW uses that to contract dS^T X out of dS itself.
+// exception: the hot kernel can also take an operand K-major (the stored array is A^T or B^T, rows = k),
+// read through transposing LDS loads; dW uses that to contract dS^T X out of dS itself, dX of smaller batches to read W as it is.
 //
 // Two kernels share tile order, LDS layout and epilogues:
-//  * gemm_nt_bf16_kernel  - the hot one (bf16, K % 128 == 0).  256x256 tile, four wavefronts of
+//  * gemm_nt_bf16_kernel  - the hot one (bf16, 16-byte aligned rows).  256x256 tile, four wavefronts of
 //    128x128 each (256 accumulator registers per lane live in AGPRs, one wavefront per SIMD),
 //    K walked in slabs of 64, MFMA shape 16x16x32 (measured on this part: at the power limit it
 //    sustains about 15 % more flops than 32x32x16 on random data).  Slabs go from global memory
@@ -21,7 +21,7 @@
 //    sched_barrier, so the interleaving in the source is the interleaving issued.  A light
 //    software prefetch (one 4-byte load per 128-byte line, two slabs ahead, shared between the
 //    workgroups of an XCD; off for dX) pulls the next panels into that XCD's L2.
-//  * gemm_nt_kernel       - general kernel (f32 inputs, K not a multiple of 128, unaligned operands): tile size as
+//  * gemm_nt_kernel       - general kernel (f32 inputs, unaligned operands): tile size as
 //    a parameter, register-staged loads with a K-tail predicate.
 //
 // LDS rows are 128 B = eight 16-byte chunks; chunk c of row r sits at slot c ^ ((r>>1)&7),
@@ -112,7 +112,8 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
 // the work, `fill` steps of the other contraction of the launch included, spread over the slots.  A partial tile costs
 // more outside the loop (it is written and read again in f32), and no more than 2 slots workgroups are made, which bounds
 // the partial buffer.  The number of tokens is only known on the device, so every workgroup works the cut out for itself:
-// lane s of a wavefront prices s + 1 slices.
+// lane s of a wavefront prices s + 1 slices.  (747 tokens at the 7B head, H 3584, V 152064: 42 tiles of 2376 slabs; dX + dW in one launch
+// 3.84 ms, cut into three slices 2.24.)
 constexpr int kMaxSplit = 64, kSplitMinSteps = 4;
 struct SplitK { int slices, per; };
 __device__ __host__ inline int64_t split_cost(int tiles, int nk, int want, int slots, int64_t fill, SplitK& k) {
@@ -783,7 +784,7 @@ void gemm_nt_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict_
 // Two independent contractions in one launch: workgroups [0, n1) work on the first, the rest on the
 // second.  Used where one of them alone has too few tiles to fill the last round of the 256 CUs: the
 // other's workgroups then fill the tail.  n1 = launch_tiles() of the first (a multiple of the XCD count).
-// BTR1: the first contraction's B operand is given K-major, the second's A operand always is (see gemm_nt_bf16_tile).
+// BTR1: the first contraction's B operand is given K-major; the second's A operand always is (see gemm_nt_bf16_tile).
 template <class Epi1, class Tune1, class Epi2, class Tune2, bool BTR1>
 __global__ __launch_bounds__(256)
 void gemm_nt_bf16_pair_kernel(const bf16_t* __restrict__ A1, const bf16_t* __restrict__ B1, GemmDims d1, Epi1 epi1, int n1,

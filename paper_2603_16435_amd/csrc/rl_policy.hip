@@ -1,14 +1,14 @@
 // rl_policy.hip - kernels of the O(T) stages and the C ABI of the library.
 //
 // Pipeline of rl_policy_loss_fwd_bwd (all on the caller's stream, no host sync):
-//   prep      : per-sequence counts -> scan -> ordered compaction of the rows that count
-//               (row_map, ids_c), masked rows of the outputs zeroed
-//   advantage : group mean / std of the rewards -> A_i
+//   prep      : row outputs cleared, group mean / std of the rewards -> A_i; per-sequence counts; scan and ordered
+//               compaction of the rows that count (row_map, ids_c), chunk records
 //   forward   : per chunk of compacted rows: logits tiles (MFMA) -> partial (max,sumexp) per
 //               vocab tile + target logit -> combine -> lse_t, logp_t
 //   loss      : one workgroup per sequence: length-normalised sums, loss_i, c_t; final reduce
-//   backward  : W^T once; per chunk: X^T, recomputed logits -> dS (input precision; f32 inputs also dS^T),
-//               dX = dS W (scattered to original rows), dW (+)= dS^T X (bf16: dS read as a K-major operand)
+//   backward  : masked rows of dX zeroed, W^T once (f32, and bf16 beyond 32768 rows); per chunk: X^T, recomputed logits -> dS (input
+//               precision; f32 inputs also dS^T), dX = dS W (scattered to original rows; cut along K when its tiles are few),
+//               dW (+)= dS^T X (bf16: dS read as a K-major operand, same launch as dX)
 // The number of real rows is only known on the device, so grids are sized for the upper
 // bound R and every kernel trims itself against the device-side count.
 #include <hip/hip_runtime.h>
@@ -34,13 +34,17 @@ constexpr int kDefaultChunkRows = 32768;        // recompute mode: 128 x 14 dX t
 constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step time is flat (+-0.7 %) from 24576 to 65536 rows
 constexpr int kBM = 256, kBN = 256;
 // General kernel in f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU), or 256 x 16 where the large
-// ones would leave CUs without work.
+// ones would leave CUs without work.  MFMA-bound: 110 TFLOP/s, pipes 0.78 full at 2.2 GHz, the rest mostly the issue of loads and
+// addresses.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K: 6.25 ms; with 256 x 256 tiles 17.9 (27 dX
+// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 84 us against 557 (with 32-wide narrow tiles it took 7 % longer).
+constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
+
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
 // The copy costs 2 x 2 V H bytes a call (7B head: 410 us, and 1.1 GB of workspace); its contiguous slabs save up to 1 % of the two
 // contractions.  747 tokens at the 7B head: 3274 us with the copy, 2860 without; 11.5 k tokens (16 k rows): 38.65 / 38.37 ms; 67 k tokens
 // (131 k rows): 163.5 / 163.4; 36 k tokens at H 2048, V 32000 (65 k rows): 11.39 / 11.47.
 constexpr int64_t kKMajorRows = 32768;
-constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
+
 constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup per CU, a step of a K cut is two slabs
 // Per-contraction tuning of the hot kernel, from sweeps on the 7B-shaped workload:
 // tile-order band height (M-tiles per band), L2 prefetch distance in slabs (0 = off), where in a

@@ -3,7 +3,7 @@
 // The codes are those of rvq_encode.h (the float64 arg-min of the definition, lowest index on ties, bf16 residual between the
 // stages); with up to 32 vectors of a group the work is reading the codebooks once (256 groups x 16 stages x 512 entries:
 // 547 MB, 115 us at the rate of a large copy), and the kernel written for 256 and more vectors spends its time scoring copies
-// of the few there are (313 us).  Here a workgroup takes 16 NV vectors of one group:
+// of the few there are (324 us; this one: 137).  Here a workgroup takes 16 NV vectors of one group:
 //  * Four scoring wavefronts share the entries of a stage (blocks of 16 in turn).  They read the codebook straight from memory
 //    in MFMA operand layout (A = 16 entries, B = 16 vectors, -|c|^2/2 as the start of the accumulator), 64 entries each at a time,
 //    and always have the next 64 on their way, also across the end of a stage: the codebook does not depend on the codes.
