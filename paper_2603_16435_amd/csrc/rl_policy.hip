@@ -886,7 +886,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.n_chunks = (int)((b->R + tc - 1) / tc);
   p.bwd = bwd;
   p.tiled = (b->dtype == RL_BF16);
-  p.k_major_w = p.tiled && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
+  // (a workspace query may come without pointers: the size then covers any)
+  p.k_major_w = p.tiled && b->weight && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len

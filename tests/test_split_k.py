@@ -98,3 +98,29 @@ def test_dx_reads_w_to_its_last_row_and_no_further(V):
     ref = run_oracle(b, "grpo")
     for mode in ("recompute", "stash"):
         print(mode, compare_all(b, run_gpu(b, "grpo", mode=mode), ref, **BF16_TOL), flush=True)
+
+
+@pytest.mark.skipif(not os.path.exists(binding.LIB_PATH), reason="library not built")
+def test_workspace_query_without_pointers_covers_any_alignment():
+    lib, n = binding.lib(), {}
+    for ptr in (None, 0x1000, 0x1002):
+        b = binding.rl_batch()
+        b.R, b.H, b.V, b.B, b.P, b.dtype, b.weight, b.hidden = 1000, 136, 5000, 4, 2, binding.RL_BF16, ptr, ptr
+        size = C.c_size_t(0)
+        assert lib.rl_workspace_bytes(C.byref(b), None, 1, C.byref(size)) == 0
+        n[ptr] = size.value
+    assert n[0x1000] < n[0x1002] <= n[None]          # an aligned W is read as it is stored, another needs its transpose
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("off", [(1, 0), (0, 1), (1, 1)])      # hidden / weight off the 16-byte grid: the general kernel, W^T in memory
+def test_bf16_operands_off_the_16_byte_grid(off):
+    cfg = synth.RolloutConfig("edge", 2, 2, 1, 64, 136, 600, "bf16", 0.5, seed=35)
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[20, 3, 0, 40])
+    for name, o in zip(("hidden", "weight"), off):
+        t = getattr(b, name)
+        buf = torch.empty(t.numel() + o, dtype=t.dtype, device="cuda")
+        buf[o:].copy_(t.flatten())
+        setattr(b, name, buf[o:].view(t.shape))
+    ref = run_oracle(b, "flow")
+    print(compare_all(b, run_gpu(b, "flow"), ref, **BF16_TOL), flush=True)
