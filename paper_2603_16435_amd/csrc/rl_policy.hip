@@ -17,6 +17,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -36,7 +37,7 @@ constexpr int kBM = 256, kBN = 256;
 // General kernel in f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU), or 256 x 16 where the large
 // ones would leave CUs without work.  MFMA-bound: 110 TFLOP/s, pipes 0.78 full at 2.2 GHz, the rest mostly the issue of loads and
 // addresses.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K: 6.25 ms; with 256 x 256 tiles 17.9 (27 dX
-// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 84 us against 557 (with 32-wide narrow tiles it took 7 % longer).
+// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 73 us against 557 (with 32-wide narrow tiles it took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
@@ -959,6 +960,14 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
   const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);
   const int tm = (d.M + kBM - 1) / kBM, tn = (d.N + bn - 1) / bn;
   const int tiles = d.split_slots > 0 ? split_launch(tm, tn, d.split_slots) : launch_tiles(tm, tn);
+  if constexpr (std::is_same_v<Epi, EpiDW>) {
+    // dW has no per-tile partials and no padding to write, which ask for 256 rows: 64 x 16 tiles where the others would leave most CUs idle
+    // (356 tokens, H 128, V 1024: 128 workgroups instead of 32, 21.7 -> 11.2 us)
+    if (bn == kF32SmallBN && tm * tn < kHotSlots) {
+      gemm_nt_kernel<float, Epi, 64, kF32SmallBN, 4, 1><<<launch_tiles((d.M + 63) / 64, tn), 256, 0, s>>>(A, B, d, epi);
+      return;
+    }
+  }
   if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 2, 2><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
