@@ -25,6 +25,48 @@ __host__ __device__ constexpr int rvq_few_max_entries(int nv) { return kRvqFewSc
 
 __device__ __attribute__((always_inline)) inline void rvq_few_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// The code of a vector none of whose distances is below infinity (the vector, or the whole codebook, is not finite): the entry that
+// the main pass of rvq_encode_kernel is left with, so that a vector's codes do not depend on how many others are encoded with it.
+// That pass keeps the largest block maximum with the block's number in its low mantissa bits (which makes a NaN of an infinity, but
+// for block 0) behind a finite stand-in; here the same steps run over the stage's scores in LDS.  All 64 lanes call it; lane group kq
+// walks entries 4 kq .. 4 kq + 3 of every block.  sc: the lane's scores of block 0; the four blocks of a round are 64 apart, rounds `stride`.
+// Out of line: inlined, its code cost a call that never needs it 1.4 % (256 groups, 12 vectors: 136.6 -> 138.4 us; this way 135.9).
+__device__ __attribute__((noinline)) int rvq_unsettled_index(const floatx4* sc, int stride, int nblk, int kq) {
+  const int nb = 32 - __builtin_clz((unsigned)(nblk - 1));
+  const unsigned idmask = (1u << nb) - 1u;
+  float best = __uint_as_float((__float_as_uint(-3.0e38f) & ~idmask) | idmask);
+  floatx4 sv;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) sv[e] = -3.0e38f;
+#pragma unroll 1
+  for (int blk = 0; blk < nblk; ++blk) {
+    const floatx4 v = sc[(blk >> 2) * stride + (blk & 3) * 64];
+    const bool last = blk == nblk - 1;
+    float m3, mx;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m3) : "v"(v[0]), "v"(v[1]), "v"(v[2]));
+    asm("v_max_f32 %0, %1, %2" : "=v"(mx) : "v"(m3), "v"(v[3]));
+    if (last) mx = fmaxf(m3, v[3]);
+    const float m4 = __uint_as_float((__float_as_uint(mx) & ~idmask) | (unsigned)blk);
+    const bool gt = m4 > best;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sv[e] = gt ? v[e] : sv[e];
+    float raw = best;
+    asm("v_max_f32 %0, %0, %1" : "+v"(raw) : "v"(m4));
+    best = last ? fmaxf(best, m4) : raw;
+  }
+  int blk = (int)(__float_as_uint(best) & idmask);
+  if (blk >= nblk) blk = 0;
+  const float m = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
+  int i = 16 * blk + 4 * kq + (sv[0] == m ? 0 : sv[1] == m ? 1 : sv[2] == m ? 2 : 3);
+  unsigned a, b, ia, ib;
+  rvq_pair<16>(__float_as_uint(best), a, b); rvq_pair<16>((unsigned)i, ia, ib);
+  bool tb = __uint_as_float(b) > __uint_as_float(a) || (__uint_as_float(b) == __uint_as_float(a) && (int)ib < (int)ia);
+  best = __uint_as_float(tb ? b : a); i = (int)(tb ? ib : ia);
+  rvq_pair<32>(__float_as_uint(best), a, b); rvq_pair<32>((unsigned)i, ia, ib);
+  tb = __uint_as_float(b) > __uint_as_float(a) || (__uint_as_float(b) == __uint_as_float(a) && (int)ib < (int)ia);
+  return (int)(tb ? ib : ia);
+}
+
 // grid as for rvq_encode_kernel with 16 NV vectors per workgroup; S % 64 == 0, S <= rvq_few_max_entries(NV)
 template <int NV>
 __global__ __launch_bounds__(320, 1)
@@ -152,13 +194,16 @@ void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb,
       const bf16_t* stage_cb = cb + (int64_t)stage * S * kRvqD;
       const int v = lane < VECS ? lane : VECS - 1;
       const int n = count[v];
-      int z = n > 0 ? cand[v][0] : 0;                             // (no entry listed: no score of the stage was a number)
+      int z = cand[v][0];                                         // (at least one is listed: neither the largest score nor one that is not a number can fail the test)
       unsigned long long open = __ballot(lane < VECS && v0 + lane < L && n != 1);
       if (stats && lane == 0 && open) atomicAdd(stats, __builtin_popcountll(open));
       while (open) {
         const int q = __builtin_ctzll(open);
         open &= open - 1;
-        const int listed = count[q], m = listed > kRvqFewList ? S : listed;
+        // a vector that is not finite has no finite distance: nothing to look at
+        const unsigned two = reinterpret_cast<const unsigned*>(&bits[q][0])[lane];
+        const bool finite = !__ballot((two & 0x7f80u) == 0x7f80u || (two & 0x7f800000u) == 0x7f800000u);
+        const int listed = count[q], m = !finite ? 0 : listed > kRvqFewList ? S : listed;
         double dmin = __builtin_inf();
         int imin = 0x7fffffff;
         for (int i = 0; i < m; i += 4) {                          // four entries at a time, one per 16 lanes
@@ -169,10 +214,11 @@ void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb,
           for (int k = 0; k < 4; ++k) {
             const double dk = __shfl(d, 16 * k);
             const int ek = __shfl(ent, 16 * k);
-            if (ek >= 0 && (dk < dmin || (dk == dmin && ek < imin))) { dmin = dk; imin = ek; }
+            if (ek >= 0 && dk < __builtin_inf() && (dk < dmin || (dk == dmin && ek < imin))) { dmin = dk; imin = ek; }
           }
         }
-        if (imin < S && lane == q) z = imin;
+        if (__builtin_expect(imin >= S, 0)) imin = rvq_unsettled_index(score + (q >> 4) * 256 + kq * 16 + (q & 15), NV * 256, nblk, kq);     // (whatever the order of the list)
+        if (lane == q) z = imin;
       }
       if (lane < VECS) {
         count[lane] = 0;

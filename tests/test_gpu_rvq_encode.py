@@ -174,3 +174,26 @@ def test_rvq_encode_of_few_vectors_settles_near_and_equal_entries_exactly(L):
     np.testing.assert_array_equal(codes[0].cpu().numpy(), want)
     np.testing.assert_array_equal(_bits(res[0]), want_res)
     assert bool((codes[0, :, 2] == 0).all()) and int(n_exact.item()) >= 2 * L
+
+
+@pytest.mark.parametrize("L", [12, 30])
+@pytest.mark.parametrize("S", [512, 192])
+def test_rvq_codes_do_not_depend_on_how_many_vectors_are_encoded(L, S):
+    """Few vectors and the same ones in front of 1100 others (two kernels), among them vectors and entries that are not finite, for
+    which the definition names no code: it is settled all the same, by the scores and not by the order the wavefronts finish in."""
+    inf, nan = float("inf"), float("nan")
+    x, cb = synth.make_rvq_case(2, 1100 + L, 3, S, seed=0x5EED0500, device="cuda")
+    x, cb = x.clone(), cb.clone()
+    x[0, 1, 7], x[0, 2], x[0, 4, 100] = nan, nan, inf
+    x[0, 5, 0], x[0, 6, 3], x[0, 6, 64], x[0, 7] = -inf, inf, -inf, inf
+    cb[1, 0, 5, 9], cb[1, 0, 6], cb[1, 0, S - 1, 127] = nan, inf, -inf          # some entries of a stage ...
+    cb[1, 2, :, 1] = inf                                                        # ... all of them
+    x[1, 3, 2] = inf
+    want, want_res = binding.rl_rvq_encode(x, cb)
+    for _ in range(4):
+        codes, res = binding.rl_rvq_encode(x[:, :L].contiguous(), cb)
+        np.testing.assert_array_equal(codes.cpu().numpy(), want[:, :L].cpu().numpy())
+        np.testing.assert_array_equal(_bits(res), _bits(want_res[:, :L].contiguous()))
+    ordinary = [0, 3] + list(range(8, L))                                       # their neighbours leave these as they were
+    ref, _ = rvq.rvq_encode(_bits(x[0, ordinary]), _bits(cb[0]))
+    np.testing.assert_array_equal(want[0, ordinary].cpu().numpy(), ref)
