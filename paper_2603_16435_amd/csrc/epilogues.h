@@ -117,6 +117,55 @@ struct EpiFwd {
     }
   }
 
+  // Narrow tile of the f32 kernel (256 x 16, four wavefronts of 64 x 16).  Its sums are those of the 256 x 64 tile to the bit, so that a
+  // token's log-prob does not depend on how many rows are staged with it: there one lane adds up, in order, the 64 rows of a half tile
+  // (128 rows) whose bit 2 is the lane's half of the wavefront.  Here such a chain is spread over two lane groups of two wavefronts, so
+  // the exponentials are formed where the logits are, pass through LDS, and wavefront 0 adds up one chain per lane.
+  template <class L, int MB>
+  __device__ __attribute__((always_inline)) void narrow(typename L::acc_t (&acc)[MB][1], const TileCtx& c, unsigned char* smem, int vleft) const {
+    static_assert(L::kBlk == 16 && MB == 4 && sizeof(T) == 4, "four 16 x 16 blocks per wavefront");
+    const float NEG = -__builtin_inff();
+    float2* ev = reinterpret_cast<float2*>(smem);               // [position in the chain][chain: half of the lanes, half of the tile, column]
+    float* mw = reinterpret_cast<float*>(smem + 64 * 64 * 8);   // [wavefront][half of the lanes, column] largest logit
+    const int col = c.lane & 15, g = c.lane >> 4, hc = c.lane & 31;
+    float mx = NEG;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx = fmaxf(mx, L::row(bi, i, c.lane) < vleft ? acc[bi][0][i] : NEG);
+    float m1, m2;
+    lane_pair<32>(mx, m1, m2);
+    if (c.lane < 32) mw[c.wm * 32 + hc] = fmaxf(m1, m2);
+    __syncthreads();
+    mx = fmaxf(mw[(c.wm & 2) * 32 + hc], mw[(c.wm | 1) * 32 + hc]);
+    const float ms = (mx == NEG) ? 0.f : mx * zs;
+    float2* my = ev + ((c.wm & 1) * 32 + (g >> 1) * 4) * 64 + (g & 1) * 32 + (c.wm >> 1) * 16 + col;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float v = acc[bi][0][i];
+        const float e = exp_shifted<T>(v, ms, 0.f, zs, 0.f);
+        my[(bi * 8 + i) * 64] = make_float2(L::row(bi, i, c.lane) < vleft ? e : 0.f, v);
+      }
+    __syncthreads();
+    if (c.wm != 0) return;
+    float m[1], s[1] = {0.f}, u[1] = {0.f};
+#pragma unroll 16
+    for (int k = 0; k < 64; ++k) {
+      const float2 x = ev[k * 64 + c.lane];
+      s[0] += x.x;
+      u[0] = __builtin_fmaf(x.x, x.y, u[0]);
+    }
+    const int w2 = g & 1, h = g >> 1;                           // the chain of this lane
+    m[0] = fmaxf(mw[2 * w2 * 32 + h * 16 + col], mw[(2 * w2 + 1) * 32 + h * 16 + col]) * zs;
+    u[0] *= zs;
+    merge_lanes<32, 1>(m, s, u);
+    merge_lanes<16, 1>(m, s, u);
+    const int n = c.n0 + col;
+    if (c.lane < 16 && n < c.Nv) part[(int64_t)c.tile_m * ldp + n] = make_float4(m[0], s[0], u[0], 0.f);
+  }
+
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char* smem, const GemmDims& d, const Pre& pre) const {
     float4* red = reinterpret_cast<float4*>(smem);              // [WAVES_M][BN]
@@ -124,6 +173,7 @@ struct EpiFwd {
     const int vleft = V - c.m0;                                 // rows of this sub-tile below vleft are real vocabulary
     const bool pad = vleft < MB * L::kBlk;                      // wavefront-uniform
     static_assert(NB <= 8, "Pre holds eight columns");
+    constexpr bool kNarrow = L::kBlk == 16 && !AGPR;
     float mx[NB], sm[NB], su[NB];
 #pragma unroll
     for (int bj = 0; bj < NB; ++bj) {
@@ -143,9 +193,15 @@ struct EpiFwd {
         zy_c[d.chunk_start + n] = zy * zs;
         ycol_c[d.chunk_start + n] = got;
       }
-      if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
+      if constexpr (kNarrow) continue;
+      else if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
       else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
     }
+    if constexpr (kNarrow) {
+      static_assert(WAVES_M == 4 && WAVES_N == 1, "the wavefronts of a column are stacked along the vocabulary");
+      narrow<L, MB>(acc, c, smem, vleft);
+      return;
+    } else {
     // merge with the lane groups that hold the other rows of these columns (row swaps at vector speed; the pair comes lower
     // lane first, which is the order the lanes whose result is kept add in)
     merge_lanes<L::kBlk, NB>(mx, sm, su);
@@ -170,6 +226,7 @@ struct EpiFwd {
         }
         part[(int64_t)c.tile_m * ldp + n] = r;
       }
+    }
     }
   }
 };
