@@ -84,11 +84,14 @@ __global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows
 
 // Hidden layer.  grid (ceil(M / 16), ceil(P / 16)): a workgroup computes 16 units for 16 prompts with v_mfma_f32_16x16x4 (A = rows
 // of W1, B = rows of the pooled states, both straight from memory in operand layout: lane l holds row l%16, four
-// consecutive k of every 16), its eight wavefronts taking 16-wide k-steps in turn, eight in flight; the eight partial blocks are
-// added through LDS in order.  VEC: rows are 16-byte aligned (else element loads).  (The vector-FMA
-// form with the pooled states in LDS was bound by its LDS reads: 94 us against 18 us on the shape above.)
+// consecutive k of every 16), its eight wavefronts taking 16-wide k-steps in turn, eight in flight, into twelve
+// accumulators: a chain adds at most H / 64 products, and few MFMAs wait for the one before them (one accumulator, H / 8 products: the layer's
+// relative error at H = 3584 is 4.1e-7 against 1.5e-7, in the same time).  These are added in pairs, and so are the eight partial blocks,
+// through LDS.  (Sixteen accumulators leave one workgroup per CU: 64 prompts at H = M = 5120 took 1.2 % longer.)  VEC: rows are
+// 16-byte aligned (else element loads).  (The vector-FMA form with the pooled states in LDS was bound by its LDS reads: 94 us against
+// 18 us on the shape above.)
 template <bool VEC>
-__global__ __launch_bounds__(512) void logz_hidden_kernel(const float* W1, const float* b1, const float* pooled, int P, int H, int M,
+__global__ __launch_bounds__(512, 4) void logz_hidden_kernel(const float* W1, const float* b1, const float* pooled, int P, int H, int M,
                                                           float* a_out, float* g_out) {
   __shared__ float part[8][16][17];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15, kq = lane >> 4;
@@ -107,9 +110,11 @@ __global__ __launch_bounds__(512) void logz_hidden_kernel(const float* W1, const
     }
     return v;
   };
-  floatx4 acc;
+  floatx4 acc[12];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc[e] = 0.f;
+  for (int u = 0; u < 12; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[u][e] = 0.f;
   for (int k0 = wave * 16; k0 < H; k0 += 8 * 128) {
     floatx4 a[8], b[8];
 #pragma unroll
@@ -117,18 +122,25 @@ __global__ __launch_bounds__(512) void logz_hidden_kernel(const float* W1, const
 #pragma unroll
     for (int u = 0; u < 8; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc, 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc[2 * (u % 6) + (e & 1)] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc[2 * (u % 6) + (e & 1)], 0, 0, 0);
   }
 #pragma unroll
-  for (int e = 0; e < 4; ++e) part[wave][row][4 * kq + e] = acc[e];                          // [prompt][unit]
+  for (int u = 0; u < 6; ++u) acc[u] += acc[u + 6];
+  acc[0] = ((acc[0] + acc[3]) + (acc[1] + acc[4])) + (acc[2] + acc[5]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[wave][row][4 * kq + e] = acc[0][e];                        // [prompt][unit]
   __syncthreads();
   if (threadIdx.x < 256) {
     const int u = threadIdx.x & 15, q = threadIdx.x >> 4;
-    float s = 0.f;
+    float s[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += part[k][q][u];
+    for (int k = 0; k < 8; ++k) s[k] = part[k][q][u];
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1)
+#pragma unroll
+      for (int k = 0; k < 8; k += 2 * o) s[k] += s[k + o];
     if (j0 + u < M && p0 + q < P) {
-      const float v = s + b1[j0 + u];
+      const float v = s[0] + b1[j0 + u];
       a_out[(int64_t)(p0 + q) * M + j0 + u] = v; g_out[(int64_t)(p0 + q) * M + j0 + u] = gelu_f(v);
     }
   }

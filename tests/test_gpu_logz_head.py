@@ -93,3 +93,18 @@ def test_logz_head_at_the_edges_of_its_blocks(dtype, P, H, M, lens, offset):
     for got, want in ((dW1, g["dW1"]), (db1, g["db1"]), (dw2, g["dw2"])):
         assert np.abs(got.double().cpu().numpy() - want).max() <= 2e-5 * np.abs(want).max()
     assert abs(float(db2.item()) - g["db2"]) <= 1e-5 * max(1.0, abs(g["db2"]))
+
+
+def test_hidden_layer_adds_short_chains():
+    """dw2 of one prompt with d = 1 is gelu(W1 x + b1) itself.  A chain of n f32 additions of like terms is off by about
+    0.4 * 2^-24 * sqrt(n / 2) of the sum (rms): 1.3e-7 for the H / 64 = 56 products a chain may have here, 3.6e-7 for H / 8 = 448."""
+    H, M = 3584, 1024
+    X, cu, W1, b1, w2, b2, _ = _head(13, 2, H, M, (1, 1), torch.bfloat16)
+    dev = "cuda"
+    _, ws = binding.rl_logz_head_forward(X.to(dev), cu.to(dev), W1.to(dev), b1.to(dev), w2.to(dev), b2.to(dev))
+    _, _, dw2, _ = binding.rl_logz_head_backward(torch.tensor([1.0, 0.0], device=dev), w2.to(dev), H, ws)
+    a = W1.double() @ X[0].double() + b1.double()
+    want = 0.5 * a * (1 + torch.erf(a / 2 ** 0.5))
+    err = float((dw2.double().cpu() - want).norm() / want.norm())
+    print("relative error of the hidden layer:", err)
+    assert err <= 2e-7
