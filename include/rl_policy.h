@@ -146,7 +146,7 @@ typedef struct rl_outputs {     /* NULL = not wanted, except loss               
   int32_t*  seq_len;            /* [B]   |y_i|                                           */
   float*    coeff;              /* [R]   c_t = dloss/dlogp_t                             */
   void*     d_hidden;           /* [R,H] input dtype; d_hidden and d_weight NULL together skips the backward */
-  float*    d_weight;           /* [V,H] f32, overwritten                                */
+  float*    d_weight;           /* [V,H] f32, overwritten (either may start at any element, e.g. inside a flat gradient buffer) */
   float*    d_log_z;            /* [P]   zero for GRPO                                   */
   rl_stats* stats;              /* [1]                                                   */
   float*    entropy;            /* [R]   entropy of softmax(W x_t), from the forward pass' online sums */

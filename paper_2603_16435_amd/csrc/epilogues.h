@@ -345,6 +345,14 @@ struct EpiFwdStash {
   }
 };
 
+// Four floats, four bf16 or 16 bytes in the caller's d_weight / d_hidden, which may start at any element (a parameter's slice of a flat
+// gradient buffer): the device takes such accesses at any address, the types say that it must.
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef __bf16 bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
+template <class T> struct Piece16;
+template <> struct Piece16<float> { typedef unsigned type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Piece16<bf16_t> { typedef unsigned type __attribute__((ext_vector_type(4), aligned(2))); };
+
 template <class T> struct Pack4;
 template <> struct Pack4<bf16_t> {
   __device__ static void store(bf16_t* p, float a, float b, float c, float d) {
@@ -506,7 +514,11 @@ struct EpiDX {
         for (int e = 0; e < 4; ++e) v[e] = f * acc_read<true>(acc[bi][bj], e);
         if (EDGE && n + bj * 16 >= H) continue;
         if constexpr (PART) *reinterpret_cast<floatx4*>(p + bj * 16) = v;
-        else Pack4<T>::store(o + bj * 16, v[0], v[1], v[2], v[3]);
+        else {
+          static_assert(sizeof(T) == 2, "hot kernel");
+          bf16x4_any b; b[0] = (T)v[0]; b[1] = (T)v[1]; b[2] = (T)v[2]; b[3] = (T)v[3];
+          *reinterpret_cast<bf16x4_any*>(o + bj * 16) = b;
+        }
       }
     }
   }
@@ -604,7 +616,7 @@ struct EpiDW {
       floatx4 old[NB];
       if (ACC) {
 #pragma unroll
-        for (int bj = 0; bj < NB; ++bj) if (!EDGE || n + bj * 16 < H) old[bj] = *reinterpret_cast<const floatx4*>(p + bj * 16);
+        for (int bj = 0; bj < NB; ++bj) if (!EDGE || n + bj * 16 < H) old[bj] = *reinterpret_cast<const floatx4_any*>(p + bj * 16);
       }
 #pragma unroll
       for (int bj = 0; bj < NB; ++bj) {
@@ -615,7 +627,7 @@ struct EpiDW {
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = old[bj][e] + v[e];
         }
-        if (!EDGE || n + bj * 16 < H) *reinterpret_cast<floatx4*>(p + bj * 16) = v;
+        if (!EDGE || n + bj * 16 < H) *reinterpret_cast<floatx4_any*>(p + bj * 16) = v;
       }
     }
   }

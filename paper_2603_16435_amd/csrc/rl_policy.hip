@@ -350,9 +350,9 @@ template <class T>
 __device__ inline void zero_masked_row(int64_t r, const int32_t* cpos, T* dX, int64_t R, int H) {
   if (r >= R || cpos[r] >= 0) return;
   const int lane = threadIdx.x & 63;
-  uint4* p = reinterpret_cast<uint4*>(dX + r * H);
+  typename Piece16<T>::type* p = reinterpret_cast<typename Piece16<T>::type*>(dX + r * H);
   const int n16 = H * (int)sizeof(T) / 16;
-  for (int k = lane; k < n16; k += 64) p[k] = make_uint4(0, 0, 0, 0);
+  for (int k = lane; k < n16; k += 64) p[k] = 0u;
 }
 template <class T>
 __global__ void zero_masked_rows_kernel(const int32_t* cpos, T* dX, int64_t R, int H) {
@@ -371,8 +371,8 @@ __global__ void target_logit_kernel(const bf16_t* X, const bf16_t* W, int64_t R,
   const int lane = threadIdx.x & 63;
   const int t = cpos[r];
   if (t < 0) {
-    uint4* p = reinterpret_cast<uint4*>(dX + r * H);
-    for (int k = lane; k < H / 8; k += 64) p[k] = make_uint4(0, 0, 0, 0);
+    Piece16<bf16_t>::type* p = reinterpret_cast<Piece16<bf16_t>::type*>(dX + r * H);
+    for (int k = lane; k < H / 8; k += 64) p[k] = 0u;
     return;
   }
   const uint4* x = reinterpret_cast<const uint4*>(X + r * H);

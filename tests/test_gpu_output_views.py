@@ -1,0 +1,39 @@
+"""Outputs that are views into larger buffers: gradients that start at any element."""
+import pytest
+import torch
+
+from paper_2603_16435_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _plan(b, mode, chunk):
+    c = b.cfg
+    batch = binding.make_batch(b.hidden, b.weight, b.token_ids, b.mask, b.cu_seqlens, b.group_idx, b.rewards, b.old_logprob,
+                               b.ref_logprob, b.log_z, c.P)
+    prm = binding.make_params(chunk_rows=chunk, backward_mode=mode, max_seq_len=int(b.lengths.max()) if mode == "stash" else 0)
+    return binding.PolicyLossPlan(batch, prm, "cuda", b.hidden.dtype)
+
+
+@pytest.mark.parametrize("dtype,H,V,mode,chunk", [
+    ("bf16", 384, 20001, "stash", 0),           # dX in slices, whole tiles and edges
+    ("bf16", 384, 20001, "recompute", 0),
+    ("bf16", 136, 600, "recompute", 256),       # two chunks: dW is read and added to
+    ("bf16", 256, 700, "stash", 256),
+    ("f32", 68, 900, "recompute", 256),
+])
+@pytest.mark.parametrize("off", [1, 3])
+def test_gradients_may_start_at_any_element(dtype, H, V, mode, chunk, off):
+    cfg = synth.RolloutConfig("views", 2, 2, 1, 64, H, V, dtype, 0.5, seed=71)
+    b = synth.make_rollouts(cfg, "cuda", "padded", lengths=[200, 56, 1, 160])
+    plan = _plan(b, mode, chunk)
+    want = plan.run(binding.RL_OBJ_FLOW)
+    dX = torch.full((b.R * H + 2 * off + 8,), 7.0, dtype=b.hidden.dtype, device="cuda")      # one guard on either side
+    dW = torch.full((V * H + 2 * off + 8,), 7.0, dtype=torch.float32, device="cuda")
+    plan.out.d_hidden, plan.out.d_weight = dX[off:].data_ptr(), dW[off:].data_ptr()
+    plan.run(binding.RL_OBJ_FLOW)
+    torch.cuda.synchronize()
+    assert dX[off:].data_ptr() % 16 and dW[off:].data_ptr() % 16
+    assert torch.equal(dX[off:off + b.R * H], want.d_hidden.flatten()) and torch.equal(dW[off:off + V * H], want.d_weight.flatten())
+    for g, n in ((dX, b.R * H), (dW, V * H)):
+        assert bool((g[:off] == 7.0).all()) and bool((g[off + n:] == 7.0).all())
