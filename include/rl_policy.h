@@ -161,8 +161,8 @@ typedef struct rl_outputs {     /* NULL = not wanted, except loss               
 } rl_outputs;
 
 /* Bytes of device workspace the two calls below need for this batch shape (host only; reads
- * R, H, V, B, P, dtype, the alignment of hidden / weight (weight NULL: the size covers any), and params->chunk_rows, backward_mode,
- * max_seq_len; params may be NULL = defaults; want_backward
+ * R, H, V, B, P, dtype, the alignment of hidden / weight (a size for aligned or NULL pointers serves any), and params->chunk_rows,
+ * backward_mode, max_seq_len; params may be NULL = defaults; want_backward
  * = 0 sizes it for rl_token_logprob / loss-only calls).  The workspace must be 256-byte
  * aligned.  Its contents on entry are irrelevant and on return unspecified. */
 rl_status rl_workspace_bytes(const rl_batch* batch, const rl_params* params,

@@ -41,7 +41,7 @@ constexpr int kBM = 256, kBN = 256;
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
-// The copy costs 2 x 2 V H bytes a call (7B head: 410 us, and 1.1 GB of workspace); its contiguous slabs save up to 1 % of the two
+// The copy costs 2 x 2 V H bytes a call (7B head: 410 us); its contiguous slabs save up to 1 % of the two
 // contractions.  747 tokens at the 7B head: 3274 us with the copy, 2860 without; 11.5 k tokens (16 k rows): 38.65 / 38.37 ms; 67 k tokens
 // (131 k rows): 163.5 / 163.4; 36 k tokens at H 2048, V 32000 (65 k rows): 11.39 / 11.47.
 constexpr int64_t kKMajorRows = 32768;
@@ -824,7 +824,7 @@ struct Plan {
   int Tc, Vp, tiles_v, n_chunks;
   bool bwd;
   bool tiled;            // bf16: the work buffers dS/E, W^T, X^T are slab-tiled (hot kernel operands)
-  bool k_major_w;        // dX reads W as it is stored: no W^T in the workspace
+  bool k_major_w;        // dX reads W as it is stored: no W^T is made
   bool stash;            // single-pass backward (forward keeps each chunk's unnormalised probabilities)
   int n_desc, max_len;   // stash: number of chunk records, promised bound on rows per sequence
   float inv_tau;         // 1 / temperature
@@ -887,8 +887,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.n_chunks = (int)((b->R + tc - 1) / tc);
   p.bwd = bwd;
   p.tiled = (b->dtype == RL_BF16);
-  // (a workspace query may come without pointers: the size then covers any)
-  p.k_major_w = p.tiled && b->weight && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
+  p.k_major_w = p.tiled && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len
@@ -912,7 +911,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.off_wt = p.off_xt = p.off_ds = p.off_dst = p.off_split = 0;
   if (bwd) {
     const size_t Hp = ((size_t)b->H + 255) & ~(size_t)255;   // tiled layouts come in blocks of 256 rows
-    if (!p.k_major_w) p.off_wt = take(p.esz * Hp * (size_t)p.Vp);
+    p.off_wt = take(p.esz * Hp * (size_t)p.Vp);            // (also where an aligned W is read as it is: the size holds for a W of any alignment)
     p.off_xt = take(p.esz * Hp * (size_t)tc);
     p.off_ds = take(p.esz * (size_t)tc * (size_t)p.Vp);
     if (b->dtype == RL_F32) {

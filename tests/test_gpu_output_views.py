@@ -1,4 +1,4 @@
-"""Outputs that are views into larger buffers: gradients that start at any element."""
+"""Tensors that are views into larger buffers: gradients that start at any element, a weight that starts off the 16-byte grid."""
 import pytest
 import torch
 
@@ -37,3 +37,18 @@ def test_gradients_may_start_at_any_element(dtype, H, V, mode, chunk, off):
     assert torch.equal(dX[off:off + b.R * H], want.d_hidden.flatten()) and torch.equal(dW[off:off + V * H], want.d_weight.flatten())
     for g, n in ((dX, b.R * H), (dW, V * H)):
         assert bool((g[:off] == 7.0).all()) and bool((g[off + n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("H,mode", [(136, "auto"), (256, "auto"), (256, "recompute")])
+def test_a_workspace_sized_for_an_aligned_weight_serves_one_that_is_not(H, mode):
+    cfg = synth.RolloutConfig("views", 2, 2, 1, 64, H, 700, "bf16", 0.5, seed=72)
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[20, 3, 0, 40])
+    plan = _plan(b, mode, 0)
+    buf = torch.empty(b.weight.numel() + 1, dtype=torch.bfloat16, device="cuda")
+    buf[1:].copy_(b.weight.flatten())
+    plan.batch.weight = buf[1:].data_ptr()
+    got = plan.run(binding.RL_OBJ_GRPO)
+    b.weight = buf[1:].view(b.weight.shape)
+    want = _plan(b, mode, 0).run(binding.RL_OBJ_GRPO)
+    torch.cuda.synchronize()
+    assert torch.equal(got.d_weight, want.d_weight) and torch.equal(got.d_hidden, want.d_hidden) and torch.equal(got.loss, want.loss)

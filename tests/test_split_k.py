@@ -101,15 +101,25 @@ def test_dx_reads_w_to_its_last_row_and_no_further(V):
 
 
 @pytest.mark.skipif(not os.path.exists(binding.LIB_PATH), reason="library not built")
-def test_workspace_query_without_pointers_covers_any_alignment():
-    lib, n = binding.lib(), {}
-    for ptr in (None, 0x1000, 0x1002):
+def test_workspace_sized_for_aligned_or_no_pointers_serves_any_alignment():
+    """A call whose weight or hidden states lie off the 16-byte grid takes other kernels; a workspace sized without pointers, or for
+    aligned ones, is large enough for those too."""
+    lib = binding.lib()
+
+    def size(hidden, weight, R, H, V, dtype, bwd, prm):
         b = binding.rl_batch()
-        b.R, b.H, b.V, b.B, b.P, b.dtype, b.weight, b.hidden = 1000, 136, 5000, 4, 2, binding.RL_BF16, ptr, ptr
-        size = C.c_size_t(0)
-        assert lib.rl_workspace_bytes(C.byref(b), None, 1, C.byref(size)) == 0
-        n[ptr] = size.value
-    assert n[0x1000] < n[0x1002] <= n[None]          # an aligned W is read as it is stored, another needs its transpose
+        b.R, b.H, b.V, b.B, b.P, b.dtype, b.weight, b.hidden = R, H, V, 4, 2, dtype, weight, hidden
+        n = C.c_size_t(0)
+        assert lib.rl_workspace_bytes(C.byref(b), C.byref(prm), bwd, C.byref(n)) == 0
+        return n.value
+
+    shapes = itertools.product((1, 300, 1000, 32768, 32769, 50000, 140000), (8, 128, 136, 3584), (300, 5000, 152064),
+                               (binding.RL_BF16, binding.RL_F32), (0, 1), (0, 512, 70000), (0, 1, 5000))
+    for R, H, V, dtype, bwd, chunk, promise in shapes:
+        prm = binding.make_params(chunk_rows=chunk, max_seq_len=promise)
+        n = {p: size(*p, R, H, V, dtype, bwd, prm) for p in itertools.product((None, 0x1000, 0x1002), repeat=2)}
+        enough = n[0x1000, 0x1000]
+        assert n[None, None] >= enough and max(n.values()) == n[None, None] and enough == max(n.values()), (R, H, V, dtype, bwd, chunk, promise)
 
 
 @pytest.mark.gpu
