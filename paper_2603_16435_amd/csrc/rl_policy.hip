@@ -129,9 +129,16 @@ __device__ inline double block_sum(double v, double* sh) {   // blockDim.x multi
 struct RowFill { int32_t* p[8]; int v[8]; };       // arrays of R words and the value of each (NULL: skipped)
 struct AdvJob {
   int blocks; const float* rewards; const int32_t* group_idx; int P; float adv_eps; int ddof;
-  float* adv; float* adv_out; int32_t* group_count;
+  float* adv; int32_t* group_count;
 };
 constexpr int kInitThreads = 256;
+
+__device__ inline void fill_rows(const RowFill& f, int64_t R, int block, int blocks) {
+  const int64_t step = (int64_t)blocks * kInitThreads;
+  for (int64_t r = (int64_t)block * kInitThreads + threadIdx.x; r < R; r += step)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) if (f.p[k]) f.p[k][r] = f.v[k];
+}
 
 // Thread per prompt p: mean and std of the rewards of its members, then A_i for each member (prompt indices and rewards
 // pass through LDS, members in order).  Sequences that name no prompt get 0.
@@ -146,7 +153,7 @@ __device__ inline void advantages_of_block(int blk, int B, const AdvJob& a, int*
       if (base + t < B) {
         const int g = a.group_idx[base + t];
         sh_g[t] = g; sh_r[t] = a.rewards[base + t];
-        if (pass == 0 && blk == 0 && (g < 0 || g >= a.P)) { a.adv[base + t] = 0.f; if (a.adv_out) a.adv_out[base + t] = 0.f; }
+        if (pass == 0 && blk == 0 && (g < 0 || g >= a.P)) a.adv[base + t] = 0.f;
       }
       __syncthreads();
       const int m = B - base < kInitThreads ? B - base : kInitThreads;
@@ -155,11 +162,7 @@ __device__ inline void advantages_of_block(int blk, int B, const AdvJob& a, int*
           const double r = (double)sh_r[i];
           if (pass == 0) { ++n; s += r; }
           else if (pass == 1) q += (r - mu) * (r - mu);
-          else if (p < a.P) {
-            const float A = (float)((r - mu) * inv);
-            a.adv[base + i] = A;
-            if (a.adv_out) a.adv_out[base + i] = A;
-          }
+          else if (p < a.P) a.adv[base + i] = (float)((r - mu) * inv);
         }
     }
   }
@@ -189,17 +192,15 @@ __global__ __launch_bounds__(kInitThreads) void prep_init_kernel(const int32_t* 
   } else if ((int)blockIdx.x <= adv.blocks) {
     advantages_of_block(blockIdx.x - 1, B, adv, sh_i, sh_f);
   } else {
-    const int64_t step = (int64_t)(gridDim.x - 1 - adv.blocks) * kInitThreads;
-    for (int64_t r = (int64_t)(blockIdx.x - 1 - adv.blocks) * kInitThreads + t; r < R; r += step)
-#pragma unroll
-      for (int k = 0; k < 8; ++k) if (f.p[k]) f.p[k][r] = f.v[k];
+    fill_rows(f, R, blockIdx.x - 1 - adv.blocks, gridDim.x - 1 - adv.blocks);
   }
 }
+__global__ __launch_bounds__(kInitThreads) void row_fill_kernel(int64_t R, RowFill f) { fill_rows(f, R, blockIdx.x, gridDim.x); }
 
 // One workgroup per sequence: validate its row range and group index, count rows that count.
 __global__ void seq_count_kernel(const uint8_t* mask, const int32_t* ids, const int32_t* cu, const int32_t* cu_hi,
                                  const int32_t* group_idx, int64_t R, int V, int P,
-                                 int32_t* seq_len, int32_t* seq_len_out, rl_stats* stats) {
+                                 int32_t* seq_len, rl_stats* stats) {
   const int i = blockIdx.x;
   __shared__ int sh_cnt, sh_bad;
   if (threadIdx.x == 0) { sh_cnt = 0; sh_bad = 0; }
@@ -221,7 +222,6 @@ __global__ void seq_count_kernel(const uint8_t* mask, const int32_t* ids, const 
   __syncthreads();
   if (threadIdx.x == 0) {
     seq_len[i] = sh_cnt;
-    if (seq_len_out) seq_len_out[i] = sh_cnt;
     if (stats) {
       if (sh_bad) atomicAdd(&stats->n_bad_token, sh_bad);
       if (!seq_ok) atomicAdd(&stats->n_bad_seq, 1);
@@ -640,15 +640,20 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
   }
 }
 
-// loss = (1/B) sum_i seq_loss_i ;  d_logZ_p = sum over members of gterm  (single workgroup)
+// loss = (1/B) sum_i seq_loss_i ;  d_logZ_p = sum over members of gterm  (single workgroup).  The caller's per-sequence arrays are
+// written here, when the rewards and the offsets have been read everywhere (rewards may turn into advantages in place).
 __global__ void finalize_kernel(const float* seq_loss, const float* gterm, const int32_t* group_idx,
-                                const int32_t* seq_len, int B, int P, int objective, const Ctrl* ctrl,
-                                float* loss, float* d_log_z, float* seq_loss_out) {
+                                const int32_t* seq_len, const float* adv, int B, int P, int objective, const Ctrl* ctrl,
+                                float* loss, float* d_log_z, float* seq_loss_out, float* adv_out, int32_t* seq_len_out) {
   __shared__ double sh[16];
   double acc = 0.0;
   for (int i = threadIdx.x; i < B; i += blockDim.x) {
-    acc += (double)seq_loss[i];
-    if (seq_loss_out) seq_loss_out[i] = seq_loss[i];
+    const float l = seq_loss[i], A = adv[i];
+    const int n = seq_len[i];
+    acc += (double)l;
+    if (seq_loss_out) seq_loss_out[i] = l;
+    if (adv_out) adv_out[i] = A;
+    if (seq_len_out) seq_len_out[i] = n;
   }
   const double tot = block_sum(acc, sh);
   // a sequence longer than the caller promised: the single-pass backward dropped rows, say so loudly
@@ -1014,6 +1019,15 @@ static Ptrs carve(void* ws, const Plan& p) {
   return q;
 }
 
+// whether a row output shares memory with what the preparation reads of the rows
+static bool on_prep_inputs(const rl_batch* b, const Plan& p, const void* out) {
+  auto meets = [&](const void* in, size_t bytes) {
+    const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(in);
+    return out && o < i + bytes && i < o + 4 * (size_t)p.R;
+  };
+  return meets(b->token_ids, 4 * (size_t)p.R) || meets(b->mask, (size_t)p.R) || meets(b->cu_seqlens, 4 * ((size_t)p.B + 1));
+}
+
 // prep: row outputs cleared (rows that do not count read 0 / -1), advantages, counts, compaction, chunk records
 static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int32_t* group_idx, const rl_outputs& out, const AdvJob& adv,
                      hipStream_t s) {
@@ -1021,16 +1035,25 @@ static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int3
   RowFill f{};
   int nf = 0;
   auto clear = [&](void* a, int v) { f.p[nf] = static_cast<int32_t*>(a); f.v[nf++] = v; };
-  clear(q.cpos, -1); clear(out.row_map, -1); clear(out.target_col, -1);
-  clear(out.logprob, 0); clear(out.lse, 0); clear(out.coeff, 0); clear(out.entropy, 0); clear(out.target_logit, 0);
+  // (the last three may take the place of what the compaction reads, e.g. target_col that of token_ids: they are then cleared after it)
+  const bool late = on_prep_inputs(b, p, out.target_col) || on_prep_inputs(b, p, out.entropy) || on_prep_inputs(b, p, out.target_logit);
+  auto clear_last = [&]() { clear(out.target_col, -1); clear(out.entropy, 0); clear(out.target_logit, 0); };
+  clear(q.cpos, -1); clear(out.row_map, -1);
+  clear(out.logprob, 0); clear(out.lse, 0); clear(out.coeff, 0);
+  if (!late) clear_last();
   const int64_t fill = (p.R + kInitThreads - 1) / kInitThreads;
   // the running maximum of the offsets borrows cstart until the compaction overwrites it with the compacted starts
   prep_init_kernel<<<1 + adv.blocks + (int)(fill < 2048 ? fill : 2048), kInitThreads, 0, s>>>(b->cu_seqlens, p.B, p.R, q.cstart, f, adv, out.stats);
-  seq_count_kernel<<<p.B, 256, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.cstart, group_idx, p.R, p.V, p.P, q.seq_len, out.seq_len, out.stats);
+  seq_count_kernel<<<p.B, 256, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.cstart, group_idx, p.R, p.V, p.P, q.seq_len, out.stats);
   const bool scan = p.B > kScanInline;
   if (scan) seq_scan_kernel<<<1, 1024, 0, s>>>(q.seq_len, p.B, q.cstart);
   compact_kernel<<<p.B + 1, 1024, 0, s>>>(b->mask, b->token_ids, b->cu_seqlens, q.seq_len, p.B, q.cstart, scan, p.V, q.row_map, q.ids_c, q.cpos,
                                           out.row_map, q.ctrl, ChunkJob{p.stash ? q.desc : nullptr, p.n_desc, p.Tc, p.max_len}, out.stats);
+  if (late) {
+    f = RowFill{}; nf = 0;
+    clear_last();
+    row_fill_kernel<<<(int)(fill < 2048 ? fill : 2048), kInitThreads, 0, s>>>(p.R, f);
+  }
 }
 
 template <class T>
@@ -1198,8 +1221,8 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     }
   }
   ProfScope ps(RL_PROF_LOSS, s);
-  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, p.B, p.P, objective, q.ctrl,
-                                    out->loss, out->d_log_z, out->seq_loss);
+  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, q.adv, p.B, p.P, objective, q.ctrl,
+                                    out->loss, out->d_log_z, out->seq_loss, out->advantages, out->seq_len);
 }
 
 static rl_status check_ws(void* ws, size_t bytes, const Plan& p) {
@@ -1367,8 +1390,7 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   (void)hipGetLastError();
   Ptrs q = carve(ws, p);
 
-  const AdvJob adv{(p.P + kInitThreads - 1) / kInitThreads, b->rewards, b->group_idx, p.P, prm->adv_eps, prm->adv_std_ddof, q.adv, out->advantages,
-                   out->group_count};
+  const AdvJob adv{(p.P + kInitThreads - 1) / kInitThreads, b->rewards, b->group_idx, p.P, prm->adv_eps, prm->adv_std_ddof, q.adv, out->group_count};
   run_prep(b, p, q, b->group_idx, *out, adv, s);
 
   if (p.stash) {
@@ -1383,8 +1405,8 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   seq_loss_kernel<<<p.B, 256, 0, s>>>(objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv,
                                      b->group_idx, b->log_z, p.B, loss_opts(prm), q.ctrl,
                                      q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, nullptr);
-  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, p.B, p.P, objective, q.ctrl,
-                                    out->loss, out->d_log_z, out->seq_loss);
+  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, q.adv, p.B, p.P, objective, q.ctrl,
+                                    out->loss, out->d_log_z, out->seq_loss, out->advantages, out->seq_len);
   }
   if (bwd) {
     if (p.dtype == RL_BF16) run_backward<bf16_t>(b, p, q, out->d_hidden, out->d_weight, s);
