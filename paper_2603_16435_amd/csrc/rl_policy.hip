@@ -1563,15 +1563,21 @@ rl_status rl_rvq_encode_counted(const void* vectors, const void* codebooks, cons
   if ((reinterpret_cast<uintptr_t>(vectors) | reinterpret_cast<uintptr_t>(codebooks) | reinterpret_cast<uintptr_t>(residual)) & 15) return RL_ERR_SHAPE;
   (void)hipGetLastError();
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // Few vectors: a kernel that reads each codebook once for 16 or 32 of them and scores nothing else (norms 16 bytes at a time).  It is
-  // the faster one up to 32 vectors of a group whatever the number of groups (16 stages of 512 entries, 16 vectors: 256 groups
-  // 332 -> 140 us, 512 groups 450 -> 278), with more of them as long as its workgroups, which read the codebook again, are all on
-  // the chip at a time, 32 on an accelerator die (the workgroups of a group share one; 32 groups of 256: 212 -> 154 us, 8 of 1024:
-  // 316 -> 153; one group of 4000 against 318 us: 583), and up to two rounds of them against one half-empty workgroup of the other
-  // kernel (64 vectors: 256 groups 336 -> 318; 512 groups 459 against 635 there).
+  // Few vectors: a kernel that reads each codebook once for 16 or 32 of them and scores nothing else (norms 16 bytes at a time).
+  //  * Up to 16 vectors of a group it is the faster one whatever the number of groups (16 stages of 512 entries, 16 vectors: 256 groups
+  //    332 -> 140 us, 512 groups 435 -> 270).
+  //  * With more it is as long as its workgroups, which read the codebook again, are all on the chip at a time, 32 on an accelerator
+  //    die (the workgroups of a group share one): 32 groups of 256 212 -> 154 us, 128 groups of 64 324 -> 159, one group of 4000 against
+  //    318 us 583.  A second round of them loses to one half-empty round of the other kernel (56 stages of 1024 entries: 160 groups of 50
+  //    1294 against 1774 us, 256 groups of 33 1419 against 1765; 40 of 64: 315 against 404) unless the codebooks of so many groups make
+  //    that one wait for memory (32 vectors, 40 stages of 1024: 264 groups 1205 against 1295, 384 groups 1470 -> 1320, 512 1697 -> 1352).
+  //  * A stage of 64 or 128 entries is over before its three barriers are: 8 groups of 17, 16 stages of 64 entries 68 against 81 us, of
+  //    128 86 against 86, of 192 103 -> 92.  The other kernel now and then looks at a whole stage again, 80 to 140 us; from some 16
+  //    thousand decisions on that is likely enough to outweigh it (8 groups of 48, 40 stages of 128: 384 -> 216).
   const int nv = L <= 16 ? 1 : 2;
   const int64_t few_per_die = (L + 16 * nv - 1) / (16 * nv) * (((int64_t)G + 7) / 8);
-  const bool few = L <= 32 || few_per_die <= 32 || (L <= 64 && few_per_die <= 64);
+  const bool short_stages = S <= 128 && L * S < 6144 && G * L * N < 16384;
+  const bool few = L <= 16 || (few_per_die <= 32 && !short_stages) || (L <= 32 && few_per_die >= 48 && S >= 256);
   if (few && S <= rvq_few_max_entries(nv) && reinterpret_cast<uintptr_t>(norms) % 16 == 0) {
     const unsigned n = (unsigned)((L + 16 * nv - 1) / (16 * nv) * (8 * (((int64_t)G + 7) / 8)));
     auto kern = nv == 1 ? rvq_few_kernel<1> : rvq_few_kernel<2>;

@@ -140,8 +140,16 @@ def test_rvq_encode_exact_path_is_rare_on_ordinary_inputs():
     (1, 64, 2, 1024),         # two workgroups of a group, the largest codebook of that form
     (1, 33, 2, 1088),         # ... and one beyond it
     (2, 65, 2, 128),          # three workgroups of each of two groups
-    (130, 33, 1, 64),         # more workgroups than fit the chip
-    (88, 65, 1, 64),          # three workgroups of each of eleven groups per die: one more than that form takes
+    (130, 33, 1, 64),         # two workgroups of each of seventeen groups per die: more than fit the chip, the other kernel
+    (88, 65, 1, 64),          # three of each of eleven: one more than fit
+    (80, 65, 2, 128),         # three of each of ten
+    (300, 16, 1, 64),         # up to 16 vectors: more workgroups than fit the chip
+    (376, 17, 2, 256),        # 47 workgroups a die ...
+    (384, 17, 2, 256),        # ... and 48, in two rounds
+    (384, 32, 2, 192),        # ... of a codebook too small for that
+    (8, 47, 2, 128),          # short stages, few decisions
+    (8, 48, 2, 128),          # enough vectors of a group
+    (241, 17, 4, 64),         # 16388 decisions
     (1, 1024, 2, 64),         # 32 workgroups on one die ...
     (1, 1025, 2, 64),         # ... and one more
 ])
