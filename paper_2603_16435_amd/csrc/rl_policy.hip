@@ -935,8 +935,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   return RL_OK;
 }
 
-// The bf16 hot kernel needs an even number of whole 64-element slabs and 16-byte aligned rows; anything else (f32
-// inputs, ragged K) takes the generic kernel.
+// bf16 contractions take the hot kernel but for logits whose operands are not 16-byte aligned, and those of small hidden sizes off its
+// grid of 128 (small_k).
 template <class Epi>
 static void launch_generic(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Epi& epi, int tiles, hipStream_t s) {
   gemm_nt_kernel<bf16_t, Epi, kBM, kBN, 2, 4><<<tiles, 512, 0, s>>>(A, B, d, epi);
@@ -948,12 +948,23 @@ static int split_launch(int tiles_m, int tiles_n, int slots) {
   return (int)(t > 2 * slots ? t : 2 * slots);
 }
 
+// Logits of small hidden sizes off the grid of 128 that take the general kernel: the hot one rounds K up to the grid, the general one
+// to 64, and with few slabs the shorter prologue and epilogue of its smaller wavefronts count for more than the main loop.  V 50257,
+// 16 k tokens, forward: H 136 724 us in the hot kernel, 584 in the general one; 200 747 / 682; 320 855 / 780; 328 878 / 898; 392 and 448,
+// where it also does a slab less, 995 / 981 and 983 / 967; 520 1119 / 1184.  The same holds from 96 tokens on (H 136 46.5 / 43.7, 328 49.9 /
+// 49.7).  The dS epilogue, whose tiles the general kernel writes in pieces of 8 bytes, tips over earlier (with the backward: H 192
+// 2502 / 2397, 200 2510 / 2621).  (By H alone: a token's bits must not depend on the batch.)
+template <class Epi> constexpr bool small_k(int) { return false; }
+template <> constexpr bool small_k<EpiFwd<bf16_t>>(int K) { return K % 128 && (K <= 320 || (K <= 448 && K % 128 <= 64)); }
+template <> constexpr bool small_k<EpiDS<bf16_t>>(int K) { return K % 128 && K <= 192; }
+
 template <class Tune, class Epi>
 static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, const Epi& epi, hipStream_t s) {
   const int tiles = launch_tiles((d.M + kBM - 1) / kBM, (d.N + kBN - 1) / kBN);
   const bool fast = (d.lda % 8 == 0) && (d.ldb % 8 == 0) && (d.K % 8 == 0) &&
                     ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0) &&
-                    !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB;     // (how the hot kernel addresses its operands)
+                    !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB &&     // (how the hot kernel addresses its operands)
+                    !small_k<Epi>(d.K);
   if (!fast) launch_generic(A, B, d, epi, tiles, s);
   else if (d.K % 128) gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);

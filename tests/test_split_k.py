@@ -71,10 +71,16 @@ def test_bf16_dx_in_slices(H, V, lengths, modes):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("H,V,lengths", [
-    (8, 257, [3, 0, 1, 2]),             # one 16-byte chunk of K, one row past a vocabulary tile
-    (120, 512, [40, 1, 0, 30]),         # the only slab pair ends inside its second slab
-    (136, 300, [100, 100, 57, 3]),      # two slab pairs, the last chunk alone in the second
-    (264, 1000, [5, 300, 0, 9]),        # three pairs: all of them in the tail loop
+    (8, 257, [3, 0, 1, 2]),             # general kernel: one 16-byte chunk of K, one row past a vocabulary tile
+    (120, 512, [40, 1, 0, 30]),         # ... its second slab ends one chunk early
+    (136, 300, [100, 100, 57, 3]),      # ... the last chunk alone in a third
+    (192, 700, [10, 0, 90, 31]),        # ... the last size with dS there
+    (200, 700, [10, 0, 90, 31]),        # dS in the hot kernel, two slab pairs
+    (264, 1000, [5, 300, 0, 9]),        # ... three pairs: all of them in the tail loop, the last chunk alone
+    (320, 1000, [5, 300, 0, 9]),        # the last size with the forward in the general kernel
+    (328, 500, [33, 1, 64, 0]),         # both in the hot kernel, all of K in the tail loop
+    (448, 500, [33, 1, 64, 0]),         # forward in the general kernel once more
+    (456, 500, [33, 1, 64, 0]),
     (520, 769, [64, 64, 64, 64]),       # five pairs: plain loop and tail loop
     (1160, 2000, [31, 2, 200, 1]),
 ])
