@@ -983,6 +983,18 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
       return;
     }
   }
+  if constexpr (std::is_same_v<Epi, EpiFwd<float>>) {
+    // The logits of the forward in 256 x 256 tiles (eight wavefronts) where these come in ten rounds of the chip or more and fill them as
+    // well: each reads its operands fewer times over (8 k tokens: H 768, V 50257 5251 -> 5056 us, H 1536, V 30000 6176 -> 5909), but with
+    // few rounds the last one, of a batch with fewer tokens than rows, costs more than that (1040 tokens, V 50257: 784 -> 843).  Same
+    // bits (EpiFwd).
+    const int64_t square = (int64_t)tm * ((d.N + 255) / 256), rounds = (square + kHotSlots - 1) / kHotSlots;
+    const int64_t halves = ((int64_t)tm * tn + kF32Slots - 1) / kF32Slots;          // rounds of 256 x 64 tiles, half as long
+    if (bn == kF32BN && rounds >= 10 && 100 * rounds <= 51 * halves) {
+      gemm_nt_kernel<float, Epi, kBM, 256, 2, 4><<<launch_tiles(tm, (d.N + 255) / 256), 512, 0, s>>>(A, B, d, epi);
+      return;
+    }
+  }
   if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 2, 2><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }

@@ -1,5 +1,5 @@
-"""A token's log-prob, lse and entropy are the same bits however many rows are staged with it: the f32 forward takes wide or narrow
-tiles by the size of the chunk, and both add in the same order."""
+"""A token's log-prob, lse and entropy are the same bits however many rows are staged with it: the f32 forward takes square, wide or narrow
+tiles by the size of the chunk, and all add in the same order."""
 import pytest
 import torch
 
@@ -9,7 +9,8 @@ from parity_util import run_gpu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V,rows,tau", [(1000, 9000, 0.0), (300, 17000, 0.8)])      # wide tiles from 8192 / 16384 staged rows on
+@pytest.mark.parametrize("V,rows,tau", [(1000, 9000, 0.0), (300, 17000, 0.8),       # wide tiles from 8192 / 16384 staged rows on
+                                          (30000, 8000, 0.0)])                     # square ones, fifteen rounds of them; wide; narrow
 def test_f32_log_probs_do_not_depend_on_the_chunk(V, rows, tau):
     cfg = synth.RolloutConfig("bits", 2, 4, 1, rows // 8, 68, V, "f32", 0.5, seed=61)
     b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[rows // 8] * 8)
