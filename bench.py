@@ -26,7 +26,8 @@ PEAK_F32_TFLOPS = 157.3
 # backward mode whose summary is profiles/gemm_nt_bf16_7b.md.  Counters cannot be read live, so these are constants of that run.
 MEASURED_TRAFFIC_7B = {        # default chunks: 40960 rows single-pass ("stash"), 32768 rows recompute
     "stash": {"gemm_fwd": 96.4e9 + 12.7e9, "gemm_bwd": 198.3e9 + 2.5e9},
-    # (dX and dW of the recompute mode share a launch; gemm_dx / gemm_dw are the two measured on their own)
+    # (dX and dW of the recompute mode share a launch, gemm_bwd; gemm_dx / gemm_dw are the profile's figures of the two on their own, a
+    # class that only f32 inputs have now)
     "recompute": {"gemm_fwd": 53.6e9 + 0.3e9, "gemm_ds": 57.4e9 + 10.0e9, "gemm_dx": 61.8e9 + 0.2e9, "gemm_dw": 85.1e9 + 2.2e9,
                   "gemm_bwd": 147.3e9 + 2.4e9},
 }
@@ -298,7 +299,7 @@ def time_mode(a, b, batch, objective: str, backward: str, steps: int, warmup: in
     thv = float(T) * cfg.H * cfg.V
     peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_F32_TFLOPS
     # dominant kernel: the contraction class with the largest share of the step
-    # flops of one step per launch class: each contraction is 2*T*H*V; gemm_bwd is dX and dW in one launch
+    # flops of one step per launch class: each contraction is 2*T*H*V; gemm_bwd is dX and dW in one launch (f32: two, of their own classes)
     class_flops = {"gemm_fwd": 2.0 * thv, "gemm_ds": 2.0 * thv, "gemm_dx": 2.0 * thv, "gemm_dw": 2.0 * thv, "gemm_bwd": 4.0 * thv}
     gemms = {k: prof[k] for k in class_flops}
     dom = max(gemms, key=lambda k: gemms[k][0])
@@ -330,9 +331,10 @@ def time_mode(a, b, batch, objective: str, backward: str, steps: int, warmup: in
             gbps = nbytes / (ms * 1e-3) / 1e9
             hbm[k] = {"ms_per_step": ms, "algorithmic_bytes_per_step": nbytes, "gbps": gbps, "frac_of_8TBps": gbps / 8000.0}
     mode_key = "stash" if stash else "recompute"
-    kernel_name = {"gemm_fwd": "gemm_nt_bf16_kernel<EpiFwdStash>" if stash else "gemm_nt_bf16_kernel<EpiFwd>",
-                   "gemm_ds": "gemm_nt_bf16_kernel<EpiDS>", "gemm_dx": "gemm_nt_bf16_kernel<EpiDX>",
-                   "gemm_dw": "gemm_nt_bf16_kernel<EpiDW>", "gemm_bwd": "gemm_nt_bf16_pair_kernel<EpiDX, EpiDW>"}[dom]
+    contraction = "gemm_nt_bf16_kernel" if cfg.dtype == "bf16" else "gemm_nt_kernel"
+    kernel_name = {"gemm_fwd": f"{contraction}<EpiFwdStash>" if stash else f"{contraction}<EpiFwd>", "gemm_ds": f"{contraction}<EpiDS>",
+                   "gemm_dx": f"{contraction}<EpiDX>", "gemm_dw": f"{contraction}<EpiDW>",
+                   "gemm_bwd": "gemm_nt_bf16_pair_kernel<EpiDX, EpiDW>"}[dom]
     out = {
         "objective": objective, "backward": backward, "backward_resolved": "single-pass" if stash else "recompute",
         "steps": steps, "warmup": warmup, "T": T, "chunk_rows": tc,

@@ -21,7 +21,7 @@
 //    sched_barrier, so the interleaving in the source is the interleaving issued.  A light
 //    software prefetch (one 4-byte load per 128-byte line, two slabs ahead, shared between the
 //    workgroups of an XCD; off for dX) pulls the next panels into that XCD's L2.
-//  * gemm_nt_kernel       - general kernel (f32 inputs, unaligned operands): tile size as
+//  * gemm_nt_kernel       - general kernel (f32 inputs, unaligned operands, logits of small hidden sizes off the grid of 128): tile size as
 //    a parameter, register-staged loads with a K-tail predicate.
 //
 // LDS rows are 128 B = eight 16-byte chunks; chunk c of row r sits at slot c ^ ((r>>1)&7),
@@ -113,7 +113,7 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
 // more outside the loop (it is written and read again in f32), and no more than 2 slots workgroups are made, which bounds
 // the partial buffer.  The number of tokens is only known on the device, so every workgroup works the cut out for itself:
 // lane s of a wavefront prices s + 1 slices.  (747 tokens at the 7B head, H 3584, V 152064: 42 tiles of 2376 slabs; dX + dW in one launch
-// 3.84 ms, cut into three slices 2.24.)
+// 3.84 ms, cut into three slices 2.24, and 1.72 since the tiles leave in 16-byte stores.)
 constexpr int kMaxSplit = 64, kSplitMinSteps = 4;
 struct SplitK { int slices, per; };
 __device__ __host__ inline int64_t split_cost(int tiles, int nk, int want, int slots, int64_t fill, SplitK& k) {
@@ -477,7 +477,8 @@ __device__ __attribute__((always_inline)) inline u32x2_t lds_read_tr16(const uns
 // KT: K need not be a multiple of 128 (only of 8): 16-byte chunks past the end of a row are fetched from a zero block.
 //
 // Both have slabs whose load addresses are not those of the plain loop, at the end of K; the last six slabs run in a copy of the
-// loop body that works them out per lane (TAIL), so that the main loop stays free of vector operations.
+// loop body that works them out per lane (`tail`), so that the plain loop needs no vector operation for its load addresses.  (With BTR
+// it has others: the 16-bit offset of the transposing reads does not reach B's part of the second stage, 32 address adds per two slabs.)
 __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
 template <class Epi, int PFD, int VMG, int VMO, bool ATR = false, int LDA = 6, int LDB = 5, bool BTR = false, bool KT = false>
 __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d,

@@ -218,7 +218,7 @@ static inline LogzPlan logz_plan(int P, int H, int M) {
   LogzPlan q; size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += (bytes + 255) & ~(size_t)255; return at; };
   q.off_pooled = take(4 * (size_t)P * H); q.off_a = take(4 * (size_t)P * M); q.off_g = take(4 * (size_t)P * M);
-  take(4 * (size_t)P * M);        // (not used; the workspace keeps the size callers know)
+  take(4 * (size_t)P * M);        // room that no kernel uses: the size is part of the interface, and what was too small a workspace stays so
   q.total = o;
   return q;
 }

@@ -35,7 +35,7 @@ constexpr int kDefaultChunkRows = 32768;        // recompute mode: 128 x 14 dX t
 constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step time is flat (+-0.7 %) from 24576 to 65536 rows
 constexpr int kBM = 256, kBN = 256;
 // General kernel in f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU), or 256 x 16 where the large
-// ones would leave CUs without work.  MFMA-bound: 110 TFLOP/s, pipes 0.78 full at 2.2 GHz, the rest mostly the issue of loads and
+// ones would leave CUs without work (the forward of large batches also 256 x 256: launch_gemm).  MFMA-bound: 102-109 TFLOP/s, pipes 0.78 full at 2.2 GHz, the rest mostly the issue of loads and
 // addresses.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K: 6.25 ms; with 256 x 256 tiles 17.9 (27 dX
 // tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 73 us against 557 (with 32-wide narrow tiles it took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
