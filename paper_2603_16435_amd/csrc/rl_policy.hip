@@ -531,12 +531,13 @@ struct LossOpts {
   int w_mean;               // FLOW: weight from the mean instead of the sum of the token log-ratios
 };
 
-// One workgroup per sequence over its compact rows [cstart[i], cstart[i+1]).
+// One workgroup per sequence over its compact rows [cstart[i], cstart[i+1]).  The caller's advantages and lengths leave here, when the
+// rewards and the offsets have been read everywhere: an output may take the place of an input.
 __global__ void seq_loss_kernel(int objective, const float* logp_c, const float* old_lp, const float* ref_lp,
                                 const int32_t* row_map, const int32_t* cstart, const float* adv,
                                 const int32_t* group_idx, const float* log_z, int B, LossOpts o, const Ctrl* ctrl,
                                 float* seq_loss, float* gterm, float* c_c, float* coeff_out, rl_stats* stats,
-                                const ChunkDesc* desc) {
+                                const ChunkDesc* desc, float* adv_out, int32_t* seq_len_out) {
   __shared__ double sh[16];
   __shared__ int sh_hi, sh_lo;
   int i = blockIdx.x;
@@ -545,12 +546,16 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
     if (i >= desc->seq_end) return;
   }
   const int a = cstart[i], b = cstart[i + 1], n = b - a;
-  if (threadIdx.x == 0) { sh_hi = 0; sh_lo = 0; }
+  const float A = adv[i];
+  if (threadIdx.x == 0) {
+    sh_hi = 0; sh_lo = 0;
+    if (adv_out) adv_out[i] = A;
+    if (seq_len_out) seq_len_out[i] = n;
+  }
   if (n <= 0) {
     if (threadIdx.x == 0) { seq_loss[i] = 0.f; gterm[i] = 0.f; }
     return;
   }
-  const float A = adv[i];
   const double Ad = (double)A;
   const double inv_bn = 1.0 / ((double)B * (double)n);
   const double lo_c = 1.0 - (double)o.clip_lo, hi_c = 1.0 + (double)o.clip_hi;
@@ -640,20 +645,15 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
   }
 }
 
-// loss = (1/B) sum_i seq_loss_i ;  d_logZ_p = sum over members of gterm  (single workgroup).  The caller's per-sequence arrays are
-// written here, when the rewards and the offsets have been read everywhere (rewards may turn into advantages in place).
+// loss = (1/B) sum_i seq_loss_i ;  d_logZ_p = sum over members of gterm  (single workgroup)
 __global__ void finalize_kernel(const float* seq_loss, const float* gterm, const int32_t* group_idx,
-                                const int32_t* seq_len, const float* adv, int B, int P, int objective, const Ctrl* ctrl,
-                                float* loss, float* d_log_z, float* seq_loss_out, float* adv_out, int32_t* seq_len_out) {
+                                const int32_t* seq_len, int B, int P, int objective, const Ctrl* ctrl,
+                                float* loss, float* d_log_z, float* seq_loss_out) {
   __shared__ double sh[16];
   double acc = 0.0;
   for (int i = threadIdx.x; i < B; i += blockDim.x) {
-    const float l = seq_loss[i], A = adv[i];
-    const int n = seq_len[i];
-    acc += (double)l;
-    if (seq_loss_out) seq_loss_out[i] = l;
-    if (adv_out) adv_out[i] = A;
-    if (seq_len_out) seq_len_out[i] = n;
+    acc += (double)seq_loss[i];
+    if (seq_loss_out) seq_loss_out[i] = seq_loss[i];
   }
   const double tot = block_sum(acc, sh);
   // a sequence longer than the caller promised: the single-pass backward dropped rows, say so loudly
@@ -1222,7 +1222,7 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
       ProfScope ps(RL_PROF_LOSS, s);
       seq_loss_kernel<<<p.B, 256, 0, s>>>(objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv,
                                          b->group_idx, b->log_z, p.B, loss_opts(prm), q.ctrl,
-                                         q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, dk);
+                                         q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, dk, out->advantages, out->seq_len);
       stash_patch_kernel<T><<<(p.Tc + 255) / 256, 256, 0, s>>>(dk, q.ids_c, q.zy, q.ref, q.zsum, q.c_c, p.inv_tau, q.scale, E, p.Vp);
     }
     {  // X^T chunk scaled by -c/Z, zero beyond the valid rows
@@ -1244,8 +1244,8 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     }
   }
   ProfScope ps(RL_PROF_LOSS, s);
-  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, q.adv, p.B, p.P, objective, q.ctrl,
-                                    out->loss, out->d_log_z, out->seq_loss, out->advantages, out->seq_len);
+  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, p.B, p.P, objective, q.ctrl,
+                                    out->loss, out->d_log_z, out->seq_loss);
 }
 
 static rl_status check_ws(void* ws, size_t bytes, const Plan& p) {
@@ -1427,9 +1427,9 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   ProfScope ps(RL_PROF_LOSS, s);
   seq_loss_kernel<<<p.B, 256, 0, s>>>(objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv,
                                      b->group_idx, b->log_z, p.B, loss_opts(prm), q.ctrl,
-                                     q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, nullptr);
-  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, q.adv, p.B, p.P, objective, q.ctrl,
-                                    out->loss, out->d_log_z, out->seq_loss, out->advantages, out->seq_len);
+                                     q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, nullptr, out->advantages, out->seq_len);
+  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, p.B, p.P, objective, q.ctrl,
+                                    out->loss, out->d_log_z, out->seq_loss);
   }
   if (bwd) {
     if (p.dtype == RL_BF16) run_backward<bf16_t>(b, p, q, out->d_hidden, out->d_weight, s);
