@@ -8,7 +8,7 @@
 // exception: the hot kernel can also take an operand K-major (the stored array is A^T or B^T, rows = k),
 // read through transposing LDS loads; dW uses that to contract dS^T X out of dS itself, dX of smaller batches to read W as it is.
 //
-// Two kernels share tile order, LDS layout and epilogues:
+// Two kernels (and that of gemm_f32.h) share tile order, LDS layout and epilogues:
 //  * gemm_nt_bf16_kernel  - the hot one (bf16, 16-byte aligned rows).  256x256 tile, four wavefronts of
 //    128x128 each (256 accumulator registers per lane live in AGPRs, one wavefront per SIMD),
 //    K walked in slabs of 64, MFMA shape 16x16x32 (measured on this part: at the power limit it
@@ -21,7 +21,7 @@
 //    sched_barrier, so the interleaving in the source is the interleaving issued.  A light
 //    software prefetch (one 4-byte load per 128-byte line, two slabs ahead, shared between the
 //    workgroups of an XCD; off for dX) pulls the next panels into that XCD's L2.
-//  * gemm_nt_kernel       - general kernel (f32 inputs, unaligned operands, logits of small hidden sizes off the grid of 128): tile size as
+//  * gemm_nt_kernel       - general kernel (narrow f32 tiles, unaligned operands, logits of small hidden sizes off the grid of 128): tile size as
 //    a parameter, register-staged loads with a K-tail predicate.
 //
 // LDS rows are 128 B = eight 16-byte chunks; chunk c of row r sits at slot c ^ ((r>>1)&7),
@@ -248,6 +248,31 @@ __device__ inline float acc_read(const V& v, int i) {
   }
 }
 
+// Tile, and slice of K, of a workgroup of the general and the f32 kernel.
+struct GeneralTile { bool any; int M, N, K, nk, tm, tn, k_begin, slice, slices; };       // nk slabs of BK from slab k_begin on
+template <int BM, int BN, int BK>
+__device__ inline GeneralTile general_tile(GemmDims& d, int pid) {
+  GeneralTile t{};
+  if (!resolve_dims(d, t.M, t.N, t.K)) return t;
+  t.nk = (t.K + BK - 1) / BK; t.slices = 1;
+  // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
+  const bool by_share = d.dyn == 1;
+  const int tiles_m = ((by_share ? t.M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
+  if (d.split_slots > 0) {
+    const SplitK sk = split_k(tiles_m * tiles_n, t.nk, d.split_slots, 0);
+    t.slices = sk.slices;
+    int q;
+    if (!run_of_block(pid, tiles_m * tiles_n * t.slices, q)) return t;      // slice after slice, M fastest inside one
+    t.slice = q / (tiles_m * tiles_n);
+    q -= t.slice * (tiles_m * tiles_n);
+    t.tn = q / tiles_m; t.tm = q - t.tn * tiles_m;
+    t.k_begin = t.slice * sk.per;
+    t.nk = t.nk - t.k_begin < sk.per ? t.nk - t.k_begin : sk.per;
+  } else if (!tile_of_block(pid, tiles_m, tiles_n, d.group_m, by_share, t.tm, t.tn)) return t;
+  t.any = t.tm * BM < t.M && t.tn * BN < t.N;
+  return t;
+}
+
 // General kernel: BM x BN tile, WAVES_M x WAVES_N wavefronts.  A slab is 128 bytes of K, staged global -> registers ->
 // LDS (any alignment, K tail zeroed) into two LDS stages; one barrier per slab.
 // Blocks of 32x32 (f32: v_mfma_f32_32x32x2), or of 16x16 where the tile is narrower than 32 (f32 only, 16x16x4).  Both add the k of an
@@ -272,24 +297,9 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
 
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * (A_BYTES + B_BYTES)];
 
-  int M, N, K;
-  if (!resolve_dims(d, M, N, K)) return;
-  int nk = (K + BK - 1) / BK, tm, tn, k_begin = 0, slice = 0, slices = 1;
-  // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
-  const bool by_share = d.dyn == 1;
-  const int tiles_m = ((by_share ? M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
-  if (d.split_slots > 0) {
-    const SplitK sk = split_k(tiles_m * tiles_n, nk, d.split_slots, 0);
-    slices = sk.slices;
-    int t;
-    if (!run_of_block(blockIdx.x, tiles_m * tiles_n * slices, t)) return;      // slice after slice, M fastest inside one
-    slice = t / (tiles_m * tiles_n);
-    t -= slice * (tiles_m * tiles_n);
-    tn = t / tiles_m; tm = t - tn * tiles_m;
-    k_begin = slice * sk.per;
-    nk = nk - k_begin < sk.per ? nk - k_begin : sk.per;
-  } else if (!tile_of_block(blockIdx.x, tiles_m, tiles_n, d.group_m, by_share, tm, tn)) return;
-  if (tm * BM >= M || tn * BN >= N) return;
+  const GeneralTile t = general_tile<BM, BN, BK>(d, blockIdx.x);
+  if (!t.any) return;
+  const int M = t.M, N = t.N, K = t.K, nk = t.nk, tm = t.tm, tn = t.tn, k_begin = t.k_begin;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -388,7 +398,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   TileCtx c;
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
-  c.slice = slice; c.slices = slices;
+  c.slice = t.slice; c.slices = t.slices;
   const typename Epi::Pre pre = epi.template preload<L>(c, d);
   epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
 }

@@ -28,15 +28,17 @@
 #include "rvq_encode.h"
 #include "rvq_few.h"
 #include "gemm_nt.h"
+#include "gemm_f32.h"
 
 namespace rlk {
 
 constexpr int kDefaultChunkRows = 32768;        // recompute mode: 128 x 14 dX tiles = 7 full rounds of 256 CUs on the 7B shape
 constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step time is flat (+-0.7 %) from 24576 to 65536 rows
 constexpr int kBM = 256, kBN = 256;
-// General kernel in f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU), or 256 x 16 where the large
-// ones would leave CUs without work (the forward of large batches also 256 x 256: launch_gemm).  MFMA-bound: 102-109 TFLOP/s, pipes 0.78 full at 2.2 GHz, the rest mostly the issue of loads and
-// addresses.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K: 6.25 ms; with 256 x 256 tiles 17.9 (27 dX
+// f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU; gemm_f32.h, operands that are not 16-byte aligned the general
+// kernel), or 256 x 16 where the large ones would leave CUs without work.  MFMA-bound: 128-141 TFLOP/s, 102-109 in the general kernel, whose
+// loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K: 5.25 ms, 6.2 in
+// the general kernel; with its 256 x 256 tiles 17.9 (27 dX
 // tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 73 us against 557 (with 32-wide narrow tiles it took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
@@ -975,6 +977,8 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
   const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);
   const int tm = (d.M + kBM - 1) / kBM, tn = (d.N + bn - 1) / bn;
   const int tiles = d.split_slots > 0 ? split_launch(tm, tn, d.split_slots) : launch_tiles(tm, tn);
+  const bool fast = (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0 && d.lda % 4 == 0 && d.ldb % 4 == 0 && d.K % 4 == 0 && d.lda < (1 << 22) && d.ldb < (1 << 22) &&
+                    !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB;                  // (how the kernel of gemm_f32.h addresses its operands)
   if constexpr (std::is_same_v<Epi, EpiDW>) {
     // dW has no per-tile partials and no padding to write, which ask for 256 rows: 64 x 16 tiles where the others would leave most CUs idle
     // (356 tokens, H 128, V 1024: 128 workgroups instead of 32, 21.7 -> 11.2 us)
@@ -984,18 +988,22 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
     }
   }
   if constexpr (std::is_same_v<Epi, EpiFwd<float>>) {
-    // The logits of the forward in 256 x 256 tiles (eight wavefronts) where these come in ten rounds of the chip or more and fill them as
-    // well: each reads its operands fewer times over (8 k tokens: H 768, V 50257 5251 -> 5056 us, H 1536, V 30000 6176 -> 5909), but with
+    // The logits of unaligned operands in 256 x 256 tiles (eight wavefronts) where these come in ten rounds of the chip or more and fill them as
+    // well (aligned ones: 256 x 64 tiles of the other kernel are the faster ones there too, 8 k tokens, H 768, V 50257 5041 -> 4497 us): each reads its operands fewer times over (8 k tokens: H 768, V 50257 5251 -> 5056 us, H 1536, V 30000 6176 -> 5909), but with
     // few rounds the last one, of a batch with fewer tokens than rows, costs more than that (1040 tokens, V 50257: 784 -> 843).  Same
     // bits (EpiFwd).
     const int64_t square = (int64_t)tm * ((d.N + 255) / 256), rounds = (square + kHotSlots - 1) / kHotSlots;
     const int64_t halves = ((int64_t)tm * tn + kF32Slots - 1) / kF32Slots;          // rounds of 256 x 64 tiles, half as long
-    if (bn == kF32BN && rounds >= 10 && 100 * rounds <= 51 * halves) {
+    if (!fast && bn == kF32BN && rounds >= 10 && 100 * rounds <= 51 * halves) {
       gemm_nt_kernel<float, Epi, kBM, 256, 2, 4><<<launch_tiles(tm, (d.N + 255) / 256), 512, 0, s>>>(A, B, d, epi);
       return;
     }
   }
-  if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 2, 2><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  if (bn == kF32BN && fast) {
+    // (a dynamic K is a multiple of 16 only)
+    if (std::is_same_v<Epi, EpiDW> || d.K % 32) gemm_nt_f32_kernel<Epi, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+    else if constexpr (!std::is_same_v<Epi, EpiDW>) gemm_nt_f32_kernel<Epi, false><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  } else if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 2, 2><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
