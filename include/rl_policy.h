@@ -65,7 +65,7 @@ typedef enum rl_dtype { RL_F32 = 0, RL_BF16 = 1 } rl_dtype;
 
 /* How the backward pass gets the probabilities of a chunk of rows.
  *  RL_BWD_RECOMPUTE  recompute the logits tile by tile from X and W (four contractions per chunk:
- *                    forward, recompute + dS, dX, dW).  Always available.
+ *                    forward, recompute + dS, dX, dW).  Always available.  (f32 batches of one chunk keep their logits instead.)
  *  RL_BWD_STASH      single pass: chunks are made of whole sequences, the forward contraction also
  *                    stores the chunk's unnormalised probabilities exp(z - ref_t) in the input
  *                    precision (ref_t = target logit - old log-prob, i.e. the row's logsumexp up to
@@ -78,7 +78,9 @@ typedef enum rl_dtype { RL_F32 = 0, RL_BF16 = 1 } rl_dtype;
  *                    -100 nats.  A row beyond that is counted in rl_stats.n_overflow_rows and the loss of the
  *                    call comes back NaN (its gradient rows are not numbers): the caller re-runs the batch with
  *                    RL_BWD_RECOMPUTE, which has no such limit.
- *  RL_BWD_AUTO       RL_BWD_STASH when its conditions hold, else RL_BWD_RECOMPUTE.
+ *  RL_BWD_AUTO       RL_BWD_STASH when its conditions hold, else RL_BWD_RECOMPUTE, where a bf16 batch of one chunk of at most
+ *                    16384 rows with H >= 456 keeps its logits, in f32, between forward and backward (same results; the workspace
+ *                    holds 4 bytes more per row and vocabulary entry).
  * Either way at most chunk_rows x V values are held at a time, never T x V. */
 typedef enum rl_aggregation { RL_AGG_SEQUENCE = 0, RL_AGG_TOKEN = 1 } rl_aggregation;
 typedef enum rl_ratio_level { RL_RATIO_TOKEN = 0, RL_RATIO_SEQUENCE = 1 } rl_ratio_level;

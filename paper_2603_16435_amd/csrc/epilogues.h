@@ -42,7 +42,12 @@ __device__ __attribute__((always_inline)) inline void lane_pair(float v, float& 
 //      range + target gather; z_t[y_t] is written by the single lane that holds vocab row y_t of token t.
 //      u feeds the entropy H_t = lse_t - u/s of the full distribution at no extra pass.
 //      z is the tempered logit zs * (W x_t), zs = 1 / temperature; everything written is in tempered units.
-template <class T>
+//      KEEP: the raw logits W x_t leave as well, in f32, for a backward that forms dS from them (kept_ds_kernel); in the hot kernel in the
+//      order of the accumulators (kept_index: 1 KiB per store), else vocabulary-major like dS^T.
+__device__ inline int64_t kept_index(int tile_m, int tile_n, int tiles_n, int wave, int bi, int bj, int lane) {    // of a lane's floatx4
+  return (((int64_t)(tile_m * tiles_n + tile_n) * 4 + wave) * 64 + bj * 8 + bi) * 64 + lane;
+}
+template <class T, bool KEEP = false>
 struct EpiFwd {
   // sampled tokens of the lane's columns, fetched ahead of the main loop (one after the other in the epilogue they cost a memory
   // latency per column block: 7 us of a tile)
@@ -68,15 +73,18 @@ struct EpiFwd {
   int V;
   float zs;             // inverse temperature
   int* ycol_c;          // [compact row] vocabulary row the target logit was taken from (the position of the accumulator read)
+  float* kept;          // KEEP: logits of the chunk
+  static constexpr bool kForward = true;
 
   // one token column of one lane: the MB * kRegs logits it holds.  PAD: some of the sub-tile's rows are
   // vocabulary padding (only in the last tile row) and must not enter the sums.
   template <class L, int MB, int NB, bool AGPR, bool PAD>
-  __device__ __attribute__((always_inline)) void column(typename L::acc_t (&acc)[MB][NB], int bj, int lane, int vleft,
+  __device__ __attribute__((always_inline)) void column(typename L::acc_t (&acc)[MB][NB], int bj, int lane, int vleft, const TileCtx& c,
                                                         float& mx, float& sm, float& su) const {
     const float NEG = -__builtin_inff();
     float z[MB * L::kRegs];
     mx = NEG;
+    if constexpr (KEEP && !AGPR) keep_column<L, MB, NB>(acc, bj, c);
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
@@ -85,6 +93,13 @@ struct EpiFwd {
         z[bi * L::kRegs + i] = v;
         mx = fmaxf(mx, (!PAD || L::row(bi, i, lane) < vleft) ? v : NEG);
       }
+    if constexpr (KEEP && AGPR) {
+#pragma unroll
+      for (int bi = 0; bi < MB; ++bi) {
+        floatx4 q; q[0] = z[bi * 4]; q[1] = z[bi * 4 + 1]; q[2] = z[bi * 4 + 2]; q[3] = z[bi * 4 + 3];
+        __builtin_nontemporal_store(q, reinterpret_cast<floatx4*>(kept) + kept_index(c.tile_m, c.tile_n, ldp / 256, c.wm * 2 + c.wn, bi, bj, lane));
+      }
+    }
     const float ms = (mx == NEG) ? 0.f : mx * zs;             // zs > 0: the largest raw logit is the largest tempered one
     const float ms_l2e = ms * kLog2e, zs_l2e = zs * kLog2e;
     sm = 0.f; su = 0.f;
@@ -99,6 +114,16 @@ struct EpiFwd {
         su = __builtin_fmaf(e, v, su);
       }
     mx *= zs; su *= zs;
+  }
+
+  // vocabulary-major (the rows and columns of a tile that do not exist have room: both extents are padded to 256)
+  template <class L, int MB, int NB>
+  __device__ __attribute__((always_inline)) void keep_column(typename L::acc_t (&acc)[MB][NB], int bj, const TileCtx& c) const {
+    float* p = kept + c.n0 + L::col(bj, c.lane);
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int i = 0; i < L::kRegs; ++i) p[(int64_t)(c.m0 + L::row(bi, i, c.lane)) * ldp] = acc[bi][bj][i];
   }
 
   template <int OFF, int NB>
@@ -193,9 +218,9 @@ struct EpiFwd {
         zy_c[d.chunk_start + n] = zy * zs;
         ycol_c[d.chunk_start + n] = got;
       }
-      if constexpr (kNarrow) continue;
-      else if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
-      else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, mx[bj], sm[bj], su[bj]);
+      if constexpr (kNarrow) { if constexpr (KEEP) keep_column<L, MB, NB>(acc, bj, c); continue; }
+      else if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
+      else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
     }
     if constexpr (kNarrow) {
       static_assert(WAVES_M == 4 && WAVES_N == 1, "the wavefronts of a column are stacked along the vocabulary");
@@ -479,6 +504,88 @@ struct EpiDS {
     }
   }
 };
+
+// ---- backward, stage 1, of a batch that is one chunk: dS from the logits the forward kept (EpiFwd<T, true>), in the arithmetic of EpiDS.
+//      A contraction of 2 T V H operations becomes a pass over memory: 4 bytes in and 2 out per logit in bf16; f32 reads dS^T's place, where
+//      the logits are, writes dS^T over them and dS besides.
+struct KeptJob {
+  const int* ids_c; const float* lse_c; const float* c_c; const int* n_real;
+  int V; float zs;
+};
+
+// bf16: a wavefront takes 16 tokens x 128 vocabulary entries of a tile; grid (4 x tiles of 256 x 256, 2).  Lane (g, cc) = (l / 16, l % 16)
+// holds entries 16 bi + 4 g .. + 3 of token cc; a row swap makes that eight consecutive entries, and lane pairs swap halves, so that
+// a store writes whole 128-byte lines (as in EpiDS).
+__global__ __launch_bounds__(256) void kept_ds_kernel(const float* kept, KeptJob j, int tiles_n, bf16_t* dS, int64_t ld_ds) {
+  const int sub = blockIdx.x & 3, tile = blockIdx.x >> 2, tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
+  const int n_real = *j.n_real;
+  if (tile_n * 256 >= n_real) return;
+  const int lane = threadIdx.x & 63, bj = blockIdx.y * 4 + (threadIdx.x >> 6), g = lane >> 4, cc = lane & 15, p = cc & 1;
+  floatx4 z[8];
+#pragma unroll
+  for (int bi = 0; bi < 8; ++bi) z[bi] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(kept) + kept_index(tile_m, tile_n, tiles_n, sub, bi, bj, lane));
+  const int n = tile_n * 256 + (sub & 1) * 128 + bj * 16 + cc, m0 = tile_m * 256 + (sub >> 1) * 128;
+  const bool valid = n < n_real;
+  const int y = valid ? j.ids_c[n] - m0 : -1;
+  const float lse = valid ? j.lse_c[n] : 3.0e38f, ct = valid ? j.c_c[n] * j.zs : 0.f;       // no token: every entry becomes 0
+  const float lse_l2e = lse * kLog2e, zs_l2e = j.zs * kLog2e;
+  u32x2_t o[8];
+#pragma unroll
+  for (int bi = 0; bi < 8; ++bi) {
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = bi * 16 + g * 4 + e;
+      const float pr = exp_shifted<bf16_t>(z[bi][e], lse, lse_l2e, j.zs, zs_l2e);
+      v[e] = (bf16_t)(m < j.V - m0 ? ct * ((m == y ? 1.f : 0.f) - pr) : 0.f);
+    }
+    o[bi] = __builtin_bit_cast(u32x2_t, v);
+  }
+  // after the swap of rows of blocks 2 k and 2 k + 1: lane group 0 / 2 has entries 0..7 / 8..15 of block 2 k, group 1 / 3 those of block 2 k + 1
+  u32x4_t h[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const auto r = __builtin_amdgcn_permlane16_swap(o[2 * k][w], o[2 * k + 1][w], false, false);
+      h[k][w] = r[0]; h[k][2 + w] = r[1];
+    }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {                                  // 64 entries: one line of a token's row
+    u32x4_t recv;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) recv[q] = (unsigned)__builtin_amdgcn_mov_dpp((int)(p ? h[2 * k][q] : h[2 * k + 1][q]), 0xB1, 0xF, 0xF, true);
+    const u32x4_t d_even = p ? recv : h[2 * k], d_odd = p ? h[2 * k + 1] : recv;
+    const int v0 = m0 + k * 64 + p * 32 + (g & 1) * 16 + (g >> 1) * 8;
+    store_stream(dS + tiled_index(n & ~1, v0, ld_ds), __builtin_bit_cast(bf16x8, d_even));
+    store_stream(dS + tiled_index(n | 1, v0, ld_ds), __builtin_bit_cast(bf16x8, d_odd));
+  }
+}
+
+// f32: 64 tokens x 64 vocabulary entries per workgroup (vocabulary fastest); dST holds the logits on entry.  Token columns up to the next multiple of 64 become 0.
+__global__ __launch_bounds__(256) void kept_ds_f32_kernel(KeptJob j, float* dST, int64_t ld_dst, float* dS, int64_t ld_ds) {
+  __shared__ float tile[64][65];
+  const int vb = (int)(ld_ds / 64), n0 = (int)(blockIdx.x / vb) * 64, m0 = (int)(blockIdx.x % vb) * 64, n_real = *j.n_real;
+  if (n0 >= n_real) return;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, n = n0 + tx;
+  const bool valid = n < n_real;
+  const int y = valid ? j.ids_c[n] : -1;
+  const float lse = valid ? j.lse_c[n] : 0.f, ct = valid ? j.c_c[n] * j.zs : 0.f;
+  float z[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) z[k] = dST[(int64_t)(m0 + ty + 4 * k) * ld_dst + n];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int m = m0 + ty + 4 * k;
+    const float ds = ct * ((m == y ? 1.f : 0.f) - fast_exp<float>(z[k] * j.zs - lse));
+    const float o = valid && m < j.V ? ds : 0.f;
+    dST[(int64_t)m * ld_dst + n] = o;
+    tile[ty + 4 * k][tx] = o;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) dS[(int64_t)(n0 + ty + 4 * k) * ld_ds + m0 + tx] = tile[tx][ty + 4 * k];
+}
 
 // ---- backward, stage 2: dX tile -> rows scattered back to their original positions
 template <class T>

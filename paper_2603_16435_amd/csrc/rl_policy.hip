@@ -6,8 +6,8 @@
 //   forward   : per chunk of compacted rows: logits tiles (MFMA) -> partial (max,sumexp) per
 //               vocab tile + target logit -> combine -> lse_t, logp_t
 //   loss      : one workgroup per sequence: length-normalised sums, loss_i, c_t; final reduce
-//   backward  : masked rows of dX zeroed, W^T once (f32, and bf16 beyond 32768 rows); per chunk: X^T, recomputed logits -> dS (input
-//               precision; f32 inputs also dS^T), dX = dS W (scattered to original rows; cut along K when its tiles are few),
+//   backward  : masked rows of dX zeroed, W^T once (f32, and bf16 beyond 32768 rows); per chunk: X^T, recomputed logits, or those that the
+//               forward of a batch of one chunk kept -> dS (input precision; f32 inputs also dS^T), dX = dS W (scattered to original rows; cut along K when its tiles are few),
 //               dW (+)= dS^T X (bf16: dS read as a K-major operand, same launch as dX)
 // The number of real rows is only known on the device, so grids are sized for the upper
 // bound R and every kernel trims itself against the device-side count.
@@ -37,8 +37,8 @@ constexpr int kDefaultChunkRowsStash = 40960;   // single-pass mode: the step ti
 constexpr int kBM = 256, kBN = 256;
 // f32: tiles of 256 x 64 (four wavefronts of 128 x 32, two workgroups per CU; gemm_f32.h, operands that are not 16-byte aligned the general
 // kernel), or 256 x 16 where the large ones would leave CUs without work.  MFMA-bound: 128-141 TFLOP/s, 102-109 in the general kernel, whose
-// loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K: 5.25 ms, 6.2 in
-// the general kernel; with its 256 x 256 tiles 17.9 (27 dX
+// loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K and the logits
+// recomputed: 5.25 ms, 6.2 in the general kernel; with its 256 x 256 tiles 17.9 (27 dX
 // tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 73 us against 557 (with 32-wide narrow tiles it took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
@@ -47,6 +47,15 @@ constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 // contractions.  747 tokens at the 7B head: 3274 us with the copy, 2860 without; 11.5 k tokens (16 k rows): 38.65 / 38.37 ms; 67 k tokens
 // (131 k rows): 163.5 / 163.4; 36 k tokens at H 2048, V 32000 (65 k rows): 11.39 / 11.47.
 constexpr int64_t kKMajorRows = 32768;
+
+// Keeping the logits between forward and backward (recompute mode, batch of one chunk) turns the dS contraction into a pass over memory, for
+// 4 bytes more per logit in the forward.  f32 always does (the logits wait in dS^T's place): 2175 tokens, H 768, V 50257 1323 -> 239 us, forward
+// 1230 -> 1274.  bf16 in the default mode, with room of its own: batches of up to kKeepRows rows, whose logits take no more of it than the dS of
+// the largest chunk (10 GB at the 7B head), and hidden sizes from kKeepH on, which the hot kernel serves.  dS + forward in us, recomputed and kept: 11.5 k tokens at
+// the 7B head 10019 + 9589, 1942 + 10277; 4741 tokens, H 1160, V 50257 663 + 609, 266 + 664; the whole call at H 456: 1310 tokens, V 50257
+// 458 -> 439, 4605 tokens, V 152064 3212 -> 3124; H 512 403 -> 396, 3276 -> 3190.
+constexpr int64_t kKeepRows = 16384;
+constexpr int kKeepH = 456;
 
 constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup per CU, a step of a K cut is two slabs
 // Per-contraction tuning of the hot kernel, from sweeps on the 7B-shaped workload:
@@ -833,10 +842,11 @@ struct Plan {
   bool tiled;            // bf16: the work buffers dS/E, W^T, X^T are slab-tiled (hot kernel operands)
   bool k_major_w;        // dX reads W as it is stored: no W^T is made
   bool stash;            // single-pass backward (forward keeps each chunk's unnormalised probabilities)
+  bool keep;             // recompute mode, one chunk: the forward keeps the logits, dS is formed from them
   int n_desc, max_len;   // stash: number of chunk records, promised bound on rows per sequence
   float inv_tau;         // 1 / temperature
   size_t off_ctrl, off_seq_len, off_cstart, off_row_map, off_ids_c, off_cpos, off_zy, off_lse_c, off_logp_c,
-      off_c_c, off_adv, off_seq_loss, off_gterm, off_part, off_wt, off_xt, off_ds, off_dst, off_split,
+      off_c_c, off_adv, off_seq_loss, off_gterm, off_part, off_wt, off_xt, off_ds, off_dst, off_split, off_kept,
       off_desc, off_ref, off_zsum, off_scale, off_ycol, total;
 };
 
@@ -883,8 +893,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   auto chunk_rows = [&](int dflt) { int t = (prm && prm->chunk_rows > 0) ? prm->chunk_rows : dflt; t = (t + 255) & ~255; return t > rp ? (int)rp : t; };
   const bool stash_kernels = b->dtype == RL_BF16 && (b->H % 128 == 0) &&
                              ((reinterpret_cast<uintptr_t>(b->hidden) | reinterpret_cast<uintptr_t>(b->weight)) % 16 == 0);
-  const bool stash_shape = bwd && stash_kernels && prm && prm->max_seq_len > 0 && mode != RL_BWD_RECOMPUTE;
-  const bool can_stash = stash_shape && prm->max_seq_len <= chunk_rows(kDefaultChunkRowsStash);
+  const bool stash_asked = bwd && prm && prm->max_seq_len > 0 && mode != RL_BWD_RECOMPUTE && prm->max_seq_len <= chunk_rows(kDefaultChunkRowsStash);
+  const bool can_stash = stash_asked && stash_kernels;
   if (mode == RL_BWD_STASH && !stash_kernels) return RL_ERR_UNIMPLEMENTED;
   if (mode == RL_BWD_STASH && !can_stash) return RL_ERR_RANGE;
   const int tc = chunk_rows(can_stash ? kDefaultChunkRowsStash : kDefaultChunkRows);
@@ -904,6 +914,10 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
     const int64_t alt = (b->R + (tc - p.max_len)) / (tc - p.max_len + 1) + 1;
     if (alt < p.n_desc) p.n_desc = (int)alt;
   }
+  // (room is set aside by shape, not alignment: a workspace serves a weight of any alignment)
+  const bool keep_room = bwd && p.n_chunks == 1 && (b->dtype == RL_F32 || (mode == RL_BWD_AUTO && b->R <= kKeepRows && b->H >= kKeepH &&
+                                                                           !(stash_asked && b->H % 128 == 0)));
+  p.keep = keep_room && (b->dtype == RL_F32 || (reinterpret_cast<uintptr_t>(b->hidden) | reinterpret_cast<uintptr_t>(b->weight)) % 16 == 0);
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
   const size_t Rp = (size_t)rp + 256;
@@ -915,7 +929,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.off_ycol = take(4 * Rp);
   p.off_adv = take(4 * (size_t)b->B); p.off_seq_loss = take(4 * (size_t)b->B); p.off_gterm = take(4 * (size_t)b->B);
   p.off_part = take(sizeof(float4) * (size_t)p.tiles_v * (size_t)tc);
-  p.off_wt = p.off_xt = p.off_ds = p.off_dst = p.off_split = 0;
+  p.off_wt = p.off_xt = p.off_ds = p.off_dst = p.off_split = p.off_kept = 0;
   if (bwd) {
     const size_t Hp = ((size_t)b->H + 255) & ~(size_t)255;   // tiled layouts come in blocks of 256 rows
     p.off_wt = take(p.esz * Hp * (size_t)p.Vp);            // (also where an aligned W is read as it is: the size holds for a W of any alignment)
@@ -926,6 +940,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
       p.off_split = take(split_bytes(tc, b->H, p.Vp, f32_tile_n(tc, b->H, p.Vp, true), 32, kF32Slots));
     } else {
       p.off_split = take(split_bytes(tc, b->H, p.Vp, kBN, kHotStep, kHotSlots));
+      if (keep_room) p.off_kept = take(4 * (size_t)tc * (size_t)p.Vp);      // f32 keeps them in dS^T's place
     }
   }
   p.off_desc = p.off_ref = p.off_zsum = p.off_scale = 0;
@@ -967,11 +982,14 @@ static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, con
                     ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0) &&
                     !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB &&     // (how the hot kernel addresses its operands)
                     !small_k<Epi>(d.K);
-  if (!fast) launch_generic(A, B, d, epi, tiles, s);
-  else if (d.K % 128) gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  if constexpr (!std::is_same_v<Epi, EpiFwd<bf16_t, true>>)      // (keeps its logits in the hot kernel's order: make_plan sees to it)
+    if (!fast) { launch_generic(A, B, d, epi, tiles, s); return; }
+  if (d.K % 128) gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
+template <class Epi> constexpr bool kIsForward = false;
+template <bool KEEP> constexpr bool kIsForward<EpiFwd<float, KEEP>> = true;
 template <class Tune, class Epi>
 static void launch_gemm(const float* A, const float* B, const GemmDims& d, const Epi& epi, hipStream_t s) {
   const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);
@@ -987,7 +1005,7 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
       return;
     }
   }
-  if constexpr (std::is_same_v<Epi, EpiFwd<float>>) {
+  if constexpr (kIsForward<Epi>) {
     // The logits of unaligned operands in 256 x 256 tiles (eight wavefronts) where these come in ten rounds of the chip or more and fill them as
     // well (aligned ones: 256 x 64 tiles of the other kernel are the faster ones there too, 8 k tokens, H 768, V 50257 5041 -> 4497 us): each reads its operands fewer times over (8 k tokens: H 768, V 50257 5251 -> 5056 us, H 1536, V 30000 6176 -> 5909), but with
     // few rounds the last one, of a batch with fewer tokens than rows, costs more than that (1040 tokens, V 50257: 784 -> 843).  Same
@@ -1028,7 +1046,7 @@ static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, Gem
 struct Ptrs {
   Ctrl* ctrl; int32_t *seq_len, *cstart, *row_map, *ids_c, *cpos;
   float *zy, *lse_c, *logp_c, *c_c, *adv, *seq_loss, *gterm; float4* part;
-  void *wt, *xt, *ds, *dst; float* split;
+  void *wt, *xt, *ds, *dst; float *split, *kept;
   ChunkDesc* desc; float *ref, *zsum, *scale;
   int32_t* ycol;
 };
@@ -1044,6 +1062,7 @@ static Ptrs carve(void* ws, const Plan& p) {
   q.wt = w + p.off_wt; q.xt = w + p.off_xt; q.ds = w + p.off_ds;
   q.dst = p.off_dst ? w + p.off_dst : nullptr;          // f32 inputs only
   q.split = (float*)(w + p.off_split);
+  q.kept = p.dtype == RL_F32 ? (float*)q.dst : (float*)(w + p.off_kept);
   q.desc = (ChunkDesc*)(w + p.off_desc); q.ref = (float*)(w + p.off_ref); q.zsum = (float*)(w + p.off_zsum);
   q.scale = (float*)(w + p.off_scale);
   q.ycol = (int32_t*)(w + p.off_ycol);
@@ -1097,8 +1116,11 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
     GemmDims d{};
     d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
     d.a_rows = nullptr; d.b_rows = q.row_map + c0; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
-    EpiFwd<T> e{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol};
-    { ProfScope ps(RL_PROF_GEMM_FWD, s); launch_gemm<TuneLogits>(W, X, d, e, s); }
+    {
+      ProfScope ps(RL_PROF_GEMM_FWD, s);
+      if (p.keep) launch_gemm<TuneLogits>(W, X, d, EpiFwd<T, true>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, s);
+      else launch_gemm<TuneLogits>(W, X, d, EpiFwd<T>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, s);
+    }
     ProfScope ps(RL_PROF_COMBINE, s);
     lse_combine_kernel<<<(p.Tc + 63) / 64, 256, 0, s>>>(q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc, q.ycol,
                                                         q.lse_c, q.logp_c, lse_out, logp_out, ent_out, zy_out, ycol_out);
@@ -1137,7 +1159,12 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       ProfScope ps(RL_PROF_TRANSPOSE, s);
       launch_transpose<T>(gx, s, X, p.H, p.Tc, p.H, q.row_map, q.ctrl, c0, 1, nullptr, nullptr, XT, p.Tc, p.Tc, p.tiled);
     }
-    {  // recompute logits, form dS (and dS^T for f32 inputs)
+    if (p.keep) {
+      ProfScope ps(RL_PROF_GEMM_DS, s);
+      const KeptJob j{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau};
+      if constexpr (sizeof(T) == 4) kept_ds_f32_kernel<<<(unsigned)((int64_t)(p.Vp / 64) * (p.Tc / 64)), 256, 0, s>>>(j, dST, p.Tc, dS, p.Vp);
+      else kept_ds_kernel<<<dim3((unsigned)(4 * p.tiles_v * (p.Tc / 256)), 2), 256, 0, s>>>(q.kept, j, p.Tc / 256, dS, p.Vp);
+    } else {  // recompute logits, form dS (and dS^T for f32 inputs)
       GemmDims d{};
       d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
       d.b_rows = q.row_map + c0; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
