@@ -703,15 +703,12 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     const int slot = ((fs * 4 + fq) ^ swz) << 4;
 #pragma unroll
     for (int q = 0; q < 32; ++q) {
-      // (the operands' layouts are alike: exchanged, they give the transposed block with the same sums.  The B blocks are then
-      // walked forth and back, so that from MFMA to MFMA only one operand changes: at the power limit that pays.  dX + dW of 67 k
-      // tokens at the 7B head: 108.3 ms before the exchange, 108.4 with it alone (on another box 111.9 and 112.7), 107.2 with the walk.
-      // Holding a B block for all eight A blocks: 108.7 where the walk takes 107.7.)
-      if constexpr (Epi::kSwap) {
-        const int w = (q >> 2) & 1 ? 3 - (q & 3) : q & 3;
-        mfma16(acc[q >> 2][half * 4 + w], fb[bset][w], fa[aset][q >> 2]);
-      }
-      else mfma16(acc[q >> 2][half * 4 + (q & 3)], fa[aset][q >> 2], fb[bset][q & 3]);
+      // The B blocks are walked forth and back, so that from MFMA to MFMA only one operand changes: at the power limit that pays.  dX + dW of
+      // 67 k tokens at the 7B head 108.4 ms without, 107.2 with it (holding a B block for all eight A blocks: 108.7 where the walk takes
+      // 107.7); the forward 56.9 and 56.4.  kSwap: the operands' layouts are alike; exchanged, they give the transposed block with the same sums.
+      const int w = (q >> 2) & 1 ? 3 - (q & 3) : q & 3;
+      if constexpr (Epi::kSwap) mfma16(acc[q >> 2][half * 4 + w], fb[bset][w], fa[aset][q >> 2]);
+      else mfma16(acc[q >> 2][half * 4 + w], fa[aset][q >> 2], fb[bset][w]);
       if (ATR && kind == 12) {                          // sixteen half-reads of A, one per MFMA, then the four of B
         if (q < 16) read_a_tr(fa[aset ^ 1][q >> 1], fstage, q >> 1, fs, q & 1);
         else if (q % DSG == 0 && q < 24) fb[bset ^ 1][(q - 16) / DSG] = *reinterpret_cast<const u32x4_t*>(fstage + brow + ((q - 16) / DSG) * 16 * kSlabBytes + slot);
