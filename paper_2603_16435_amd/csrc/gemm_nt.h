@@ -20,7 +20,7 @@
 //    fragment reads of the next slab.  The MFMAs are inline asm and every one is fenced with
 //    sched_barrier, so the interleaving in the source is the interleaving issued.  A light
 //    software prefetch (one 4-byte load per 128-byte line, two slabs ahead, shared between the
-//    workgroups of an XCD; off for dX) pulls the next panels into that XCD's L2.
+//    workgroups of an XCD) pulls the next panels into that XCD's L2.
 //  * gemm_nt_kernel       - general kernel (narrow f32 tiles, unaligned operands, logits of small hidden sizes off the grid of 128): tile size as
 //    a parameter, register-staged loads with a K-tail predicate.
 //
@@ -503,9 +503,9 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
                 "the slab loads of the fullest phase must fit into its 32 MFMAs");
   static_assert(STAGE == kHotStageBytes, "stage size");
   static_assert(!ATR || !Epi::kPermute, "the K-major A path loads rows in natural order");
-  static_assert(!BTR || (!ATR && !KT && !Epi::kGatherB && PFD == 0), "K-major B: dX");
+  static_assert(!BTR || (!ATR && !KT && !Epi::kGatherB), "K-major B: dX");
   static_assert(!KT || !ATR, "K tail: row-wise operands");
-  static_assert(!Epi::kSplit || (!ATR && PFD == 0 && !Epi::kGatherB), "a slice starts at a slab offset of both row-wise operands");
+  static_assert(!Epi::kSplit || (!ATR && !Epi::kGatherB), "a slice starts at a slab offset of both row-wise operands");
 
   int M, N, K;
   if (!resolve_dims(d, M, N, K)) return;
@@ -529,7 +529,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   }
   if (slices == 1 && !tile_of_block(pid, tiles_m, tiles_n, d.group_m, by_share, tm, tn)) return;
   if constexpr (Epi::kSplit) {                                    // (all uniform; said so, because the slab loads want scalar addresses)
-    nk = __builtin_amdgcn_readfirstlane(nk); tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
+    nk = __builtin_amdgcn_readfirstlane(nk); k_first = __builtin_amdgcn_readfirstlane(k_first); tm = __builtin_amdgcn_readfirstlane(tm); tn = __builtin_amdgcn_readfirstlane(tn);
   }
   if (tm * BM >= M || tn * BN >= N) return;
 
@@ -589,6 +589,8 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     return ATR ? (int64_t)(slab >> 2) * (d.lda * 256) + (slab & 3) * 4096 : (int64_t)slab * a_ks;
   };
   // load j of the 16 per slab (0..7 = A rows, 8..15 = B rows)
+  // (the pointers are uniform, but behind a cut along K and a prefetch the compiler does not see it)
+  auto uni = [&](const bf16_t* p) __attribute__((always_inline)) { if constexpr (Epi::kSplit && PFD > 0) return (const bf16_t*)uniform_ptr(p); else return p; };
   auto issue1 = [&](bool tail, int slab, unsigned char* stage, int j) __attribute__((always_inline)) {
     unsigned char* as = stage + wave * 64 * kSlabBytes;
     unsigned char* dst = j < 8 ? as + j * 8 * kSlabBytes : as + A_BYTES + (j - 8) * 8 * kSlabBytes;
@@ -597,7 +599,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       const bf16_t* g = j < 8 ? ap[j & 7] + a_slab(slab) : bp[j & 7] + (int64_t)slab * b_ks;
       load16_to_lds_lanes(slab * BK + c * 8 < K ? (const void*)g : (const void*)&kZeroChunk, dst);
     } else if (j < 8) {
-      load16_to_lds_uniform(abase + a_slab(slab), aoff[j], dst);      // (the hot kernel is not launched with gathered A rows)
+      load16_to_lds_uniform(uni(abase + a_slab(slab)), aoff[j], dst);      // (the hot kernel is not launched with gathered A rows)
     } else if (BTR && tail) {
       const int last = (d.b_k_rows - 1) >> 6, s_abs = k_first + slab, sc = s_abs < last ? s_abs : last;       // a slab that has rows
       const int row = ((wave * 8 + j - 8) * 64 + lane) >> 5, left = d.b_k_rows - 1 - sc * BK;
@@ -605,7 +607,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     } else if constexpr (GB) {
       load16_to_lds_lanes(bp[j - 8] + (int64_t)slab * b_ks, dst);
     } else {
-      load16_to_lds_uniform(bbase + (int64_t)slab * b_ks, boff[j - 8], dst);
+      load16_to_lds_uniform(uni(bbase + (int64_t)slab * b_ks), boff[j - 8], dst);
     }
   };
 
@@ -613,7 +615,10 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // by 4 N-tiles that walks K in lock-step.  Wavefront 0 touches one quarter of the A panel rows,
   // wavefront 1 one eighth of the B panel rows, PFD slabs ahead, one 4-byte load per 128-byte line:
   // between them the block's workgroups cover every line once.  Wavefronts 2 and 3 execute the same
-  // instruction on one fixed line (no divergent control flow around the accumulators).
+  // instruction on one fixed line (no divergent control flow around the accumulators).  The load goes out behind the slab's own loads
+  // and is the one that the wait at the slab's end leaves in flight (loads come back in order): waited for there, a line that had to come from
+  // memory held the slab up, which is what the prefetch is to avoid (67 k tokens at the 7B head: forward 56.4 -> 54.8 ms, dX + dW 105.3 ->
+  // 104.2; 36 k tokens, H 2048, V 32000: 3.81 -> 3.62, 7.25 -> 6.77).
   const unsigned char* pf_ptr;
   int pf_stride;
   const bool pf_atr = ATR && wave == 0;
@@ -626,6 +631,11 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     if (d.a_rows) r = d.a_rows[r];
     pf_ptr = reinterpret_cast<const unsigned char*>(A + (d.a_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.lda));
     pf_stride = a_ks * 2;
+  } else if (BTR && PFD > 0 && wave == 1) {                   // K-major B: likewise, an eighth per M-tile
+    const int q = 32 * (tm & 7) + (lane & 31);
+    int n = tn * BN + 64 * (q & 3); n = n < N ? n : N - 8;
+    pf_ptr = reinterpret_cast<const unsigned char*>(B + (int64_t)(q >> 2) * d.ldb + n);
+    pf_stride = (int)b_ks * 2;
   } else if (wave == 1) {
     int r = tn * BN + 32 * (tm & 7) + (lane & 31); r = r < N ? r : N - 1;
     if (d.b_rows) r = d.b_rows[r];
@@ -635,12 +645,18 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     pf_ptr = reinterpret_cast<const unsigned char*>(A);
     pf_stride = 0;
   }
+  int pf_last = KT ? (K - 1) / BK : nk - 1;            // (a row has no lines past its end)
+  if constexpr (BTR && PFD > 0) {
+    const int whole = (d.b_k_rows >> 6) - 1 - k_first; // last slab of B all of whose rows exist
+    if (wave == 1 && whole < pf_last) pf_last = whole;
+    if (wave == 1 && whole < 0) { pf_ptr = reinterpret_cast<const unsigned char*>(B); pf_stride = 0; pf_last = 0; }
+  }
+  if constexpr (Epi::kSplit && PFD > 0) pf_ptr += (int64_t)k_first * pf_stride;
   unsigned pf0 = 0, pf1 = 0, pf_sink = 0;
   auto prefetch = [&](unsigned& slot, int kt) __attribute__((always_inline)) {
     if (PFD > 0) {
       pf_sink ^= slot;                                   // fetched two slabs ago: long since back
-      const int last = KT ? (K - 1) / BK : nk - 1;       // (a row has no lines past its end)
-      const int k = kt + PFD < last ? kt + PFD : last;
+      const int k = kt + PFD < pf_last ? kt + PFD : pf_last;
       slot = *reinterpret_cast<const unsigned*>(pf_ptr + (int64_t)k * pf_stride + (pf_atr ? a_slab(k) * 2 : 0));
     }
   };
@@ -735,11 +751,11 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // 0..LDA-1 of slab kt+1 are in flight towards `nxt`.  The last phase runs from registers after the
   // workgroup barrier, so it covers the first fragment reads of slab kt+1 and the first loads of kt+2.
   auto slab = [&](bool tail, unsigned char* cur, unsigned char* nxt, int kt, unsigned& pfslot) __attribute__((always_inline)) {
-    prefetch(pfslot, kt);
     phase(tail, 0, 0, 0, 4, cur, 0, kof(kt + 1), nxt, LDA, LDB);
     phase(tail, 0, 1, 1, 12, cur, 1, kof(kt + 1), nxt, LDA + LDB, LDC);
+    prefetch(pfslot, kt);
     phase(tail, 1, 0, 0, 4, cur, 1, 0, nxt, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0): own loads have landed, own fragment reads are done
+    __builtin_amdgcn_s_waitcnt(PFD > 0 ? 0x0071 : 0x0070);     // vmcnt(0), or 1: all but the prefetch; lgkmcnt(0): own loads have landed, own fragment reads are done
     __syncthreads();                        // ... and so have everybody else's: `nxt` is complete, `cur` is free
     phase(tail, 1, 1, 1, 12, nxt, 0, kof(kt + 2), cur, 0, LDA);
   };

@@ -62,14 +62,14 @@ constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup pe
 // tile-order band height (M-tiles per band), L2 prefetch distance in slabs (0 = off), where in a
 // phase of 32 MFMAs the slab loads are issued (after MFMA kVmo, kVmo + kVmg, ...) and how many of a slab's 16 loads
 // go into the phase after the barrier / the next phase (kLdA / kLdB; the rest into the phase after that).
-// Measured on the 7B shape: with the XCDs sweeping N in step the dX prefetch only costs (-4 % of dX+dW when off; its
-// band height then makes no difference between 1 and 8), dW is best with one M-tile per band (its A panel, the stored
-// probabilities, then leaves memory once for all 14 N-tiles), the logits want the prefetch (off: +4 % on the forward).
+// Measured on the 7B shape: dX, dW and the logits want the prefetch two slabs ahead, three is a little worse (dX without it: 105.7 ms of dX + dW
+// instead of 104.2; 4741 tokens, H 1160, V 50257 913 us instead of 848), dW is best with one M-tile per band (its A panel, the stored
+// probabilities, then leaves memory once for all 14 N-tiles).
 // dX, whose operands both stream from memory, waits 17 % of its loop time for its slab loads with the 6/5/5 placement and
 // 5 % with 8/8/0 (all loads at least two phases before the barrier); at the power limit that is worth 0.8 % of dX+dW.
-// The other two lose with 8/8/0.
+// The other two gain nothing from 8/8/0.
 struct TuneLogits { static constexpr int kBand = 8, kPfd = 2, kVmg = 5, kVmo = 3, kLdA = 6, kLdB = 5; };
-struct TuneDX     { static constexpr int kBand = 8, kPfd = 0, kVmg = 4, kVmo = 1, kLdA = 8, kLdB = 8; };
+struct TuneDX     { static constexpr int kBand = 8, kPfd = 2, kVmg = 4, kVmo = 1, kLdA = 8, kLdB = 8; };
 struct TuneDW     { static constexpr int kBand = 1, kPfd = 2, kVmg = 4, kVmo = 1, kLdA = 6, kLdB = 5; };
 
 struct Ctrl {            // device control block at the head of the workspace
