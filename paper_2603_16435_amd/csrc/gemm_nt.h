@@ -58,6 +58,7 @@ struct GemmDims {
   int64_t lda, ldb;       // row strides in elements
   const int* a_rows;      // optional gather: logical row m of A lives at row a_rows[m]
   const int* b_rows;
+  int64_t b_span;         // rows of B that b_rows picks from
   const int* n_real;      // device scalar: number of compacted rows in the whole batch
   int chunk_start;        // first compacted row of this chunk
   const int* chunk;       // if set, device pair {first compacted row, rows} of this chunk; replaces n_real / chunk_start,
@@ -415,7 +416,7 @@ __device__ __attribute__((always_inline)) inline void load16_to_lds_uniform(cons
   const unsigned lds = (unsigned)(size_t)(lds_ptr_t)l;      // uniform
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(lane_bytes), "s"(base), "s"(lds) : "memory");
 }
-// ... and with a 64-bit address per lane, for rows that come through a row map.  (Every load of the hot kernel's main loop is
+// ... and with a 64-bit address per lane, for rows that span 4 GiB or more and for the last slabs of an operand.  (Every load of the hot kernel's main loop is
 // one of these two, so that the compiler itself never sets M0 there.)
 __device__ __attribute__((always_inline)) inline void load16_to_lds_lanes(const void* g, void* l) {
   const unsigned lds = (unsigned)(size_t)(lds_ptr_t)l;      // uniform
@@ -486,11 +487,13 @@ __device__ __attribute__((always_inline)) inline u32x2_t lds_read_tr16(const uns
 //
 // KT: K need not be a multiple of 128 (only of 8): 16-byte chunks past the end of a row are fetched from a zero block.
 //
+// FAR: the gathered B rows span 4 GiB or more, so that 32 bits do not hold a row's offset.
+//
 // Both have slabs whose load addresses are not those of the plain loop, at the end of K; the last six slabs run in a copy of the
 // loop body that works them out per lane (`tail`), so that the plain loop needs no vector operation for its load addresses.  (With BTR
 // it has others: the 16-bit offset of the transposing reads does not reach B's part of the second stage, 32 address adds per two slabs.)
 __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
-template <class Epi, int PFD, int VMG, int VMO, bool ATR = false, int LDA = 6, int LDB = 5, bool BTR = false, bool KT = false>
+template <class Epi, int PFD, int VMG, int VMO, bool ATR = false, int LDA = 6, int LDB = 5, bool BTR = false, bool KT = false, bool FAR = false>
 __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d,
                                                                         const Epi& epi, int pid, unsigned char* stage0, unsigned char* stage1) {
   constexpr int BM = 256, BN = 256, BK = 64, WAVES_M = 2, WAVES_N = 2;
@@ -540,10 +543,11 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // ---- slab staging.  Wavefront w fills rows [64w, 64w+64) of A and of B: eight loads of eight
   // rows each.  A load writes lane l's 16 bytes to LDS offset 16*l of its 1 KiB target, i.e. row
   // l/8, slot l%8; the swizzle is therefore applied on the global side (which chunk a lane fetches).
-  // An operand whose rows are where they are numbered (every one but the hidden states, whose rows come through the row
-  // map) is addressed as a wavefront-uniform base plus a 32-bit lane offset: the address of a load is then a scalar add per
+  // Both operands are addressed as a wavefront-uniform base plus a 32-bit lane offset: the address of a load is then a scalar add per
   // slab and no vector operation (vector operations and MFMAs take turns on a SIMD).  All rows of a tile lie within
-  // 256 rows of the tile's first, so the offsets fit.
+  // 256 rows of the tile's first, so the offsets fit; the hidden states, whose rows come through the row map, are addressed from their
+  // first row, where they span less than 4 GiB (FAR otherwise: an address per lane; forward of 67 k tokens at the 7B head 56.4 ms that way, 55.8
+  // with offsets, scoring of 10 k 8.22 and 8.06).
   constexpr bool GB = Epi::kGatherB;
   const bf16_t* ap[8];
   const bf16_t* bp[8];
@@ -579,7 +583,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       bp[j] = B + (d.b_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.ldb) + c * 8;
     }
     aoff[j] = (unsigned)(ap[j] - abase) * 2u;                   // in bytes
-    boff[j] = GB ? 0u : (unsigned)(bp[j] - bbase) * 2u;
+    boff[j] = (unsigned)(bp[j] - (GB ? B : bbase)) * 2u;
   }
   const int a_ks = d.a_tiled ? 16384 : BK;                                    // elements from one slab to the next
   const int64_t b_ks = BTR ? (int64_t)BK * d.ldb : d.b_tiled ? 16384 : BK;
@@ -604,10 +608,10 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       const int last = (d.b_k_rows - 1) >> 6, s_abs = k_first + slab, sc = s_abs < last ? s_abs : last;       // a slab that has rows
       const int row = ((wave * 8 + j - 8) * 64 + lane) >> 5, left = d.b_k_rows - 1 - sc * BK;
       load16_to_lds_lanes(bp[j - 8] + (int64_t)(sc * BK + (row < left ? row : left) - row) * d.ldb, dst);
-    } else if constexpr (GB) {
+    } else if constexpr (GB && FAR) {
       load16_to_lds_lanes(bp[j - 8] + (int64_t)slab * b_ks, dst);
     } else {
-      load16_to_lds_uniform(uni(bbase + (int64_t)slab * b_ks), boff[j - 8], dst);
+      load16_to_lds_uniform(uni((GB ? B : bbase) + (int64_t)slab * b_ks), boff[j - 8], dst);
     }
   };
 
@@ -803,12 +807,12 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   if (PFD > 0 && (pf_sink ^ pf0 ^ pf1) == 0x9E3779B9u && K < 0) epi.keep_alive();   // never true: keeps the prefetch loads
 }
 
-template <class Epi, class Tune, bool KT = false>
+template <class Epi, class Tune, bool KT = false, bool FAR = false>
 __global__ __launch_bounds__(256)
 void gemm_nt_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, Epi epi) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage0[kHotStageBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char stage1[kHotStageBytes];
-  gemm_nt_bf16_tile<Epi, Tune::kPfd, Tune::kVmg, Tune::kVmo, false, Tune::kLdA, Tune::kLdB, false, KT>(A, B, d, epi, blockIdx.x, stage0, stage1);
+  gemm_nt_bf16_tile<Epi, Tune::kPfd, Tune::kVmg, Tune::kVmo, false, Tune::kLdA, Tune::kLdB, false, KT, FAR>(A, B, d, epi, blockIdx.x, stage0, stage1);
 }
 
 // Two independent contractions in one launch: workgroups [0, n1) work on the first, the rest on the

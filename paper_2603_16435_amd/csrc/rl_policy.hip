@@ -982,9 +982,16 @@ static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, con
                     ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0) &&
                     !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB &&     // (how the hot kernel addresses its operands)
                     !small_k<Epi>(d.K);
-  if constexpr (!std::is_same_v<Epi, EpiFwd<bf16_t, true>>)      // (keeps its logits in the hot kernel's order: make_plan sees to it)
+  // (two epilogues are written for the hot kernel, one of them for K on its grid: make_plan sees to it)
+  constexpr bool stash = std::is_same_v<Epi, EpiFwdStash<bf16_t>>;
+  if constexpr (!stash && !std::is_same_v<Epi, EpiFwd<bf16_t, true>>)
     if (!fast) { launch_generic(A, B, d, epi, tiles, s); return; }
-  if (d.K % 128) gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  const bool far = d.b_rows && d.b_span * d.ldb * 2 >= ((int64_t)1 << 32);
+  if (!stash && d.K % 128) {
+    if constexpr (stash) return;
+    else if (far) gemm_nt_bf16_kernel<Epi, Tune, true, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+    else gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  } else if (far) gemm_nt_bf16_kernel<Epi, Tune, false, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
@@ -1115,7 +1122,7 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
     const int c0 = ch * p.Tc;
     GemmDims d{};
     d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
-    d.a_rows = nullptr; d.b_rows = q.row_map + c0; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
+    d.a_rows = nullptr; d.b_rows = q.row_map + c0; d.b_span = p.R; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
     {
       ProfScope ps(RL_PROF_GEMM_FWD, s);
       if (p.keep) launch_gemm<TuneLogits>(W, X, d, EpiFwd<T, true>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, s);
@@ -1167,7 +1174,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     } else {  // recompute logits, form dS (and dS^T for f32 inputs)
       GemmDims d{};
       d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
-      d.b_rows = q.row_map + c0; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
+      d.b_rows = q.row_map + c0; d.b_span = p.R; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
       EpiDS<T> e{q.ids_c, q.lse_c, q.c_c, dS, p.Vp, dST, p.Tc, p.V, p.tiled, p.inv_tau};
       ProfScope ps(RL_PROF_GEMM_DS, s);
       launch_gemm<TuneLogits>(W, X, d, e, s);
@@ -1241,11 +1248,10 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     {  // forward: partial sums + E
       GemmDims d{};
       d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
-      d.b_rows = q.row_map; d.chunk = chunk; d.dyn = 2; d.group_m = TuneLogits::kBand;
+      d.b_rows = q.row_map; d.b_span = p.R; d.chunk = chunk; d.dyn = 2; d.group_m = TuneLogits::kBand;
       EpiFwdStash<T> e{q.ref, part, p.Tc, E, p.Vp, p.V, p.inv_tau};
       ProfScope ps(RL_PROF_GEMM_FWD, s);
-      gemm_nt_bf16_kernel<EpiFwdStash<T>, TuneLogits>
-          <<<launch_tiles((p.V + kBM - 1) / kBM, (p.Tc + kBN - 1) / kBN), 256, 0, s>>>(W, X, d, e);
+      launch_gemm<TuneLogits>(W, X, d, e, s);
     }
     {
       ProfScope ps(RL_PROF_COMBINE, s);
