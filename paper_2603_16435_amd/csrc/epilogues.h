@@ -690,7 +690,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmDims d, EpiDX<T>
     const int m = (int)(q / h4), n = (int)(q - (int64_t)m * h4) * 4;
     const float* p = e.split_part + (int64_t)m * e.H + n;
     floatx4 s = *reinterpret_cast<const floatx4*>(p);
-    for (int k = 1; k < sk.slices; ++k) s += *reinterpret_cast<const floatx4*>(p + k * stride);
+    for (int k0 = 1; k0 < sk.slices; k0 += 8) {                  // eight loads in flight
+      floatx4 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) if (k0 + k < sk.slices) v[k] = *reinterpret_cast<const floatx4*>(p + (k0 + k) * stride);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) if (k0 + k < sk.slices) s += v[k];
+    }
     const float f = e.row_scale ? e.row_scale[m] : 1.f;
     T* o = e.dX + (int64_t)e.row_map[d.chunk_start + m] * e.ldx + n;
 #pragma unroll

@@ -76,7 +76,8 @@ struct Ctrl {            // device control block at the head of the workspace
   int n_real;
   int too_long;          // single-pass backward: some sequence has more rows than the caller promised / a chunk holds
   int overflow;          // single-pass backward: rows whose stored probabilities left the range of the staging precision
-  int pad[13];
+  int done;              // sequences whose loss is formed: the last one finishes the call's loss
+  int pad[12];
 };
 
 struct ChunkDesc {       // device record of one sequence-aligned chunk (single-pass backward)
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* mask, cons
   if (i == B) {
     if (threadIdx.x == 0) {
       cstart[B] = first;
-      ctrl->n_real = first; ctrl->too_long = 0; ctrl->overflow = 0;
+      ctrl->n_real = first; ctrl->too_long = 0; ctrl->overflow = 0; ctrl->done = 0;
       if (stats) stats->n_tokens = first;
     }
     if (chunks.desc) build_chunks(seq_len, B, chunks, ctrl, stats, sh_len);
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
     for (int i = 0; i < s.B; ++i) at += i < t ? sh_len[i] : 0;
     sh_at[t] = at; s.cstart[t] = at;
     if (t == s.B) {
-      s.ctrl->n_real = at; s.ctrl->too_long = 0; s.ctrl->overflow = 0;
+      s.ctrl->n_real = at; s.ctrl->too_long = 0; s.ctrl->overflow = 0; s.ctrl->done = 0;
       if (s.stats) s.stats->n_tokens = at;
     }
   }
@@ -567,13 +568,16 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 
 // ------------------------------------------------------------------ forward combine
 // Fold the per-vocab-tile partials (max, sumexp) of a chunk into lse, logp.  A workgroup handles 64
-// compact rows x 4 slices of the tile range: one online (rescaling) pass per thread, coalesced
-// along the rows, then the four slices are merged through LDS in a fixed order.
-__global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
+// compact rows x 16 slices of the tile range: one online (rescaling) pass per thread, coalesced
+// along the rows, then the slices are scaled to the row's maximum, one exponential per thread, and added through LDS in order.
+// (Four slices, each scaled by the thread that adds them up: 8 us for 99 rows x 125 tiles, all latency.)
+constexpr int kCombineSlices = 16;
+__global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
                                    const int32_t* row_map, const Ctrl* ctrl, int chunk_start, int chunk_rows, const int32_t* ycol_c,
                                    float* lse_c, float* logp_c, float* lse_out, float* logp_out, float* ent_out,
                                    float* zy_out, int32_t* ycol_out) {
-  __shared__ float sm[4][64], ss[4][64], su[4][64];
+  __shared__ float sm[kCombineSlices][64];
+  __shared__ double ss[kCombineSlices][64], su[kCombineSlices][64];
   int left = ctrl->n_real - chunk_start;
   if (left > chunk_rows) left = chunk_rows;
   if ((int)blockIdx.x * 64 >= left) return;
@@ -582,13 +586,13 @@ __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, con
   const float NEG = -__builtin_inff();
   float m = NEG, s = 0.f, u = 0.f;
   if (n < left) {
-    for (int t0 = slice; t0 < tiles_v; t0 += 32) {             // eight loads in flight, folded in order
+    for (int t0 = slice; t0 < tiles_v; t0 += 8 * kCombineSlices) {             // eight loads in flight, folded in order
       float4 q[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) if (t0 + 4 * k < tiles_v) q[k] = part[(int64_t)(t0 + 4 * k) * ldp + n];
+      for (int k = 0; k < 8; ++k) if (t0 + kCombineSlices * k < tiles_v) q[k] = part[(int64_t)(t0 + kCombineSlices * k) * ldp + n];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        if (t0 + 4 * k >= tiles_v) break;
+        if (t0 + kCombineSlices * k >= tiles_v) break;
         const float4 v = q[k];
         const float mm = fmaxf(m, v.x);
         if (mm != NEG) {
@@ -600,17 +604,20 @@ __global__ void lse_combine_kernel(const float4* part, int ldp, int tiles_v, con
       }
     }
   }
-  sm[slice][col] = m; ss[slice][col] = s; su[slice][col] = u;
+  sm[slice][col] = m;
+  __syncthreads();
+  float M = sm[0][col];
+#pragma unroll
+  for (int k = 1; k < kCombineSlices; ++k) M = fmaxf(M, sm[k][col]);
+  {
+    const double f = m != NEG ? exp((double)(m - M)) : 0.0;
+    ss[slice][col] = (double)s * f; su[slice][col] = (double)u * f;
+  }
   __syncthreads();
   if (slice == 0 && n < left) {
-    float M = sm[0][col];
-    for (int k = 1; k < 4; ++k) M = fmaxf(M, sm[k][col]);
     double S = 0.0, U = 0.0;
-    for (int k = 0; k < 4; ++k)
-      if (sm[k][col] != NEG) {
-        const double f = exp((double)(sm[k][col] - M));
-        S += (double)ss[k][col] * f; U += (double)su[k][col] * f;
-      }
+#pragma unroll
+    for (int k = 0; k < kCombineSlices; ++k) { S += ss[k][col]; U += su[k][col]; }
     const double lse_d = (double)M + log(S);
     const float lse = (float)lse_d;
     const int g = chunk_start + n;
@@ -634,26 +641,80 @@ struct LossOpts {
   int w_mean;               // FLOW: weight from the mean instead of the sum of the token log-ratios
 };
 
+struct LossJob {
+  int objective; const float *logp_c, *old_lp, *ref_lp; const int32_t *row_map, *cstart; const float* adv;
+  const int32_t* group_idx; const float* log_z; int B, P; LossOpts o; Ctrl* ctrl;
+  float *seq_loss, *gterm, *c_c, *coeff_out; rl_stats* stats;
+  const ChunkDesc* desc;                // only the sequences of this chunk
+  float* adv_out; int32_t* seq_len_out;
+  float *loss, *d_log_z, *seq_loss_out;
+};
+// Up to kFinishSeqs sequences, the workgroup that forms the last one's loss adds them up as well; with more, the release that every workgroup
+// then owes the others costs as much as a launch or more (256 sequences 16 us against 15, 20000 469 against 46).
+constexpr int kLossThreads = 256, kFinishSeqs = 64;
+
+// loss = (1/B) sum_i seq_loss_i
+__device__ inline void add_up_loss(const LossJob& j) {
+  __shared__ double sh[16];
+  double acc = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < j.B; i += blockDim.x) {
+    const float v = j.seq_loss[i];
+    acc += (double)v;
+    if (j.seq_loss_out) j.seq_loss_out[i] = v;
+  }
+  const double tot = block_sum(acc, sh);
+  // a sequence longer than the caller promised: the single-pass backward dropped rows, say so loudly
+  // ... or stored probabilities that left the representable range: the gradients of those rows are not numbers
+  if (threadIdx.x == 0) *j.loss = (j.ctrl->too_long || j.ctrl->overflow) ? __builtin_nanf("") : (float)(tot / j.B);
+}
+// ... and d_logZ_p = sum over members of gterm (0 for an empty sequence), in order
+__device__ inline void finish_loss(const LossJob& j) {
+  __shared__ int sh_g[kFinishSeqs];
+  __shared__ float sh_t[kFinishSeqs];
+  add_up_loss(j);
+  if (!j.d_log_z) return;
+  for (int i = threadIdx.x; i < j.B; i += kLossThreads) { sh_g[i] = j.group_idx[i]; sh_t[i] = j.gterm[i]; }
+  __syncthreads();
+  for (int p = threadIdx.x; p < j.P; p += kLossThreads) {
+    double s = 0.0;
+    if (j.objective == RL_OBJ_FLOW)
+#pragma unroll 8
+      for (int k = 0; k < j.B; ++k) s += sh_g[k] == p ? (double)sh_t[k] : 0.0;
+    j.d_log_z[p] = (float)s;
+  }
+}
+// The same for more sequences, in a launch of its own: workgroup 0 the loss, a wavefront per prompt d_log_z.
+__global__ __launch_bounds__(1024) void finalize_kernel(LossJob j) {
+  if (blockIdx.x == 0) { add_up_loss(j); return; }
+  const int p = ((int)blockIdx.x - 1) * 16 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (p >= j.P) return;
+  double s = 0.0;
+  if (j.objective == RL_OBJ_FLOW) {
+#pragma unroll 8
+    for (int i = lane; i < j.B; i += 64) s += j.group_idx[i] == p ? (double)j.gterm[i] : 0.0;
+    s = wave_sum(s);
+  }
+  if (lane == 0) j.d_log_z[p] = (float)s;
+}
+
 // One workgroup per sequence over its compact rows [cstart[i], cstart[i+1]).  The caller's advantages and lengths leave here, when the
 // rewards and the offsets have been read everywhere: an output may take the place of an input.
-__global__ void seq_loss_kernel(int objective, const float* logp_c, const float* old_lp, const float* ref_lp,
-                                const int32_t* row_map, const int32_t* cstart, const float* adv,
-                                const int32_t* group_idx, const float* log_z, int B, LossOpts o, const Ctrl* ctrl,
-                                float* seq_loss, float* gterm, float* c_c, float* coeff_out, rl_stats* stats,
-                                const ChunkDesc* desc, float* adv_out, int32_t* seq_len_out) {
+__device__ inline void sequence_loss(const LossJob& j, int i) {
+  const float *logp_c = j.logp_c, *old_lp = j.old_lp, *ref_lp = j.ref_lp, *log_z = j.log_z;
+  const int32_t *row_map = j.row_map, *group_idx = j.group_idx;
+  const int objective = j.objective, B = j.B;
+  const LossOpts& o = j.o;
+  float *seq_loss = j.seq_loss, *gterm = j.gterm, *c_c = j.c_c, *coeff_out = j.coeff_out;
+  rl_stats* stats = j.stats;
   __shared__ double sh[16];
   __shared__ int sh_hi, sh_lo;
-  int i = blockIdx.x;
-  if (desc) {                           // only the sequences of one chunk
-    i += desc->seq_begin;
-    if (i >= desc->seq_end) return;
-  }
-  const int a = cstart[i], b = cstart[i + 1], n = b - a;
-  const float A = adv[i];
+  const int a = j.cstart[i], b = j.cstart[i + 1], n = b - a;
+  const float A = j.adv[i];
   if (threadIdx.x == 0) {
     sh_hi = 0; sh_lo = 0;
-    if (adv_out) adv_out[i] = A;
-    if (seq_len_out) seq_len_out[i] = n;
+    if (j.adv_out) j.adv_out[i] = A;
+    if (j.seq_len_out) j.seq_len_out[i] = n;
   }
   if (n <= 0) {
     if (threadIdx.x == 0) { seq_loss[i] = 0.f; gterm[i] = 0.f; }
@@ -664,7 +725,7 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
   const double lo_c = 1.0 - (double)o.clip_lo, hi_c = 1.0 + (double)o.clip_hi;
   if (objective == RL_OBJ_GRPO && !o.seq_ratio) {
     // weight of a token term in the loss: 1/(B n_i) (mean of per-sequence means) or 1/T (mean over all tokens)
-    const double wt = o.token_agg ? 1.0 / (double)ctrl->n_real : inv_bn;
+    const double wt = o.token_agg ? 1.0 / (double)j.ctrl->n_real : inv_bn;
     double acc = 0.0; int hi = 0, lo = 0;
     for (int k = a + threadIdx.x; k < b; k += blockDim.x) {
       const int r = row_map[k];
@@ -748,29 +809,26 @@ __global__ void seq_loss_kernel(int objective, const float* logp_c, const float*
   }
 }
 
-// loss = (1/B) sum_i seq_loss_i ;  d_logZ_p = sum over members of gterm  (single workgroup)
-__global__ void finalize_kernel(const float* seq_loss, const float* gterm, const int32_t* group_idx,
-                                const int32_t* seq_len, int B, int P, int objective, const Ctrl* ctrl,
-                                float* loss, float* d_log_z, float* seq_loss_out) {
-  __shared__ double sh[16];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < B; i += blockDim.x) {
-    acc += (double)seq_loss[i];
-    if (seq_loss_out) seq_loss_out[i] = seq_loss[i];
+// ... and the workgroup that is the last of the call to get here adds the sequences up (a launch of its own took 2 to 5 us, 16 with
+// 64 sequences and the flow objective, whose prompts a thread each walked all sequences for).
+__device__ inline void sequence_loss_and_finish(const LossJob& j, int i) {
+  __shared__ int sh_last;
+  if (j.desc) {
+    i += j.desc->seq_begin;
+    if (i >= j.desc->seq_end) return;
   }
-  const double tot = block_sum(acc, sh);
-  // a sequence longer than the caller promised: the single-pass backward dropped rows, say so loudly
-  // ... or stored probabilities that left the representable range: the gradients of those rows are not numbers
-  if (threadIdx.x == 0) *loss = (ctrl->too_long || ctrl->overflow) ? __builtin_nanf("") : (float)(tot / B);
-  if (d_log_z) {
-    for (int p = threadIdx.x; p < P; p += blockDim.x) {
-      double s = 0.0;
-      if (objective == RL_OBJ_FLOW)
-        for (int i = 0; i < B; ++i) if (group_idx[i] == p && seq_len[i] > 0) s += (double)gterm[i];
-      d_log_z[p] = (float)s;
-    }
+  sequence_loss(j, i);
+  if (j.B > kFinishSeqs) return;
+  if (threadIdx.x == 0) {                 // (it wrote the sequence's terms)
+    __threadfence();
+    sh_last = atomicAdd(&j.ctrl->done, 1) == j.B - 1;
   }
+  __syncthreads();
+  if (!sh_last) return;
+  __threadfence();
+  finish_loss(j);
 }
+__global__ __launch_bounds__(kLossThreads) void seq_loss_kernel(LossJob j) { sequence_loss_and_finish(j, blockIdx.x); }
 
 // ------------------------------------------------------------------ transposes (K-contiguous operands)
 // dst[c][r] = src[row_of(r)][c] for r < rows_valid, 0 for rows_valid <= r < ld_dst rows covered by the grid.
@@ -814,12 +872,14 @@ __global__ void transpose_kernel(TransposeJob<T> j) {
   __shared__ T tile[64][65];
   transpose_block(j, blockIdx.x, blockIdx.y, tile);
 }
-// W^T, X^T of the only chunk and the zeroing of the rows that do not count in one launch (f32: a small call is bound by its
-// launches): workgroups [0, nw) and [nw, nw + nx) transpose, the rest zero four rows each.
-__global__ __launch_bounds__(256) void backward_prep_kernel(TransposeJob<float> w, int wx, int nw, TransposeJob<float> x, int xx, int nx,
-                                                            const int32_t* cpos, float* dX, int64_t R, int H) {
+// The loss with W^T, X^T of the only chunk and the zeroing of the rows that do not count beside it in one launch (f32: a small call is bound by
+// its launches): workgroups [0, B) form the loss, [B, B + nw) and the next nx transpose, the rest zero four rows each.
+__global__ __launch_bounds__(kLossThreads) void loss_prep_kernel(LossJob j, TransposeJob<float> w, int wx, int nw, TransposeJob<float> x, int xx, int nx,
+                                                                 const int32_t* cpos, float* dX, int64_t R, int H) {
   __shared__ float tile[64][65];
   int b = blockIdx.x;
+  if (b < j.B) { sequence_loss_and_finish(j, b); return; }
+  b -= j.B;
   if (b < nw) { transpose_block(w, b % wx, b / wx, tile); return; }
   b -= nw;
   if (b < nx) { transpose_block(x, b % xx, b / xx, tile); return; }
@@ -1227,32 +1287,21 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
       else launch_gemm<TuneLogits>(W, X, d, EpiFwd<T>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, s);
     }
     ProfScope ps(RL_PROF_COMBINE, s);
-    lse_combine_kernel<<<(p.Tc + 63) / 64, 256, 0, s>>>(q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc, q.ycol,
+    lse_combine_kernel<<<(p.Tc + 63) / 64, 64 * kCombineSlices, 0, s>>>(q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc, q.ycol,
                                                         q.lse_c, q.logp_c, lse_out, logp_out, ent_out, zy_out, ycol_out);
   }
 }
 
 template <class T>
-static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* d_hidden, float* d_weight, hipStream_t s) {
+static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* d_hidden, float* d_weight, bool xt_done, hipStream_t s) {
   const T* X = static_cast<const T*>(b->hidden);
   const T* W = static_cast<const T*>(b->weight);
   T* WT = static_cast<T*>(q.wt); T* XT = static_cast<T*>(q.xt);
   T* dS = static_cast<T*>(q.ds); T* dST = static_cast<T*>(q.dst);
   T* dX = static_cast<T*>(d_hidden);
   // masked rows of dX are zero; rows that count are written by the dX epilogue.  W^T [H][Vp] with zero padding columns, once per
-  // call (bf16: unless dX reads W as it is).  With one chunk the f32 path does both, and X^T, in one launch.
+  // call (bf16: unless dX reads W as it is).  xt_done: both, and X^T of the only chunk, are there (loss_prep_kernel).
   const dim3 gw((p.Vp + 63) / 64, (p.H + 63) / 64), gx((p.Tc + 63) / 64, (p.H + 63) / 64);
-  bool xt_done = false;
-  if constexpr (sizeof(T) == 4) {
-    const int64_t nw = (int64_t)gw.x * gw.y, nx = (int64_t)gx.x * gx.y, n = nw + nx + (p.R + 3) / 4;
-    xt_done = p.n_chunks == 1 && n < (1 << 30);
-    if (xt_done) {
-      ProfScope ps(RL_PROF_TRANSPOSE, s);
-      backward_prep_kernel<<<(unsigned)n, 256, 0, s>>>(
-          TransposeJob<T>{W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, false}, (int)gw.x, (int)nw,
-          TransposeJob<T>{X, p.H, p.Tc, p.H, q.row_map, q.ctrl, 0, 1, nullptr, nullptr, XT, p.Tc, p.Tc, false}, (int)gx.x, (int)nx, q.cpos, dX, p.R, p.H);
-    }
-  }
   if (!xt_done) {
     ProfScope ps(RL_PROF_TRANSPOSE, s);
     zero_masked_rows_kernel<T><<<(unsigned)((p.R + 3) / 4), 256, 0, s>>>(q.cpos, dX, p.R, p.H);
@@ -1306,6 +1355,19 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
   }
 }
 
+// f32 batch of one chunk: the loss and what the backward needs prepared, in one launch.  False if the launch would be too large.
+static bool run_loss_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const LossJob& j, float* dX, hipStream_t s) {
+  const float *X = static_cast<const float*>(b->hidden), *W = static_cast<const float*>(b->weight);
+  float *WT = static_cast<float*>(q.wt), *XT = static_cast<float*>(q.xt);
+  const int wx = (p.Vp + 63) / 64, xx = (p.Tc + 63) / 64, hy = (p.H + 63) / 64;
+  const int64_t nw = (int64_t)wx * hy, nx = (int64_t)xx * hy, n = p.B + nw + nx + (p.R + 3) / 4;
+  if (p.dtype != RL_F32 || p.n_chunks != 1 || n >= (1 << 24)) return false;        // (2^32 threads a launch)
+  loss_prep_kernel<<<(unsigned)n, kLossThreads, 0, s>>>(
+      j, TransposeJob<float>{W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, false}, wx, (int)nw,
+      TransposeJob<float>{X, p.H, p.Tc, p.H, q.row_map, q.ctrl, 0, 1, nullptr, nullptr, XT, p.Tc, p.Tc, false}, xx, (int)nx, q.cpos, dX, p.R, p.H);
+  return true;
+}
+
 static LossOpts loss_opts(const rl_params* prm) {
   LossOpts o;
   o.clip_lo = prm->clip_eps;
@@ -1315,6 +1377,15 @@ static LossOpts loss_opts(const rl_params* prm) {
   o.seq_ratio = prm->ratio_level == RL_RATIO_SEQUENCE;
   o.w_mean = prm->flow_weight_norm == RL_WNORM_MEAN;
   return o;
+}
+
+static void run_finalize(const LossJob& j, hipStream_t s) {
+  if (j.B > kFinishSeqs) finalize_kernel<<<1 + (j.d_log_z ? (j.P + 15) / 16 : 0), 1024, 0, s>>>(j);
+}
+static LossJob loss_job(const rl_batch* b, const rl_params* prm, int objective, const Plan& p, const Ptrs& q, const rl_outputs* out,
+                        const ChunkDesc* desc) {
+  return LossJob{objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv, b->group_idx, b->log_z, p.B, p.P, loss_opts(prm),
+                 q.ctrl, q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, desc, out->advantages, out->seq_len, out->loss, out->d_log_z, out->seq_loss};
 }
 
 // Single-pass variant of forward + loss + backward (bf16 hot kernels): chunks are made of whole
@@ -1359,9 +1430,7 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     }
     {
       ProfScope ps(RL_PROF_LOSS, s);
-      seq_loss_kernel<<<p.B, 256, 0, s>>>(objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv,
-                                         b->group_idx, b->log_z, p.B, loss_opts(prm), q.ctrl,
-                                         q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, dk, out->advantages, out->seq_len);
+      seq_loss_kernel<<<p.B, kLossThreads, 0, s>>>(loss_job(b, prm, objective, p, q, out, dk));
       stash_patch_kernel<T><<<(p.Tc + 255) / 256, 256, 0, s>>>(dk, q.ids_c, q.zy, q.ref, q.zsum, q.c_c, p.inv_tau, q.scale, E, p.Vp);
     }
     {  // X^T chunk scaled by -c/Z, zero beyond the valid rows
@@ -1383,8 +1452,7 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     }
   }
   ProfScope ps(RL_PROF_LOSS, s);
-  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, p.B, p.P, objective, q.ctrl,
-                                    out->loss, out->d_log_z, out->seq_loss);
+  run_finalize(loss_job(b, prm, objective, p, q, out, nullptr), s);
 }
 
 static rl_status check_ws(void* ws, size_t bytes, const Plan& p) {
@@ -1562,17 +1630,17 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, s);
   else run_forward<float>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, s);
 
+  bool prep_done = false;
   {
-  ProfScope ps(RL_PROF_LOSS, s);
-  seq_loss_kernel<<<p.B, 256, 0, s>>>(objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv,
-                                     b->group_idx, b->log_z, p.B, loss_opts(prm), q.ctrl,
-                                     q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, nullptr, out->advantages, out->seq_len);
-  finalize_kernel<<<1, 1024, 0, s>>>(q.seq_loss, q.gterm, b->group_idx, q.seq_len, p.B, p.P, objective, q.ctrl,
-                                    out->loss, out->d_log_z, out->seq_loss);
+    ProfScope ps(RL_PROF_LOSS, s);
+    const LossJob j = loss_job(b, prm, objective, p, q, out, nullptr);
+    prep_done = bwd && run_loss_prep(b, p, q, j, static_cast<float*>(out->d_hidden), s);
+    if (!prep_done) seq_loss_kernel<<<p.B, kLossThreads, 0, s>>>(j);
+    run_finalize(j, s);
   }
   if (bwd) {
-    if (p.dtype == RL_BF16) run_backward<bf16_t>(b, p, q, out->d_hidden, out->d_weight, s);
-    else run_backward<float>(b, p, q, out->d_hidden, out->d_weight, s);
+    if (p.dtype == RL_BF16) run_backward<bf16_t>(b, p, q, out->d_hidden, out->d_weight, prep_done, s);
+    else run_backward<float>(b, p, q, out->d_hidden, out->d_weight, prep_done, s);
   }
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
