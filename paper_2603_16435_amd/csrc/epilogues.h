@@ -142,17 +142,18 @@ struct EpiFwd {
     }
   }
 
-  // Narrow tile of the f32 kernel (256 x 16, four wavefronts of 64 x 16).  Its sums are those of the 256 x 64 tile to the bit, so that a
-  // token's log-prob does not depend on how many rows are staged with it: there one lane adds up, in order, the 64 rows of a half tile
-  // (128 rows) whose bit 2 is the lane's half of the wavefront.  Here such a chain is spread over two lane groups of two wavefronts, so
+  // Narrow tile of the f32 kernel (256 x 16, WAVES wavefronts stacked along the vocabulary).  Its sums are those of the 256 x 64 tile to the bit,
+  // so that a token's log-prob does not depend on how many rows are staged with it: there one lane adds up, in order, the 64 rows of a half tile
+  // (128 rows) whose bit 2 is the lane's half of the wavefront.  Here such a chain is spread over two lane groups of several wavefronts, so
   // the exponentials are formed where the logits are, pass through LDS, and wavefront 0 adds up one chain per lane.
-  template <class L, int MB>
+  template <class L, int MB, int WAVES>
   __device__ __attribute__((always_inline)) void narrow(typename L::acc_t (&acc)[MB][1], const TileCtx& c, unsigned char* smem, int vleft) const {
-    static_assert(L::kBlk == 16 && MB == 4 && sizeof(T) == 4, "four 16 x 16 blocks per wavefront");
+    static_assert(L::kBlk == 16 && MB * WAVES == 16 && WAVES % 2 == 0 && sizeof(T) == 4, "256 rows in blocks of 16 x 16");
     const float NEG = -__builtin_inff();
     float2* ev = reinterpret_cast<float2*>(smem);               // [position in the chain][chain: half of the lanes, half of the tile, column]
     float* mw = reinterpret_cast<float*>(smem + 64 * 64 * 8);   // [wavefront][half of the lanes, column] largest logit
     const int col = c.lane & 15, g = c.lane >> 4, hc = c.lane & 31;
+    constexpr int HALF = WAVES / 2;                             // wavefronts of a half tile
     float mx = NEG;
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)
@@ -162,9 +163,16 @@ struct EpiFwd {
     lane_pair<32>(mx, m1, m2);
     if (c.lane < 32) mw[c.wm * 32 + hc] = fmaxf(m1, m2);
     __syncthreads();
-    mx = fmaxf(mw[(c.wm & 2) * 32 + hc], mw[(c.wm | 1) * 32 + hc]);
+    const int half = c.wm / HALF;
+    auto half_max = [&](int hf, int at) __attribute__((always_inline)) {
+      float m = mw[hf * HALF * 32 + at];
+#pragma unroll
+      for (int w = 1; w < HALF; ++w) m = fmaxf(m, mw[(hf * HALF + w) * 32 + at]);
+      return m;
+    };
+    mx = half_max(half, hc);
     const float ms = (mx == NEG) ? 0.f : mx * zs;
-    float2* my = ev + ((c.wm & 1) * 32 + (g >> 1) * 4) * 64 + (g & 1) * 32 + (c.wm >> 1) * 16 + col;
+    float2* my = ev + ((c.wm % HALF) * MB * 8 + (g >> 1) * 4) * 64 + (g & 1) * 32 + half * 16 + col;
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
@@ -182,8 +190,7 @@ struct EpiFwd {
       s[0] += x.x;
       u[0] = __builtin_fmaf(x.x, x.y, u[0]);
     }
-    const int w2 = g & 1, h = g >> 1;                           // the chain of this lane
-    m[0] = fmaxf(mw[2 * w2 * 32 + h * 16 + col], mw[(2 * w2 + 1) * 32 + h * 16 + col]) * zs;
+    m[0] = half_max(g & 1, (g >> 1) * 16 + col) * zs;           // the chain of this lane: half tile g & 1, lane half g >> 1
     u[0] *= zs;
     merge_lanes<32, 1>(m, s, u);
     merge_lanes<16, 1>(m, s, u);
@@ -223,8 +230,8 @@ struct EpiFwd {
       else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
     }
     if constexpr (kNarrow) {
-      static_assert(WAVES_M == 4 && WAVES_N == 1, "the wavefronts of a column are stacked along the vocabulary");
-      narrow<L, MB>(acc, c, smem, vleft);
+      static_assert(WAVES_N == 1, "the wavefronts of a column are stacked along the vocabulary");
+      narrow<L, MB, WAVES_M>(acc, c, smem, vleft);
       return;
     } else {
     // merge with the lane groups that hold the other rows of these columns (row swaps at vector speed; the pair comes lower

@@ -280,9 +280,13 @@ __device__ inline GeneralTile general_tile(GemmDims& d, int pid) {
 // eight-wide step in the order 0 4 1 5 2 6 3 7, so that an f32 logit does not depend on the tile it came from: in the
 // 16x16 form lane group g supplies element g/2, then g/2 + 2, of chunk g%2 - one 8-byte read, the chunks being stored in the
 // order 0 2 1 3 for it.
-template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(WAVES_M * WAVES_N * 64, 2)
-void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, Epi epi) {
+//
+// KG > 1: KG groups of such wavefronts share a tile, each taking every KG-th slab through LDS stages of its own; their accumulators are added in
+// order at the end (for tiles that are few and have a long K; a step of a K cut is then KG slabs).
+template <class T, int BM, int BN, int KG> constexpr int general_lds_bytes() { return KG * 2 * (BM + BN) * kSlabBytes; }
+template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG>
+__device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, const Epi& epi,
+                                                                           int pid, unsigned char* smem_all) {
   constexpr int NT = WAVES_M * WAVES_N * 64;
   constexpr int BK = Elem<T>::kBK;
   constexpr int EPC = Elem<T>::kPerChunk;
@@ -296,14 +300,15 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   static_assert(BM % ROWS_PER_PASS == 0 && (BN % ROWS_PER_PASS == 0 || BN < ROWS_PER_PASS), "tile vs threads");
   constexpr int A_BYTES = BM * kSlabBytes, B_BYTES = BN * kSlabBytes;
 
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * (A_BYTES + B_BYTES)];
-
-  const GeneralTile t = general_tile<BM, BN, BK>(d, blockIdx.x);
+  const GeneralTile t = general_tile<BM, BN, BK * KG>(d, pid);
   if (!t.any) return;
-  const int M = t.M, N = t.N, K = t.K, nk = t.nk, tm = t.tm, tn = t.tn, k_begin = t.k_begin;
+  const int M = t.M, N = t.N, K = t.K, nk = t.nk, tm = t.tm, tn = t.tn;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int group = KG > 1 ? (int)threadIdx.x / NT : 0;
+  const int tid = threadIdx.x - group * NT, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  unsigned char* smem = smem_all + group * 2 * (A_BYTES + B_BYTES);
+  const int k_begin = t.k_begin * KG + group;                        // first slab of the group; then every KG-th
 
   // ---- global -> register staging: thread owns chunk (tid&7) of rows (tid>>3) + p*ROWS_PER_PASS
   const int lchunk = tid & 7, lrow = tid >> 3;
@@ -365,7 +370,7 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
   const int frow = lane & (L::kBlk - 1), fq = lane / L::kBlk;
   for (int kt = 0; kt < nk; ++kt) {
     const int cur = kt & 1;
-    if (kt + 1 < nk) gload((k_begin + kt + 1) * BK);
+    if (kt + 1 < nk) gload((k_begin + (kt + 1) * KG) * BK);
     const unsigned char* as = smem + cur * (A_BYTES + B_BYTES);
     const unsigned char* bs = as + A_BYTES;
     typedef typename GeneralLayout<SMALL>::F F;
@@ -396,12 +401,36 @@ void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d
     __syncthreads();
   }
 
+  if constexpr (KG > 1) {                            // (the epilogues used with it need no barrier)
+    static_assert(MB == 1 && NB == 1, "one block per wavefront");
+    typename L::acc_t* part = reinterpret_cast<typename L::acc_t*>(smem_all);
+    if (group > 0) part[(group - 1) * NT + tid] = acc[0][0];
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll
+    for (int g = 1; g < KG; ++g) acc[0][0] += part[(g - 1) * NT + tid];
+  }
   TileCtx c;
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
   c.slice = t.slice; c.slices = t.slices;
   const typename Epi::Pre pre = epi.template preload<L>(c, d);
   epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
+}
+template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG = 1>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * KG * 64, WAVES_M * WAVES_N * KG > 8 ? 1 : 2)
+void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, Epi epi) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[general_lds_bytes<T, BM, BN, KG>()];
+  gemm_nt_general_tile<T, Epi, BM, BN, WAVES_M, WAVES_N, KG>(A, B, d, epi, blockIdx.x, smem);
+}
+// Two f32 contractions in tiles of 64 x 16 with four K groups in one launch: workgroups [0, n1) work on the first, the rest on the second.
+template <class Epi1, class Epi2>
+__global__ __launch_bounds__(1024)
+void gemm_nt_small_pair_kernel(const float* __restrict__ A1, const float* __restrict__ B1, GemmDims d1, Epi1 epi1, int n1,
+                               const float* __restrict__ A2, const float* __restrict__ B2, GemmDims d2, Epi2 epi2) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[general_lds_bytes<float, 64, 16, 4>()];
+  if ((int)blockIdx.x < n1) gemm_nt_general_tile<float, Epi1, 64, 16, 4, 1, 4>(A1, B1, d1, epi1, blockIdx.x, smem);
+  else gemm_nt_general_tile<float, Epi2, 64, 16, 4, 1, 4>(A2, B2, d2, epi2, (int)blockIdx.x - n1, smem);
 }
 
 // ------------------------------------------------------------------ bf16 hot kernel

@@ -1147,6 +1147,10 @@ static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, con
   else gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
+// Whether an M x N f32 contraction has so few tiles of 64 x 16 that four groups of wavefronts share one, each taking every fourth slab (dW of
+// 2048 tokens, H 64, V 1024: 47 us; with dX in the same launch 17 + 47 -> 36; 16 k tokens, V 2000 435 -> 193; 356 tokens, H 128, V 1024, both 29 -> 22).
+static bool few_small_tiles(int M, int N) { return (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kF32Slots; }
+
 template <class Epi> constexpr bool kIsForward = false;
 template <bool KEEP> constexpr bool kIsForward<EpiFwd<float, KEEP>> = true;
 template <class Tune, class Epi>
@@ -1158,9 +1162,11 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
                     !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB;                  // (how the kernel of gemm_f32.h addresses its operands)
   if constexpr (std::is_same_v<Epi, EpiDW>) {
     // dW has no per-tile partials and no padding to write, which ask for 256 rows: 64 x 16 tiles where the others would leave most CUs idle
-    // (356 tokens, H 128, V 1024: 128 workgroups instead of 32, 21.7 -> 11.2 us)
+    // (356 tokens, H 128, V 1024: 128 workgroups instead of 32, 21.7 -> 11.2 us), in four K groups where even these are few.
     if (bn == kF32SmallBN && tm * tn < kHotSlots) {
-      gemm_nt_kernel<float, Epi, 64, kF32SmallBN, 4, 1><<<launch_tiles((d.M + 63) / 64, tn), 256, 0, s>>>(A, B, d, epi);
+      const int n = launch_tiles((d.M + 63) / 64, tn);
+      if (few_small_tiles(d.M, d.N)) gemm_nt_kernel<float, Epi, 64, kF32SmallBN, 4, 1, 4><<<n, 1024, 0, s>>>(A, B, d, epi);
+      else gemm_nt_kernel<float, Epi, 64, kF32SmallBN, 4, 1><<<n, 256, 0, s>>>(A, B, d, epi);
       return;
     }
   }
@@ -1173,6 +1179,13 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
     const int64_t halves = ((int64_t)tm * tn + kF32Slots - 1) / kF32Slots;          // rounds of 256 x 64 tiles, half as long
     if (!fast && bn == kF32BN && rounds >= 10 && 100 * rounds <= 51 * halves) {
       gemm_nt_kernel<float, Epi, kBM, 256, 2, 4><<<launch_tiles(tm, (d.N + 255) / 256), 512, 0, s>>>(A, B, d, epi);
+      return;
+    }
+  }
+  if constexpr (kIsForward<Epi>) {
+    // Logits in so few tiles that each has a CU to itself: sixteen wavefronts share one instead of four.
+    if (bn == kF32SmallBN && tm * tn <= kHotSlots) {
+      gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 16, 1><<<tiles, 1024, 0, s>>>(A, B, d, epi);
       return;
     }
   }
@@ -1200,6 +1213,11 @@ static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, Gem
     gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, W, dx, ex, n1, E, XT, dw, ew);
   }
   splitk_reduce_kernel<bf16_t><<<512, 256, 0, s>>>(dx, ex, kBM, kBN, kHotStep);
+}
+
+// dX (and dW beside it) in tiles of 64 x 16 with four K groups: one round of them at most.
+static bool small_dx(int M, int N, int K) {
+  return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
 struct Ptrs {
@@ -1343,9 +1361,16 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       ProfScope ps(RL_PROF_GEMM_BWD, s);
       launch_dx_dw(dS, W, p.k_major_w ? nullptr : WT, dx, ex, XT, dw, ew, s);
     } else {
+      dx.split_slots = kF32Slots;
+      if (small_dx(dx.M, dx.N, dx.K) && small_dx(dw.M, dw.N, dw.K)) {         // both in tiles of 64 x 16, in one launch
+        ProfScope ps(RL_PROF_GEMM_BWD, s);
+        const int n1 = split_launch((dx.M + 63) / 64, (dx.N + kF32SmallBN - 1) / kF32SmallBN, kF32Slots);
+        gemm_nt_small_pair_kernel<<<n1 + launch_tiles((dw.M + 63) / 64, (dw.N + kF32SmallBN - 1) / kF32SmallBN), 1024, 0, s>>>(dS, WT, dx, ex, n1, dST, XT, dw, ew);
+        splitk_reduce_kernel<T><<<512, 256, 0, s>>>(dx, ex, 64, kF32SmallBN, 128);
+        continue;
+      }
       {
         ProfScope ps(RL_PROF_GEMM_DX, s);
-        dx.split_slots = kF32Slots;
         launch_gemm<TuneDX>(dS, WT, dx, ex, s);
         splitk_reduce_kernel<T><<<512, 256, 0, s>>>(dx, ex, kBM, f32_tile_n(dx.M, dx.N, dx.K, true), 32);
       }
