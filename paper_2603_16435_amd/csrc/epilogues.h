@@ -198,6 +198,57 @@ struct EpiFwd {
     if (c.lane < 16 && n < c.Nv) part[(int64_t)c.tile_m * ldp + n] = make_float4(m[0], s[0], u[0], 0.f);
   }
 
+  // target gather of token t, whose sampled token is y (-1: none): at most one lane of the whole grid holds row y of its column, so this branch
+  // is almost never taken
+  template <class L, int MB, int NB, bool AGPR>
+  __device__ __attribute__((always_inline)) void target(typename L::acc_t (&acc)[MB][NB], int bj, const TileCtx& c, int y, int t) const {
+    const int yrel = y >= 0 ? y - c.m0 : -1;
+    if (yrel >= 0 && yrel < MB * L::kBlk && L::owns(yrel, c.lane)) {
+      float zy = 0.f;
+      int got = -1;
+#pragma unroll
+      for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+        for (int i = 0; i < L::kRegs; ++i) {
+          const float v = acc_read<AGPR>(acc[bi][bj], i);
+          if (L::row(bi, i, c.lane) == yrel) { zy = v; got = c.m0 + L::row(bi, i, c.lane); }
+        }
+      zy_c[t] = zy * zs;
+      ycol_c[t] = got;
+    }
+  }
+
+  // Half a 256-row tile by one wavefront (logits_few_kernel): the partials of its columns leave without the merge with the other half.
+  template <class L, int MB, int NB>
+  __device__ __attribute__((always_inline)) void half_tile(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, const int (&y)[NB]) const {
+    const int vleft = V - c.m0;
+    float mx[NB], sm[NB], su[NB];
+#pragma unroll
+    for (int bj = 0; bj < NB; ++bj) {
+      target<L, MB, NB, false>(acc, bj, c, y[bj], c.n0 + L::col(bj, c.lane));
+      if (vleft < MB * L::kBlk) column<L, MB, NB, false, true>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
+      else column<L, MB, NB, false, false>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
+    }
+    merge_lanes<16, NB>(mx, sm, su);
+    merge_lanes<32, NB>(mx, sm, su);
+#pragma unroll
+    for (int bj = 0; bj < NB; ++bj) {
+      const int n = c.n0 + L::col(bj, c.lane);
+      if (c.lane < 16 && n < c.Nv) part[(int64_t)c.tile_m * ldp + n] = make_float4(mx[bj], sm[bj], su[bj], 0.f);
+    }
+  }
+  // ... and that merge, as the epilogue of a whole tile does it
+  __device__ static float4 merge_halves(float4 r, const float4& o) {
+    const float NEG = -__builtin_inff();
+    const float mm = fmaxf(r.x, o.x);
+    const float mms = (mm == NEG) ? 0.f : mm;
+    const float f1 = fast_exp<T>(r.x - mms), f2 = fast_exp<T>(o.x - mms);
+    r.y = r.y * f1 + o.y * f2;
+    r.z = r.z * f1 + o.z * f2;
+    r.x = mm;
+    return r;
+  }
+
   template <class L, int MB, int NB, int BM, int BN, int WAVES_M, int WAVES_N, bool AGPR>
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char* smem, const GemmDims& d, const Pre& pre) const {
     float4* red = reinterpret_cast<float4*>(smem);              // [WAVES_M][BN]
@@ -210,21 +261,7 @@ struct EpiFwd {
 #pragma unroll
     for (int bj = 0; bj < NB; ++bj) {
       const int n = c.n0 + L::col(bj, c.lane);
-      // target gather: at most one lane of the whole grid holds row y of column n, so this branch is almost never taken
-      const int yrel = pre.y[bj] >= 0 ? pre.y[bj] - c.m0 : -1;
-      if (yrel >= 0 && yrel < MB * L::kBlk && L::owns(yrel, c.lane)) {
-        float zy = 0.f;
-        int got = -1;
-#pragma unroll
-        for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-          for (int i = 0; i < L::kRegs; ++i) {
-            const float v = acc_read<AGPR>(acc[bi][bj], i);
-            if (L::row(bi, i, c.lane) == yrel) { zy = v; got = c.m0 + L::row(bi, i, c.lane); }
-          }
-        zy_c[d.chunk_start + n] = zy * zs;
-        ycol_c[d.chunk_start + n] = got;
-      }
+      target<L, MB, NB, AGPR>(acc, bj, c, pre.y[bj], d.chunk_start + n);
       if constexpr (kNarrow) { if constexpr (KEEP) keep_column<L, MB, NB>(acc, bj, c); continue; }
       else if (pad) column<L, MB, NB, AGPR, true>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
       else column<L, MB, NB, AGPR, false>(acc, bj, c.lane, vleft, c, mx[bj], sm[bj], su[bj]);
@@ -248,13 +285,7 @@ struct EpiFwd {
         float4 r = red[c.tid];
 #pragma unroll
         for (int w = 1; w < WAVES_M; ++w) {
-          const float4 o = red[w * BN + c.tid];
-          const float mm = fmaxf(r.x, o.x);
-          const float mms = (mm == NEG) ? 0.f : mm;
-          const float f1 = fast_exp<T>(r.x - mms), f2 = fast_exp<T>(o.x - mms);
-          r.y = r.y * f1 + o.y * f2;
-          r.z = r.z * f1 + o.z * f2;
-          r.x = mm;
+          r = merge_halves(r, red[w * BN + c.tid]);
         }
         part[(int64_t)c.tile_m * ldp + n] = r;
       }

@@ -29,6 +29,7 @@
 #include "rvq_few.h"
 #include "gemm_nt.h"
 #include "gemm_f32.h"
+#include "logits_few.h"
 
 namespace rlk {
 
@@ -572,6 +573,8 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 // along the rows, then the slices are scaled to the row's maximum, one exponential per thread, and added through LDS in order.
 // (Four slices, each scaled by the thread that adds them up: 8 us for 99 rows x 125 tiles, all latency.)
 constexpr int kCombineSlices = 16;
+// HALVES: the partials are those of half tiles (logits_few_kernel), two of which make one.
+template <bool HALVES>
 __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
                                    const int32_t* row_map, const Ctrl* ctrl, int chunk_start, int chunk_rows, const int32_t* ycol_c,
                                    float* lse_c, float* logp_c, float* lse_out, float* logp_out, float* ent_out,
@@ -589,7 +592,13 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
     for (int t0 = slice; t0 < tiles_v; t0 += 8 * kCombineSlices) {             // eight loads in flight, folded in order
       float4 q[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) if (t0 + kCombineSlices * k < tiles_v) q[k] = part[(int64_t)(t0 + kCombineSlices * k) * ldp + n];
+      for (int k = 0; k < 8; ++k) {
+        const int t = t0 + kCombineSlices * k;
+        if (t < tiles_v) {
+          if constexpr (HALVES) q[k] = EpiFwd<bf16_t>::merge_halves(part[(int64_t)(2 * t) * ldp + n], part[(int64_t)(2 * t + 1) * ldp + n]);
+          else q[k] = part[(int64_t)t * ldp + n];
+        }
+      }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         if (t0 + kCombineSlices * k >= tiles_v) break;
@@ -1299,14 +1308,28 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
     GemmDims d{};
     d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
     d.a_rows = nullptr; d.b_rows = q.row_map + c0; d.b_span = p.R; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
+    bool few = false;
     {
       ProfScope ps(RL_PROF_GEMM_FWD, s);
-      if (p.keep) launch_gemm<TuneLogits>(W, X, d, EpiFwd<T, true>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, s);
+      if constexpr (sizeof(T) == 2) {
+        // The other kernel's tiles of 256 rows are at most half as many as there are CUs: 128 rows each, see logits_few.h.  (H by the same rule as there, so
+        // that a token's bits do not depend on the batch.)
+        few = !p.keep && p.R <= kFewTokens && p.tiles_v <= kFewTilesV && !small_k<EpiFwd<T>>(p.H) &&
+              (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(X)) % 16 == 0;
+        if (few) {
+          const EpiFwd<T> e{q.ids_c, q.zy, q.part, kFewTokens, p.V, p.inv_tau, q.ycol, nullptr};
+          if (p.R <= 64) logits_few_kernel<64><<<2 * p.tiles_v, 256, 0, s>>>(W, X, d, e);
+          else logits_few_kernel<128><<<2 * p.tiles_v, 256, 0, s>>>(W, X, d, e);
+        }
+      }
+      if (few) {}
+      else if (p.keep) launch_gemm<TuneLogits>(W, X, d, EpiFwd<T, true>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, s);
       else launch_gemm<TuneLogits>(W, X, d, EpiFwd<T>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, s);
     }
     ProfScope ps(RL_PROF_COMBINE, s);
-    lse_combine_kernel<<<(p.Tc + 63) / 64, 64 * kCombineSlices, 0, s>>>(q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc, q.ycol,
-                                                        q.lse_c, q.logp_c, lse_out, logp_out, ent_out, zy_out, ycol_out);
+    auto kern = few ? lse_combine_kernel<true> : lse_combine_kernel<false>;
+    kern<<<few ? kFewTokens / 64 : (p.Tc + 63) / 64, 64 * kCombineSlices, 0, s>>>(q.part, few ? kFewTokens : p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc,
+                                                                               q.ycol, q.lse_c, q.logp_c, lse_out, logp_out, ent_out, zy_out, ycol_out);
   }
 }
 
