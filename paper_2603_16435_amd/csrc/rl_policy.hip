@@ -1787,7 +1787,7 @@ rl_status rl_logz_head_forward(const void* prompt_hidden, int32_t dtype, int64_t
   const dim3 gh((M + 15) / 16, (P + 15) / 16);
   if (H % 4 == 0 && reinterpret_cast<uintptr_t>(W1) % 16 == 0) logz_hidden_kernel<true><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
   else logz_hidden_kernel<false><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
-  logz_out_kernel<<<P, 256, 0, s>>>(g, w2, b2, M, log_z);
+  logz_out_kernel<<<P, kLogzOutThreads, 0, s>>>(g, w2, b2, M, log_z);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
