@@ -1,4 +1,4 @@
-// logits_few.h - the logits of a few tokens (bf16): up to 128 against a vocabulary whose 256-row tiles would leave half of the chip idle.
+// logits_few.h - the logits of a few tokens (bf16), up to 128.
 //
 // What bounds it is reading W once.  The hot kernel has one workgroup per 256 vocabulary rows, 125 of them for V = 32000, two slabs in
 // flight each, and multiplies 256 columns whatever the number of tokens.  Here a workgroup takes 128 rows (four wavefronts of 128 x BN / 4), and
@@ -11,7 +11,7 @@
 
 namespace rlk {
 
-constexpr int kFewTokens = 128, kFewTilesV = 128;
+constexpr int kFewTokens = 128;
 
 template <int BN>      // tokens per workgroup: 64 or 128
 __global__ __launch_bounds__(256, 1)

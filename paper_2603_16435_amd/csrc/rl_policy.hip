@@ -1312,9 +1312,11 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
     {
       ProfScope ps(RL_PROF_GEMM_FWD, s);
       if constexpr (sizeof(T) == 2) {
-        // The other kernel's tiles of 256 rows are at most half as many as there are CUs: 128 rows each, see logits_few.h.  (H by the same rule as there, so
-        // that a token's bits do not depend on the batch.)
-        few = !p.keep && p.R <= kFewTokens && p.tiles_v <= kFewTilesV && !small_k<EpiFwd<T>>(p.H) &&
+        // Tiles of 128 rows, see logits_few.h, where their rounds of 256 CUs are worth less than those of the 256-row tiles: an odd number of
+        // rounds.  100 tokens, H 2048: V 40000 (313 tiles, two rounds against one of twice their length) 57 us in the hot kernel, 67 in the other; V 80000 124 and 111,
+        // V 100000 (four against two) 142 and 142; 30 tokens at the 7B head 294 and 224, 128 tokens, H 4096, V 151936 335 and 324.  (H by the same rule
+        // as there, so that a token's bits do not depend on the batch.)
+        few = !p.keep && p.R <= kFewTokens && (p.tiles_v + 127) / 128 % 2 && !small_k<EpiFwd<T>>(p.H) &&
               (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(X)) % 16 == 0;
         if (few) {
           const EpiFwd<T> e{q.ids_c, q.zy, q.part, kFewTokens, p.V, p.inv_tau, q.ycol, nullptr};

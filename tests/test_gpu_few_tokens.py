@@ -19,8 +19,8 @@ def score(b, hidden, ids, tau, static=False):
     return binding.rl_token_logprob_tempered(hidden, b.weight, ids, mask, tau, cu)
 
 
-# hidden sizes of one slab, two, a few with and without a tail; vocabularies inside a half tile, at its border, past it, the largest of the range
-@pytest.mark.parametrize("H,V", [(64, 100), (128, 128), (384, 129), (456, 5000), (576, 32768), (1160, 257)])
+# hidden sizes of one slab, two, a few with and without a tail; vocabularies inside a half tile, at its border, past it, the largest of one round, three rounds
+@pytest.mark.parametrize("H,V", [(64, 100), (128, 128), (384, 129), (456, 5000), (576, 32768), (1160, 257), (512, 65537)])
 @pytest.mark.parametrize("T", [1, 16, 63, 64, 65, 128])
 def test_few_tokens(H, V, T):
     cfg = synth.RolloutConfig("few", 1, 1, 1, 8, H, V, "bf16", 0.5, seed=95)
