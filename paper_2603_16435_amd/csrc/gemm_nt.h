@@ -541,7 +541,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
 
   int M, N, K;
   if (!resolve_dims(d, M, N, K)) return;
-  int nk = KT ? (K + 127) / 128 * 2 : K / BK;
+  int nk = KT ? (K + BK - 1) / BK : K / BK;
   // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
   const bool by_share = d.dyn == 1;
   const int tiles_m = ((by_share ? M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
@@ -813,20 +813,22 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
         else fb[0][j] = *reinterpret_cast<const u32x4_t*>(stage0 + brow + j * 16 * kSlabBytes + slot);
       }
     }
-    // nk is even (K is a multiple of 128, or rounded up to one).  Slabs that reach past the end of an operand are among the
-    // last four (b_k_rows) or two (KT), and loads run up to two slabs ahead: the last six slabs.
+    // nk is even but with KT (K is a multiple of 128).  Slabs that reach past the end of an operand are among the
+    // last four (b_k_rows), or the last (KT), and loads run up to two slabs ahead: the last six slabs.
     const bool has_tail = KT || (BTR && (k_first + nk) * BK > d.b_k_rows);
-    const int plain = !has_tail ? nk : nk > 6 ? nk - 6 : 0;
+    const int plain = !has_tail ? nk : nk > 6 ? (nk - 6) & ~1 : 0;
     int kt = 0;
     for (; kt < plain; kt += 2) {
       slab(false, stage0, stage1, kt, pf0);
       slab(false, stage1, stage0, kt + 1, pf1);
     }
     if constexpr (KT || BTR)
-      for (; kt < nk; kt += 2) {
+      for (; kt + 1 < nk; kt += 2) {
         slab(true, stage0, stage1, kt, pf0);
         slab(true, stage1, stage0, kt + 1, pf1);
       }
+    if constexpr (KT)
+      if (kt < nk) slab(true, stage0, stage1, kt, pf0);
   }
   __builtin_amdgcn_s_waitcnt(0x0070);       // trailing re-loads must land before the epilogue reuses LDS
   __syncthreads();

@@ -1126,14 +1126,13 @@ static int split_launch(int tiles_m, int tiles_n, int slots) {
   return (int)(t > 2 * slots ? t : 2 * slots);
 }
 
-// Logits of small hidden sizes off the grid of 128 that take the general kernel: the hot one rounds K up to the grid, the general one
-// to 64, and with few slabs the shorter prologue and epilogue of its smaller wavefronts count for more than the main loop.  V 50257,
-// 16 k tokens, forward: H 136 724 us in the hot kernel, 584 in the general one; 200 747 / 682; 320 855 / 780; 328 878 / 898; 392 and 448,
-// where it also does a slab less, 995 / 981 and 983 / 967; 520 1119 / 1184.  The same holds from 96 tokens on (H 136 46.5 / 43.7, 328 49.9 /
-// 49.7).  The dS epilogue, whose tiles the general kernel writes in pieces of 8 bytes, tips over earlier (with the backward: H 192
+// Logits of small hidden sizes off the grid of 128 that take the general kernel: with few slabs the shorter prologue and epilogue of its
+// smaller wavefronts count for more than the main loop.  V 50257, 16 k tokens, forward: H 136 724 us in the hot kernel, 584 in the general one;
+// 200 747 / 682; 320 855 / 780; 328 878 / 898; 392 969 / 966 and 440 981 / 983, with 200 tokens 24 / 27; 520 1119 / 1184.  The same holds from 96 tokens on
+// (H 136 46.5 / 43.7, 328 49.9 / 49.7).  The dS epilogue, whose tiles the general kernel writes in pieces of 8 bytes, tips over earlier (with the backward: H 192
 // 2502 / 2397, 200 2510 / 2621).  (By H alone: a token's bits must not depend on the batch.)
 template <class Epi> constexpr bool small_k(int) { return false; }
-template <> constexpr bool small_k<EpiFwd<bf16_t>>(int K) { return K % 128 && (K <= 320 || (K <= 448 && K % 128 <= 64)); }
+template <> constexpr bool small_k<EpiFwd<bf16_t>>(int K) { return K % 128 && K <= 320; }
 template <> constexpr bool small_k<EpiDS<bf16_t>>(int K) { return K % 128 && K <= 192; }
 
 template <class Tune, class Epi>
