@@ -570,7 +570,7 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 // ------------------------------------------------------------------ forward combine
 // Fold the per-vocab-tile partials (max, sumexp) of a chunk into lse, logp.  A workgroup handles 64
 // compact rows x 16 slices of the tile range: one online (rescaling) pass per thread, coalesced
-// along the rows, then the slices are scaled to the row's maximum, one exponential per thread, and added through LDS in order.
+// along the rows, sums in f64, then the slices are scaled to the row's maximum, one exponential per thread, and added through LDS in order.
 // (Four slices, each scaled by the thread that adds them up: 8 us for 99 rows x 125 tiles, all latency.)
 constexpr int kCombineSlices = 16;
 // HALVES: the partials are those of half tiles (logits_few_kernel), two of which make one.
@@ -587,30 +587,32 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
   const int col = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + col;
   const float NEG = -__builtin_inff();
-  float m = NEG, s = 0.f, u = 0.f;
+  float m = NEG;
+  double s = 0.0, u = 0.0;
   if (n < left) {
     for (int t0 = slice; t0 < tiles_v; t0 += 8 * kCombineSlices) {             // eight loads in flight, folded in order
       float4 q[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const int t = t0 + kCombineSlices * k;
+        q[k] = make_float4(NEG, 0.f, 0.f, 0.f);
         if (t < tiles_v) {
           if constexpr (HALVES) q[k] = EpiFwd<bf16_t>::merge_halves(part[(int64_t)(2 * t) * ldp + n], part[(int64_t)(2 * t + 1) * ldp + n]);
           else q[k] = part[(int64_t)t * ldp + n];
         }
       }
+      float mm = m;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) mm = fmaxf(mm, q[k].x);
+      if (mm == NEG) continue;
+      const double f0 = (double)expf(m - mm);
+      s *= f0; u *= f0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        if (t0 + kCombineSlices * k >= tiles_v) break;
-        const float4 v = q[k];
-        const float mm = fmaxf(m, v.x);
-        if (mm != NEG) {
-          const float f1 = expf(m - mm), f2 = expf(v.x - mm);
-          s = s * f1 + v.y * f2;
-          u = u * f1 + v.z * f2;
-        }
-        m = mm;
+        const double f = (double)expf(q[k].x - mm);
+        s += (double)q[k].y * f; u += (double)q[k].z * f;
       }
+      m = mm;
     }
   }
   sm[slice][col] = m;
@@ -620,7 +622,7 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
   for (int k = 1; k < kCombineSlices; ++k) M = fmaxf(M, sm[k][col]);
   {
     const double f = m != NEG ? exp((double)(m - M)) : 0.0;
-    ss[slice][col] = (double)s * f; su[slice][col] = (double)u * f;
+    ss[slice][col] = s * f; su[slice][col] = u * f;
   }
   __syncthreads();
   if (slice == 0 && n < left) {
