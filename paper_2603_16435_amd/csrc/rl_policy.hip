@@ -40,7 +40,7 @@ constexpr int kBM = 256, kBN = 256;
 // kernel), or 256 x 16 where the large ones would leave CUs without work.  MFMA-bound: 128-141 TFLOP/s, 102-109 in the general kernel, whose
 // loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K and the logits
 // recomputed: 5.25 ms, 6.2 in the general kernel; with its 256 x 256 tiles 17.9 (27 dX
-// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 73 us against 557 (with 32-wide narrow tiles it took 7 % longer).
+// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us, 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
@@ -1790,7 +1790,7 @@ rl_status rl_logz_head_forward(const void* prompt_hidden, int32_t dtype, int64_t
   const dim3 gh((M + 15) / 16, (P + 15) / 16);
   if (H % 4 == 0 && reinterpret_cast<uintptr_t>(W1) % 16 == 0) logz_hidden_kernel<true><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
   else logz_hidden_kernel<false><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
-  logz_out_kernel<<<P, kLogzOutThreads, 0, s>>>(g, w2, b2, M, log_z);
+  logz_out_kernel<<<P, M > kLogzOutThreads ? kLogzOutThreads : 256, 0, s>>>(g, w2, b2, M, log_z);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
