@@ -3,7 +3,7 @@
  *
  * What it computes (problem statement of the benchmark contract; the mounted paper has
  * no passage on it): for every response token t of a group of sampled responses,
- *     z_t   = W x_t                      (never stored)
+ *     z_t   = W x_t                      (never more than a chunk of them stored)
  *     lse_t = log sum_v exp z_t[v],      logp_t = z_t[y_t] - lse_t
  * then the group-relative advantage A_i = (r_i - mean_g)/(std_g + adv_eps) over the G
  * rollouts of a prompt, then one of two objectives
@@ -14,8 +14,8 @@
  *            delta_i = logZ_g(i) + (1/|y_i|) sum_t (logp_t - ref_t) - beta A_i,
  *            w_i = clip(exp(sum_t (logp_t - old_t)), 1-e, 1+e) held constant
  * and the backward pass  c_t = dloss/dlogp_t,  dS[t,v] = c_t (1[v=y_t] - softmax(z_t)[v]),
- * dX = dS W, dW = dS^T X.  T x V is never stored: either the logits are recomputed tile by
- * tile and a chunk of dS in the input precision is staged between the contractions, or the
+ * dX = dS W, dW = dS^T X.  At most a chunk of rows is staged: either the logits are recomputed tile by
+ * tile (those of a batch of one chunk may be kept) and a chunk of dS in the input precision is staged between the contractions, or the
  * forward keeps a chunk's unnormalised probabilities and the backward is contracted from
  * those (rl_backward_mode).  Optionally the policy is softmax(W x_t / temperature).
  *
@@ -81,7 +81,7 @@ typedef enum rl_dtype { RL_F32 = 0, RL_BF16 = 1 } rl_dtype;
  *  RL_BWD_AUTO       RL_BWD_STASH when its conditions hold, else RL_BWD_RECOMPUTE, where a bf16 batch of one chunk of at most
  *                    16384 rows with H >= 456 keeps its logits, in f32, between forward and backward (same results; the workspace
  *                    holds 4 bytes more per row and vocabulary entry).
- * Either way at most chunk_rows x V values are held at a time, never T x V. */
+ * Either way at most chunk_rows x V values are held at a time (and as many kept logits), however large T is. */
 typedef enum rl_aggregation { RL_AGG_SEQUENCE = 0, RL_AGG_TOKEN = 1 } rl_aggregation;
 typedef enum rl_ratio_level { RL_RATIO_TOKEN = 0, RL_RATIO_SEQUENCE = 1 } rl_ratio_level;
 typedef enum rl_weight_norm { RL_WNORM_SUM = 0, RL_WNORM_MEAN = 1 } rl_weight_norm;

@@ -25,12 +25,12 @@ extern "C" {
 enum { RL_PROF_PREP = 0,       /* counts, scan, compaction, output zero-fill            */
        RL_PROF_GEMM_FWD = 1,   /* forward logits contraction + online partial softmax   */
        RL_PROF_COMBINE = 2,    /* partials -> lse, logp                                 */
-       RL_PROF_LOSS = 3,       /* advantage, per-sequence loss, final reduce            */
+       RL_PROF_LOSS = 3,       /* per-sequence loss, final reduce; f32 batches of one chunk: W^T, X^T and zeroing too */
        RL_PROF_TRANSPOSE = 4,  /* W^T, X^T chunks, zeroing masked dX rows               */
-       RL_PROF_GEMM_DS = 5,    /* recomputed logits -> dS                               */
+       RL_PROF_GEMM_DS = 5,    /* recomputed or kept logits -> dS                       */
        RL_PROF_GEMM_DX = 6,    /* dX = dS W (f32 inputs)                                */
        RL_PROF_GEMM_DW = 7,    /* dW += dS^T X (f32 inputs)                             */
-       RL_PROF_GEMM_BWD = 8,   /* bf16: dX and dW of a chunk in one launch, either backward mode */
+       RL_PROF_GEMM_BWD = 8,   /* dX and dW of a chunk in one launch (bf16; f32 where both are small) */
        RL_PROF_CLASSES = 9 };
 typedef struct rl_profile {     /* host struct */
   double  ms[RL_PROF_CLASSES];
