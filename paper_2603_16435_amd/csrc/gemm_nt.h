@@ -649,7 +649,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // wavefront 1 one eighth of the B panel rows, PFD slabs ahead, one 4-byte load per 128-byte line:
   // between them the block's workgroups cover every line once.  Wavefronts 2 and 3 execute the same
   // instruction on one fixed line (no divergent control flow around the accumulators).  The load goes out behind the slab's own loads
-  // and is the one that the wait at the slab's end leaves in flight (loads come back in order): waited for there, a line that had to come from
+  // and is the one that the wait at the slab's end leaves in flight (loads come back in order; prefetch() says what holds it in its place): waited for there, a line that had to come from
   // memory held the slab up, which is what the prefetch is to avoid (67 k tokens at the 7B head: forward 56.4 -> 54.8 ms, dX + dW 105.3 ->
   // 104.2; 36 k tokens, H 2048, V 32000: 3.81 -> 3.62, 7.25 -> 6.77).
   const unsigned char* pf_ptr;
@@ -690,7 +690,11 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     if (PFD > 0) {
       pf_sink ^= slot;                                   // fetched two slabs ago: long since back
       const int k = kt + PFD < pf_last ? kt + PFD : pf_last;
-      slot = *reinterpret_cast<const unsigned*>(pf_ptr + (int64_t)k * pf_stride + (pf_atr ? a_slab(k) * 2 : 0));
+      typedef const __attribute__((address_space(1))) unsigned* line_ptr;
+      line_ptr p = (line_ptr)(pf_ptr + (int64_t)k * pf_stride + (pf_atr ? a_slab(k) * 2 : 0));
+      asm volatile("" : "+v"(p));                        // not ahead of the slab's loads, volatile assembly like this ...
+      slot = *p;
+      asm volatile("" ::: "memory");                     // ... and not past the wait behind this, for all that is known of where p points
     }
   };
 

@@ -1,0 +1,32 @@
+"""The wait at the end of a slab of the bf16 hot kernel leaves one load in flight and relies on that being the L2 prefetch.  The source holds the
+prefetch behind the slab's loads and ahead of the wait; here the library as it is built: a load into a register (the slab's go to LDS) is the
+last vector memory operation before each such wait."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2603_16435_amd import binding
+
+LLVM = "/opt/rocm/llvm/bin"
+TOOLS = [os.path.join(LLVM, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-objdump")]
+
+
+@pytest.mark.skipif(not os.path.exists(binding.LIB_PATH) or not all(map(os.path.exists, TOOLS)), reason="library or LLVM tools not there")
+def test_the_prefetch_is_the_last_load_before_each_wait_that_leaves_one_in_flight(tmp_path):
+    copy, unbundle, dump = TOOLS
+    fat, dev = str(tmp_path / "fat"), str(tmp_path / "dev.o")
+    subprocess.run([copy, f"--dump-section=.hip_fatbin={fat}", binding.LIB_PATH, os.devnull], check=True)
+    subprocess.run([unbundle, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}", f"--output={dev}"], check=True)
+    text = subprocess.run([dump, "-d", "--no-show-raw-insn", "--no-leading-addr", dev], check=True, capture_output=True, text=True).stdout
+    waits = 0
+    last = ""                                            # last vector memory operation
+    ins = [line.split("//")[0].strip() for line in text.splitlines()]
+    for this, following in zip(ins, ins[1:]):
+        if re.match(r"(global|buffer|flat|scratch)_", this):
+            last = this
+        elif this == "s_waitcnt vmcnt(1) lgkmcnt(0)" and following.startswith("s_barrier"):
+            waits += 1
+            assert last.startswith("global_load_dword "), last
+    assert waits >= 2 * 8                                # two slabs per turn of the loop, eight kernels at the least
