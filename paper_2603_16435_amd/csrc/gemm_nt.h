@@ -70,6 +70,7 @@ struct GemmDims {
   int group_m;            // tile-order parameter: M-tiles per band
   int split_slots;        // > 0: the contraction may be cut along K (see split_k); workgroups the chip runs at a time
   int b_k_rows;           // hot kernel, B operand given K-major: its rows (K is their number rounded up, with zeros in the other operand)
+  int min_rows, max_rows; // the launch is for chunks of more than min_rows / at most max_rows rows only (0: any); a twin does the others
   int fill_tiles;         // tiles of another contraction over K = M in the same launch, which fill the CUs this one leaves
 };
 
@@ -97,6 +98,7 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
   } else {
     left = *d.n_real - d.chunk_start;
   }
+  if ((d.min_rows && left <= d.min_rows) || (d.max_rows && left > d.max_rows)) return false;
   if (left <= 0) {
     if (d.dyn == 3 && d.zero_if_empty) K = 0; else return false;
   } else if (d.dyn == 1) M = left < M ? left : M;
@@ -483,9 +485,9 @@ __device__ __attribute__((always_inline)) inline void mfma16(floatx4& acc, const
 }
 __device__ __attribute__((always_inline)) inline void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
-// PFD: L2 prefetch distance in slabs (0 = none).  VMG / VMO: inside a phase of 32 MFMAs the slab loads
-// are issued after MFMA number VMO, VMO + VMG, VMO + 2 VMG, ...  LDA / LDB: how many of a slab's 16 loads go
-// into the phase after the barrier and into the first phase of the next slab (the rest into its second phase);
+// Tune::kPfd: L2 prefetch distance in slabs (0 = none).  kPfWait: the prefetch goes out ahead of the slab's loads and is waited for with them.
+// kVmg / kVmo: inside a phase of 32 MFMAs the slab loads are issued after MFMA number kVmo, kVmo + kVmg, ...  kLdA / kLdB: how many of
+// a slab's 16 loads go into the phase after the barrier and into the first phase of the next slab (the rest into its second phase);
 // the earlier they go, the longer they have to land before the next barrier.
 constexpr int kHotStageBytes = (256 + 256) * kSlabBytes;      // one LDS stage of the hot kernel: a slab of A and of B
 
@@ -522,9 +524,10 @@ __device__ __attribute__((always_inline)) inline u32x2_t lds_read_tr16(const uns
 // loop body that works them out per lane (`tail`), so that the plain loop needs no vector operation for its load addresses.  (With BTR
 // it has others: the 16-bit offset of the transposing reads does not reach B's part of the second stage, 32 address adds per two slabs.)
 __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
-template <class Epi, int PFD, int VMG, int VMO, bool ATR = false, int LDA = 6, int LDB = 5, bool BTR = false, bool KT = false, bool FAR = false>
+template <class Epi, class Tune, bool ATR = false, bool BTR = false, bool KT = false, bool FAR = false>
 __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d,
                                                                         const Epi& epi, int pid, unsigned char* stage0, unsigned char* stage1) {
+  constexpr int PFD = Tune::kPfd, VMG = Tune::kVmg, VMO = Tune::kVmo, LDA = Tune::kLdA, LDB = Tune::kLdB;
   constexpr int BM = 256, BN = 256, BK = 64, WAVES_M = 2, WAVES_N = 2;
   constexpr int WM = 128, WN = 128, MB = 8, NB = 8;             // 8 x 8 blocks of 16 x 16 per wavefront
   constexpr int DSG = 2;                                        // one fragment read per DSG MFMAs
@@ -650,8 +653,9 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // between them the block's workgroups cover every line once.  Wavefronts 2 and 3 execute the same
   // instruction on one fixed line (no divergent control flow around the accumulators).  The load goes out behind the slab's own loads
   // and is the one that the wait at the slab's end leaves in flight (loads come back in order; prefetch() says what holds it in its place): waited for there, a line that had to come from
-  // memory held the slab up, which is what the prefetch is to avoid (67 k tokens at the 7B head: forward 56.4 -> 54.8 ms, dX + dW 105.3 ->
-  // 104.2; 36 k tokens, H 2048, V 32000: 3.81 -> 3.62, 7.25 -> 6.77).
+  // memory held the slab up, which is what the prefetch is to avoid (67 k tokens at the 7B head: forward 56.4 -> 54.8 ms; 36 k tokens, H 2048,
+  // V 32000: 3.81 -> 3.62, dX + dW 7.25 -> 6.77).  But the wait also keeps the workgroups of a block in step, so that a line is fetched once
+  // for all of them: where a launch has very many rounds of tiles it stays (kPfWait).
   const unsigned char* pf_ptr;
   int pf_stride;
   const bool pf_atr = ATR && wave == 0;
@@ -788,11 +792,12 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // 0..LDA-1 of slab kt+1 are in flight towards `nxt`.  The last phase runs from registers after the
   // workgroup barrier, so it covers the first fragment reads of slab kt+1 and the first loads of kt+2.
   auto slab = [&](bool tail, unsigned char* cur, unsigned char* nxt, int kt, unsigned& pfslot) __attribute__((always_inline)) {
+    if constexpr (Tune::kPfWait) prefetch(pfslot, kt);
     phase(tail, 0, 0, 0, 4, cur, 0, kof(kt + 1), nxt, LDA, LDB);
     phase(tail, 0, 1, 1, 12, cur, 1, kof(kt + 1), nxt, LDA + LDB, LDC);
-    prefetch(pfslot, kt);
+    if constexpr (!Tune::kPfWait) prefetch(pfslot, kt);
     phase(tail, 1, 0, 0, 4, cur, 1, 0, nxt, 0, 0);
-    __builtin_amdgcn_s_waitcnt(PFD > 0 ? 0x0071 : 0x0070);     // vmcnt(0), or 1: all but the prefetch; lgkmcnt(0): own loads have landed, own fragment reads are done
+    __builtin_amdgcn_s_waitcnt(PFD > 0 && !Tune::kPfWait ? 0x0071 : 0x0070);     // vmcnt(0), or 1: all but the prefetch; lgkmcnt(0): own loads have landed, own fragment reads are done
     __syncthreads();                        // ... and so have everybody else's: `nxt` is complete, `cur` is free
     phase(tail, 1, 1, 1, 12, nxt, 0, kof(kt + 2), cur, 0, LDA);
   };
@@ -847,7 +852,7 @@ __global__ __launch_bounds__(256)
 void gemm_nt_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, GemmDims d, Epi epi) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage0[kHotStageBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char stage1[kHotStageBytes];
-  gemm_nt_bf16_tile<Epi, Tune::kPfd, Tune::kVmg, Tune::kVmo, false, Tune::kLdA, Tune::kLdB, false, KT, FAR>(A, B, d, epi, blockIdx.x, stage0, stage1);
+  gemm_nt_bf16_tile<Epi, Tune, false, false, KT, FAR>(A, B, d, epi, blockIdx.x, stage0, stage1);
 }
 
 // Two independent contractions in one launch: workgroups [0, n1) work on the first, the rest on the
@@ -861,9 +866,9 @@ void gemm_nt_bf16_pair_kernel(const bf16_t* __restrict__ A1, const bf16_t* __res
   __shared__ __attribute__((aligned(1024))) unsigned char stage0[kHotStageBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char stage1[kHotStageBytes];
   if ((int)blockIdx.x < n1)
-    gemm_nt_bf16_tile<Epi1, Tune1::kPfd, Tune1::kVmg, Tune1::kVmo, false, Tune1::kLdA, Tune1::kLdB, BTR1>(A1, B1, d1, epi1, blockIdx.x, stage0, stage1);
+    gemm_nt_bf16_tile<Epi1, Tune1, false, BTR1>(A1, B1, d1, epi1, blockIdx.x, stage0, stage1);
   else
-    gemm_nt_bf16_tile<Epi2, Tune2::kPfd, Tune2::kVmg, Tune2::kVmo, true, Tune2::kLdA, Tune2::kLdB>(A2, B2, d2, epi2, (int)blockIdx.x - n1, stage0, stage1);
+    gemm_nt_bf16_tile<Epi2, Tune2, true>(A2, B2, d2, epi2, (int)blockIdx.x - n1, stage0, stage1);
 }
 
 }  // namespace rlk

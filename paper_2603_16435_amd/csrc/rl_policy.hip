@@ -63,15 +63,34 @@ constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup pe
 // tile-order band height (M-tiles per band), L2 prefetch distance in slabs (0 = off), where in a
 // phase of 32 MFMAs the slab loads are issued (after MFMA kVmo, kVmo + kVmg, ...) and how many of a slab's 16 loads
 // go into the phase after the barrier / the next phase (kLdA / kLdB; the rest into the phase after that).
-// Measured on the 7B shape: dX, dW and the logits want the prefetch two slabs ahead, three is a little worse (dX without it: 105.7 ms of dX + dW
-// instead of 104.2; 4741 tokens, H 1160, V 50257 913 us instead of 848), dW is best with one M-tile per band (its A panel, the stored
+// Measured on the 7B shape: dX, dW and the logits want the prefetch two slabs ahead, three is a little worse (dX without it: 4741 tokens, H 1160,
+// V 50257 913 us instead of 848), dW is best with one M-tile per band (its A panel, the stored
 // probabilities, then leaves memory once for all 14 N-tiles).
 // dX, whose operands both stream from memory, waits 17 % of its loop time for its slab loads with the 6/5/5 placement and
 // 5 % with 8/8/0 (all loads at least two phases before the barrier); at the power limit that is worth 0.8 % of dX+dW.
 // The other two gain nothing from 8/8/0.
-struct TuneLogits { static constexpr int kBand = 8, kPfd = 2, kVmg = 5, kVmo = 3, kLdA = 6, kLdB = 5; };
-struct TuneDX     { static constexpr int kBand = 8, kPfd = 2, kVmg = 4, kVmo = 1, kLdA = 8, kLdB = 8; };
-struct TuneDW     { static constexpr int kBand = 1, kPfd = 2, kVmg = 4, kVmo = 1, kLdA = 6, kLdB = 5; };
+// dX and dW in very many rounds of the chip (step_prefetch): dX without prefetch, dW's waited for.  Otherwise the workgroups drift apart over
+// the launch and fetch lines again that they would have found in L2: 38.5 k tokens at the 7B head fetch 233 GB instead of 174, which takes
+// fewer cycles (95 M against 102 M) at a lower clock: at the power limit (1.60 GHz against 1.75) dX + dW take 62.4 ms instead of 59.9, and
+// the 286 k tokens of 16 prompts 438 instead of 433 (on another box 459 and 439).
+struct TuneLogits { static constexpr int kBand = 8, kPfd = 2, kVmg = 5, kVmo = 3, kLdA = 6, kLdB = 5; static constexpr bool kPfWait = false; };
+struct TuneDX     { static constexpr int kBand = 8, kPfd = 2, kVmg = 4, kVmo = 1, kLdA = 8, kLdB = 8; static constexpr bool kPfWait = false; };
+struct TuneDW     { static constexpr int kBand = 1, kPfd = 2, kVmg = 4, kVmo = 1, kLdA = 6, kLdB = 5; static constexpr bool kPfWait = false; };
+struct TuneDXStep : TuneDX { static constexpr int kPfd = 0; };
+struct TuneDWStep : TuneDW { static constexpr bool kPfWait = true; };
+
+// dW tiles in a row (tn) and in all, of a chunk of at most M rows: more than 24 rounds, in rows that are not of whole blocks of four tiles (the
+// lines of a panel are shared out among four), or longer than 20.  ms of dX + dW, prefetches not waited for / as above, 36, 38.5 and
+// 40.5 k tokens:
+//   V 152064, 128256 from 24 tiles on       10 tiles 39.2 42.2 44.9 / 39.8 42.5 44.6      11 45.2 48.7 50.9 / 44.8 47.5 50.2      12 47.0 50.5 54.0 / 48.2 50.1 53.9
+//   13 54.1 57.2 60.3 / 51.6 55.5 57.8      14 55.8 60.3 63.4 / 55.9 58.6 61.7            15 62.7 65.9 70.7 / 60.9 63.4 68.6      16 62.1 66.9 69.2 / 63.5 68.4 70.6
+//   18 73.7 78.0 82.6 / 71.9 75.7 79.9      20 78.5 84.6 89.3 / 80.0 84.9 92.2            24 83.9 88.8 93.0 / 82.1 86.3 90.4      28 98.4 107 112 / 98.1 103 109
+//   14 tiles in 21, 14, 7 rounds (V 100000, 65536, 32000): 37.2 40.0 41.0 / 37.2 39.4 40.6, 24.0 26.6 27.7 / 24.5 26.3 27.5, 11.8 13.2 13.6 / 12.3 13.6 13.9
+//   8 tiles in 18 rounds, 16 in 16 (V 152064, 65536): 31.1 32.9 34.1 / 31.3 33.3 34.8, 26.8 29.2 29.7 / 27.8 29.9 31.0
+// A chunk with fewer tokens, which only the device knows, does not drift far enough: 14 tiles, 28 k, 33 k, 34 k tokens 41.3 50.6 53.9 / 42.2 51.7 52.8.  So
+// such a launch goes out in both forms, and the one that the chunk is not for returns at once (20 us, of some 50 ms).
+static bool step_prefetch(int M, int tn, int64_t tiles) { return M > kKMajorRows && tiles > 24 * kHotSlots && (tn % 4 || tn > 20); }
+constexpr int kStepRows = 33280;
 
 struct Ctrl {            // device control block at the head of the workspace
   int n_real;
@@ -1210,14 +1229,20 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
 // dX = diag(f) dS W  (A = dS or E' [Tc][Vp], B = W^T [H][Vp]) and dW (+)= dS^T (diag(f) X)  (A = the same array read as a K-major
 // operand, B = X^T [H][Tc]) of a bf16 chunk in one launch: dX alone has few (long) tiles, whose last round would leave CUs
 // idle; the dW tiles fill them.  dX is cut along K where its tiles are fewer still.
-static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, const GemmDims& dw,
+static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, GemmDims dw,
                          const EpiDW& ew, hipStream_t s) {
   const int tn = (dx.N + kBN - 1) / kBN;
   dx.split_slots = kHotSlots; dx.fill_tiles = (dw.M + kBM - 1) / kBM * tn;
   const int n1 = split_launch((dx.M + kBM - 1) / kBM, tn, kHotSlots);
   const int n2 = launch_tiles((dw.M + kBM - 1) / kBM, tn);
   if (WT) {
+    const bool both = step_prefetch(dx.M, tn, dx.fill_tiles);
+    dx.max_rows = dw.max_rows = both ? kStepRows : 0;
     gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
+    dx.max_rows = dw.max_rows = 0;
+    dx.min_rows = dw.min_rows = kStepRows;
+    if (both) gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDXStep, EpiDW, TuneDWStep, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
+    dx.min_rows = 0;
   } else {
     dx.ldb = dx.N; dx.b_tiled = 0; dx.b_k_rows = dw.M;
     gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, W, dx, ex, n1, E, XT, dw, ew);
