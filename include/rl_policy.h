@@ -79,8 +79,8 @@ typedef enum rl_dtype { RL_F32 = 0, RL_BF16 = 1 } rl_dtype;
  *                    call comes back NaN (its gradient rows are not numbers): the caller re-runs the batch with
  *                    RL_BWD_RECOMPUTE, which has no such limit.
  *  RL_BWD_AUTO       RL_BWD_STASH when its conditions hold, else RL_BWD_RECOMPUTE, where a bf16 batch of one chunk of at most
- *                    16384 rows with H >= 456 keeps its logits, in f32, between forward and backward (same results; the workspace
- *                    holds 4 bytes more per row and vocabulary entry).
+ *                    16384 rows with H >= 456 keeps its logits, in f32, between forward and backward if the workspace has room
+ *                    for them, 4 bytes per row and vocabulary entry, and recomputes them if not (same results).
  * Either way at most chunk_rows x V values are held at a time (and as many kept logits), however large T is. */
 typedef enum rl_aggregation { RL_AGG_SEQUENCE = 0, RL_AGG_TOKEN = 1 } rl_aggregation;
 typedef enum rl_ratio_level { RL_RATIO_TOKEN = 0, RL_RATIO_SEQUENCE = 1 } rl_ratio_level;
@@ -166,7 +166,10 @@ typedef struct rl_outputs {     /* NULL = not wanted, except loss               
  * R, H, V, B, P, dtype, the alignment of hidden / weight (a size for aligned or NULL pointers serves any), and params->chunk_rows,
  * backward_mode, max_seq_len; params may be NULL = defaults; want_backward
  * = 0 sizes it for rl_token_logprob / loss-only calls).  The workspace must be 256-byte
- * aligned.  Its contents on entry are irrelevant and on return unspecified. */
+ * aligned.  Its contents on entry are irrelevant and on return unspecified.
+ * With room for kept logits (RL_BWD_AUTO) the size is not monotone in the rows: at H 3584, V 152064 12000 rows ask for 12.4 GB,
+ * 16384 for 16.4 and 16385 for 6.6.  The room is optional: a workspace sized for a larger batch, or for RL_BWD_RECOMPUTE,
+ * serves RL_BWD_AUTO as well (the single-pass backward excepted, which has a size of its own). */
 rl_status rl_workspace_bytes(const rl_batch* batch, const rl_params* params,
                              int32_t want_backward, size_t* bytes);
 

@@ -272,7 +272,14 @@ class PolicyLossPlan:
             i32 = dict(dtype=torch.int32, device=device)
             self.res.row_map, self.res.group_count = torch.empty(R, **i32), torch.empty(P, **i32)
             self.res.target_col, self.res.target_logit = torch.empty(R, **i32), torch.empty(R, **f32)
-        self.ws = _workspace(rl_workspace_bytes(batch, params, backward), device)
+        try:
+            self.ws = _workspace(rl_workspace_bytes(batch, params, backward), device)
+        except torch.OutOfMemoryError:           # the room for kept logits is optional
+            if params.backward_mode != BACKWARD_MODES["auto"]:
+                raise
+            small = rl_params.from_buffer_copy(params)
+            small.backward_mode = BACKWARD_MODES["recompute"]
+            self.ws = _workspace(rl_workspace_bytes(batch, small, backward), device)
         o = rl_outputs()
         r = self.res
         o.loss, o.seq_loss, o.logprob, o.lse = r.loss.data_ptr(), r.seq_loss.data_ptr(), r.logprob.data_ptr(), r.lse.data_ptr()

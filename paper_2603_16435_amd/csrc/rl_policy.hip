@@ -1029,7 +1029,7 @@ struct Plan {
   float inv_tau;         // 1 / temperature
   size_t off_ctrl, off_seq_len, off_cstart, off_row_map, off_ids_c, off_cpos, off_zy, off_lse_c, off_logp_c,
       off_c_c, off_adv, off_seq_loss, off_gterm, off_part, off_wt, off_xt, off_ds, off_dst, off_split, off_kept,
-      off_desc, off_ref, off_zsum, off_scale, off_ycol, total;
+      off_desc, off_ref, off_zsum, off_scale, off_ycol, least, total;       // total: with room for kept logits; least: what the calls accept
 };
 
 static inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1122,7 +1122,6 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
       p.off_split = take(split_bytes(tc, b->H, p.Vp, f32_tile_n(tc, b->H, p.Vp, true), 32, kF32Slots));
     } else {
       p.off_split = take(split_bytes(tc, b->H, p.Vp, kBN, kHotStep, kHotSlots));
-      if (keep_room) p.off_kept = take(4 * (size_t)tc * (size_t)p.Vp);      // f32 keeps them in dS^T's place
     }
   }
   p.off_desc = p.off_ref = p.off_zsum = p.off_scale = 0;
@@ -1130,6 +1129,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
     p.off_desc = take(sizeof(ChunkDesc) * (size_t)p.n_desc);
     p.off_ref = take(4 * Rp); p.off_zsum = take(4 * Rp); p.off_scale = take(4 * (size_t)tc);
   }
+  p.least = o;
+  if (keep_room && b->dtype == RL_BF16) p.off_kept = take(4 * (size_t)tc * (size_t)p.Vp);      // last: without room for them they are recomputed
   p.total = o;
   return RL_OK;
 }
@@ -1531,8 +1532,9 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
   run_finalize(loss_job(b, prm, objective, p, q, out, nullptr), s);
 }
 
-static rl_status check_ws(void* ws, size_t bytes, const Plan& p) {
-  if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) || bytes < p.total) return RL_ERR_WORKSPACE;
+static rl_status check_ws(void* ws, size_t bytes, Plan& p) {
+  if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) || bytes < p.least) return RL_ERR_WORKSPACE;
+  if (bytes < p.total) p.keep = false;
   return RL_OK;
 }
 
