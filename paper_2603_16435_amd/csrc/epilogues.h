@@ -43,9 +43,13 @@ __device__ __attribute__((always_inline)) inline void lane_pair(float v, float& 
 //      u feeds the entropy H_t = lse_t - u/s of the full distribution at no extra pass.
 //      z is the tempered logit zs * (W x_t), zs = 1 / temperature; everything written is in tempered units.
 //      KEEP: the raw logits W x_t leave as well, in f32, for a backward that forms dS from them (kept_ds_kernel); in the hot kernel in the
-//      order of the accumulators (kept_index: 1 KiB per store), else vocabulary-major like dS^T.
-__device__ inline int64_t kept_index(int tile_m, int tile_n, int tiles_n, int wave, int bi, int bj, int lane) {    // of a lane's floatx4
-  return (((int64_t)(tile_m * tiles_n + tile_n) * 4 + wave) * 64 + bj * 8 + bi) * 64 + lane;
+//      order of the accumulators (1 KiB per store), else vocabulary-major like dS^T.
+// Where a lane's floatx4 of those goes in the hot kernel.  The tiles of the first 256 tokens come first, then those of the next, and
+// blocks of 16 columns without a token are neither written nor read: a batch of many rows and few tokens touches little memory, all of it in one piece.
+// (With the token tiles innermost and all columns written: 16 and 128 tokens in 2000 rows, H 512, V 152064, the whole call 411 and 420 us, where
+// recomputed logits take 354 and 360; like this 272 and 304.  4741 tokens, H 1160, V 50257: dS out of kept logits 261 us, like this 245; 11.5 k at the 7B head 1933 and 1833.)
+__device__ inline int64_t kept_index(int tile_m, int tile_n, int tiles_m, int wave, int bi, int bj, int lane) {
+  return (((int64_t)(tile_n * tiles_m + tile_m) * 4 + wave) * 64 + bj * 8 + bi) * 64 + lane;
 }
 template <class T, bool KEEP = false>
 struct EpiFwd {
@@ -93,11 +97,11 @@ struct EpiFwd {
         z[bi * L::kRegs + i] = v;
         mx = fmaxf(mx, (!PAD || L::row(bi, i, lane) < vleft) ? v : NEG);
       }
-    if constexpr (KEEP && AGPR) {
+    if (KEEP && AGPR && c.n0 + bj * 16 < c.Nv) {
 #pragma unroll
       for (int bi = 0; bi < MB; ++bi) {
         floatx4 q; q[0] = z[bi * 4]; q[1] = z[bi * 4 + 1]; q[2] = z[bi * 4 + 2]; q[3] = z[bi * 4 + 3];
-        __builtin_nontemporal_store(q, reinterpret_cast<floatx4*>(kept) + kept_index(c.tile_m, c.tile_n, ldp / 256, c.wm * 2 + c.wn, bi, bj, lane));
+        __builtin_nontemporal_store(q, reinterpret_cast<floatx4*>(kept) + kept_index(c.tile_m, c.tile_n, (V + 255) / 256, c.wm * 2 + c.wn, bi, bj, lane));
       }
     }
     const float ms = (mx == NEG) ? 0.f : mx * zs;             // zs > 0: the largest raw logit is the largest tempered one
@@ -554,15 +558,19 @@ struct KeptJob {
 // bf16: a wavefront takes 16 tokens x 128 vocabulary entries of a tile; grid (4 x tiles of 256 x 256, 2).  Lane (g, cc) = (l / 16, l % 16)
 // holds entries 16 bi + 4 g .. + 3 of token cc; a row swap makes that eight consecutive entries, and lane pairs swap halves, so that
 // a store writes whole 128-byte lines (as in EpiDS).
-__global__ __launch_bounds__(256) void kept_ds_kernel(const float* kept, KeptJob j, int tiles_n, bf16_t* dS, int64_t ld_ds) {
-  const int sub = blockIdx.x & 3, tile = blockIdx.x >> 2, tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
+__global__ __launch_bounds__(256) void kept_ds_kernel(const float* kept, KeptJob j, int tiles_m, bf16_t* dS, int64_t ld_ds) {
+  const int sub = blockIdx.x & 3, tile = blockIdx.x >> 2, tile_n = tile / tiles_m, tile_m = tile - tile_n * tiles_m;
   const int n_real = *j.n_real;
   if (tile_n * 256 >= n_real) return;
   const int lane = threadIdx.x & 63, bj = blockIdx.y * 4 + (threadIdx.x >> 6), g = lane >> 4, cc = lane & 15, p = cc & 1;
+  const int n16 = tile_n * 256 + (sub & 1) * 128 + bj * 16;
   floatx4 z[8];
 #pragma unroll
-  for (int bi = 0; bi < 8; ++bi) z[bi] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(kept) + kept_index(tile_m, tile_n, tiles_n, sub, bi, bj, lane));
-  const int n = tile_n * 256 + (sub & 1) * 128 + bj * 16 + cc, m0 = tile_m * 256 + (sub >> 1) * 128;
+  for (int bi = 0; bi < 8; ++bi) {
+    z[bi] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (n16 < n_real) z[bi] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(kept) + kept_index(tile_m, tile_n, tiles_m, sub, bi, bj, lane));
+  }
+  const int n = n16 + cc, m0 = tile_m * 256 + (sub >> 1) * 128;
   const bool valid = n < n_real;
   const int y = valid ? j.ids_c[n] - m0 : -1;
   const float lse = valid ? j.lse_c[n] : 3.0e38f, ct = valid ? j.c_c[n] * j.zs : 0.f;       // no token: every entry becomes 0

@@ -1387,7 +1387,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       ProfScope ps(RL_PROF_GEMM_DS, s);
       const KeptJob j{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau};
       if constexpr (sizeof(T) == 4) kept_ds_f32_kernel<<<(unsigned)((int64_t)(p.Vp / 64) * (p.Tc / 64)), 256, 0, s>>>(j, dST, p.Tc, dS, p.Vp);
-      else kept_ds_kernel<<<dim3((unsigned)(4 * p.tiles_v * (p.Tc / 256)), 2), 256, 0, s>>>(q.kept, j, p.Tc / 256, dS, p.Vp);
+      else kept_ds_kernel<<<dim3((unsigned)(4 * p.tiles_v * (p.Tc / 256)), 2), 256, 0, s>>>(q.kept, j, p.tiles_v, dS, p.Vp);
     } else {  // recompute logits, form dS (and dS^T for f32 inputs)
       GemmDims d{};
       d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;

@@ -22,6 +22,18 @@ def test_bf16_kept_logits_give_the_bits_of_recomputed_ones(H, V, lengths, tau, l
         assert torch.equal(getattr(got, name), getattr(want, name)), name
 
 
+# a few tokens in many rows: a block of 16 tokens less one / exactly / plus one, tokens of the second tile alone past its border
+@pytest.mark.parametrize("tokens", [15, 16, 17, 257])
+def test_bf16_few_tokens_in_many_rows(tokens):
+    cfg = synth.RolloutConfig("kept", 2, 2, 1, 64, 520, 2559, "bf16", 0.5, seed=85)
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[400, 300, 1, 300])
+    on = b.mask.nonzero().flatten()
+    b.mask[on[torch.randperm(len(on), generator=torch.Generator().manual_seed(1)).cuda()[tokens:]]] = 0
+    want, got = (run_gpu(b, "flow", backward_mode=m) for m in ("recompute", "auto"))
+    for name in OUT:
+        assert torch.equal(getattr(got, name), getattr(want, name)), name
+
+
 def test_bf16_no_row_counts():
     cfg = synth.RolloutConfig("kept", 1, 2, 1, 8, 512, 600, "bf16", 0.5, seed=82)
     b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[8, 8])
