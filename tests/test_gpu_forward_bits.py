@@ -1,16 +1,17 @@
-"""A token's log-prob, lse and entropy are the same bits however many rows are staged with it: the f32 forward takes square, wide or narrow
-tiles by the size of the chunk, and all add in the same order."""
+"""A token's log-prob, lse and entropy are the same bits however many rows are staged with it: the f32 forward takes wide or narrow tiles by the
+size of the chunk, square ones where operands off the 16-byte grid come in many rounds of them, and all add in the same order."""
 import pytest
 import torch
 
 from paper_2603_16435_amd import binding, synth
 from parity_util import run_gpu
+from test_gpu_f32_tiles import OUT, off_grid
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("V,rows,tau", [(1000, 9000, 0.0), (300, 17000, 0.8),       # wide tiles from 8192 / 16384 staged rows on
-                                          (30000, 8000, 0.0)])                     # square ones, fifteen rounds of them; wide; narrow
+                                          (30000, 8000, 0.0)])                     # wide in many rounds; narrow
 def test_f32_log_probs_do_not_depend_on_the_chunk(V, rows, tau):
     cfg = synth.RolloutConfig("bits", 2, 4, 1, rows // 8, 68, V, "f32", 0.5, seed=61)
     b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[rows // 8] * 8)
@@ -19,6 +20,18 @@ def test_f32_log_probs_do_not_depend_on_the_chunk(V, rows, tau):
         got = run_gpu(b, "grpo", chunk_rows=chunk, backward=False, temperature=tau)
         for name in ("logprob", "lse", "entropy", "target_logit", "loss", "coeff"):
             assert torch.equal(getattr(got, name), getattr(want, name)), (chunk, name)
+
+
+@pytest.mark.parametrize("backward", [False, True])                        # True: the logits are kept as well
+def test_f32_square_tiles_of_unaligned_operands_give_the_same_bits(backward):
+    cfg = synth.RolloutConfig("bits", 2, 4, 1, 1000, 68, 30000, "f32", 0.5, seed=63)          # 118 x 32 square tiles: fifteen rounds
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[1000] * 7 + [937])
+    want = run_gpu(b, "flow", backward=backward)
+    b.weight, b.hidden = off_grid(b.weight), off_grid(b.hidden)
+    got = run_gpu(b, "flow", backward=backward)
+    for name in OUT:
+        if backward or not name.startswith("d_"):
+            assert torch.equal(getattr(got, name), getattr(want, name)), name
 
 
 def test_f32_static_scoring_call_in_smaller_chunks_gives_the_same_bits():

@@ -54,25 +54,28 @@ def test_a_workspace_sized_for_an_aligned_weight_serves_one_that_is_not(H, mode)
     assert torch.equal(got.d_weight, want.d_weight) and torch.equal(got.d_hidden, want.d_hidden) and torch.equal(got.loss, want.loss)
 
 
-@pytest.mark.parametrize("mode", ["recompute", "stash"])
-def test_outputs_in_the_place_of_inputs(mode):
-    """Rewards turn into advantages, token ids into target columns (or target logits, entropies) in place: an input is only overwritten
-    when the call has read it everywhere.  300 prompts: the advantages of more than one workgroup."""
-    P, G = 300, 3
-    cfg = synth.RolloutConfig("views", P, G, 1, 4, 128, 300, "bf16", 0.5, seed=73)
+@pytest.mark.parametrize("P,G", [(300, 3), (8, 4)])       # the preparation and the finish of the loss in launches of their own, or with others
+@pytest.mark.parametrize("dtype,mode,objective", [("bf16", "recompute", "GRPO"), ("bf16", "stash", "GRPO"), ("bf16", "auto", "FLOW"), ("bf16", "stash", "FLOW"),
+                                                  ("f32", "auto", "FLOW")])
+def test_outputs_in_the_place_of_inputs(P, G, dtype, mode, objective):
+    """Rewards turn into advantages, token ids into target columns (or target logits, entropies), log-Z into its gradient in place: an input is
+    only overwritten when the call has read it everywhere.  300 prompts: the advantages of more than one workgroup."""
+    objective = getattr(binding, "RL_OBJ_" + objective)
+    cfg = synth.RolloutConfig("views", P, G, 1, 4, 128, 300, dtype, 0.5, seed=73)
     b = synth.make_rollouts(cfg, "cuda", "padded", lengths=[(7 * i) % 5 for i in range(P * G)])
     plan = _plan(b, mode, 0)
     plan.res.target_col, plan.res.target_logit = torch.empty(b.R, dtype=torch.int32, device="cuda"), torch.empty(b.R, device="cuda")
     plan.out.target_col, plan.out.target_logit = plan.res.target_col.data_ptr(), plan.res.target_logit.data_ptr()
-    names = ("loss", "seq_loss", "logprob", "advantages", "seq_len", "target_col", "target_logit", "entropy", "d_hidden", "d_weight")
-    want = {n: getattr(plan.run(binding.RL_OBJ_GRPO), n).clone() for n in names}
+    names = ("loss", "seq_loss", "logprob", "advantages", "seq_len", "target_col", "target_logit", "entropy", "d_hidden", "d_weight", "d_log_z")
+    res = plan.run(objective)
+    want = {n: getattr(res, n).clone() for n in names}
     for field, inp in (("advantages", "rewards"), ("seq_len", "cu_seqlens"), ("target_col", "token_ids"), ("target_logit", "token_ids"),
-                       ("entropy", "token_ids")):
+                       ("entropy", "token_ids"), ("d_log_z", "log_z")):
         keep, own = getattr(b, inp).clone(), getattr(plan.out, field)
         setattr(plan.out, field, getattr(b, inp).data_ptr())
         for n in names:
             getattr(plan.res, n).zero_()
-        plan.run(binding.RL_OBJ_GRPO)
+        plan.run(objective)
         torch.cuda.synchronize()
         assert torch.equal(getattr(b, inp)[:want[field].numel()].view(want[field].dtype), want[field]), field
         for n in names:
