@@ -78,7 +78,6 @@ struct EpiFwd {
   float zs;             // inverse temperature
   int* ycol_c;          // [compact row] vocabulary row the target logit was taken from (the position of the accumulator read)
   float* kept;          // KEEP: logits of the chunk
-  static constexpr bool kForward = true;
 
   // one token column of one lane: the MB * kRegs logits it holds.  PAD: some of the sub-tile's rows are
   // vocabulary padding (only in the last tile row) and must not enter the sums.

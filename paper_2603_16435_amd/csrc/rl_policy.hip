@@ -56,6 +56,7 @@ constexpr int64_t kKMajorRows = 32768;
 // the 7B head 10019 + 9589, 1942 + 10277; 4741 tokens, H 1160, V 50257 663 + 609, 266 + 664; the whole call at H 456: 1310 tokens, V 50257
 // 458 -> 439, 4605 tokens, V 152064 3212 -> 3124; H 512 403 -> 396, 3276 -> 3190.
 constexpr int64_t kKeepRows = 16384;
+constexpr int64_t kFarBytes = (int64_t)1 << 32;      // hidden states that span this much are addressed per lane (FAR)
 constexpr int kKeepH = 456;
 
 constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup per CU, a step of a K cut is two slabs
@@ -1097,7 +1098,7 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
     if (alt < p.n_desc) p.n_desc = (int)alt;
   }
   // (room is set aside by shape, not alignment: a workspace serves a weight of any alignment)
-  const bool keep_room = bwd && p.n_chunks == 1 && (b->dtype == RL_F32 || (mode == RL_BWD_AUTO && b->R <= kKeepRows && b->H >= kKeepH &&
+  const bool keep_room = bwd && p.n_chunks == 1 && (b->dtype == RL_F32 || (mode == RL_BWD_AUTO && b->R <= kKeepRows && b->H >= kKeepH && b->R * b->H * 2 < kFarBytes &&
                                                                            !(stash_asked && b->H % 128 == 0)));
   p.keep = keep_room && (b->dtype == RL_F32 || (reinterpret_cast<uintptr_t>(b->hidden) | reinterpret_cast<uintptr_t>(b->weight)) % 16 == 0);
   size_t o = 0;
@@ -1164,17 +1165,21 @@ static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, con
                     ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) % 16 == 0) &&
                     !d.a_rows && (d.b_rows != nullptr) == Epi::kGatherB &&     // (how the hot kernel addresses its operands)
                     !small_k<Epi>(d.K);
-  // (two epilogues are written for the hot kernel, one of them for K on its grid: make_plan sees to it)
-  constexpr bool stash = std::is_same_v<Epi, EpiFwdStash<bf16_t>>;
-  if constexpr (!stash && !std::is_same_v<Epi, EpiFwd<bf16_t, true>>)
+  // (two epilogues are written for the hot kernel, one of them for K on its grid, the other for rows that span less than 4 GiB: make_plan sees to it)
+  constexpr bool stash = std::is_same_v<Epi, EpiFwdStash<bf16_t>>, keep = std::is_same_v<Epi, EpiFwd<bf16_t, true>>;
+  if constexpr (!stash && !keep)
     if (!fast) { launch_generic(A, B, d, epi, tiles, s); return; }
-  const bool far = d.b_rows && d.b_span * d.ldb * 2 >= ((int64_t)1 << 32);
-  if (!stash && d.K % 128) {
-    if constexpr (stash) return;
-    else if (far) gemm_nt_bf16_kernel<Epi, Tune, true, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
-    else gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
-  } else if (far) gemm_nt_bf16_kernel<Epi, Tune, false, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
-  else gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
+  const bool far = d.b_rows && d.b_span * d.ldb * 2 >= kFarBytes;
+  if constexpr (!keep)
+    if (far) {
+      if constexpr (!stash)
+        if (d.K % 128) { gemm_nt_bf16_kernel<Epi, Tune, true, true><<<tiles, 256, 0, s>>>(A, B, d, epi); return; }
+      gemm_nt_bf16_kernel<Epi, Tune, false, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
+      return;
+    }
+  if constexpr (!stash)
+    if (d.K % 128) { gemm_nt_bf16_kernel<Epi, Tune, true><<<tiles, 256, 0, s>>>(A, B, d, epi); return; }
+  gemm_nt_bf16_kernel<Epi, Tune><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
 
 // Whether an M x N f32 contraction has so few tiles of 64 x 16 that four groups of wavefronts share one, each taking every fourth slab (dW of
@@ -1220,9 +1225,10 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
     }
   }
   if (bn == kF32BN && fast) {
-    // (a dynamic K is a multiple of 16 only)
-    if (std::is_same_v<Epi, EpiDW> || d.K % 32) gemm_nt_f32_kernel<Epi, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
-    else if constexpr (!std::is_same_v<Epi, EpiDW>) gemm_nt_f32_kernel<Epi, false><<<tiles, 256, 0, s>>>(A, B, d, epi);
+    // (K of dW, a number of tokens, is a multiple of 16 only; K of dX, the padded vocabulary, one of 256)
+    constexpr bool tail = std::is_same_v<Epi, EpiDW>, whole = std::is_same_v<Epi, EpiDX<float>>;
+    if (!whole && (tail || d.K % 32)) { if constexpr (!whole) gemm_nt_f32_kernel<Epi, true><<<tiles, 256, 0, s>>>(A, B, d, epi); }
+    else if constexpr (!tail) gemm_nt_f32_kernel<Epi, false><<<tiles, 256, 0, s>>>(A, B, d, epi);
   } else if (bn == kF32BN) gemm_nt_kernel<float, Epi, kBM, kF32BN, 2, 2><<<tiles, 256, 0, s>>>(A, B, d, epi);
   else gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1><<<tiles, 256, 0, s>>>(A, B, d, epi);
 }
