@@ -373,56 +373,78 @@ __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* mask, cons
   }
 }
 
-// All of the preparation in one launch of one workgroup, for small batches: three launches of mostly latency become one (356 rows of 8
-// sequences 13 -> 9 us, scoring 99 rows 13 -> 6; 2400 rows 14 -> 12, at 8192 rows it would take 19 instead of 16).  The rows are read
-// once, into bit masks in LDS (counting rows, rows dropped for their token id), and everything after that looks at those.
-constexpr int kSmallRows = 4096, kSmallSeqs = 128;
+// All of the preparation in one launch of one workgroup, for small batches: three launches of mostly latency become one.  The rows are read
+// once, all at a time, into bit masks in LDS (counting rows, rows dropped for their token id) with the ids beside them, and everything after
+// that looks at those: the rows of a sequence are a difference of two ranks.  The whole call of a scoring or loss-only batch at H 64, V 300, three launches and
+// one, us: scoring 128, 1024, 4096 rows of 8 sequences 22.2 22.5 23.1 / 18.0 18.6 21.0; 32 sequences 22.2 22.5 22.9 / 18.8 19.4 21.3; 64 sequences 22.3 22.6 22.9 /
+// 20.2 20.8 22.1 (3072 rows 22.8 / 23.0); 128 sequences 22.3 22.6 22.9 / 23.3 23.8 25.3.  Loss of 1024 rows: 8 prompts 30.4 / 26.8, 32 prompts 31.6 / 30.1, 64 (four for a
+// wavefront, one after the other) 32.5 / 35.1.
+constexpr int kSmallRows = 4096, kSmallSeqs = 64, kSmallPrompts = 32;
 struct SmallPrep {
   const uint8_t* mask; const int32_t *ids, *cu, *group_idx;
   int R, V, P, B;
   int32_t *seq_len, *cstart, *row_map, *ids_c, *cpos, *row_map_out;
   Ctrl* ctrl; ChunkJob chunks; rl_stats* stats;
 };
+// inclusive, over the first n lanes (fewer steps for few)
+__device__ inline int wave_scan_max(int x, int n) { for (int o = 1; o < 64 && o < n; o <<= 1) { const int y = __shfl_up(x, o); if ((int)(threadIdx.x & 63) >= o) x = max(x, y); } return x; }
+__device__ inline int wave_scan_sum(int x, int n) { for (int o = 1; o < 64 && o < n; o <<= 1) { const int y = __shfl_up(x, o); if ((int)(threadIdx.x & 63) >= o) x += y; } return x; }
 __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f, AdvJob adv) {
-  __shared__ unsigned long long good[kSmallRows / 64], bad[kSmallRows / 64];
-  __shared__ int pre[kSmallRows / 64];                         // counting rows before a word of good
-  __shared__ int sh_g[kSmallSeqs], sh_cu[kSmallSeqs + 1], sh_hi[kSmallSeqs], sh_len[1024], sh_at[kSmallSeqs + 1];
+  constexpr int kWords = kSmallRows / 64, kPer = kSmallRows / 1024;
+  __shared__ unsigned long long good[kWords], bad[kWords];
+  __shared__ int good_before[kWords + 1], bad_before[kWords + 1];        // rows in the words before a word
+  __shared__ int sh_y[kSmallRows];
+  __shared__ int sh_g[kSmallSeqs], sh_cu[kSmallSeqs + 1], sh_len[1024], sh_at[kSmallSeqs + 1];
   __shared__ float sh_r[kSmallSeqs];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  int y[kPer];
+  bool on[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {                             // (all loads in flight together)
+    const int r = k * 1024 + t;
+    on[k] = false; y[k] = -1;
+    if (r < s.R) { on[k] = s.mask[r]; y[k] = s.ids[r]; }
+  }
   if (t <= s.B) sh_cu[t] = s.cu[t];
   if (t < s.B) {
     sh_g[t] = s.group_idx ? s.group_idx[t] : 0;
     if (adv.blocks) sh_r[t] = adv.rewards[t];
   }
   if (s.stats && t < (int)(sizeof(rl_stats) / 4)) reinterpret_cast<int32_t*>(s.stats)[t] = 0;
-  for (int r0 = w * 64; r0 < s.R; r0 += 1024) {
-    const int r = r0 + lane;
-    bool g = false, b = false;
-    if (r < s.R) {
-      if (s.mask[r]) { const int y = s.ids[r]; g = y >= 0 && y < s.V; b = !g; }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) if (f.p[k]) f.p[k][r] = f.v[k];
-    }
-    const unsigned long long gm = __ballot(g), bm = __ballot(b);
-    if (lane == 0) { good[r0 >> 6] = gm; bad[r0 >> 6] = bm; }
+  for (int k = 0; k < kPer; ++k) {
+    const int r = k * 1024 + t;
+    if (r - lane >= s.R) continue;
+    const bool ok = y[k] >= 0 && y[k] < s.V;
+    const unsigned long long gm = __ballot(on[k] && ok), bm = __ballot(on[k] && !ok);
+    if (lane == 0) { good[r >> 6] = gm; bad[r >> 6] = bm; }
+    sh_y[r] = y[k];
+    if (r < s.R)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) if (f.p[q]) f.p[q][r] = f.v[q];
   }
   __syncthreads();
-  // rows of sequence i: a valid range at or behind every earlier offset (see prep_init_kernel), of a valid prompt
+  if (w == 8 || w == 9) {
+    static_assert(kWords == 64, "a word per lane");
+    const int words = (s.R + 63) / 64, n = wave_scan_sum(lane < words ? __popcll(w == 8 ? good[lane] : bad[lane]) : 0, words);
+    int* before = w == 8 ? good_before : bad_before;
+    before[lane + 1] = n;
+    if (lane == 0) before[0] = 0;
+  }
+  // sequences: a valid range at or behind every earlier offset (see prep_init_kernel), of a valid prompt
+  static_assert(kSmallSeqs == 64, "a sequence per lane");
+  const int hi = w == 0 ? wave_scan_max(t < s.B ? sh_cu[t] : INT32_MIN, s.B) : 0;
+  __syncthreads();
+  auto rank = [&](const unsigned long long* m, const int* before, int r) { return before[r >> 6] + (r & 63 ? __popcll(m[r >> 6] & ((1ull << (r & 63)) - 1ull)) : 0); };
   if (t < s.B) {
-    int hi = sh_cu[0];
-#pragma unroll 8
-    for (int i = 1; i < s.B; ++i) hi = max(hi, i <= t ? sh_cu[i] : hi);
     const int a = sh_cu[t], b = sh_cu[t + 1];
     const bool seq_ok = a >= 0 && a <= b && b <= s.R && a >= hi;
     const bool grp_ok = !s.group_idx || (sh_g[t] >= 0 && sh_g[t] < s.P);
     int cnt = 0, nb = 0;
-    if (seq_ok && grp_ok && b > a)
-      for (int q = a >> 6; q <= (b - 1) >> 6; ++q) {
-        unsigned long long m = ~0ull;
-        if (q == a >> 6) m &= ~0ull << (a & 63);
-        if (q == (b - 1) >> 6) m &= ~0ull >> (63 - ((b - 1) & 63));
-        cnt += __popcll(good[q] & m); nb += __popcll(bad[q] & m);
-      }
+    if (seq_ok && grp_ok) {
+      cnt = rank(good, good_before, b) - rank(good, good_before, a);
+      nb = rank(bad, bad_before, b) - rank(bad, bad_before, a);
+    }
     sh_len[t] = cnt; s.seq_len[t] = cnt;
     if (s.stats) {
       if (nb) atomicAdd(&s.stats->n_bad_token, nb);
@@ -430,19 +452,11 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
       if (!grp_ok) atomicAdd(&s.stats->n_bad_group, 1);
     }
   }
-  __syncthreads();
-  if (t >= 512 && t < 512 + kSmallRows / 64) {
-    int n = 0;
-#pragma unroll 8
-    for (int q = 0; q < (s.R + 63) / 64; ++q) n += q < t - 512 ? __popcll(good[q]) : 0;
-    pre[t - 512] = n;
-  }
-  if (t <= s.B) {
-    int at = 0;
-#pragma unroll 8
-    for (int i = 0; i < s.B; ++i) at += i < t ? sh_len[i] : 0;
-    sh_at[t] = at; s.cstart[t] = at;
-    if (t == s.B) {
+  if (w == 0) {
+    const int at = wave_scan_sum(t < s.B ? sh_len[t] : 0, s.B);         // (its own)
+    if (t < s.B) { sh_at[t + 1] = at; s.cstart[t + 1] = at; }
+    if (t == 0) { sh_at[0] = 0; s.cstart[0] = 0; }
+    if (t == s.B - 1) {
       s.ctrl->n_real = at; s.ctrl->too_long = 0; s.ctrl->overflow = 0; s.ctrl->done = 0;
       if (s.stats) s.stats->n_tokens = at;
     }
@@ -452,15 +466,14 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
   for (int u = w; u < s.B * sub; u += 16) {
     const int i = u / sub;
     if (sh_len[i] == 0) continue;
-    const int a = sh_cu[i], b = sh_cu[i + 1];
-    const int before = pre[a >> 6] + __popcll(good[a >> 6] & ((1ull << (a & 63)) - 1ull));
+    const int a = sh_cu[i], b = sh_cu[i + 1], at = sh_at[i] - rank(good, good_before, a);
     for (int r0 = (a & ~63) + 64 * (u - i * sub); r0 < b; r0 += 64 * sub) {
       unsigned long long m = good[r0 >> 6];
-      if (r0 < a) m &= ~0ull << (a & 63);
       if (r0 + 64 > b) m &= ~0ull >> (64 - (b - r0));
-      if (m >> lane & 1) {
-        const int r = r0 + lane, c = sh_at[i] + (r0 > a ? pre[r0 >> 6] - before : 0) + __popcll(m & ((1ull << lane) - 1ull));
-        s.row_map[c] = r; s.ids_c[c] = s.ids[r]; s.cpos[r] = c;
+      const int r = r0 + lane;
+      if (r >= a && (m >> lane & 1)) {
+        const int c = at + good_before[r0 >> 6] + __popcll(m & ((1ull << lane) - 1ull));
+        s.row_map[c] = r; s.ids_c[c] = sh_y[r]; s.cpos[r] = c;
         if (s.row_map_out) s.row_map_out[c] = r;
       }
     }
@@ -1310,7 +1323,7 @@ static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int3
   clear(q.cpos, -1); clear(out.row_map, -1);
   clear(out.logprob, 0); clear(out.lse, 0); clear(out.coeff, 0);
   if (!late) clear_last();
-  if (!late && p.R <= kSmallRows && p.B <= kSmallSeqs && p.P <= kSmallSeqs) {
+  if (!late && p.R <= kSmallRows && p.B <= kSmallSeqs && (!adv.blocks || p.P <= kSmallPrompts)) {
     prep_small_kernel<<<1, 1024, 0, s>>>(SmallPrep{b->mask, b->token_ids, b->cu_seqlens, group_idx, (int)p.R, p.V, p.P, p.B, q.seq_len, q.cstart, q.row_map,
                                                    q.ids_c, q.cpos, out.row_map, q.ctrl, ChunkJob{p.stash ? q.desc : nullptr, p.n_desc, p.Tc, p.max_len},
                                                    out.stats}, f, adv);

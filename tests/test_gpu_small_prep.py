@@ -1,5 +1,5 @@
 """The one-launch preparation of small batches, at its edges: sequences that begin and end inside, at and across 64-row words, rows of no
-sequence, bad tokens, prompts without members; and the batch one row or one sequence beyond its range."""
+sequence, bad tokens, prompts without members; and the batch one row, one sequence or one prompt beyond its range."""
 import numpy as np
 import pytest
 import torch
@@ -11,14 +11,15 @@ from parity_util import np_bits, run_gpu
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,R", [(1, 1), (1, 4096), (3, 200), (15, 4096), (16, 4095), (17, 1000), (128, 4096), (128, 130), (129, 4096), (5, 4097)])
-def test_index_work_of_small_batches(B, R):
+@pytest.mark.parametrize("B,R,P", [(1, 1, 0), (1, 4096, 0), (3, 200, 0), (15, 4096, 0), (16, 4095, 0), (17, 1000, 0), (64, 4096, 0), (64, 130, 32), (64, 2049, 33),
+                                   (65, 1025, 32), (128, 4096, 0), (128, 130, 0), (129, 4096, 0), (5, 4097, 0)])
+def test_index_work_of_small_batches(B, R, P):
     rng = np.random.default_rng(B * 10007 + R)
     cuts = np.sort(rng.integers(0, R + 1, B - 1))
     if R > 128:
         cuts = np.sort(np.where(rng.random(B - 1) < 0.4, cuts // 64 * 64, cuts))        # some at words' borders, some sequences empty
     cu = np.concatenate([[0], cuts, [R if B % 2 else R - R // 10]]).astype(np.int32)      # rows behind the last sequence
-    P = max(1, B // 3)
+    P = P or max(1, B // 3)
     cfg = synth.RolloutConfig("prep", P, 1, 1, 4, 8, 300, "f32", 0.5, seed=5)
     b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[R] + [0] * (P - 1))
     mask = (rng.random(R) < 0.8).astype(np.uint8)
