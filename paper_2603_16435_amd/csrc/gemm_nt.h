@@ -70,7 +70,6 @@ struct GemmDims {
   int group_m;            // tile-order parameter: M-tiles per band
   int split_slots;        // > 0: the contraction may be cut along K (see split_k); workgroups the chip runs at a time
   int b_k_rows;           // hot kernel, B operand given K-major: its rows (K is their number rounded up, with zeros in the other operand)
-  int min_rows, max_rows; // the launch is for chunks of more than min_rows / at most max_rows rows only (0: any); a twin does the others
   int fill_tiles;         // tiles of another contraction over K = M in the same launch, which fill the CUs this one leaves
 };
 
@@ -98,7 +97,6 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
   } else {
     left = *d.n_real - d.chunk_start;
   }
-  if ((d.min_rows && left <= d.min_rows) || (d.max_rows && left > d.max_rows)) return false;
   if (left <= 0) {
     if (d.dyn == 3 && d.zero_if_empty) K = 0; else return false;
   } else if (d.dyn == 1) M = left < M ? left : M;
@@ -859,10 +857,15 @@ void gemm_nt_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict_
 // second.  Used where one of them alone has too few tiles to fill the last round of the 256 CUs: the
 // other's workgroups then fill the tail.  n1 = launch_tiles() of the first (a multiple of the XCD count).
 // BTR1: the first contraction's B operand is given K-major; the second's A operand always is (see gemm_nt_bf16_tile).
+// min_rows / max_rows: the launch is for chunks of more / of at most so many rows only (0: any); its twin does the others.
 template <class Epi1, class Tune1, class Epi2, class Tune2, bool BTR1>
 __global__ __launch_bounds__(256)
 void gemm_nt_bf16_pair_kernel(const bf16_t* __restrict__ A1, const bf16_t* __restrict__ B1, GemmDims d1, Epi1 epi1, int n1,
-                              const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2, GemmDims d2, Epi2 epi2) {
+                              const bf16_t* __restrict__ A2, const bf16_t* __restrict__ B2, GemmDims d2, Epi2 epi2, int min_rows, int max_rows) {
+  if (min_rows | max_rows) {
+    const int rows = d1.chunk ? d1.chunk[1] : *d1.n_real - d1.chunk_start;
+    if ((min_rows && rows <= min_rows) || (max_rows && rows > max_rows)) return;
+  }
   __shared__ __attribute__((aligned(1024))) unsigned char stage0[kHotStageBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char stage1[kHotStageBytes];
   if ((int)blockIdx.x < n1)

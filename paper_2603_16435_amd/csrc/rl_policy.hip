@@ -1249,7 +1249,7 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
 // dX = diag(f) dS W  (A = dS or E' [Tc][Vp], B = W^T [H][Vp]) and dW (+)= dS^T (diag(f) X)  (A = the same array read as a K-major
 // operand, B = X^T [H][Tc]) of a bf16 chunk in one launch: dX alone has few (long) tiles, whose last round would leave CUs
 // idle; the dW tiles fill them.  dX is cut along K where its tiles are fewer still.
-static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, GemmDims dw,
+static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, GemmDims dx, EpiDX<bf16_t> ex, const bf16_t* XT, const GemmDims& dw,
                          const EpiDW& ew, hipStream_t s) {
   const int tn = (dx.N + kBN - 1) / kBN;
   dx.split_slots = kHotSlots; dx.fill_tiles = (dw.M + kBM - 1) / kBM * tn;
@@ -1257,15 +1257,11 @@ static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, Gem
   const int n2 = launch_tiles((dw.M + kBM - 1) / kBM, tn);
   if (WT) {
     const bool both = step_prefetch(dx.M, tn, dx.fill_tiles);
-    dx.max_rows = dw.max_rows = both ? kStepRows : 0;
-    gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
-    dx.max_rows = dw.max_rows = 0;
-    dx.min_rows = dw.min_rows = kStepRows;
-    if (both) gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDXStep, EpiDW, TuneDWStep, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew);
-    dx.min_rows = 0;
+    gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew, 0, both ? kStepRows : 0);
+    if (both) gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDXStep, EpiDW, TuneDWStep, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew, kStepRows, 0);
   } else {
     dx.ldb = dx.N; dx.b_tiled = 0; dx.b_k_rows = dw.M;
-    gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, W, dx, ex, n1, E, XT, dw, ew);
+    gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, W, dx, ex, n1, E, XT, dw, ew, 0, 0);
   }
   splitk_reduce_kernel<bf16_t><<<512, 256, 0, s>>>(dx, ex, kBM, kBN, kHotStep);
 }
