@@ -602,18 +602,20 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 
 // ------------------------------------------------------------------ forward combine
 // Fold the per-vocab-tile partials (max, sumexp) of a chunk into lse, logp.  A workgroup handles 64
-// compact rows x 16 slices of the tile range: one online (rescaling) pass per thread, coalesced
+// compact rows x SLICES slices of the tile range: one online (rescaling) pass per thread, coalesced
 // along the rows, sums in f64, then the slices are scaled to the row's maximum, one exponential per thread, and added through LDS in order.
-// (Four slices, each scaled by the thread that adds them up: 8 us for 99 rows x 125 tiles, all latency.)
-constexpr int kCombineSlices = 16;
+// Few rows are all latency and want many slices, many rows of few tiles pay for the exponential of every slice.  32768 rows, 4, 8, 16 slices, us: 4 tiles
+// 4.3 - 4.6, 16 tiles 4.8 4.7 5.9, 63 tiles 9.0 8.3 11.3; 96 rows: 4 tiles 3.0 - 3.6, 16 tiles 3.8 3.5 4.2, 63 tiles 8.4 5.6 5.2, 125 tiles 8.8 - 6.7.  (By the
+// vocabulary alone: a token's bits must not depend on the batch.)
+constexpr int combine_slices(int tiles_v) { return tiles_v <= 8 ? 4 : tiles_v <= 64 ? 8 : 16; }
 // HALVES: the partials are those of half tiles (logits_few_kernel), two of which make one.
-template <bool HALVES>
-__global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
+template <bool HALVES, int SLICES>
+__global__ __launch_bounds__(64 * SLICES) void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
                                    const int32_t* row_map, const Ctrl* ctrl, int chunk_start, int chunk_rows, const int32_t* ycol_c,
                                    float* lse_c, float* logp_c, float* lse_out, float* logp_out, float* ent_out,
                                    float* zy_out, int32_t* ycol_out) {
-  __shared__ float sm[kCombineSlices][64];
-  __shared__ double ss[kCombineSlices][64], su[kCombineSlices][64];
+  __shared__ float sm[SLICES][64];
+  __shared__ double ss[SLICES][64], su[SLICES][64];
   int left = ctrl->n_real - chunk_start;
   if (left > chunk_rows) left = chunk_rows;
   if ((int)blockIdx.x * 64 >= left) return;
@@ -623,11 +625,11 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
   float m = NEG;
   double s = 0.0, u = 0.0;
   if (n < left) {
-    for (int t0 = slice; t0 < tiles_v; t0 += 8 * kCombineSlices) {             // eight loads in flight, folded in order
+    for (int t0 = slice; t0 < tiles_v; t0 += 8 * SLICES) {             // eight loads in flight, folded in order
       float4 q[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const int t = t0 + kCombineSlices * k;
+        const int t = t0 + SLICES * k;
         q[k] = make_float4(NEG, 0.f, 0.f, 0.f);
         if (t < tiles_v) {
           if constexpr (HALVES) q[k] = EpiFwd<bf16_t>::merge_halves(part[(int64_t)(2 * t) * ldp + n], part[(int64_t)(2 * t + 1) * ldp + n]);
@@ -642,6 +644,7 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
       s *= f0; u *= f0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
+        if (t0 + SLICES * k >= tiles_v) break;
         const double f = (double)expf(q[k].x - mm);
         s += (double)q[k].y * f; u += (double)q[k].z * f;
       }
@@ -652,7 +655,7 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
   __syncthreads();
   float M = sm[0][col];
 #pragma unroll
-  for (int k = 1; k < kCombineSlices; ++k) M = fmaxf(M, sm[k][col]);
+  for (int k = 1; k < SLICES; ++k) M = fmaxf(M, sm[k][col]);
   {
     const double f = m != NEG ? exp((double)(m - M)) : 0.0;
     ss[slice][col] = s * f; su[slice][col] = u * f;
@@ -661,7 +664,7 @@ __global__ __launch_bounds__(64 * kCombineSlices) void lse_combine_kernel(const 
   if (slice == 0 && n < left) {
     double S = 0.0, U = 0.0;
 #pragma unroll
-    for (int k = 0; k < kCombineSlices; ++k) { S += ss[k][col]; U += su[k][col]; }
+    for (int k = 0; k < SLICES; ++k) { S += ss[k][col]; U += su[k][col]; }
     const double lse_d = (double)M + log(S);
     const float lse = (float)lse_d;
     const int g = chunk_start + n;
@@ -1371,8 +1374,10 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
       else launch_gemm<TuneLogits>(W, X, d, EpiFwd<T>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, s);
     }
     ProfScope ps(RL_PROF_COMBINE, s);
-    auto kern = few ? lse_combine_kernel<true> : lse_combine_kernel<false>;
-    kern<<<few ? kFewTokens / 64 : (p.Tc + 63) / 64, 64 * kCombineSlices, 0, s>>>(q.part, few ? kFewTokens : p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc,
+    const int slices = combine_slices(p.tiles_v);
+    auto kern = slices == 4 ? (few ? lse_combine_kernel<true, 4> : lse_combine_kernel<false, 4>)
+                : slices == 8 ? (few ? lse_combine_kernel<true, 8> : lse_combine_kernel<false, 8>) : few ? lse_combine_kernel<true, 16> : lse_combine_kernel<false, 16>;
+    kern<<<few ? kFewTokens / 64 : (p.Tc + 63) / 64, 64 * slices, 0, s>>>(q.part, few ? kFewTokens : p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc,
                                                                                q.ycol, q.lse_c, q.logp_c, lse_out, logp_out, ent_out, zy_out, ycol_out);
   }
 }
