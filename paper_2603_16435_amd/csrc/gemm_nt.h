@@ -653,7 +653,9 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // and is the one that the wait at the slab's end leaves in flight (loads come back in order; prefetch() says what holds it in its place): waited for there, a line that had to come from
   // memory held the slab up, which is what the prefetch is to avoid (67 k tokens at the 7B head: forward 56.4 -> 54.8 ms; 36 k tokens, H 2048,
   // V 32000: 3.81 -> 3.62, dX + dW 7.25 -> 6.77).  But the wait also keeps the workgroups of a block in step, so that a line is fetched once
-  // for all of them: where a launch has very many rounds of tiles it stays (kPfWait).
+  // for all of them: where a launch has very many rounds of tiles it stays (kPfWait), and in the slabs of a K tail, which do not run far enough
+  // to drift and whose loads go out later for the work on their addresses (forward of 16 k tokens, V 50257, waited for or not: H 328, all six slabs 831 and
+  // 842 us, H 392 892 and 909, H 504 956 and 981, H 1160 1796 and 1801).
   const unsigned char* pf_ptr;
   int pf_stride;
   const bool pf_atr = ATR && wave == 0;
@@ -790,12 +792,14 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // 0..LDA-1 of slab kt+1 are in flight towards `nxt`.  The last phase runs from registers after the
   // workgroup barrier, so it covers the first fragment reads of slab kt+1 and the first loads of kt+2.
   auto slab = [&](bool tail, unsigned char* cur, unsigned char* nxt, int kt, unsigned& pfslot) __attribute__((always_inline)) {
-    if constexpr (Tune::kPfWait) prefetch(pfslot, kt);
+    const bool early = Tune::kPfWait || (KT && tail);
+    if (early) prefetch(pfslot, kt);
     phase(tail, 0, 0, 0, 4, cur, 0, kof(kt + 1), nxt, LDA, LDB);
     phase(tail, 0, 1, 1, 12, cur, 1, kof(kt + 1), nxt, LDA + LDB, LDC);
-    if constexpr (!Tune::kPfWait) prefetch(pfslot, kt);
+    if (!early) prefetch(pfslot, kt);
     phase(tail, 1, 0, 0, 4, cur, 1, 0, nxt, 0, 0);
-    __builtin_amdgcn_s_waitcnt(PFD > 0 && !Tune::kPfWait ? 0x0071 : 0x0070);     // vmcnt(0), or 1: all but the prefetch; lgkmcnt(0): own loads have landed, own fragment reads are done
+    // vmcnt(0), or 1: all but the prefetch; lgkmcnt(0): own loads have landed, own fragment reads are done
+    if (PFD > 0 && !early) __builtin_amdgcn_s_waitcnt(0x0071); else __builtin_amdgcn_s_waitcnt(0x0070);
     __syncthreads();                        // ... and so have everybody else's: `nxt` is complete, `cur` is free
     phase(tail, 1, 1, 1, 12, nxt, 0, kof(kt + 2), cur, 0, LDA);
   };
