@@ -436,7 +436,8 @@ template <> struct Pack4<float> {
 //      logit, zs = 1 / temperature the chain factor back to W x_t), formed in
 //      f32 (subtraction and scaling before rounding) and stored in the input precision, token-major
 //      dS[t][v] (operand of dX = dS W).  dW = dS^T X reads the same array as a K-major operand in the
-//      bf16 hot kernel; f32 inputs (generic kernel) also get the vocab-major copy dST[v][t].
+//      bf16 hot kernel; f32 inputs (the kernel of gemm_f32.h, narrow tiles and unaligned operands the general one) also get the vocab-major
+//      copy dST[v][t].
 //
 //      In the hot kernel (16x16 blocks) the tile rows and columns are relabelled (kPermute, see
 //      perm_row / perm_col in gemm_nt.h) such that a lane ends up holding eight consecutive

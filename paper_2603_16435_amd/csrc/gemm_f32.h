@@ -3,7 +3,7 @@
 // 256 x 64 tile, four wavefronts of 128 x 32 (v_mfma_f32_32x32x2, 64 cycles each), two workgroups per CU.  What bounds it is the f32 MFMA
 // rate (157 TFLOP/s at 2.4 GHz), and on this part vector instructions and MFMAs take turns on a SIMD: the register-staged loads of the
 // general kernel, their addresses and their stores into LDS took a tenth of the time.  Here slabs (32 k) go straight from memory into
-// LDS, addressed like those of the bf16 hot kernel (uniform base + lane offset; only gathered rows need vector adds), into two stages of
+// LDS, addressed like those of the bf16 hot kernel (uniform base + lane offset, no vector operation in the loops of dX and dW; the gathered rows of the forward and dS take four 64-bit adds per two slabs), into two stages of
 // 40 KiB.  A slab is four steps of 16 MFMAs, the order written is the order issued: the fragments of a step are read during the
 // step before, the last step of a slab runs after the workgroup barrier and covers the first reads of the next slab, and the ten loads of a
 // wavefront go out six in that last step and four in the first one, so that they have two steps to land.

@@ -51,13 +51,15 @@ constexpr int64_t kKMajorRows = 32768;
 
 // Keeping the logits between forward and backward (recompute mode, batch of one chunk) turns the dS contraction into a pass over memory, for
 // 4 bytes more per logit in the forward.  f32 always does (the logits wait in dS^T's place): 2175 tokens, H 768, V 50257 1323 -> 239 us, forward
-// 1230 -> 1274.  bf16 in the default mode, with room of its own: batches of up to kKeepRows rows, whose logits take no more of it than the dS of
-// the largest chunk (10 GB at the 7B head), and hidden sizes from kKeepH on, which the hot kernel serves.  dS + forward in us, recomputed and kept: 11.5 k tokens at
-// the 7B head 10019 + 9589, 1942 + 10277; 4741 tokens, H 1160, V 50257 663 + 609, 266 + 664; the whole call at H 456: 1310 tokens, V 50257
-// 458 -> 439, 4605 tokens, V 152064 3212 -> 3124; H 512 403 -> 396, 3276 -> 3190.
+// 1230 -> 1274.  bf16 in the default mode, with room of its own (4 bytes per row and vocabulary entry), if the workspace has it: batches of up to
+// kKeepRows rows, padding included, since only the device knows the tokens.  At the 7B head that room is 10 GB, as much as the dS of the largest
+// chunk, at V 32000 2 GB: the line is one of memory and drawn for large vocabularies.  Hidden sizes from kKeepH on: the general kernel, which keeps nothing
+// in bf16, had the forward up to 448 when it was drawn; with its limit of 320 (small_k) keeping gains 2 to 9 % from 328 on too.  dS + forward in us, recomputed
+// and kept: 11.5 k tokens at the 7B head 10019 + 9589, 1833 + 9904; 4741 tokens, H 1160, V 50257 663 + 609, 245 + 659; the whole call at H 456:
+// 430 and 1350 tokens, V 50257 266 -> 238, 433 -> 402, 4600 tokens, V 152064 3509 -> 3249; H 512 258 -> 233, 438 -> 415, 3191 -> 3005.
 constexpr int64_t kKeepRows = 16384;
-constexpr int64_t kFarBytes = (int64_t)1 << 32;      // hidden states that span this much are addressed per lane (FAR)
 constexpr int kKeepH = 456;
+constexpr int64_t kFarBytes = (int64_t)1 << 32;      // hidden states that span this much are addressed per lane (FAR)
 
 constexpr int kHotSlots = 256, kHotStep = 128;   // hot kernel: one workgroup per CU, a step of a K cut is two slabs
 // Per-contraction tuning of the hot kernel, from sweeps on the 7B-shaped workload:
