@@ -24,7 +24,7 @@ extern "C" {
  * milliseconds and bracket counts per class since the previous read, and clears the list. */
 enum { RL_PROF_PREP = 0,       /* counts, scan, compaction, output zero-fill            */
        RL_PROF_GEMM_FWD = 1,   /* forward logits contraction + online partial softmax   */
-       RL_PROF_COMBINE = 2,    /* partials -> lse, logp                                 */
+       RL_PROF_COMBINE = 2,    /* partials -> lse, logp (small f32 batches: in the loss)  */
        RL_PROF_LOSS = 3,       /* per-sequence loss, final reduce; f32 batches of one chunk: W^T, X^T and zeroing too */
        RL_PROF_TRANSPOSE = 4,  /* W^T, X^T chunks, zeroing masked dX rows               */
        RL_PROF_GEMM_DS = 5,    /* recomputed or kept logits -> dS                       */

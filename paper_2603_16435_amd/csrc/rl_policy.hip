@@ -29,6 +29,7 @@
 #include "rvq_few.h"
 #include "gemm_nt.h"
 #include "gemm_f32.h"
+#include "grads_small.h"
 #include "logits_few.h"
 
 namespace rlk {
@@ -40,7 +41,7 @@ constexpr int kBM = 256, kBN = 256;
 // kernel), or 256 x 16 where the large ones would leave CUs without work.  MFMA-bound: 128-141 TFLOP/s, 102-109 in the general kernel, whose
 // loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K and the logits
 // recomputed: 5.25 ms, 6.2 in the general kernel; with its 256 x 256 tiles 17.9 (27 dX
-// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us, 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
+// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us (35 since small batches have a backward of their own, grads_small.h), 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
@@ -690,6 +691,12 @@ struct LossOpts {
   int w_mean;               // FLOW: weight from the mean instead of the sum of the token log-ratios
 };
 
+// The combine of a batch of few rows and tiles inside its loss launch (fold_combine): a thread takes a token.
+struct CombineJob {
+  const float4* part; int ldp, tiles_v; const float* zy_c; const int32_t *row_map, *ycol_c;
+  float *lse_c, *logp_c, *lse_out, *logp_out, *ent_out, *zy_out; int32_t* ycol_out;
+};
+
 struct LossJob {
   int objective; const float *logp_c, *old_lp, *ref_lp; const int32_t *row_map, *cstart; const float* adv;
   const int32_t* group_idx; const float* log_z; int B, P; LossOpts o; Ctrl* ctrl;
@@ -697,6 +704,7 @@ struct LossJob {
   const ChunkDesc* desc;                // only the sequences of this chunk
   float* adv_out; int32_t* seq_len_out;
   float *loss, *d_log_z, *seq_loss_out;
+  CombineJob comb;                      // part == nullptr: lse_combine_kernel has been there
 };
 // Up to kFinishSeqs sequences, the workgroup that forms the last one's loss adds them up as well; with more, the release that every workgroup
 // then owes the others costs as much as a launch or more (256 sequences 16 us against 15, 20000 469 against 46).
@@ -747,8 +755,50 @@ __global__ __launch_bounds__(1024) void finalize_kernel(LossJob j) {
   if (lane == 0) j.d_log_z[p] = (float)s;
 }
 
+// What lse_combine_kernel<false, 4> does for token g, to the bit: its four slices one after the other (at most two tiles each), then their sum.
+constexpr int kFoldTiles = 8, kFoldRows = 1024;
+__device__ inline void combine_token(const CombineJob& c, int g) {
+  const float NEG = -__builtin_inff();
+  float4 q[kFoldTiles];
+#pragma unroll
+  for (int t = 0; t < kFoldTiles; ++t) q[t] = t < c.tiles_v ? c.part[(int64_t)t * c.ldp + g] : make_float4(NEG, 0.f, 0.f, 0.f);
+  const float zy = c.zy_c[g];
+  const int r = c.row_map[g], ycol = c.ycol_c[g];
+  float m[4];
+  double s[4], u[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    m[k] = fmaxf(q[k].x, q[k + 4].x); s[k] = 0.0; u[k] = 0.0;
+    if (m[k] == NEG) continue;
+    const double f0 = (double)expf(q[k].x - m[k]);
+    s[k] += (double)q[k].y * f0; u[k] += (double)q[k].z * f0;
+    if (k + 4 < c.tiles_v) {
+      const double f1 = (double)expf(q[k + 4].x - m[k]);
+      s[k] += (double)q[k + 4].y * f1; u[k] += (double)q[k + 4].z * f1;
+    }
+  }
+  const float M = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+  double S = 0.0, U = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double f = m[k] != NEG ? exp((double)(m[k] - M)) : 0.0;
+    double sf = s[k] * f, uf = u[k] * f;
+    asm volatile("" : "+v"(sf), "+v"(uf));                  // rounded, as on their way through LDS: no fused multiply-add
+    S += sf; U += uf;
+  }
+  const double lse_d = (double)M + log(S);
+  const float lse = (float)lse_d, lp = zy - lse;
+  c.lse_c[g] = lse; c.logp_c[g] = lp;
+  if (c.lse_out) c.lse_out[r] = lse;
+  if (c.logp_out) c.logp_out[r] = lp;
+  if (c.ent_out) c.ent_out[r] = (float)fmax(lse_d - U / S, 0.0);
+  if (c.zy_out) c.zy_out[r] = zy;
+  if (c.ycol_out) c.ycol_out[r] = ycol;
+}
+
 // One workgroup per sequence over its compact rows [cstart[i], cstart[i+1]).  The caller's advantages and lengths leave here, when the
 // rewards and the offsets have been read everywhere: an output may take the place of an input.
+template <bool FOLD>
 __device__ inline void sequence_loss(const LossJob& j, int i) {
   const float *logp_c = j.logp_c, *old_lp = j.old_lp, *ref_lp = j.ref_lp, *log_z = j.log_z;
   const int32_t *row_map = j.row_map, *group_idx = j.group_idx;
@@ -769,6 +819,8 @@ __device__ inline void sequence_loss(const LossJob& j, int i) {
     if (threadIdx.x == 0) { seq_loss[i] = 0.f; gterm[i] = 0.f; }
     return;
   }
+  if constexpr (FOLD)
+    for (int k = a + threadIdx.x; k < b; k += blockDim.x) combine_token(j.comb, k);        // (read back below by the thread that wrote them)
   const double Ad = (double)A;
   const double inv_bn = 1.0 / ((double)B * (double)n);
   const double lo_c = 1.0 - (double)o.clip_lo, hi_c = 1.0 + (double)o.clip_hi;
@@ -860,13 +912,14 @@ __device__ inline void sequence_loss(const LossJob& j, int i) {
 
 // ... and the workgroup that is the last of the call to get here adds the sequences up (a launch of its own took 2 to 5 us, 16 with
 // 64 sequences and the flow objective, whose prompts a thread each walked all sequences for).
+template <bool FOLD>
 __device__ inline void sequence_loss_and_finish(const LossJob& j, int i) {
   __shared__ int sh_last;
   if (j.desc) {
     i += j.desc->seq_begin;
     if (i >= j.desc->seq_end) return;
   }
-  sequence_loss(j, i);
+  sequence_loss<FOLD>(j, i);
   if (j.B > kFinishSeqs) return;
   if (threadIdx.x == 0) {                 // (it wrote the sequence's terms)
     __threadfence();
@@ -877,7 +930,7 @@ __device__ inline void sequence_loss_and_finish(const LossJob& j, int i) {
   __threadfence();
   finish_loss(j);
 }
-__global__ __launch_bounds__(kLossThreads) void seq_loss_kernel(LossJob j) { sequence_loss_and_finish(j, blockIdx.x); }
+__global__ __launch_bounds__(kLossThreads) void seq_loss_kernel(LossJob j) { sequence_loss_and_finish<false>(j, blockIdx.x); }
 
 // ------------------------------------------------------------------ transposes (K-contiguous operands)
 // dst[c][r] = src[row_of(r)][c] for r < rows_valid, 0 for rows_valid <= r < ld_dst rows covered by the grid.
@@ -927,12 +980,19 @@ __global__ __launch_bounds__(kLossThreads) void loss_prep_kernel(LossJob j, Tran
                                                                  const int32_t* cpos, float* dX, int64_t R, int H) {
   __shared__ float tile[64][65];
   int b = blockIdx.x;
-  if (b < j.B) { sequence_loss_and_finish(j, b); return; }
+  if (b < j.B) { sequence_loss_and_finish<false>(j, b); return; }
   b -= j.B;
   if (b < nw) { transpose_block(w, b % wx, b / wx, tile); return; }
   b -= nw;
   if (b < nx) { transpose_block(x, b % xx, b / xx, tile); return; }
   zero_masked_row((int64_t)(b - nx) * 4 + (threadIdx.x >> 6), cpos, dX, R, H);
+}
+
+// Combine, loss and that zeroing (dX != nullptr) in one launch: fold_combine().
+__global__ __launch_bounds__(kLossThreads) void loss_fold_kernel(LossJob j, const int32_t* cpos, float* dX, int64_t R, int H) {
+  const int b = blockIdx.x;
+  if (b < j.B) { sequence_loss_and_finish<true>(j, b); return; }
+  zero_masked_row((int64_t)(b - j.B) * 4 + (threadIdx.x >> 6), cpos, dX, R, H);
 }
 
 // The same for bf16 with 16-byte accesses on both sides (cols % 8 == 0, 16-byte aligned rows; rows_padded % 8 == 0, tiled
@@ -1276,6 +1336,15 @@ static bool small_dx(int M, int N, int K) {
   return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
+// The whole backward of a small f32 batch in one launch, see grads_small.h.  What it gains is launches; a workgroup of dX walks the whole vocabulary by itself, so a
+// large one takes longer than they did.  us of the call, former launches / this one, 16, 400, 2000 rows: H 16, V 1000 43 46 73 / 28 31 51, V 2000 40 48 84 / 34 39 61,
+// V 4000 41 54 99 / 48 56 78, V 16000 47 87 212 / 120 143 185; H 128, V 300 42 47 77 / 28 31 57, V 2000 45 59 113 / 40 47 88; H 512, V 500 55 68 - / 40 50 -.
+static bool small_grads(const Plan& p) {
+  return p.dtype == RL_F32 && p.bwd && p.keep && p.V <= 2048 && small_dx(p.Tc, p.H, p.Vp) && small_dx(p.V, p.H, p.Tc);
+}
+// ... and its combine inside the loss launch, also that of a loss without gradients: up to 1024 rows, which are four tokens of a thread at most.
+static bool fold_combine(const Plan& p) { return p.dtype == RL_F32 && p.n_chunks == 1 && p.tiles_v <= kFoldTiles && p.Tc <= kFoldRows && (!p.bwd || small_grads(p)); }
+
 struct Ptrs {
   Ctrl* ctrl; int32_t *seq_len, *cstart, *row_map, *ids_c, *cpos;
   float *zy, *lse_c, *logp_c, *c_c, *adv, *seq_loss, *gterm; float4* part;
@@ -1347,7 +1416,7 @@ static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int3
 
 template <class T>
 static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* logp_out, float* lse_out, float* ent_out,
-                        float* zy_out, int32_t* ycol_out, hipStream_t s) {
+                        float* zy_out, int32_t* ycol_out, bool fold, hipStream_t s) {
   const T* X = static_cast<const T*>(b->hidden);
   const T* W = static_cast<const T*>(b->weight);
   for (int ch = 0; ch < p.n_chunks; ++ch) {
@@ -1375,6 +1444,7 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
       else if (p.keep) launch_gemm<TuneLogits>(W, X, d, EpiFwd<T, true>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, s);
       else launch_gemm<TuneLogits>(W, X, d, EpiFwd<T>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, s);
     }
+    if (fold) continue;
     ProfScope ps(RL_PROF_COMBINE, s);
     const int slices = combine_slices(p.tiles_v);
     auto kern = slices == 4 ? (few ? lse_combine_kernel<true, 4> : lse_combine_kernel<false, 4>)
@@ -1399,6 +1469,16 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     zero_masked_rows_kernel<T><<<(unsigned)((p.R + 3) / 4), 256, 0, s>>>(q.cpos, dX, p.R, p.H);
     if (!p.k_major_w) launch_transpose<T>(gw, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
   }
+  if constexpr (sizeof(T) == 4)
+    if (small_grads(p)) {
+      ProfScope ps(RL_PROF_GEMM_BWD, s);
+      // (blocks of 32 columns where those of dX are one round of the CUs at most, else of 64)
+      const int rows = p.Tc / 16, nbx = rows * ((p.H + 31) / 32) <= kHotSlots ? 2 : 4, xc = (p.H + 16 * nbx - 1) / (16 * nbx), nx = rows * xc;
+      const int wc = (p.H + 16 * kGradNBW - 1) / (16 * kGradNBW);
+      (nbx == 2 ? small_grads_kernel<2> : small_grads_kernel<4>)<<<nx + (p.V + 15) / 16 * wc, kGradWaves * 64, 0, s>>>(
+          SmallGrads{{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau}, q.kept, p.Tc, X, W, q.row_map, p.H, dX, d_weight, xc, nx});
+      return;
+    }
   for (int ch = 0; ch < p.n_chunks; ++ch) {
     const int c0 = ch * p.Tc;
     if (!xt_done) {  // X^T chunk [H][Tc], gathered through row_map, zero beyond the valid rows
@@ -1459,7 +1539,8 @@ static bool run_loss_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const
   const float *X = static_cast<const float*>(b->hidden), *W = static_cast<const float*>(b->weight);
   float *WT = static_cast<float*>(q.wt), *XT = static_cast<float*>(q.xt);
   const int wx = (p.Vp + 63) / 64, xx = (p.Tc + 63) / 64, hy = (p.H + 63) / 64;
-  const int64_t nw = (int64_t)wx * hy, nx = (int64_t)xx * hy, n = p.B + nw + nx + (p.R + 3) / 4;
+  const bool small = small_grads(p);                    // (reads W and X as they are)
+  const int64_t nw = small ? 0 : (int64_t)wx * hy, nx = small ? 0 : (int64_t)xx * hy, n = p.B + nw + nx + (p.R + 3) / 4;
   if (p.dtype != RL_F32 || p.n_chunks != 1 || n >= (1 << 24)) return false;        // (2^32 threads a launch)
   loss_prep_kernel<<<(unsigned)n, kLossThreads, 0, s>>>(
       j, TransposeJob<float>{W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, false}, wx, (int)nw,
@@ -1484,7 +1565,7 @@ static void run_finalize(const LossJob& j, hipStream_t s) {
 static LossJob loss_job(const rl_batch* b, const rl_params* prm, int objective, const Plan& p, const Ptrs& q, const rl_outputs* out,
                         const ChunkDesc* desc) {
   return LossJob{objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv, b->group_idx, b->log_z, p.B, p.P, loss_opts(prm),
-                 q.ctrl, q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, desc, out->advantages, out->seq_len, out->loss, out->d_log_z, out->seq_loss};
+                 q.ctrl, q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, desc, out->advantages, out->seq_len, out->loss, out->d_log_z, out->seq_loss, CombineJob{}};
 }
 
 // Single-pass variant of forward + loss + backward (bf16 hot kernels): chunks are made of whole
@@ -1687,8 +1768,8 @@ rl_status rl_token_logprob_tempered(const rl_batch* b, float temperature, float*
   rl_outputs out{};
   out.logprob = logprob; out.lse = lse;
   run_prep(b, p, q, nullptr, out, AdvJob{}, s);
-  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
-  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
+  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
+  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
@@ -1727,15 +1808,22 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
     run_fused(b, prm, objective, p, q, out, s);
     return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
   }
-  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, s);
-  else run_forward<float>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, s);
+  const bool fold = fold_combine(p);
+  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, false, s);
+  else run_forward<float>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, fold, s);
 
   bool prep_done = false;
   {
     ProfScope ps(RL_PROF_LOSS, s);
-    const LossJob j = loss_job(b, prm, objective, p, q, out, nullptr);
-    prep_done = bwd && run_loss_prep(b, p, q, j, static_cast<float*>(out->d_hidden), s);
-    if (!prep_done) seq_loss_kernel<<<p.B, kLossThreads, 0, s>>>(j);
+    LossJob j = loss_job(b, prm, objective, p, q, out, nullptr);
+    if (fold) {
+      j.comb = CombineJob{q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ycol, q.lse_c, q.logp_c, out->lse, out->logprob, out->entropy, out->target_logit, out->target_col};
+      loss_fold_kernel<<<p.B + (bwd ? (p.R + 3) / 4 : 0), kLossThreads, 0, s>>>(j, q.cpos, static_cast<float*>(out->d_hidden), p.R, p.H);
+      prep_done = bwd;
+    } else {
+      prep_done = bwd && run_loss_prep(b, p, q, j, static_cast<float*>(out->d_hidden), s);
+      if (!prep_done) seq_loss_kernel<<<p.B, kLossThreads, 0, s>>>(j);
+    }
     run_finalize(j, s);
   }
   if (bwd) {
@@ -1793,8 +1881,8 @@ rl_status rl_token_logprob_static(const rl_batch* b, float temperature, float* l
   rl_outputs out{};
   out.logprob = logprob; out.lse = lse;
   run_prep(b, p, q, nullptr, out, AdvJob{}, s);
-  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
-  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, s);
+  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
+  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
