@@ -22,7 +22,7 @@ extern "C" {
  * every group of launches of rl_token_logprob / rl_policy_loss_fwd_bwd is bracketed by a pair of events recorded on
  * the caller's stream.  rl_profile_read waits for the recorded events, adds up elapsed
  * milliseconds and bracket counts per class since the previous read, and clears the list. */
-enum { RL_PROF_PREP = 0,       /* counts, scan, compaction, output zero-fill            */
+enum { RL_PROF_PREP = 0,       /* counts, scan, compaction, zero-fill (not in a forward) */
        RL_PROF_GEMM_FWD = 1,   /* forward logits contraction + online partial softmax   */
        RL_PROF_COMBINE = 2,    /* partials -> lse, logp (small f32 batches: in the loss)  */
        RL_PROF_LOSS = 3,       /* per-sequence loss, final reduce; f32 batches of one chunk: W^T, X^T and zeroing too */

@@ -284,7 +284,9 @@ __device__ inline GeneralTile general_tile(GemmDims& d, int pid) {
 // KG > 1: KG groups of such wavefronts share a tile, each taking every KG-th slab through LDS stages of its own; their accumulators are added in
 // order at the end (for tiles that are few and have a long K; a step of a K cut is then KG slabs).
 template <class T, int BM, int BN, int KG> constexpr int general_lds_bytes() { return KG * 2 * (BM + BN) * kSlabBytes; }
-template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG>
+//
+// PRE: slabs that are on their way in registers ahead of the one computed on.
+template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG, int PRE = 1>
 __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, const Epi& epi,
                                                                            int pid, unsigned char* smem_all) {
   constexpr int NT = WAVES_M * WAVES_N * 64;
@@ -328,30 +330,30 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
     if (d.b_rows) r = d.b_rows[r];
     bp[p] = B + (int64_t)r * d.ldb + lchunk * EPC;
   }
-  uint4 ra[PA], rb[PB];
-  auto gload = [&](int k0) __attribute__((always_inline)) {
+  uint4 ra[PRE][PA], rb[PRE][PB];
+  auto gload = [&](int k0, int i) __attribute__((always_inline)) {
     if (k0 + BK <= K) {                              // a whole slab
 #pragma unroll
-      for (int p = 0; p < PA; ++p) ra[p] = *reinterpret_cast<const uint4*>(ap[p] + k0);
+      for (int p = 0; p < PA; ++p) ra[i][p] = *reinterpret_cast<const uint4*>(ap[p] + k0);
 #pragma unroll
-      for (int p = 0; p < PB; ++p) rb[p] = *reinterpret_cast<const uint4*>(bp[p] + k0);
+      for (int p = 0; p < PB; ++p) rb[i][p] = *reinterpret_cast<const uint4*>(bp[p] + k0);
     } else {
       const bool ok = (k0 + lchunk * EPC) < K;
 #pragma unroll
-      for (int p = 0; p < PA; ++p) ra[p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
+      for (int p = 0; p < PA; ++p) ra[i][p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-      for (int p = 0; p < PB; ++p) rb[p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
+      for (int p = 0; p < PB; ++p) rb[i][p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
     }
   };
   auto stored = [](const uint4& v) __attribute__((always_inline)) { return SMALL ? make_uint4(v.x, v.z, v.y, v.w) : v; };
-  auto lstore = [&](int buf) __attribute__((always_inline)) {
+  auto lstore = [&](int buf, int i) __attribute__((always_inline)) {
     unsigned char* as = smem + buf * (A_BYTES + B_BYTES);
     unsigned char* bs = as + A_BYTES;
 #pragma unroll
-    for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(ra[p]);
+    for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(ra[i][p]);
 #pragma unroll
     for (int p = 0; p < PB; ++p)
-      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(rb[p]);
+      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(rb[i][p]);
   };
 
   typename L::acc_t acc[MB][NB];
@@ -362,15 +364,27 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
 #pragma unroll
       for (int e = 0; e < L::kRegs; ++e) acc[i][j][e] = 0.f;
 
+  static_assert(PRE == 1 || PRE % 2 == 0, "stage of a slab");
+  TileCtx c;
+  c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
+  c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
+  c.slice = t.slice; c.slices = t.slices;
+  typename Epi::Pre pre;
+  if constexpr (PRE > 1) pre = epi.template preload<L>(c, d);
   if (nk > 0) {
-    gload(k_begin * BK);
-    lstore(0);
+#pragma unroll
+    for (int i = 0; i < PRE; ++i)
+      if (i < nk) gload((k_begin + i * KG) * BK, i);
+    lstore(0, 0);
   }
   __syncthreads();
   const int frow = lane & (L::kBlk - 1), fq = lane / L::kBlk;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) gload((k_begin + (kt + 1) * KG) * BK);
+  for (int kt0 = 0; kt0 < nk; kt0 += PRE)
+#pragma unroll
+  for (int i = 0; i < PRE; ++i) {
+    const int kt = kt0 + i, cur = kt & 1;
+    if (PRE > 1 && kt >= nk) break;
+    if (kt + PRE < nk) gload((k_begin + (kt + PRE) * KG) * BK, i);
     const unsigned char* as = smem + cur * (A_BYTES + B_BYTES);
     const unsigned char* bs = as + A_BYTES;
     typedef typename GeneralLayout<SMALL>::F F;
@@ -397,7 +411,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
               acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
           }
     }
-    if (kt + 1 < nk) lstore(cur ^ 1);
+    if (kt + 1 < nk) lstore(cur ^ 1, (i + 1) % PRE);
     __syncthreads();
   }
 
@@ -410,11 +424,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
 #pragma unroll
     for (int g = 1; g < KG; ++g) acc[0][0] += part[(g - 1) * NT + tid];
   }
-  TileCtx c;
-  c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
-  c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
-  c.slice = t.slice; c.slices = t.slices;
-  const typename Epi::Pre pre = epi.template preload<L>(c, d);
+  if constexpr (PRE == 1) pre = epi.template preload<L>(c, d);
   epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
 }
 template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG = 1>

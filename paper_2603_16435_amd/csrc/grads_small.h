@@ -9,7 +9,7 @@
 // on each other, and their sums are added in order through LDS.  dS is formed in registers, in the arithmetic of kept_ds_f32_kernel, once per
 // block of columns: H / 32 or H / 64 times for dX, H / 64 for dW.
 // 356 tokens, H 128, V 1024: transposes, dS, the contractions in tiles of 64 x 16 through LDS and the sum of dX's slices took 27 us of a call of 50.6 us; this
-// launch takes 9.7 and, with the combine inside the loss launch, the call 35.1.
+// launch takes 7 of 28 (3.7 until its sums are formed, bound by the exponentials, 3 until the slowest wavefront's have been added).
 #pragma once
 #include "epilogues.h"
 
@@ -27,49 +27,51 @@ __device__ __attribute__((always_inline)) inline float small_ds(float z, bool ta
   return ct * ((target ? 1.f : 0.f) - fast_exp<float>(z * zs - lse));
 }
 
-// sums of the wavefronts, in order -> out(row, column, sum) of the block
+// sums of the wavefronts, in a fixed tree -> out(row, column, sum) of the block; a thread has one element at most, row small_row()
+__device__ inline int small_row() { return (((int)threadIdx.x >> 6 & 3) << 2) + ((int)threadIdx.x & 3); }
 template <int NB, class Out>
 __device__ __attribute__((always_inline)) inline void small_reduce(const floatx4 (&acc)[NB], float* part, Out out) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = threadIdx.x;
 #pragma unroll
   for (int j = 0; j < NB; ++j) *reinterpret_cast<floatx4*>(part + ((wave * NB + j) * 64 + lane) * 4) = acc[j];
   __syncthreads();
-  for (int q = threadIdx.x; q < NB * 256; q += kGradWaves * 64) {
-    float s[kGradWaves];
+  if (q >= NB * 256) return;
+  float s[kGradWaves];
 #pragma unroll
-    for (int w = 0; w < kGradWaves; ++w) s[w] = part[w * NB * 256 + q];
+  for (int w = 0; w < kGradWaves; ++w) s[w] = part[w * NB * 256 + q];
 #pragma unroll
-    for (int o = 1; o < kGradWaves; o <<= 1)
+  for (int o = 1; o < kGradWaves; o <<= 1)
 #pragma unroll
-      for (int w = 0; w < kGradWaves; w += 2 * o) s[w] += s[w + o];
-    const int l = (q >> 2) & 63;
-    out(((l >> 4) << 2) + (q & 3), (q >> 8) * 16 + (l & 15), s[0]);
-  }
+    for (int w = 0; w < kGradWaves; w += 2 * o) s[w] += s[w + o];
+  out(small_row(), (q >> 8) * 16 + (q >> 2 & 15), s[0]);
 }
 
-template <int NBX>
-__global__ __launch_bounds__(kGradWaves * 64, 8) void small_grads_kernel(SmallGrads s) {
+// Workgroup `block` of the launch.  NBX: blocks of 16 columns of a dX workgroup; U: pieces whose loads go out together (two of 16 for dX, one for dW).
+template <int NBX, int U>
+__device__ __attribute__((always_inline)) inline void small_grads(const SmallGrads& s, int block) {
   __shared__ __attribute__((aligned(16))) float part[kGradWaves * kGradNBW * 256];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), r = lane & 15, g = lane >> 4;
   const int n_real = *s.j.n_real, V = s.j.V, H = s.H;
   const float zs = s.j.zs;
-  if ((int)blockIdx.x < s.dx_blocks) {                  // ---- 16 tokens x 16 NBX columns, K = vocabulary
-    constexpr int NB = NBX;
-    const int t0 = (int)(blockIdx.x / s.x_cols) * 16, h0 = (int)(blockIdx.x % s.x_cols) * 16 * NB;
+  if (block < s.dx_blocks) {                            // ---- 16 tokens x 16 NBX columns, K = vocabulary
+    constexpr int NB = NBX, E = 8 * U;
+    const int t0 = block / s.x_cols * 16, h0 = block % s.x_cols * 16 * NB;
+    const int t = t0 + r, out_row = s.row_map[t0 + small_row()];        // (the token arrays have room past the last)
+    const int yt = s.j.ids_c[t];
+    const float lset = s.j.lse_c[t], cc = s.j.c_c[t];
     if (t0 >= n_real) return;
-    const int t = t0 + r;
     const bool valid = t < n_real;
-    const int y = valid ? s.j.ids_c[t] : -1;
-    const float lse = valid ? s.j.lse_c[t] : 0.f, ct = valid ? s.j.c_c[t] * zs : 0.f;
+    const int y = valid ? yt : -1;
+    const float lse = valid ? lset : 0.f, ct = valid ? cc * zs : 0.f;
     floatx4 acc[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int v0 = wave * 32; v0 < V; v0 += kGradWaves * 32) {
-      float a[8], b[8][NB];
+    for (int v0 = wave * 4 * E; v0 < V; v0 += kGradWaves * 4 * E) {
+      float a[E], b[E][NB];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < E; ++e) {
         const int v = v0 + 16 * (e >> 2) + 4 * g + (e & 3);
-        a[e] = s.kept[(int64_t)v * s.ld + t];           // (the array has room up to the next multiple of 256 of both extents)
+        a[e] = v < V ? s.kept[(int64_t)v * s.ld + t] : 0.f;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           const int h = h0 + j * 16 + r;
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(kGradWaves * 64, 8) void small_grads_kernel(SmallGr
         }
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < E; ++e) {
         const int v = v0 + 16 * (e >> 2) + 4 * g + (e & 3);
         const float ds = small_ds(a[e], v == y, ct, lse, zs), x = valid && v < V ? ds : 0.f;
 #pragma unroll
@@ -85,34 +87,46 @@ __global__ __launch_bounds__(kGradWaves * 64, 8) void small_grads_kernel(SmallGr
       }
     }
     small_reduce<NB>(acc, part, [&](int row, int col, float v) __attribute__((always_inline)) {
-      if (t0 + row < n_real && h0 + col < H) s.dX[(int64_t)s.row_map[t0 + row] * H + h0 + col] = v;
+      if (t0 + row < n_real && h0 + col < H) s.dX[(int64_t)out_row * H + h0 + col] = v;
     });
   } else {                                              // ---- 16 vocabulary entries x 64 columns, K = tokens
     constexpr int NB = kGradNBW;
-    const int cols = (H + 16 * NB - 1) / (16 * NB), q = (int)blockIdx.x - s.dx_blocks;
+    const int cols = (H + 16 * NB - 1) / (16 * NB), q = block - s.dx_blocks;
     const int m0 = q / cols * 16, h0 = q % cols * 16 * NB, v = m0 + r;
     floatx4 acc[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int t0 = wave * 16; t0 < n_real; t0 += kGradWaves * 16) {
-      const int t = t0 + 4 * g;                         // the lane's four tokens (the arrays have room past the last)
-      const floatx4 z = *reinterpret_cast<const floatx4*>(s.kept + (int64_t)v * s.ld + t);
-      const floatx4 lse = *reinterpret_cast<const floatx4*>(s.j.lse_c + t), c = *reinterpret_cast<const floatx4*>(s.j.c_c + t);
-      const int4 y = *reinterpret_cast<const int4*>(s.j.ids_c + t), row = *reinterpret_cast<const int4*>(s.row_map + t);
-      const int ye[4] = {y.x, y.y, y.z, y.w}, re[4] = {row.x, row.y, row.z, row.w};
-      float b[4][NB];
+    for (int t0 = wave * 16; t0 < n_real; t0 += kGradWaves * 16 * U) {
+      floatx4 z[U], lse[U], c[U];
+      int4 y[U], row[U];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int u = 0; u < U; ++u) {
+        const int tb = t0 + u * kGradWaves * 16, t = (tb < n_real ? tb : t0) + 4 * g;     // the lane's four tokens
+        z[u] = *reinterpret_cast<const floatx4*>(s.kept + (int64_t)v * s.ld + t);
+        lse[u] = *reinterpret_cast<const floatx4*>(s.j.lse_c + t); c[u] = *reinterpret_cast<const floatx4*>(s.j.c_c + t);
+        y[u] = *reinterpret_cast<const int4*>(s.j.ids_c + t); row[u] = *reinterpret_cast<const int4*>(s.row_map + t);
+      }
+      float b[U][4][NB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          const int h = h0 + j * 16 + r;
-          b[e][j] = t + e < n_real && h < H ? s.X[(int64_t)re[e] * H + h] : 0.f;
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + u * kGradWaves * 16 + 4 * g, re[4] = {row[u].x, row[u].y, row[u].z, row[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const int h = h0 + j * 16 + r;
+            b[u][e][j] = t + e < n_real && h < H ? s.X[(int64_t)re[e] * H + h] : 0.f;
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + u * kGradWaves * 16 + 4 * g, ye[4] = {y[u].x, y[u].y, y[u].z, y[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float ds = small_ds(z[u][e], v == ye[e], c[u][e] * zs, lse[u][e], zs), x = t + e < n_real && v < V ? ds : 0.f;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b[u][e][j], acc[j], 0, 0, 0);
         }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float ds = small_ds(z[e], v == ye[e], c[e] * zs, lse[e], zs), x = t + e < n_real && v < V ? ds : 0.f;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b[e][j], acc[j], 0, 0, 0);
       }
     }
     small_reduce<NB>(acc, part, [&](int rr, int col, float x) __attribute__((always_inline)) {

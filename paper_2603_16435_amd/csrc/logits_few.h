@@ -13,16 +13,17 @@ namespace rlk {
 
 constexpr int kFewTokens = 128;
 
-template <int BN>      // tokens per workgroup: 64 or 128
-__global__ __launch_bounds__(256, 1)
-void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, GemmDims d, EpiFwd<bf16_t> epi) {
-  constexpr int BM = 128, BK = 64, MB = 8, NB = BN / 64, STAGES = 4;
+constexpr int kFewStages = 4;
+template <int BN> constexpr int few_lds_bytes() { return kFewStages * (128 + BN) * kSlabBytes; }
+// The work of workgroup `tile` of the launch, N tokens whose rows of X are in `rows`, their sampled tokens in `ids`.  BN: tokens per workgroup, 64 or 128.
+template <int BN>
+__device__ __attribute__((always_inline)) inline void logits_few_tile(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, const GemmDims& d, const EpiFwd<bf16_t>& epi,
+                                                                      int tile, int N, const int* rows, const int* ids, unsigned char* smem) {
+  constexpr int BM = 128, BK = 64, MB = 8, NB = BN / 64, STAGES = kFewStages;
   constexpr int A_BYTES = BM * kSlabBytes, STAGE = A_BYTES + BN * kSlabBytes, LA = BM / 32, LB = BN / 32, LOADS = LA + LB;   // loads per slab and wavefront
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int left = *d.n_real, N = left < d.N ? left : d.N;
   if (N <= 0) return;
-  const int K = d.K, nk = (K + BK - 1) / BK, m0 = blockIdx.x * BM;
+  const int K = d.K, nk = (K + BK - 1) / BK, m0 = tile * BM;
 
   const bf16_t* wbase = W + (int64_t)(m0 < d.M ? m0 : 0) * d.lda;       // (a half tile of nothing but padding: any rows)
   unsigned off[LOADS];
@@ -33,7 +34,7 @@ void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ 
     chunk[j] = (lane & 7) ^ ((lr >> 1) & 7);
     int r;
     if (j < LA) { const int last = (m0 < d.M ? d.M - m0 : d.M) - 1; r = lr < last ? lr : last; }
-    else r = d.b_rows[lr < N ? lr : N - 1];
+    else r = rows[lr < N ? lr : N - 1];
     off[j] = (unsigned)(((int64_t)r * (j < LA ? d.lda : d.ldb) + chunk[j] * 8) * 2);      // (128 rows of X: far below 4 GiB)
   }
   auto issue = [&](int kt) __attribute__((always_inline)) {
@@ -51,10 +52,10 @@ void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ 
 
   TileCtx c;
   c.m0 = m0; c.n0 = wave * (BN / 4);
-  c.Mv = d.M; c.Nv = N; c.lane = lane; c.wm = 0; c.wn = wave; c.tile_m = blockIdx.x; c.tile_n = 0; c.tid = tid; c.slice = 0; c.slices = 1;
+  c.Mv = d.M; c.Nv = N; c.lane = lane; c.wm = 0; c.wn = wave; c.tile_m = tile; c.tile_n = 0; c.tid = tid; c.slice = 0; c.slices = 1;
   int y[NB];
 #pragma unroll
-  for (int bj = 0; bj < NB; ++bj) { const int n = c.n0 + Layout16::col(bj, lane); y[bj] = n < N ? epi.ids_c[n] : -1; }
+  for (int bj = 0; bj < NB; ++bj) { const int n = c.n0 + Layout16::col(bj, lane); y[bj] = n < N ? ids[n] : -1; }
 
   floatx4 acc[MB][NB];
 #pragma unroll

@@ -41,7 +41,7 @@ constexpr int kBM = 256, kBN = 256;
 // kernel), or 256 x 16 where the large ones would leave CUs without work.  MFMA-bound: 128-141 TFLOP/s, 102-109 in the general kernel, whose
 // loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K and the logits
 // recomputed: 5.25 ms, 6.2 in the general kernel; with its 256 x 256 tiles 17.9 (27 dX
-// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us (35 since small batches have a backward of their own, grads_small.h), 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
+// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us (28 since small batches have a backward of their own, grads_small.h), 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
@@ -392,19 +392,20 @@ struct SmallPrep {
 // inclusive, over the first n lanes (fewer steps for few)
 __device__ inline int wave_scan_max(int x, int n) { for (int o = 1; o < 64 && o < n; o <<= 1) { const int y = __shfl_up(x, o); if ((int)(threadIdx.x & 63) >= o) x = max(x, y); } return x; }
 __device__ inline int wave_scan_sum(int x, int n) { for (int o = 1; o < 64 && o < n; o <<= 1) { const int y = __shfl_up(x, o); if ((int)(threadIdx.x & 63) >= o) x += y; } return x; }
-__global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f, AdvJob adv) {
-  constexpr int kWords = kSmallRows / 64, kPer = kSmallRows / 1024;
+template <int NT, int ROWS>       // threads of the workgroup, most rows
+__device__ inline void prep_small(const SmallPrep& s, const RowFill& f, const AdvJob& adv) {
+  constexpr int kWords = ROWS / 64, kPer = (ROWS + NT - 1) / NT, W = NT / 64;
   __shared__ unsigned long long good[kWords], bad[kWords];
   __shared__ int good_before[kWords + 1], bad_before[kWords + 1];        // rows in the words before a word
-  __shared__ int sh_y[kSmallRows];
-  __shared__ int sh_g[kSmallSeqs], sh_cu[kSmallSeqs + 1], sh_len[1024], sh_at[kSmallSeqs + 1];
+  __shared__ int sh_y[kPer * NT];
+  __shared__ int sh_g[kSmallSeqs], sh_cu[kSmallSeqs + 1], sh_len[NT], sh_at[kSmallSeqs + 1];
   __shared__ float sh_r[kSmallSeqs];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   int y[kPer];
   bool on[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {                             // (all loads in flight together)
-    const int r = k * 1024 + t;
+    const int r = k * NT + t;
     on[k] = false; y[k] = -1;
     if (r < s.R) { on[k] = s.mask[r]; y[k] = s.ids[r]; }
   }
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
   if (s.stats && t < (int)(sizeof(rl_stats) / 4)) reinterpret_cast<int32_t*>(s.stats)[t] = 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int r = k * 1024 + t;
+    const int r = k * NT + t;
     if (r - lane >= s.R) continue;
     const bool ok = y[k] >= 0 && y[k] < s.V;
     const unsigned long long gm = __ballot(on[k] && ok), bm = __ballot(on[k] && !ok);
@@ -427,11 +428,11 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
       for (int q = 0; q < 8; ++q) if (f.p[q]) f.p[q][r] = f.v[q];
   }
   __syncthreads();
-  if (w == 8 || w == 9) {
-    static_assert(kWords == 64, "a word per lane");
-    const int words = (s.R + 63) / 64, n = wave_scan_sum(lane < words ? __popcll(w == 8 ? good[lane] : bad[lane]) : 0, words);
-    int* before = w == 8 ? good_before : bad_before;
-    before[lane + 1] = n;
+  if (w == W / 2 || w == W / 2 + 1) {
+    static_assert(kWords <= 64, "a word per lane");
+    const int words = (s.R + 63) / 64, n = wave_scan_sum(lane < words ? __popcll(w == W / 2 ? good[lane] : bad[lane]) : 0, words);
+    int* before = w == W / 2 ? good_before : bad_before;
+    if (lane < kWords) before[lane + 1] = n;
     if (lane == 0) before[0] = 0;
   }
   // sequences: a valid range at or behind every earlier offset (see prep_init_kernel), of a valid prompt
@@ -465,8 +466,8 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
     }
   }
   __syncthreads();
-  const int sub = s.B < 16 ? 16 / s.B : 1;                     // wavefronts per sequence, 64 rows in turn
-  for (int u = w; u < s.B * sub; u += 16) {
+  const int sub = s.B < W ? W / s.B : 1;                     // wavefronts per sequence, 64 rows in turn
+  for (int u = w; u < s.B * sub; u += W) {
     const int i = u / sub;
     if (sh_len[i] == 0) continue;
     const int a = sh_cu[i], b = sh_cu[i + 1], at = sh_at[i] - rank(good, good_before, a);
@@ -482,8 +483,92 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
     }
   }
   if (adv.blocks)
-    for (int p = w; p < adv.P; p += 16) advantages_of_prompt(p, s.B, adv, sh_g, sh_r);
-  if (s.chunks.desc) build_chunks(s.seq_len, s.B, s.chunks, s.ctrl, s.stats, sh_len);
+    for (int p = w; p < adv.P; p += W) advantages_of_prompt(p, s.B, adv, sh_g, sh_r);
+  if constexpr (ROWS == kSmallRows)
+    if (s.chunks.desc) build_chunks(s.seq_len, s.B, s.chunks, s.ctrl, s.stats, sh_len);
+}
+
+__global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f, AdvJob adv) { prep_small<1024, kSmallRows>(s, f, adv); }
+
+// The preparation inside the launch of the logits (logits_small_kernel, logits_few_kernel), for batches of so few rows that every workgroup can work out for itself
+// which ones count: workgroup 0 does the above, for the launches that follow, the others go by their own list in LDS (2 us, about what the two
+// dependent loads of the row map took).  A launch is saved: scoring of 99 tokens, H 2048, V 32000 46.7 -> 42.4 us; f32 loss of 356 tokens, H 128, V 1024 35.1 -> 30.3.
+template <int ROWS> struct LocalRows {
+  int n, rows[ROWS], ids[ROWS];
+  int a[kSmallSeqs], b[kSmallSeqs], count[ROWS / 64];
+};
+template <int NT, int ROWS>
+__device__ inline void local_rows(const SmallPrep& s, LocalRows<ROWS>& l) {
+  constexpr int kPer = (ROWS + NT - 1) / NT;
+  const int t = threadIdx.x, lane = t & 63;
+  int y[kPer];
+  bool on[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int r = k * NT + t;
+    on[k] = false; y[k] = -1;
+    if (r < s.R) { on[k] = s.mask[r]; y[k] = s.ids[r]; }
+  }
+  if (t < 64) {                                                // (as there: a valid range at or behind every earlier offset, of a valid prompt)
+    int a = INT32_MIN, b = 0, g = 0;
+    if (t < s.B) { a = s.cu[t]; b = s.cu[t + 1]; if (s.group_idx) g = s.group_idx[t]; }
+    const int hi = wave_scan_max(a, s.B);
+    const bool ok = a >= 0 && a <= b && b <= s.R && a >= hi && (!s.group_idx || (g >= 0 && g < s.P));
+    l.a[t] = ok ? a : 0; l.b[t] = ok ? b : 0;
+  }
+  __syncthreads();
+  unsigned long long m[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int r = k * NT + t;
+    bool in = false;
+    for (int i = 0; i < s.B; ++i) in |= r >= l.a[i] && r < l.b[i];
+    m[k] = __ballot(in && on[k] && y[k] >= 0 && y[k] < s.V);
+    if (lane == 0 && r < ROWS) l.count[r >> 6] = __popcll(m[k]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int r = k * NT + t;
+    int at = 0;
+    for (int q = 0; q < (r >> 6) && q < ROWS / 64; ++q) at += l.count[q];       // (the kept sequences are in the order of their rows)
+    if (m[k] >> lane & 1) {
+      const int c = at + __popcll(m[k] & ((1ull << lane) - 1ull));
+      l.rows[c] = r; l.ids[c] = y[k];
+    }
+  }
+  if (t == 0) { int n = 0; for (int q = 0; q < ROWS / 64; ++q) n += l.count[q]; l.n = n; }
+  __syncthreads();
+}
+
+// Logits of a few tokens (bf16), see logits_few.h.  PREP: with the preparation.
+template <int BN, bool PREP>
+__global__ __launch_bounds__(256, 1)
+void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, GemmDims d, EpiFwd<bf16_t> epi, SmallPrep s, RowFill f, AdvJob adv) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[few_lds_bytes<BN>()];
+  if constexpr (PREP) {
+    if (blockIdx.x == 0) { prep_small<256, kFewTokens>(s, f, adv); return; }
+    __shared__ LocalRows<kFewTokens> l;
+    local_rows<256>(s, l);
+    logits_few_tile<BN>(W, X, d, epi, (int)blockIdx.x - 1, l.n, l.rows, l.ids, smem);
+  } else {
+    const int left = *d.n_real;
+    logits_few_tile<BN>(W, X, d, epi, blockIdx.x, left < d.N ? left : d.N, d.b_rows, epi.ids_c, smem);
+  }
+}
+
+// Logits of a small f32 batch with the preparation: the general kernel's narrow tiles by sixteen wavefronts, four slabs on their way.  (A's loads ahead of local_rows
+// as well: 29.0 us of that call instead of 27.9.)
+constexpr int kLocalRows = 1024;
+template <class Epi>
+__global__ __launch_bounds__(1024)
+void logits_small_kernel(const float* __restrict__ W, const float* __restrict__ X, GemmDims d, Epi epi, SmallPrep s, RowFill f, AdvJob adv) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[general_lds_bytes<float, kBM, kF32SmallBN, 1>()];
+  if (blockIdx.x == 0) { prep_small<1024, kLocalRows>(s, f, adv); return; }
+  __shared__ LocalRows<kLocalRows> l;
+  local_rows<1024>(s, l);
+  d.n_real = &l.n; d.b_rows = l.rows; epi.ids_c = l.ids;
+  gemm_nt_general_tile<float, Epi, kBM, kF32SmallBN, 16, 1, 1, 4>(W, X, d, epi, (int)blockIdx.x - 1, smem);
 }
 
 // one wavefront per row; rows that count are left alone (the dX epilogue writes them)
@@ -704,7 +789,8 @@ struct LossJob {
   const ChunkDesc* desc;                // only the sequences of this chunk
   float* adv_out; int32_t* seq_len_out;
   float *loss, *d_log_z, *seq_loss_out;
-  CombineJob comb;                      // part == nullptr: lse_combine_kernel has been there
+  CombineJob comb;                      // loss_fold_kernel
+  int finish_later;                     // a workgroup of the next launch adds the sequences up (small_grads_kernel)
 };
 // Up to kFinishSeqs sequences, the workgroup that forms the last one's loss adds them up as well; with more, the release that every workgroup
 // then owes the others costs as much as a launch or more (256 sequences 16 us against 15, 20000 469 against 46).
@@ -731,9 +817,9 @@ __device__ inline void finish_loss(const LossJob& j) {
   __shared__ float sh_t[kFinishSeqs];
   add_up_loss(j);
   if (!j.d_log_z) return;
-  for (int i = threadIdx.x; i < j.B; i += kLossThreads) { sh_g[i] = j.group_idx[i]; sh_t[i] = j.gterm[i]; }
+  for (int i = threadIdx.x; i < j.B; i += blockDim.x) { sh_g[i] = j.group_idx[i]; sh_t[i] = j.gterm[i]; }
   __syncthreads();
-  for (int p = threadIdx.x; p < j.P; p += kLossThreads) {
+  for (int p = threadIdx.x; p < j.P; p += blockDim.x) {
     double s = 0.0;
     if (j.objective == RL_OBJ_FLOW)
 #pragma unroll 8
@@ -920,7 +1006,7 @@ __device__ inline void sequence_loss_and_finish(const LossJob& j, int i) {
     if (i >= j.desc->seq_end) return;
   }
   sequence_loss<FOLD>(j, i);
-  if (j.B > kFinishSeqs) return;
+  if (j.B > kFinishSeqs || j.finish_later) return;
   if (threadIdx.x == 0) {                 // (it wrote the sequence's terms)
     __threadfence();
     sh_last = atomicAdd(&j.ctrl->done, 1) == j.B - 1;
@@ -993,6 +1079,13 @@ __global__ __launch_bounds__(kLossThreads) void loss_fold_kernel(LossJob j, cons
   const int b = blockIdx.x;
   if (b < j.B) { sequence_loss_and_finish<true>(j, b); return; }
   zero_masked_row((int64_t)(b - j.B) * 4 + (threadIdx.x >> 6), cpos, dX, R, H);
+}
+
+// The backward of such a batch, see grads_small.h; workgroup 0 adds up the loss (as the last workgroup of the loss launch did at the cost of 3 us).  U = 2: for launches that leave a CU to each workgroup.
+template <int NBX, int U>
+__global__ __launch_bounds__(kGradWaves * 64, U == 1 ? 8 : 4) void small_grads_kernel(SmallGrads s, LossJob j) {
+  if (blockIdx.x == 0) { if (j.finish_later) finish_loss(j); return; }
+  small_grads<NBX, U>(s, (int)blockIdx.x - 1);
 }
 
 // The same for bf16 with 16-byte accesses on both sides (cols % 8 == 0, 16-byte aligned rows; rows_padded % 8 == 0, tiled
@@ -1264,6 +1357,11 @@ static void launch_gemm(const bf16_t* A, const bf16_t* B, const GemmDims& d, con
 // 2048 tokens, H 64, V 1024: 47 us; with dX in the same launch 17 + 47 -> 36; 16 k tokens, V 2000 435 -> 193; 356 tokens, H 128, V 1024, both 29 -> 22).
 static bool few_small_tiles(int M, int N) { return (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kF32Slots; }
 
+// f32 logits in so few tiles of 256 x 16 that each has a CU to itself: sixteen wavefronts share one instead of four
+static bool few_forward_tiles(int M, int N, int K) {
+  return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + kBM - 1) / kBM) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
+}
+
 template <class Epi> constexpr bool kIsForward = false;
 template <bool KEEP> constexpr bool kIsForward<EpiFwd<float, KEEP>> = true;
 template <class Tune, class Epi>
@@ -1296,8 +1394,7 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
     }
   }
   if constexpr (kIsForward<Epi>) {
-    // Logits in so few tiles that each has a CU to itself: sixteen wavefronts share one instead of four.
-    if (bn == kF32SmallBN && tm * tn <= kHotSlots) {
+    if (few_forward_tiles(d.M, d.N, d.K)) {
       gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 16, 1><<<tiles, 1024, 0, s>>>(A, B, d, epi);
       return;
     }
@@ -1371,32 +1468,52 @@ static Ptrs carve(void* ws, const Plan& p) {
   return q;
 }
 
-// whether a row output shares memory with what the preparation reads of the rows
-static bool on_prep_inputs(const rl_batch* b, const Plan& p, const void* out) {
+// whether an output (of `size` bytes) shares memory with what the preparation reads
+static bool on_prep_inputs(const rl_batch* b, const Plan& p, const void* out, size_t size) {
   auto meets = [&](const void* in, size_t bytes) {
     const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(in);
-    return out && o < i + bytes && i < o + 4 * (size_t)p.R;
+    return out && in && o < i + bytes && i < o + size;
   };
-  return meets(b->token_ids, 4 * (size_t)p.R) || meets(b->mask, (size_t)p.R) || meets(b->cu_seqlens, 4 * ((size_t)p.B + 1));
+  return meets(b->token_ids, 4 * (size_t)p.R) || meets(b->mask, (size_t)p.R) || meets(b->cu_seqlens, 4 * ((size_t)p.B + 1)) || meets(b->group_idx, 4 * (size_t)p.B);
 }
+
+// The preparation as the launch of the logits does it, if it does (on).
+struct PrepJob { bool on; SmallPrep s; RowFill f; AdvJob adv; };
+
+// bf16 logits in tiles of 128 rows, see logits_few.h, where their rounds of 256 CUs are worth less than those of the 256-row tiles: an odd number of
+// rounds.  100 tokens, H 2048: V 40000 (313 tiles, two rounds against one of twice their length) 57 us in the hot kernel, 67 in the other; V 80000 124 and 111,
+// V 100000 (four against two) 142 and 142; 30 tokens at the 7B head 294 and 224, 128 tokens, H 4096, V 151936 335 and 324.  (H by the same rule
+// as there, so that a token's bits do not depend on the batch.)
+static bool few_tokens(const rl_batch* b, const Plan& p) {
+  return p.dtype == RL_BF16 && !p.stash && !p.keep && p.R <= kFewTokens && (p.tiles_v + 127) / 128 % 2 && !small_k<EpiFwd<bf16_t>>(p.H) &&
+         (reinterpret_cast<uintptr_t>(b->weight) | reinterpret_cast<uintptr_t>(b->hidden)) % 16 == 0;
+}
+static bool small_logits(const Plan& p) { return p.dtype == RL_F32 && p.n_chunks == 1 && p.R <= kLocalRows && few_forward_tiles(p.V, p.Tc, p.H); }
 
 // prep: row outputs cleared (rows that do not count read 0 / -1), advantages, counts, compaction, chunk records
 static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int32_t* group_idx, const rl_outputs& out, const AdvJob& adv,
-                     hipStream_t s) {
+                     PrepJob& job, hipStream_t s) {
   ProfScope ps(RL_PROF_PREP, s);
+  job.on = false;
   RowFill f{};
   int nf = 0;
   auto clear = [&](void* a, int v) { f.p[nf] = static_cast<int32_t*>(a); f.v[nf++] = v; };
   // (the last three may take the place of what the compaction reads, e.g. target_col that of token_ids: they are then cleared after it)
-  const bool late = on_prep_inputs(b, p, out.target_col) || on_prep_inputs(b, p, out.entropy) || on_prep_inputs(b, p, out.target_logit);
+  const size_t rows4 = 4 * (size_t)p.R;
+  const bool late = on_prep_inputs(b, p, out.target_col, rows4) || on_prep_inputs(b, p, out.entropy, rows4) || on_prep_inputs(b, p, out.target_logit, rows4);
   auto clear_last = [&]() { clear(out.target_col, -1); clear(out.entropy, 0); clear(out.target_logit, 0); };
   clear(q.cpos, -1); clear(out.row_map, -1);
   clear(out.logprob, 0); clear(out.lse, 0); clear(out.coeff, 0);
   if (!late) clear_last();
   if (!late && p.R <= kSmallRows && p.B <= kSmallSeqs && (!adv.blocks || p.P <= kSmallPrompts)) {
-    prep_small_kernel<<<1, 1024, 0, s>>>(SmallPrep{b->mask, b->token_ids, b->cu_seqlens, group_idx, (int)p.R, p.V, p.P, p.B, q.seq_len, q.cstart, q.row_map,
-                                                   q.ids_c, q.cpos, out.row_map, q.ctrl, ChunkJob{p.stash ? q.desc : nullptr, p.n_desc, p.Tc, p.max_len},
-                                                   out.stats}, f, adv);
+    job = PrepJob{small_logits(p) || few_tokens(b, p),
+                  SmallPrep{b->mask, b->token_ids, b->cu_seqlens, group_idx, (int)p.R, p.V, p.P, p.B, q.seq_len, q.cstart, q.row_map, q.ids_c, q.cpos, out.row_map, q.ctrl,
+                            ChunkJob{p.stash ? q.desc : nullptr, p.n_desc, p.Tc, p.max_len}, out.stats}, f, adv};
+    // (there, outputs are cleared while other workgroups still read the inputs: with one in the place of another the preparation goes first)
+    for (const void* o : {(const void*)out.row_map, (const void*)out.logprob, (const void*)out.lse, (const void*)out.coeff})
+      if (on_prep_inputs(b, p, o, rows4)) job.on = false;
+    if (on_prep_inputs(b, p, out.stats, sizeof(rl_stats)) || on_prep_inputs(b, p, out.group_count, 4 * (size_t)p.P)) job.on = false;
+    if (!job.on) prep_small_kernel<<<1, 1024, 0, s>>>(job.s, f, adv);
     return;
   }
   const int64_t fill = (p.R + kInitThreads - 1) / kInitThreads;
@@ -1416,7 +1533,7 @@ static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int3
 
 template <class T>
 static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* logp_out, float* lse_out, float* ent_out,
-                        float* zy_out, int32_t* ycol_out, bool fold, hipStream_t s) {
+                        float* zy_out, int32_t* ycol_out, bool fold, const PrepJob& prep, hipStream_t s) {
   const T* X = static_cast<const T*>(b->hidden);
   const T* W = static_cast<const T*>(b->weight);
   for (int ch = 0; ch < p.n_chunks; ++ch) {
@@ -1428,19 +1545,19 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
     {
       ProfScope ps(RL_PROF_GEMM_FWD, s);
       if constexpr (sizeof(T) == 2) {
-        // Tiles of 128 rows, see logits_few.h, where their rounds of 256 CUs are worth less than those of the 256-row tiles: an odd number of
-        // rounds.  100 tokens, H 2048: V 40000 (313 tiles, two rounds against one of twice their length) 57 us in the hot kernel, 67 in the other; V 80000 124 and 111,
-        // V 100000 (four against two) 142 and 142; 30 tokens at the 7B head 294 and 224, 128 tokens, H 4096, V 151936 335 and 324.  (H by the same rule
-        // as there, so that a token's bits do not depend on the batch.)
-        few = !p.keep && p.R <= kFewTokens && (p.tiles_v + 127) / 128 % 2 && !small_k<EpiFwd<T>>(p.H) &&
-              (reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(X)) % 16 == 0;
+        few = few_tokens(b, p);
         if (few) {
           const EpiFwd<T> e{q.ids_c, q.zy, q.part, kFewTokens, p.V, p.inv_tau, q.ycol, nullptr};
-          if (p.R <= 64) logits_few_kernel<64><<<2 * p.tiles_v, 256, 0, s>>>(W, X, d, e);
-          else logits_few_kernel<128><<<2 * p.tiles_v, 256, 0, s>>>(W, X, d, e);
+          auto kern = prep.on ? (p.R <= 64 ? logits_few_kernel<64, true> : logits_few_kernel<128, true>) : p.R <= 64 ? logits_few_kernel<64, false> : logits_few_kernel<128, false>;
+          kern<<<2 * p.tiles_v + (prep.on ? 1 : 0), 256, 0, s>>>(W, X, d, e, prep.s, prep.f, prep.adv);
         }
+      } else if (prep.on) {
+        d.b_rows = nullptr; d.n_real = nullptr;                // (lists of the workgroups)
+        const int tiles = launch_tiles(p.tiles_v, (p.Tc + kF32SmallBN - 1) / kF32SmallBN);
+        if (p.keep) logits_small_kernel<<<tiles + 1, 1024, 0, s>>>(W, X, d, EpiFwd<T, true>{nullptr, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, prep.s, prep.f, prep.adv);
+        else logits_small_kernel<<<tiles + 1, 1024, 0, s>>>(W, X, d, EpiFwd<T>{nullptr, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, prep.s, prep.f, prep.adv);
       }
-      if (few) {}
+      if (few || prep.on) {}
       else if (p.keep) launch_gemm<TuneLogits>(W, X, d, EpiFwd<T, true>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, q.kept}, s);
       else launch_gemm<TuneLogits>(W, X, d, EpiFwd<T>{q.ids_c, q.zy, q.part, p.Tc, p.V, p.inv_tau, q.ycol, nullptr}, s);
     }
@@ -1455,7 +1572,7 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
 }
 
 template <class T>
-static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* d_hidden, float* d_weight, bool xt_done, hipStream_t s) {
+static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* d_hidden, float* d_weight, bool xt_done, const LossJob& loss, hipStream_t s) {
   const T* X = static_cast<const T*>(b->hidden);
   const T* W = static_cast<const T*>(b->weight);
   T* WT = static_cast<T*>(q.wt); T* XT = static_cast<T*>(q.xt);
@@ -1474,9 +1591,10 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       ProfScope ps(RL_PROF_GEMM_BWD, s);
       // (blocks of 32 columns where those of dX are one round of the CUs at most, else of 64)
       const int rows = p.Tc / 16, nbx = rows * ((p.H + 31) / 32) <= kHotSlots ? 2 : 4, xc = (p.H + 16 * nbx - 1) / (16 * nbx), nx = rows * xc;
-      const int wc = (p.H + 16 * kGradNBW - 1) / (16 * kGradNBW);
-      (nbx == 2 ? small_grads_kernel<2> : small_grads_kernel<4>)<<<nx + (p.V + 15) / 16 * wc, kGradWaves * 64, 0, s>>>(
-          SmallGrads{{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau}, q.kept, p.Tc, X, W, q.row_map, p.H, dX, d_weight, xc, nx});
+      const int n = nx + (p.V + 15) / 16 * ((p.H + 16 * kGradNBW - 1) / (16 * kGradNBW));
+      auto kern = nbx == 4 ? small_grads_kernel<4, 1> : n <= kHotSlots ? small_grads_kernel<2, 2> : small_grads_kernel<2, 1>;
+      kern<<<n + 1, kGradWaves * 64, 0, s>>>(
+          SmallGrads{{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau}, q.kept, p.Tc, X, W, q.row_map, p.H, dX, d_weight, xc, nx}, loss);
       return;
     }
   for (int ch = 0; ch < p.n_chunks; ++ch) {
@@ -1565,7 +1683,7 @@ static void run_finalize(const LossJob& j, hipStream_t s) {
 static LossJob loss_job(const rl_batch* b, const rl_params* prm, int objective, const Plan& p, const Ptrs& q, const rl_outputs* out,
                         const ChunkDesc* desc) {
   return LossJob{objective, q.logp_c, b->old_logprob, b->ref_logprob, q.row_map, q.cstart, q.adv, b->group_idx, b->log_z, p.B, p.P, loss_opts(prm),
-                 q.ctrl, q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, desc, out->advantages, out->seq_len, out->loss, out->d_log_z, out->seq_loss, CombineJob{}};
+                 q.ctrl, q.seq_loss, q.gterm, q.c_c, out->coeff, out->stats, desc, out->advantages, out->seq_len, out->loss, out->d_log_z, out->seq_loss, CombineJob{}, 0};
 }
 
 // Single-pass variant of forward + loss + backward (bf16 hot kernels): chunks are made of whole
@@ -1767,9 +1885,10 @@ rl_status rl_token_logprob_tempered(const rl_batch* b, float temperature, float*
   Ptrs q = carve(ws, p);
   rl_outputs out{};
   out.logprob = logprob; out.lse = lse;
-  run_prep(b, p, q, nullptr, out, AdvJob{}, s);
-  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
-  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
+  PrepJob prep;
+  run_prep(b, p, q, nullptr, out, AdvJob{}, prep, s);
+  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, prep, s);
+  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, prep, s);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
@@ -1802,20 +1921,22 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   Ptrs q = carve(ws, p);
 
   const AdvJob adv{(p.P + kInitThreads / 64 - 1) / (kInitThreads / 64), b->rewards, b->group_idx, p.P, prm->adv_eps, prm->adv_std_ddof, q.adv, out->group_count};
-  run_prep(b, p, q, b->group_idx, *out, adv, s);
+  PrepJob prep;
+  run_prep(b, p, q, b->group_idx, *out, adv, prep, s);
 
   if (p.stash) {
     run_fused(b, prm, objective, p, q, out, s);
     return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
   }
   const bool fold = fold_combine(p);
-  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, false, s);
-  else run_forward<float>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, fold, s);
+  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, false, prep, s);
+  else run_forward<float>(b, p, q, out->logprob, out->lse, out->entropy, out->target_logit, out->target_col, fold, prep, s);
 
   bool prep_done = false;
+  LossJob j = loss_job(b, prm, objective, p, q, out, nullptr);
   {
     ProfScope ps(RL_PROF_LOSS, s);
-    LossJob j = loss_job(b, prm, objective, p, q, out, nullptr);
+    j.finish_later = small_grads(p) && p.B <= kFinishSeqs;
     if (fold) {
       j.comb = CombineJob{q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ycol, q.lse_c, q.logp_c, out->lse, out->logprob, out->entropy, out->target_logit, out->target_col};
       loss_fold_kernel<<<p.B + (bwd ? (p.R + 3) / 4 : 0), kLossThreads, 0, s>>>(j, q.cpos, static_cast<float*>(out->d_hidden), p.R, p.H);
@@ -1827,8 +1948,8 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
     run_finalize(j, s);
   }
   if (bwd) {
-    if (p.dtype == RL_BF16) run_backward<bf16_t>(b, p, q, out->d_hidden, out->d_weight, prep_done, s);
-    else run_backward<float>(b, p, q, out->d_hidden, out->d_weight, prep_done, s);
+    if (p.dtype == RL_BF16) run_backward<bf16_t>(b, p, q, out->d_hidden, out->d_weight, prep_done, j, s);
+    else run_backward<float>(b, p, q, out->d_hidden, out->d_weight, prep_done, j, s);
   }
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
@@ -1880,9 +2001,10 @@ rl_status rl_token_logprob_static(const rl_batch* b, float temperature, float* l
   Ptrs q = carve(ws, p);
   rl_outputs out{};
   out.logprob = logprob; out.lse = lse;
-  run_prep(b, p, q, nullptr, out, AdvJob{}, s);
-  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
-  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, s);
+  PrepJob prep;
+  run_prep(b, p, q, nullptr, out, AdvJob{}, prep, s);
+  if (p.dtype == RL_BF16) run_forward<bf16_t>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, prep, s);
+  else run_forward<float>(b, p, q, logprob, lse, nullptr, nullptr, nullptr, false, prep, s);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
