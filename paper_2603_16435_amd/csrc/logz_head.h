@@ -2,7 +2,7 @@
 //
 //   pooled_p = mean of the prompt's hidden-state rows        logz_pool_kernel   (HBM-bound: reads the rows once)
 //   a_p = W1 pooled_p + b1,  g_p = gelu(a_p)                 logz_hidden_kernel (HBM-bound: W1 streamed once per 16 prompts)
-//   logZ_p = w2 . g_p + b2                                   logz_out_kernel
+//   logZ_p = w2 . g_p + b2                                   logz_out_kernel, few units: by the last workgroup of the hidden layer
 //   backward from d_logZ: db2, db1, dw2, dW1 = sum_p da_p pooled_p^T   logz_bwd_kernel (HBM-bound: writes dW1 once)
 //
 // The hidden states are constants here (no gradient into the language model).  Parameters and
@@ -32,16 +32,20 @@ template <class T, int VEC> __device__ inline void logz_load(const T* p, float (
   }
 }
 
+template <class T, int VEC> struct LogzPiece { typedef uint4 type; };
+template <class T> struct LogzPiece<T, 1> { typedef T type; };
+
 // grid (P, ceil(H / (LANES VEC))): a workgroup of eight wavefronts pools LANES VEC columns of one prompt, 512 / LANES rows at a
-// time, four pieces in flight per lane; f32 sums, merged through LDS in a fixed order.
+// time, four pieces in flight per lane (f32: eight; 8 prompts of 200 to 1100 rows, H 4096: the forward 43.1 -> 41.2 us, bf16 no better); f32 sums, merged through LDS in a fixed order.
 // (One element per lane, 64 columns per workgroup: 22 us on the shape above, 16 bytes per lane: 14 us.)
 template <int VEC> constexpr int logz_pool_lanes() { return VEC == 1 ? 64 : 16; }
 template <class T, int VEC>
-__global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows, int H, const int32_t* cu, float* pooled) {
+__global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows, int H, const int32_t* cu, float* pooled, int* done) {
   constexpr int LANES = logz_pool_lanes<VEC>(), SLICES = 512 / LANES;
   __shared__ float part[SLICES][LANES * VEC + 1];
   const int p = blockIdx.x, c = threadIdx.x % LANES, slice = threadIdx.x / LANES;
   const int h = (blockIdx.y * LANES + c) * VEC;
+  if (blockIdx.y == 0 && p % 16 == 0 && threadIdx.x == 0) done[p / 16] = 0;
   int64_t a = cu[p], b = cu[p + 1];
   if (a < 0) a = 0;
   if (b > rows) b = rows;
@@ -53,15 +57,22 @@ __global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows
   if (h < H) {
     const T* x = X + h;
     int64_t r = a + slice;
-    for (; r + 3 * SLICES < b; r += 4 * SLICES) {
-      float v[4][VEC];
+    auto rows_at = [&](auto n) __attribute__((always_inline)) {
+      constexpr int N = decltype(n)::value;
+      typename LogzPiece<T, VEC>::type v[N];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) logz_load<T, VEC>(x + (r + SLICES * u) * H, v[u]);
+      for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const typename LogzPiece<T, VEC>::type*>(x + (r + SLICES * u) * H);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < N; ++u) {
+        float f[VEC];
+        logz_load<T, VEC>(reinterpret_cast<const T*>(&v[u]), f);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) s[u][i] += v[u][i];
-    }
+        for (int i = 0; i < VEC; ++i) s[u & 3][i] += f[i];
+      }
+      r += N * SLICES;
+    };
+    if constexpr (sizeof(T) == 4) while (r + 7 * SLICES < b) rows_at(std::integral_constant<int, 8>());
+    while (r + 3 * SLICES < b) rows_at(std::integral_constant<int, 4>());
     for (; r < b; r += SLICES) {
       float v[VEC];
       logz_load<T, VEC>(x + r * H, v);
@@ -90,12 +101,20 @@ __global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows
 // through LDS.  (Sixteen accumulators leave one workgroup per CU: 64 prompts at H = M = 5120 took 1.2 % longer.)  VEC: rows are
 // 16-byte aligned (else element loads).  (The vector-FMA form with the pooled states in LDS was bound by its LDS reads: 94 us against
 // 18 us on the shape above.)
+// part_z != nullptr: log Z too.  A workgroup adds up its units' w2 g and the one that is last of its 16 prompts the workgroups'.  These sums go past the
+// L2s (agent-scope accesses), each waited for before the count that announces it: with a release fence, which writes back all that the L2 holds, the call took
+// 61.8 us instead of 60.8.  A launch is saved: forward + backward of one prompt of 20 rows, H 100, M 64 13.6 -> 11.3 us, 4 of 800, H = M = 1024 15.7 -> 15.2.  Many
+// workgroups count one after the other: 40 prompts, H 300, M 3000 14.3 -> 17.6 (the forward), on the shape above no gain.  So up to kLogzSumUnits units and 16 prompts (33 prompts, M 500
+// 30.1 -> 30.5).
+constexpr int kLogzSumUnits = 1024;
+constexpr int kLogzWaves = 8;
 template <bool VEC>
-__global__ __launch_bounds__(512, 4) void logz_hidden_kernel(const float* W1, const float* b1, const float* pooled, int P, int H, int M,
-                                                          float* a_out, float* g_out) {
-  __shared__ float part[8][16][17];
+__global__ __launch_bounds__(kLogzWaves * 64, 4) void logz_hidden_kernel(const float* W1, const float* b1, const float* pooled, int P, int H, int M,
+                                                          float* a_out, float* g_out, const float* w2, const float* b2, float* part_z, int* done, float* log_z) {
+  constexpr int WAVES = kLogzWaves, STEP = 16 * WAVES;
+  __shared__ float part[WAVES][16][17];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15, kq = lane >> 4;
-  const int j0 = blockIdx.x * 16, p0 = blockIdx.y * 16;
+  const int j0 = blockIdx.x * 16, p0 = blockIdx.y * 16, np = P < 16 ? P : 16;
   const int j = j0 + row < M ? j0 + row : M - 1, p = p0 + row < P ? p0 + row : P - 1;       // (rows past the end: not written)
   const float* w = W1 + (int64_t)j * H;
   const float* x = pooled + (int64_t)p * H;
@@ -115,10 +134,10 @@ __global__ __launch_bounds__(512, 4) void logz_hidden_kernel(const float* W1, co
   for (int u = 0; u < 12; ++u)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[u][e] = 0.f;
-  for (int k0 = wave * 16; k0 < H; k0 += 8 * 128) {
+  for (int k0 = wave * 16; k0 < H; k0 += 8 * STEP) {
     floatx4 a[8], b[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) { a[u] = load(w, k0 + 128 * u + 4 * kq); b[u] = load(x, k0 + 128 * u + 4 * kq); }
+    for (int u = 0; u < 8; ++u) { a[u] = load(w, k0 + STEP * u + 4 * kq); b[u] = load(x, k0 + STEP * u + 4 * kq); }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -132,23 +151,49 @@ __global__ __launch_bounds__(512, 4) void logz_hidden_kernel(const float* W1, co
   __syncthreads();
   if (threadIdx.x < 256) {
     const int u = threadIdx.x & 15, q = threadIdx.x >> 4;
-    float s[8];
+    float s[WAVES];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s[k] = part[k][q][u];
+    for (int k = 0; k < WAVES; ++k) s[k] = part[k][q][u];
 #pragma unroll
-    for (int o = 1; o < 8; o <<= 1)
+    for (int o = 1; o < WAVES; o <<= 1)
 #pragma unroll
-      for (int k = 0; k < 8; k += 2 * o) s[k] += s[k + o];
+      for (int k = 0; k < WAVES; k += 2 * o) s[k] += s[k + o];
+    float z = 0.f;
     if (j0 + u < M && p0 + q < P) {
-      const float v = s[0] + b1[j0 + u];
-      a_out[(int64_t)(p0 + q) * M + j0 + u] = v; g_out[(int64_t)(p0 + q) * M + j0 + u] = gelu_f(v);
+      const float v = s[0] + b1[j0 + u], gv = gelu_f(v);
+      a_out[(int64_t)(p0 + q) * M + j0 + u] = v; g_out[(int64_t)(p0 + q) * M + j0 + u] = gv;
+      if (part_z) z = w2[j0 + u] * gv;
     }
+    if (part_z) {
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) z += __shfl_xor(z, o);
+      if (u == 0 && q < np) __hip_atomic_store(part_z + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * np + q, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (!part_z) return;
+  __shared__ int last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) last = __hip_atomic_fetch_add(done + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  const int q = threadIdx.x & 15, t = threadIdx.x >> 4;                                     // prompt; workgroups t, t + 4 WAVES, ...
+  const float* z = part_z + (int64_t)blockIdx.y * gridDim.x * np + (q < np ? q : 0);
+  float s = 0.f;
+#pragma unroll 4
+  for (int k = t; k < (int)gridDim.x; k += 4 * WAVES) s += __hip_atomic_load(z + (int64_t)k * np, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  s += __shfl_xor(s, 16); s += __shfl_xor(s, 32);
+  if (lane < 16) part[wave][0][lane] = s;
+  __syncthreads();
+  if (threadIdx.x < 16 && p0 + q < P) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) v += part[k][0][q];
+    log_z[p0 + q] = v + b2[0];
   }
 }
 
-// one workgroup per prompt: logZ_p = w2 . g_p + b2.  Latency only: many threads, their loads ahead of the additions.  (Left to the last workgroup of the hidden
-// layer it saves the launch and costs more in releases: 61.8 us for forward + backward on the shape above against 60.8.)
-// (1024 threads from 1025 units on, 256 up to there: with M = 3584 the call takes 57.4 us instead of 61.0, but with few units half a microsecond more.)
+// one workgroup per prompt: logZ_p = w2 . g_p + b2, where the hidden layer has not done it.  Latency only: many threads, their loads ahead of the additions.
 constexpr int kLogzOutThreads = 1024;
 __global__ __launch_bounds__(kLogzOutThreads) void logz_out_kernel(const float* g, const float* w2, const float* b2, int M, float* log_z) {
   __shared__ float sh[kLogzOutThreads / 64];
@@ -170,7 +215,10 @@ __global__ __launch_bounds__(kLogzOutThreads) void logz_out_kernel(const float* 
 // also writes db2.  With more than 32 prompts or more than 256 VEC columns the da are formed again for every pass over
 // the columns (a few hundred values).  grid (ceil(M / 8), ceil(H / (256 VEC))); the column blocks other than the first skip the sums.
 // (da by a kernel of its own and single-element stores: 11 + 37 us on the shape above, fused with 16-byte stores: 16.5 us.)
-template <int VEC>
+// NT: the stores are non-temporal, where dW1 is whole lines of 128 bytes in every row and too large for the L2s to keep (logz_nontemporal): on buffers that no cache holds,
+// forward + backward 57.9 -> 54.6 us, 64 prompts at H = M = 5120 227 -> 215; H 300, M 3000, rows of 1200 bytes, loses 0.8 of 11.1, and a dW1 of 4 MB gains nothing.
+static inline bool logz_nontemporal(int M, int H, const float* dW1) { return H % 32 == 0 && reinterpret_cast<uintptr_t>(dW1) % 128 == 0 && (int64_t)M * H >= (1 << 21); }
+template <int VEC, bool NT>
 __global__ __launch_bounds__(256) void logz_bwd_kernel(const float* d, const float* a, const float* g, const float* w2, const float* pooled,
                                                        int P, int M, int H, float* dW1, float* db1, float* dw2, float* db2) {
   __shared__ float da[32][8], dg[32][8];
@@ -212,20 +260,20 @@ __global__ __launch_bounds__(256) void logz_bwd_kernel(const float* d, const flo
     for (int u = 0; u < 8; ++u)
       if (j0 + u < M) {
         float* o = dW1 + (int64_t)(j0 + u) * H + h;
-        if constexpr (VEC == 4) { floatx4 v; v[0] = s[u][0]; v[1] = s[u][1]; v[2] = s[u][2]; v[3] = s[u][3]; *reinterpret_cast<floatx4*>(o) = v; }
+        if constexpr (VEC == 4) { floatx4 v; v[0] = s[u][0]; v[1] = s[u][1]; v[2] = s[u][2]; v[3] = s[u][3]; if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<floatx4*>(o)); else *reinterpret_cast<floatx4*>(o) = v; }
         else o[0] = s[u][0];
       }
   if (first && t < 16 && j0 + (t & 7) < M) (t < 8 ? db1 : dw2)[j0 + (t & 7)] = sum;
   if (first && blockIdx.x == 0 && t == 16) { float b = 0.f; for (int p = 0; p < P; ++p) b += d[p]; db2[0] = b; }
 }
 
-struct LogzPlan { size_t off_pooled, off_a, off_g, total; };
+struct LogzPlan { size_t off_pooled, off_a, off_g, off_part, total; };
 
 static inline LogzPlan logz_plan(int P, int H, int M) {
   LogzPlan q; size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += (bytes + 255) & ~(size_t)255; return at; };
   q.off_pooled = take(4 * (size_t)P * H); q.off_a = take(4 * (size_t)P * M); q.off_g = take(4 * (size_t)P * M);
-  take(4 * (size_t)P * M);        // room that no kernel uses: the size is part of the interface, and what was too small a workspace stays so
+  q.off_part = take(4 * (size_t)P * M);        // counts and partial sums of log Z (more than they need: the size is part of the interface)
   q.total = o;
   return q;
 }

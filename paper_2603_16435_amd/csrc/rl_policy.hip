@@ -2037,8 +2037,10 @@ rl_status rl_logz_head_forward(const void* prompt_hidden, int32_t dtype, int64_t
   (void)hipGetLastError();
   unsigned char* w = static_cast<unsigned char*>(ws);
   float* pooled = (float*)(w + q.off_pooled); float* a = (float*)(w + q.off_a); float* g = (float*)(w + q.off_g);
+  // (one float per prompt and workgroup of the hidden layer, of the P M there are; with fewer than 32 units the counts might not fit)
+  int* done = (int*)(w + q.off_part); float* part_z = P <= 16 && M >= 32 && M <= kLogzSumUnits ? (float*)(w + q.off_part) + (P + 15) / 16 : nullptr;
   const bool vec_x = H % (dtype == RL_BF16 ? 8 : 4) == 0 && reinterpret_cast<uintptr_t>(prompt_hidden) % 16 == 0;
-  auto pool = [&](auto kern, auto* X, int cols) { kern<<<dim3(P, (H + cols - 1) / cols), 512, 0, s>>>(X, rows, H, cu_prompt, pooled); };
+  auto pool = [&](auto kern, auto* X, int cols) { kern<<<dim3(P, (H + cols - 1) / cols), 512, 0, s>>>(X, rows, H, cu_prompt, pooled, done); };
   if (dtype == RL_BF16) {
     const bf16_t* X = static_cast<const bf16_t*>(prompt_hidden);
     if (vec_x) pool(logz_pool_kernel<bf16_t, 8>, X, 128); else pool(logz_pool_kernel<bf16_t, 1>, X, 64);
@@ -2047,9 +2049,9 @@ rl_status rl_logz_head_forward(const void* prompt_hidden, int32_t dtype, int64_t
     if (vec_x) pool(logz_pool_kernel<float, 4>, X, 64); else pool(logz_pool_kernel<float, 1>, X, 64);
   }
   const dim3 gh((M + 15) / 16, (P + 15) / 16);
-  if (H % 4 == 0 && reinterpret_cast<uintptr_t>(W1) % 16 == 0) logz_hidden_kernel<true><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
-  else logz_hidden_kernel<false><<<gh, 512, 0, s>>>(W1, b1, pooled, P, H, M, a, g);
-  logz_out_kernel<<<P, M > kLogzOutThreads ? kLogzOutThreads : 256, 0, s>>>(g, w2, b2, M, log_z);
+  if (H % 4 == 0 && reinterpret_cast<uintptr_t>(W1) % 16 == 0) logz_hidden_kernel<true><<<gh, 64 * kLogzWaves, 0, s>>>(W1, b1, pooled, P, H, M, a, g, w2, b2, part_z, done, log_z);
+  else logz_hidden_kernel<false><<<gh, 64 * kLogzWaves, 0, s>>>(W1, b1, pooled, P, H, M, a, g, w2, b2, part_z, done, log_z);
+  if (!part_z) logz_out_kernel<<<P, M > kLogzOutThreads ? kLogzOutThreads : 256, 0, s>>>(g, w2, b2, M, log_z);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
@@ -2066,9 +2068,9 @@ rl_status rl_logz_head_backward(const float* d_log_z, int32_t P, int32_t H, int3
   unsigned char* w = static_cast<unsigned char*>(ws);
   float* pooled = (float*)(w + q.off_pooled); float* a = (float*)(w + q.off_a); float* g = (float*)(w + q.off_g);
   if (H % 4 == 0 && reinterpret_cast<uintptr_t>(dW1) % 16 == 0)
-    logz_bwd_kernel<4><<<dim3((M + 7) / 8, (H + 1023) / 1024), 256, 0, s>>>(d_log_z, a, g, w2, pooled, P, M, H, dW1, db1, dw2, db2);
+    (logz_nontemporal(M, H, dW1) ? logz_bwd_kernel<4, true> : logz_bwd_kernel<4, false>)<<<dim3((M + 7) / 8, (H + 1023) / 1024), 256, 0, s>>>(d_log_z, a, g, w2, pooled, P, M, H, dW1, db1, dw2, db2);
   else
-    logz_bwd_kernel<1><<<dim3((M + 7) / 8, (H + 255) / 256), 256, 0, s>>>(d_log_z, a, g, w2, pooled, P, M, H, dW1, db1, dw2, db2);
+    logz_bwd_kernel<1, false><<<dim3((M + 7) / 8, (H + 255) / 256), 256, 0, s>>>(d_log_z, a, g, w2, pooled, P, M, H, dW1, db1, dw2, db2);
   return hipGetLastError() == hipSuccess ? RL_OK : RL_ERR_HIP;
 }
 
