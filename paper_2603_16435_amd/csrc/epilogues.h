@@ -61,7 +61,8 @@ struct EpiFwd {
 #pragma unroll
     for (int bj = 0; bj < 8; ++bj) {
       const int n = c.n0 + L::col(bj, c.lane);
-      p.y[bj] = n < c.Nv ? ids_c[d.chunk_start + n] : -1;
+      const int y = ids_c[d.chunk_start + (n < c.Nv ? n : c.Nv - 1)];        // (no branch around a load)
+      p.y[bj] = n < c.Nv ? y : -1;
     }
     return p;
   }
@@ -316,7 +317,8 @@ struct EpiFwdStash {
 #pragma unroll
     for (int bj = 0; bj < 8; ++bj) {
       const int n = c.n0 + perm_col(bj, cc);
-      p.rl[bj] = (n < c.Nv) ? ref_l2e[d.chunk_start + n] : __builtin_inff();   // column without a token: e = exp2(-inf) = 0
+      const float rl = ref_l2e[d.chunk_start + (n < c.Nv ? n : c.Nv - 1)];
+      p.rl[bj] = n < c.Nv ? rl : __builtin_inff();                             // column without a token: e = exp2(-inf) = 0
     }
     return p;
   }
@@ -450,11 +452,13 @@ struct EpiDS {
     if constexpr (sizeof(T) == 2 && L::kBlk == 16) {
 #pragma unroll
       for (int bj = 0; bj < 8; ++bj) {
-        const int n = c.n0 + perm_col(bj, c.lane & 15), t = d.chunk_start + n;
+        const int n = c.n0 + perm_col(bj, c.lane & 15);
         const bool valid = n < c.Nv;
-        p.y[bj] = valid ? ids_c[t] : -1;
-        p.lse[bj] = valid ? lse_c[t] : 3.0e38f;           // invalid token: p = exp(z - huge) = 0 and
-        p.ct[bj] = valid ? c_c[t] : 0.f;                  // c = 0, so every dS entry becomes 0
+        const int t = d.chunk_start + (valid ? n : c.Nv - 1), y = ids_c[t];
+        const float lse = lse_c[t], ct = c_c[t];
+        p.y[bj] = valid ? y : -1;
+        p.lse[bj] = valid ? lse : 3.0e38f;                // invalid token: p = exp(z - huge) = 0 and
+        p.ct[bj] = valid ? ct : 0.f;                      // c = 0, so every dS entry becomes 0
       }
     }
     return p;

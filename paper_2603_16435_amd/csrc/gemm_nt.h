@@ -63,7 +63,6 @@ struct GemmDims {
   int chunk_start;        // first compacted row of this chunk
   const int* chunk;       // if set, device pair {first compacted row, rows} of this chunk; replaces n_real / chunk_start,
                           // and the gather tables are then indexed from the chunk's first row
-  int a_tiled, b_tiled;   // hot kernel only: operand stored slab-tiled (see tiled_index) instead of row-major; K is then its full K extent
   int dyn;                // which extent is min(rows left in the chunk, bound): 0 none, 1 M, 2 N, 3 K (rounded up to k_round)
   int k_round;            // dyn == 3: rows beyond the chunk's last that the producers of both operands have zeroed, a power of two
   int zero_if_empty;      // dyn == 3 only: an empty chunk still runs the epilogue (with K = 0) instead of returning
@@ -89,8 +88,9 @@ __device__ inline bool resolve_dims(GemmDims& d, int& M, int& N, int& K) {
   if (!d.dyn) return true;
   int left;
   if (d.chunk) {
-    const int cs = d.chunk[0];
-    left = d.chunk[1];
+    const int2 c = *reinterpret_cast<const int2*>(d.chunk);         // (8-byte aligned)
+    const int cs = c.x;
+    left = c.y;
     d.chunk_start = cs;
     if (d.a_rows) d.a_rows += cs;
     if (d.b_rows) d.b_rows += cs;
@@ -528,7 +528,7 @@ __device__ __attribute__((always_inline)) inline u32x2_t lds_read_tr16(const uns
 //
 // FAR: the gathered B rows span 4 GiB or more, so that 32 bits do not hold a row's offset.
 //
-// Both have slabs whose load addresses are not those of the plain loop, at the end of K; the last six slabs run in a copy of the
+// Both have slabs whose load addresses are not those of the plain loop, at the end of K; the last six slabs (KT: three or four) run in a copy of the
 // loop body that works them out per lane (`tail`), so that the plain loop needs no vector operation for its load addresses.  (With BTR
 // it has others: the 16-bit offset of the transposing reads does not reach B's part of the second stage, 32 address adds per two slabs.)
 __device__ const uint4 kZeroChunk = {0u, 0u, 0u, 0u};
@@ -588,18 +588,29 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   // 256 rows of the tile's first, so the offsets fit; the hidden states, whose rows come through the row map, are addressed from their
   // first row, where they span less than 4 GiB (FAR otherwise: an address per lane; forward of 67 k tokens at the 7B head 56.4 ms that way, 55.8
   // with offsets, scoring of 10 k 8.22 and 8.06).
+  // The rows that are gathered are all fetched before anything is done with one, and nothing in the way asks at run time how an operand is laid out: a
+  // branch between the loads makes eight memory latencies of them, 1.3 us of a tile.
   constexpr bool GB = Epi::kGatherB;
+  constexpr bool TILED = !GB;                                   // dX and dW contract the library's buffers, slab-tiled, the logits the caller's rows
   const bf16_t* ap[8];
   const bf16_t* bp[8];
   unsigned aoff[8], boff[8];
+  int brow_of[8], pf_row = tn * BN + 32 * (tm & 7) + (lane & 31);
+  pf_row = pf_row < N ? pf_row : N - 1;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int lr = wave * 64 + j * 8 + (lane >> 3), r = tn * BN + (Epi::kPermute ? perm_lds_row_b(lr) : lr);
+    brow_of[j] = r < N ? r : N - 1;
+    if constexpr (GB) brow_of[j] = d.b_rows[brow_of[j]];
+  }
+  if constexpr (GB && PFD > 0) pf_row = d.b_rows[pf_row];
   const bf16_t* abase = ATR ? A + tiled_index(0, tm * BM, d.lda)
-                                  : A + (d.a_tiled ? tiled_index(tm * BM, 0, d.K) : (int64_t)(tm * BM) * d.lda);
-  const bf16_t* bbase = BTR ? B + tn * BN : B + (d.b_tiled ? tiled_index(tn * BN, 0, d.K) : (int64_t)(tn * BN) * d.ldb);
+                                  : A + (TILED ? tiled_index(tm * BM, 0, d.K) : (int64_t)(tm * BM) * d.lda);
+  const bf16_t* bbase = BTR ? B + tn * BN : B + (TILED ? tiled_index(tn * BN, 0, d.K) : (int64_t)(tn * BN) * d.ldb);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int lr = wave * 64 + j * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((lr >> 1) & 7);
-    int r;
     if constexpr (ATR) {
       const int p = (wave * 8 + j) * 64 + lane;                  // 16-byte unit of the A slab this lane fills
       const int row = p >> 5, u = p & 31;                        // k-row of the slab, unit inside the row
@@ -607,9 +618,8 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       const int m = tm * BM + (((u >> 1) ^ f) << 4) + ((u & 1) << 3);
       ap[j] = A + tiled_index(row, m, d.lda);
     } else {
-      r = tm * BM + (Epi::kPermute ? perm_lds_row_a(lr) : lr); r = r < M ? r : M - 1;
-      if (d.a_rows) r = d.a_rows[r];
-      ap[j] = A + (d.a_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.lda) + c * 8;
+      int r = tm * BM + (Epi::kPermute ? perm_lds_row_a(lr) : lr); r = r < M ? r : M - 1;
+      ap[j] = A + (TILED ? tiled_index(r, 0, d.K) : (int64_t)r * d.lda) + c * 8;
     }
     if constexpr (BTR) {
       const int p = (wave * 8 + j) * 64 + lane;
@@ -618,15 +628,13 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       int n = tn * BN + (((u >> 1) ^ f) << 4) + ((u & 1) << 3); n = n < N ? n : N - 8;       // (N % 8 == 0)
       bp[j] = B + (int64_t)row * d.ldb + n;
     } else {
-      r = tn * BN + (Epi::kPermute ? perm_lds_row_b(lr) : lr); r = r < N ? r : N - 1;
-      if (d.b_rows) r = d.b_rows[r];
-      bp[j] = B + (d.b_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.ldb) + c * 8;
+      bp[j] = B + (TILED ? tiled_index(brow_of[j], 0, d.K) : (int64_t)brow_of[j] * d.ldb) + c * 8;
     }
     aoff[j] = (unsigned)(ap[j] - abase) * 2u;                   // in bytes
     boff[j] = (unsigned)(bp[j] - (GB ? B : bbase)) * 2u;
   }
-  const int a_ks = d.a_tiled ? 16384 : BK;                                    // elements from one slab to the next
-  const int64_t b_ks = BTR ? (int64_t)BK * d.ldb : d.b_tiled ? 16384 : BK;
+  const int a_ks = TILED ? 16384 : BK;                                    // elements from one slab to the next
+  const int64_t b_ks = BTR ? (int64_t)BK * d.ldb : TILED ? 16384 : BK;
   if constexpr (Epi::kSplit) { abase = uniform_ptr(abase + (int64_t)k_first * a_ks); bbase = uniform_ptr(bbase + (int64_t)k_first * b_ks); }
   // K-major A: slab s is k-rows [64 s, 64 s + 64), i.e. quarter s%4 of row block s/4 of the tiled layout
   auto a_slab = [&](int slab) __attribute__((always_inline)) -> int64_t {
@@ -675,8 +683,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     pf_stride = 0;
   } else if (wave == 0) {
     int r = tm * BM + 64 * (tn & 3) + lane; r = r < M ? r : M - 1;
-    if (d.a_rows) r = d.a_rows[r];
-    pf_ptr = reinterpret_cast<const unsigned char*>(A + (d.a_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.lda));
+    pf_ptr = reinterpret_cast<const unsigned char*>(A + (TILED ? tiled_index(r, 0, d.K) : (int64_t)r * d.lda));
     pf_stride = a_ks * 2;
   } else if (BTR && PFD > 0 && wave == 1) {                   // K-major B: likewise, an eighth per M-tile
     const int q = 32 * (tm & 7) + (lane & 31);
@@ -684,9 +691,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
     pf_ptr = reinterpret_cast<const unsigned char*>(B + (int64_t)(q >> 2) * d.ldb + n);
     pf_stride = (int)b_ks * 2;
   } else if (wave == 1) {
-    int r = tn * BN + 32 * (tm & 7) + (lane & 31); r = r < N ? r : N - 1;
-    if (d.b_rows) r = d.b_rows[r];
-    pf_ptr = reinterpret_cast<const unsigned char*>(B + (d.b_tiled ? tiled_index(r, 0, d.K) : (int64_t)r * d.ldb));
+    pf_ptr = reinterpret_cast<const unsigned char*>(B + (TILED ? tiled_index(pf_row, 0, d.K) : (int64_t)pf_row * d.ldb));
     pf_stride = (int)b_ks * 2;
   } else {
     pf_ptr = reinterpret_cast<const unsigned char*>(A);
@@ -817,6 +822,13 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
   if (nk > 0) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) issue1(true, 0, stage0, j);
+  }
+  // (the accumulators are cleared while these are on their way: left to itself the compiler does it when they have landed, half a microsecond)
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) asm volatile("" : "+a"(acc[i][j]));
+  if (nk > 0) {
     __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
     __syncthreads();
 #pragma unroll
@@ -835,9 +847,10 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_bf16_tile(const bf
       }
     }
     // nk is even but with KT (K is a multiple of 128).  Slabs that reach past the end of an operand are among the
-    // last four (b_k_rows), or the last (KT), and loads run up to two slabs ahead: the last six slabs.
+    // last four (b_k_rows), or the last (KT), and loads run up to two slabs ahead: the last six slabs, or three.
     const bool has_tail = KT || (BTR && (k_first + nk) * BK > d.b_k_rows);
-    const int plain = !has_tail ? nk : nk > 6 ? (nk - 6) & ~1 : 0;
+    constexpr int LAST = KT ? 3 : 6;
+    const int plain = !has_tail ? nk : nk > LAST ? (nk - LAST) & ~1 : 0;
     int kt = 0;
     for (; kt < plain; kt += 2) {
       slab(false, stage0, stage1, kt, pf0);

@@ -1422,7 +1422,7 @@ static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, Gem
     gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew, 0, both ? kStepRows : 0);
     if (both) gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDXStep, EpiDW, TuneDWStep, false><<<n1 + n2, 256, 0, s>>>(E, WT, dx, ex, n1, E, XT, dw, ew, kStepRows, 0);
   } else {
-    dx.ldb = dx.N; dx.b_tiled = 0; dx.b_k_rows = dw.M;
+    dx.ldb = dx.N; dx.b_k_rows = dw.M;
     gemm_nt_bf16_pair_kernel<EpiDX<bf16_t>, TuneDX, EpiDW, TuneDW, true><<<n1 + n2, 256, 0, s>>>(E, W, dx, ex, n1, E, XT, dw, ew, 0, 0);
   }
   splitk_reduce_kernel<bf16_t><<<512, 256, 0, s>>>(dx, ex, kBM, kBN, kHotStep);
@@ -1619,14 +1619,13 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     // dX = dS W: A = dS [Tc][Vp], B = W^T [H][Vp]
     GemmDims dx{};
     dx.M = p.Tc; dx.N = p.H; dx.K = p.Vp; dx.lda = p.Vp; dx.ldb = p.Vp;
-    dx.n_real = &q.ctrl->n_real; dx.chunk_start = c0; dx.dyn = 1; dx.group_m = TuneDX::kBand; dx.a_tiled = dx.b_tiled = p.tiled;
+    dx.n_real = &q.ctrl->n_real; dx.chunk_start = c0; dx.dyn = 1; dx.group_m = TuneDX::kBand;
     EpiDX<T> ex{q.row_map, dX, p.H, p.H, nullptr, q.split};
     // dW (+)= dS^T X: B = X^T [H][Tc]; A = dS^T, for bf16 read out of dS itself as a K-major operand (K = Tc is a multiple of 256
     // and the workspace is aligned: always the hot kernel), for f32 the stored copy [Vp][Tc]
     GemmDims dw{};
     dw.M = p.V; dw.N = p.H; dw.K = p.Tc; dw.lda = p.tiled ? p.Vp : p.Tc; dw.ldb = p.Tc;
     dw.n_real = &q.ctrl->n_real; dw.chunk_start = c0; dw.dyn = 3; dw.k_round = p.tiled ? 256 : kF32SmallBN; dw.group_m = TuneDW::kBand;
-    dw.a_tiled = dw.b_tiled = p.tiled;
     dw.zero_if_empty = (ch == 0);
     EpiDW ew{d_weight, p.H, p.V, p.H, ch > 0 ? 1 : 0};
     if constexpr (sizeof(T) == 2) {
@@ -1739,11 +1738,11 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     {  // dX = diag(-c/Z) E' W and dW (+)= E'^T (diag(-c/Z) X)
       GemmDims dx{};
       dx.M = p.Tc; dx.N = p.H; dx.K = p.Vp; dx.lda = p.Vp; dx.ldb = p.Vp;
-      dx.chunk = chunk; dx.dyn = 1; dx.group_m = TuneDX::kBand; dx.a_tiled = dx.b_tiled = 1;
+      dx.chunk = chunk; dx.dyn = 1; dx.group_m = TuneDX::kBand;
       EpiDX<T> ex{q.row_map, dX, p.H, p.H, q.scale, q.split};
       GemmDims dw{};
       dw.M = p.V; dw.N = p.H; dw.K = p.Tc; dw.lda = p.Vp; dw.ldb = p.Tc;
-      dw.chunk = chunk; dw.dyn = 3; dw.k_round = 256; dw.zero_if_empty = (k == 0); dw.group_m = TuneDW::kBand; dw.a_tiled = dw.b_tiled = 1;
+      dw.chunk = chunk; dw.dyn = 3; dw.k_round = 256; dw.zero_if_empty = (k == 0); dw.group_m = TuneDW::kBand;
       EpiDW ew{out->d_weight, p.H, p.V, p.H, k > 0 ? 1 : 0};
       ProfScope ps(RL_PROF_GEMM_BWD, s);
       launch_dx_dw(E, W, p.k_major_w ? nullptr : WT, dx, ex, XT, dw, ew, s);
