@@ -768,29 +768,41 @@ struct EpiDW {
   __device__ void keep_alive() const { dW[0] = 0.f; }
   float* dW; int64_t ldw; int V, H; int accumulate;
 
-  template <int MB, int NB, bool ACC, bool EDGE>
+  // Hot kernel.  A lane holds four columns of one row in each of two neighbouring blocks, a lane pair thus two rows: it swaps halves, so that a
+  // store writes eight rows in whole lines of 128 bytes instead of sixteen in halves, and the lines leave in non-temporal stores (NT) where the array has
+  // its rows on lines.  256 KB a tile, with few slabs a tile this is what it waits for: 747 tokens at the 7B head (twelve slabs), the whole call 2390 us, whole
+  // lines 2316, non-temporal as well 2258 (non-temporal halves 2485); 11.5 k tokens 29.73 ms and 29.57.  Rows off the lines, H 1160: 1822 us, whole lines 1822, non-temporal 1829.
+  template <int MB, int NB, bool ACC, bool EDGE, bool NT>
   __device__ __attribute__((always_inline)) void rows(floatx4 (&acc)[MB][NB], const TileCtx& c) const {
-    const int r = c.lane & 15, n = c.n0 + (c.lane >> 4) * 4;
+    const int r = c.lane & 15, p = r & 1, n = c.n0 + p * 16 + (c.lane >> 4) * 4;
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi) {
-      const int m = c.m0 + bi * 16 + r;
-      if (EDGE && m >= V) continue;
-      float* p = dW + (int64_t)m * ldw + n;
-      floatx4 old[NB];
+      const int m = c.m0 + bi * 16 + (r & ~1);                     // the pair's first row
+      float* const q[2] = {dW + (int64_t)m * ldw + n, dW + (int64_t)(m + 1) * ldw + n};
+      auto there = [&](int w, int k) __attribute__((always_inline)) { return !EDGE || (m + w < V && n + k * 32 < H); };
+      floatx4 old[2][NB / 2];
       if (ACC) {
 #pragma unroll
-        for (int bj = 0; bj < NB; ++bj) if (!EDGE || n + bj * 16 < H) old[bj] = *reinterpret_cast<const floatx4_any*>(p + bj * 16);
+        for (int k = 0; k < NB / 2; ++k)
+#pragma unroll
+          for (int w = 0; w < 2; ++w) if (there(w, k)) old[w][k] = *reinterpret_cast<const floatx4_any*>(q[w] + k * 32);
       }
 #pragma unroll
-      for (int bj = 0; bj < NB; ++bj) {
-        floatx4 v;
+      for (int k = 0; k < NB / 2; ++k) {
+        floatx4 v[2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc_read<true>(acc[bi][bj], e);
-        if (ACC) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = old[bj][e] + v[e];
+        for (int e = 0; e < 4; ++e) {
+          const float a = acc_read<true>(acc[bi][2 * k], e), b = acc_read<true>(acc[bi][2 * k + 1], e);
+          const float recv = __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(p ? a : b), 0xB1, 0xF, 0xF, true));
+          v[0][e] = p ? recv : a; v[1][e] = p ? b : recv;
+          if (ACC) { v[0][e] = old[0][k][e] + v[0][e]; v[1][e] = old[1][k][e] + v[1][e]; }
         }
-        if (!EDGE || n + bj * 16 < H) *reinterpret_cast<floatx4_any*>(p + bj * 16) = v;
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+          if (there(w, k)) {
+            if (NT) __builtin_nontemporal_store(v[w], reinterpret_cast<floatx4*>(q[w] + k * 32));
+            else *reinterpret_cast<floatx4_any*>(q[w] + k * 32) = v[w];
+          }
       }
     }
   }
@@ -799,10 +811,11 @@ struct EpiDW {
   __device__ __attribute__((always_inline)) void run(typename L::acc_t (&acc)[MB][NB], const TileCtx& c, unsigned char*, const GemmDims&, const Pre&) const {
     if constexpr (AGPR) {
       const bool edge = c.m0 + MB * 16 > V || c.n0 + NB * 16 > H;
+      const bool lines = ldw % 32 == 0 && (reinterpret_cast<uintptr_t>(dW) & 127) == 0;
       if (accumulate) {
-        if (edge) rows<MB, NB, true, true>(acc, c); else rows<MB, NB, true, false>(acc, c);
+        if (edge) rows<MB, NB, true, true, false>(acc, c); else if (lines) rows<MB, NB, true, false, true>(acc, c); else rows<MB, NB, true, false, false>(acc, c);
       } else {
-        if (edge) rows<MB, NB, false, true>(acc, c); else rows<MB, NB, false, false>(acc, c);
+        if (edge) rows<MB, NB, false, true, false>(acc, c); else if (lines) rows<MB, NB, false, false, true>(acc, c); else rows<MB, NB, false, false, false>(acc, c);
       }
       return;
     }
