@@ -51,7 +51,7 @@ constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 constexpr int64_t kKMajorRows = 32768;
 
 // Keeping the logits between forward and backward (recompute mode, batch of one chunk) turns the dS contraction into a pass over memory, for
-// 4 bytes more per logit in the forward.  f32 always does (the logits wait in dS^T's place): 2175 tokens, H 768, V 50257 1323 -> 239 us, forward
+// 4 bytes more per logit in the forward.  f32 always does (the logits wait in dS^T's place): 2175 tokens, H 768, V 50257 1323 -> 137 us, forward
 // 1230 -> 1274.  bf16 in the default mode, with room of its own (4 bytes per row and vocabulary entry), if the workspace has it: batches of up to
 // kKeepRows rows, padding included, since only the device knows the tokens.  At the 7B head that room is 10 GB, as much as the dS of the largest
 // chunk, at V 32000 2 GB: the line is one of memory and drawn for large vocabularies.  Hidden sizes from kKeepH on: the general kernel, which keeps nothing
@@ -1194,7 +1194,7 @@ struct Plan {
   int Tc, Vp, tiles_v, n_chunks;
   bool bwd;
   bool tiled;            // bf16: the work buffers dS/E, W^T, X^T are slab-tiled (hot kernel operands)
-  bool k_major_w;        // dX reads W as it is stored: no W^T is made
+  bool k_major_w;        // dX reads W as it is stored: no W^T is made (f32: dS^T too, no dS)
   bool stash;            // single-pass backward (forward keeps each chunk's unnormalised probabilities)
   bool keep;             // recompute mode, one chunk: the forward keeps the logits, dS is formed from them
   int n_desc, max_len;   // stash: number of chunk records, promised bound on rows per sequence
@@ -1259,6 +1259,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.bwd = bwd;
   p.tiled = (b->dtype == RL_BF16);
   p.k_major_w = p.tiled && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
+  if (b->dtype == RL_F32)          // (256 x 64 tiles of gemm_f32.h: their dX reads dS^T and W K-major)
+    p.k_major_w = bwd && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && tc < (1 << 22) && b->H < (1 << 22) && f32_tile_n(tc, b->H, p.Vp, true) == kF32BN;
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len
@@ -1399,6 +1401,8 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
       return;
     }
   }
+  if constexpr (std::is_same_v<Epi, EpiDX<float>>)
+    if (d.b_k_rows) { gemm_nt_f32_kernel<Epi, false, true><<<tiles, 256, 0, s>>>(A, B, d, epi); return; }        // (k_major_w)
   if (bn == kF32BN && fast) {
     // (K of dW, a number of tokens, is a multiple of 16 only; K of dX, the padded vocabulary, one of 256)
     constexpr bool tail = std::is_same_v<Epi, EpiDW>, whole = std::is_same_v<Epi, EpiDX<float>>;
@@ -1606,13 +1610,15 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     if (p.keep) {
       ProfScope ps(RL_PROF_GEMM_DS, s);
       const KeptJob j{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau};
-      if constexpr (sizeof(T) == 4) kept_ds_f32_kernel<<<(unsigned)((int64_t)(p.Vp / 64) * (p.Tc / 64)), 256, 0, s>>>(j, dST, p.Tc, dS, p.Vp);
-      else kept_ds_kernel<<<dim3((unsigned)(4 * p.tiles_v * (p.Tc / 256)), 2), 256, 0, s>>>(q.kept, j, p.tiles_v, dS, p.Vp);
+      if constexpr (sizeof(T) == 4) {
+        if (p.k_major_w) kept_ds_t_kernel<<<(unsigned)((int64_t)(p.Vp / 32) * (p.Tc / 256)), 256, 0, s>>>(j, dST, p.Tc, p.Vp);
+        else kept_ds_f32_kernel<<<(unsigned)((int64_t)(p.Vp / 64) * (p.Tc / 64)), 256, 0, s>>>(j, dST, p.Tc, dS, p.Vp);
+      } else kept_ds_kernel<<<dim3((unsigned)(4 * p.tiles_v * (p.Tc / 256)), 2), 256, 0, s>>>(q.kept, j, p.tiles_v, dS, p.Vp);
     } else {  // recompute logits, form dS (and dS^T for f32 inputs)
       GemmDims d{};
       d.M = p.V; d.N = p.Tc; d.K = p.H; d.lda = p.H; d.ldb = p.H;
       d.b_rows = q.row_map + c0; d.b_span = p.R; d.n_real = &q.ctrl->n_real; d.chunk_start = c0; d.dyn = 2; d.group_m = TuneLogits::kBand;
-      EpiDS<T> e{q.ids_c, q.lse_c, q.c_c, dS, p.Vp, dST, p.Tc, p.V, p.tiled, p.inv_tau};
+      EpiDS<T> e{q.ids_c, q.lse_c, q.c_c, sizeof(T) == 4 && p.k_major_w ? nullptr : dS, p.Vp, dST, p.Tc, p.V, p.tiled, p.inv_tau};
       ProfScope ps(RL_PROF_GEMM_DS, s);
       launch_gemm<TuneLogits>(W, X, d, e, s);
     }
@@ -1642,7 +1648,8 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       }
       {
         ProfScope ps(RL_PROF_GEMM_DX, s);
-        launch_gemm<TuneDX>(dS, WT, dx, ex, s);
+        if (p.k_major_w) { dx.lda = p.Tc; dx.ldb = p.H; dx.b_k_rows = p.V; }
+        launch_gemm<TuneDX>(p.k_major_w ? dST : dS, p.k_major_w ? W : WT, dx, ex, s);
         splitk_reduce_kernel<T><<<512, 256, 0, s>>>(dx, ex, kBM, f32_tile_n(dx.M, dx.N, dx.K, true), 32);
       }
       ProfScope ps(RL_PROF_GEMM_DW, s);
@@ -1657,7 +1664,7 @@ static bool run_loss_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const
   float *WT = static_cast<float*>(q.wt), *XT = static_cast<float*>(q.xt);
   const int wx = (p.Vp + 63) / 64, xx = (p.Tc + 63) / 64, hy = (p.H + 63) / 64;
   const bool small = small_grads(p);                    // (reads W and X as they are)
-  const int64_t nw = small ? 0 : (int64_t)wx * hy, nx = small ? 0 : (int64_t)xx * hy, n = p.B + nw + nx + (p.R + 3) / 4;
+  const int64_t nw = small || p.k_major_w ? 0 : (int64_t)wx * hy, nx = small ? 0 : (int64_t)xx * hy, n = p.B + nw + nx + (p.R + 3) / 4;
   if (p.dtype != RL_F32 || p.n_chunks != 1 || n >= (1 << 24)) return false;        // (2^32 threads a launch)
   loss_prep_kernel<<<(unsigned)n, kLossThreads, 0, s>>>(
       j, TransposeJob<float>{W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, false}, wx, (int)nw,
