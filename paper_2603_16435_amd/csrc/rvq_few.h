@@ -5,15 +5,21 @@
 // 547 MB, 115 us at the rate of a large copy), and the kernel written for 256 and more vectors spends its time scoring copies
 // of the few there are (324 us; this one: 137).  Here a workgroup takes 16 NV vectors of one group:
 //  * Four scoring wavefronts share the entries of a stage (blocks of 16 in turn).  They read the codebook straight from memory
-//    in MFMA operand layout (A = 16 entries, B = 16 vectors, -|c|^2/2 as the start of the accumulator), 64 entries each at a time,
-//    and always have the next 64 on their way, also across the end of a stage: the codebook does not depend on the codes.
+//    in MFMA operand layout (A = 16 entries, B = 16 vectors, -|c|^2/2 as the start of the accumulator), a round of 64 entries each at a
+//    time (32 with 32 vectors: registers), and have two more rounds on their way, also across the end of a stage: the codebook does not depend on the codes.
 //  * The scores of a stage stay in LDS.  When all are there, every lane compares its own with the vector's largest and lists the
 //    entries within the margin (twice the bound on a float32 score's error, see rvq_encode.h); only those can be the exact arg-min.
 //  * A fifth wavefront settles the stage: one entry listed is the code; several are evaluated in float64 from the stored values,
 //    and if more were listed than the list holds, all entries are.  It also fetches the chosen entries for the
 //    residual update.  It is a wavefront of its own because a wait for these loads would wait for all loads issued
 //    before them too: the scoring wavefronts' loads of the next stage stay in flight meanwhile.
-// Three workgroup barriers per stage, written out (lgkmcnt only) so that they do not wait for loads in flight.
+// Four workgroup barriers per stage, written out (lgkmcnt only) so that they do not wait for loads in flight.
+// What bounds it: a CU takes in about 28 bytes a ns, 4.7 us a stage of 512 entries, and little more than 32 KB of loads wait in its queue: beyond that a wavefront
+// stands still at the load it issues.  Settling a stage takes 2.8 us in which nobody would issue one.  So the last round of a stage is
+// fetched again behind the second barrier, once the chosen entries' loads are out (the third), while they come in: of 111 us 102.  And the registers of a round are all
+// read before its loads are issued: where the norms were used later, the compiler copied them, a wait for everything in flight in each round (136 us -> 111).
+// Non-temporal loads, faster in a stream, lose here (119): a line is taken in two halves.  Other rounds, 64 / 32 entries: three of 32 for 16 vectors 109, of one block for 32 vectors
+// 140 against 135.  256 groups, us before and now: 12 vectors of 16 stages of 512 entries 136 -> 102, of 56 of 1024 774 -> 663, 30 vectors 177 -> 135; 8 groups, 1 vector, 56 of 1024 639 -> 491.
 #pragma once
 #include "rvq_encode.h"
 
@@ -72,7 +78,7 @@ template <int NV>
 __global__ __launch_bounds__(320, 1)
 void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb, const float* __restrict__ cn,
                     int G, int L, int N, int S, int32_t* __restrict__ codes, bf16_t* __restrict__ residual, int32_t* __restrict__ stats) {
-  constexpr int VECS = 16 * NV, U = 4;                            // U: blocks per scoring wavefront and round (64 entries)
+  constexpr int VECS = 16 * NV, U = NV == 1 ? 4 : 2, D = 2;       // U: blocks per scoring wavefront and round (four wavefronts of 64 entries, or of 32)
   __shared__ floatx4 score[kRvqFewScoreBytes / 16];               // [round][block of the wavefront][vector block][wavefront, lane]
   __shared__ u32x4_t bits[VECS][kRvqD / 8], rows[VECS][kRvqD / 8]; // the vectors as stored; the chosen entries
   __shared__ float top[4][VECS], cmx[4];
@@ -91,23 +97,26 @@ void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb,
   const bool scoring = wave < 4;
   u32x4_t ra[NV][4];                                              // [vector block][k-step]: vector l%16, k = 32 ks + 8 (l/16) .. +7
   float rn2[NV];
-  u32x4_t nx[U][4];                                               // the next round's entries and squared norms
-  floatx4 nn[U];
-  // round t of the whole walk: block 16 r + 4 u + wave of stage t / rounds (past the stage's end: its last block, not used)
-  auto fetch = [&](int stage, int r) __attribute__((always_inline)) {
-    const bf16_t* scb = cb + (int64_t)stage * S * kRvqD;
-    const float* scn = cn + (int64_t)stage * S;
+  u32x4_t nx[D][U][4];                                            // the entries and squared norms of the next D rounds
+  floatx4 nn[D][U];
+  // the next round to be fetched, into buffer i: block 16 r + 4 u + wave of its stage (past the stage's end: its last block, not used)
+  int f_stage = 0, f_r = 0;
+  auto fetch = [&](int i) __attribute__((always_inline)) {
+    const int st = f_stage < N ? f_stage : N - 1;                 // (past the end one block again and again, not used: no branch around the loads)
+    const bf16_t* scb = cb + (int64_t)st * S * kRvqD;
+    const float* scn = cn + (int64_t)st * S;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int blk = r * 4 * U + u * 4 + wave; blk = blk < nblk ? blk : nblk - 1;
+      int blk = f_r * 4 * U + u * 4 + wave; blk = f_stage == N ? 0 : blk < nblk ? blk : nblk - 1;
       const bf16_t* ent = scb + (int64_t)(blk * 16 + e16) * kRvqD + kq * 8;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) nx[u][ks] = *reinterpret_cast<const u32x4_t*>(ent + ks * 32);
-      nn[u] = *reinterpret_cast<const floatx4*>(scn + blk * 16 + 4 * kq);
+      for (int ks = 0; ks < 4; ++ks) nx[i][u][ks] = *reinterpret_cast<const u32x4_t*>(ent + ks * 32);
+      nn[i][u] = *reinterpret_cast<const floatx4*>(scn + blk * 16 + 4 * kq);
     }
+    if (++f_r == rounds) { f_r = 0; f_stage = f_stage < N ? f_stage + 1 : N; }
   };
   if (scoring) {
-    fetch(0, 0);
+    fetch(0);
 #pragma unroll
     for (int b = 0; b < NV; ++b) {
       int v = v0 + b * 16 + e16; v = v < L ? v : L - 1;
@@ -120,77 +129,112 @@ void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb,
       }
       rn2[b] = rvq_sum4(a);
     }
+#pragma unroll
+    for (int i = 1; i < D; ++i) fetch(i);
   }
   if (tid < VECS) count[tid] = 0;                                 // (the first append comes after the first barrier)
 
   const float NEG = -__builtin_inff();
-  for (int stage = 0; stage < N; ++stage) {
-    if (scoring) {
-      float mx[NV], cm = 0.f;
+  if (scoring) {
+    float mx[NV], cm = 0.f;
 #pragma unroll
-      for (int b = 0; b < NV; ++b) mx[b] = NEG;
-      for (int r = 0; r < rounds; ++r) {
-        floatx4 acc[U][NV];
+    for (int b = 0; b < NV; ++b) mx[b] = NEG;
+    int r = 0;
+    auto round = [&](int i) __attribute__((always_inline)) {
+      floatx4 acc[U][NV];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          floatx4 h;
+      for (int u = 0; u < U; ++u) {
+        floatx4 h;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) { cm = fmaxf(cm, nn[u][e]); h[e] = -0.5f * nn[u][e]; }
+        for (int e = 0; e < 4; ++e) { cm = fmaxf(cm, nn[i][u][e]); h[e] = -0.5f * nn[i][u][e]; }
+#pragma unroll
+        for (int b = 0; b < NV; ++b) {
+          acc[u][b] = h;
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+            acc[u][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, nx[i][u][ks]), __builtin_bit_cast(bf16x8, ra[b][ks]), acc[u][b], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r * 4 * U + u * 4 + wave < nblk) {                    // (uniform)
 #pragma unroll
           for (int b = 0; b < NV; ++b) {
-            acc[u][b] = h;
+            score[((r * U + u) * NV + b) * 256 + tid] = acc[u][b];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-              acc[u][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, nx[u][ks]), __builtin_bit_cast(bf16x8, ra[b][ks]), acc[u][b], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) mx[b] = fmaxf(mx[b], acc[u][b][e]);
           }
         }
-        {                                                         // the next round, perhaps of the next stage, into the same registers
-          const int t = stage * rounds + r + 1;
-          if (t < total) fetch(r + 1 < rounds ? stage : stage + 1, r + 1 < rounds ? r + 1 : 0);
+      const bool last = ++r == rounds;
+      if (last) {
+        r = 0;
+#pragma unroll
+        for (int b = 0; b < NV; ++b) {
+          const float m = rvq_max4(mx[b]);
+          if (kq == 0) top[wave][b * 16 + e16] = m;
+          mx[b] = NEG;
         }
+        cm = rvq_max4(cm);                                          // (the lanes of a group have the same norms)
+        if (lane == 0) cmx[wave] = cm;
+        rvq_few_barrier();
+        // list the entries that come within the margin of the largest score
+        const float cmax = fmaxf(fmaxf(cmx[0], cmx[1]), fmaxf(cmx[2], cmx[3]));
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (r * 4 * U + u * 4 + wave < nblk) {                  // (uniform)
+        for (int b = 0; b < NV; ++b) {
+          const int v = b * 16 + e16;
+          const float best = fmaxf(fmaxf(top[0][v], top[1][v]), fmaxf(top[2][v], top[3][v]));
+          const float margin = kRvqGamma2 * (sqrtf(rn2[b] * 1.02f * cmax) + 0.5f * cmax);   // (1.02: rn2 is known to one part in 2^7)
+          for (int q0 = 0; q0 < rounds * U; q0 += U) {
+            floatx4 s[U];
 #pragma unroll
-            for (int b = 0; b < NV; ++b) {
-              score[((r * U + u) * NV + b) * 256 + tid] = acc[u][b];
+            for (int u = 0; u < U; ++u) s[u] = score[((q0 + u) * NV + b) * 256 + tid];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) mx[b] = fmaxf(mx[b], acc[u][b][e]);
+            for (int u = 0; u < U; ++u) {
+              const int blk = (q0 + u) * 4 + wave;
+              bool in[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) in[e] = blk < nblk && !(best - s[u][e] > margin);
+              if (in[0] | in[1] | in[2] | in[3])
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (in[e]) {
+                    const int pos = atomicAdd(&count[v], 1);
+                    if (pos < kRvqFewList) cand[v][pos] = blk * 16 + 4 * kq + e;
+                  }
             }
           }
-      }
-#pragma unroll
-      for (int b = 0; b < NV; ++b) {
-        const float m = rvq_max4(mx[b]);
-        if (kq == 0) top[wave][b * 16 + e16] = m;
-      }
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) cm = fmaxf(cm, __shfl_xor(cm, o));
-      if (lane == 0) cmx[wave] = cm;
-    }
-    rvq_few_barrier();
-    if (scoring) {                                                // list the entries that come within the margin of the largest score
-      const float cm = fmaxf(fmaxf(cmx[0], cmx[1]), fmaxf(cmx[2], cmx[3]));
-#pragma unroll
-      for (int b = 0; b < NV; ++b) {
-        const int v = b * 16 + e16;
-        const float best = fmaxf(fmaxf(top[0][v], top[1][v]), fmaxf(top[2][v], top[3][v]));
-        const float margin = kRvqGamma2 * (sqrtf(rn2[b] * 1.02f * cm) + 0.5f * cm);     // (1.02: rn2 is known to one part in 2^7)
-        for (int q = 0; q < rounds * U; ++q) {
-          const int blk = q * 4 + wave;
-          if (blk >= nblk) break;
-          const floatx4 s = score[(q * NV + b) * 256 + tid];
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (!(best - s[e] > margin)) {
-              const int pos = atomicAdd(&count[v], 1);
-              if (pos < kRvqFewList) cand[v][pos] = blk * 16 + 4 * kq + e;
-            }
         }
+        cm = 0.f;
+        rvq_few_barrier();
+        rvq_few_barrier();                                          // (the chosen entries' loads are on their way)
       }
-    }
-    rvq_few_barrier();
-    if (!scoring) {                                               // settle the stage: lane v answers for vector v
+      // into the registers just read: any of these read later would want copies, and a copy waits for all loads on their way
+      asm volatile("" : "+v"(cm) :: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(i);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!last) return;
+      rvq_few_barrier();
+#pragma unroll
+      for (int b = 0; b < NV; ++b) {
+        float a = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          ra[b][ks] = rvq_sub_bf16(ra[b][ks], rows[b * 16 + e16][ks * 4 + kq], a);
+          if (wave == 0) bits[b * 16 + e16][ks * 4 + kq] = ra[b][ks];       // (read again after two more barriers)
+        }
+        rn2[b] = rvq_sum4(a);
+      }
+    };
+    int t = 0;
+    for (; t + D <= total; t += D)
+#pragma unroll
+      for (int i = 0; i < D; ++i) round(i);
+    if (t < total) round(0);
+  } else {
+    for (int stage = 0; stage < N; ++stage) {                     // settle the stage: lane v answers for vector v
+      rvq_few_barrier();
+      rvq_few_barrier();
       const bf16_t* stage_cb = cb + (int64_t)stage * S * kRvqD;
       const int v = lane < VECS ? lane : VECS - 1;
       const int n = count[v];
@@ -230,21 +274,11 @@ void rvq_few_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ cb,
         const int zi = __shfl(z, 4 * i + kq);
         c[i] = *reinterpret_cast<const u32x4_t*>(stage_cb + (int64_t)zi * kRvqD + 8 * e16);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      rvq_few_barrier();
 #pragma unroll
       for (int i = 0; i < VECS / 4; ++i) rows[4 * i + kq][e16] = c[i];
-    }
-    rvq_few_barrier();
-    if (scoring) {
-#pragma unroll
-      for (int b = 0; b < NV; ++b) {
-        float a = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          ra[b][ks] = rvq_sub_bf16(ra[b][ks], rows[b * 16 + e16][ks * 4 + kq], a);
-          if (wave == 0) bits[b * 16 + e16][ks * 4 + kq] = ra[b][ks];       // (read again after two more barriers)
-        }
-        rn2[b] = rvq_sum4(a);
-      }
+      rvq_few_barrier();
     }
   }
   if (residual && wave == 0) {
