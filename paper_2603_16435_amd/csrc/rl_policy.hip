@@ -2087,6 +2087,19 @@ static rl_status rvq_check(int32_t G, int64_t L, int32_t D, int32_t N, int32_t S
   return RL_OK;
 }
 
+// Whether more than 16 vectors of a group are encoded faster by the kernel that takes 32 of them per workgroup than by the one that takes 256 or 512.  Both keep
+// one workgroup on a CU (the other at most two, which slow each other down), 32 on an accelerator die, which the workgroups of a group share: rounds of workgroups times what one
+// takes, us fitted to calls of 8 to 512 groups.  The other kernel now and then looks at a whole stage again, about once in 100 thousand
+// decisions, which takes 130 us: 37 groups of 253 vectors, 16 stages of 512 entries, 325 us with it and 205 without, here 228.  Other kernel and this one, us, 16 stages of 512 entries: 256 groups of 33 to 64 vectors (two rounds) 325 to 332 and 234 to 245, of 96 (three) 332 and 360,
+// 40 of 300 424 and 231, 4 of 1100 310 and 226; 56 of 1024: 160 groups of 50 1265 and 1365, 64 of 140 1234 and 1352, 4 of 1100 1719 and 1345; 40 of 1024, 264 groups of
+// 32 1157 and 1076; 10 of 256, 256 groups of 40 213 and 98; 8 groups of 17, 16 stages of 64 entries 69 and 53, of 128 86 and 54.
+static bool rvq_few_is_faster(int64_t G, int64_t L, int N, int S) {
+  const int64_t die = (G + 7) / 8, big = L > 256 ? 512 : 256;
+  const double rounds = (double)(((L + 31) / 32 * die + 31) / 32), n = (double)((L + big - 1) / big * die);       // of this kernel; workgroups of the other
+  const double d = (double)G * L * N, share = n <= 32 ? 1.0 : n <= 64 ? 1.15 + 0.6 * (n - 33) / 32 : 0.87 * n / 32;
+  return rounds * N * (1.9 + 0.0103 * S) <= share * N * (3.2 + (big == 256 ? 0.017 : 0.024) * S) + 130.0 * d / (d + 1e5);
+}
+
 rl_status rl_rvq_codebook_norms(const void* codebooks, int32_t G, int32_t N, int32_t S, int32_t D, float* norms, void* stream) {
   if (!codebooks || !norms) return RL_ERR_NULL;
   rl_status st = rvq_check(G, 1, D, N, S);
@@ -2111,21 +2124,10 @@ rl_status rl_rvq_encode_counted(const void* vectors, const void* codebooks, cons
   if ((reinterpret_cast<uintptr_t>(vectors) | reinterpret_cast<uintptr_t>(codebooks) | reinterpret_cast<uintptr_t>(residual)) & 15) return RL_ERR_SHAPE;
   (void)hipGetLastError();
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // Few vectors: a kernel that reads each codebook once for 16 or 32 of them and scores nothing else (norms 16 bytes at a time).
-  //  * Up to 16 vectors of a group it is the faster one whatever the number of groups (16 stages of 512 entries, 16 vectors: 256 groups
-  //    332 -> 140 us, 512 groups 435 -> 270).
-  //  * With more it is as long as its workgroups, which read the codebook again, are all on the chip at a time, 32 on an accelerator
-  //    die (the workgroups of a group share one): 32 groups of 256 212 -> 154 us, 128 groups of 64 324 -> 159, one group of 4000 against
-  //    318 us 583.  A second round of them loses to one half-empty round of the other kernel (56 stages of 1024 entries: 160 groups of 50
-  //    1294 against 1774 us, 256 groups of 33 1419 against 1765; 40 of 64: 315 against 404) unless the codebooks of so many groups make
-  //    that one wait for memory (32 vectors, 40 stages of 1024: 264 groups 1205 against 1295, 384 groups 1470 -> 1320, 512 1697 -> 1352).
-  //  * A stage of 64 or 128 entries is over before its three barriers are: 8 groups of 17, 16 stages of 64 entries 68 against 81 us, of
-  //    128 86 against 86, of 192 103 -> 92.  The other kernel now and then looks at a whole stage again, 80 to 140 us; from some 16
-  //    thousand decisions on that is likely enough to outweigh it (8 groups of 48, 40 stages of 128: 384 -> 216).
+  // Few vectors: a kernel that reads each codebook once for 16 or 32 of them and scores nothing else (norms 16 bytes at a time).  Up to 16 vectors of
+  // a group it is the faster one whatever the number of groups; with more its workgroups read the codebook again, and the cheaper one is taken, see rvq_few_is_faster.
   const int nv = L <= 16 ? 1 : 2;
-  const int64_t few_per_die = (L + 16 * nv - 1) / (16 * nv) * (((int64_t)G + 7) / 8);
-  const bool short_stages = S <= 128 && L * S < 6144 && G * L * N < 16384;
-  const bool few = L <= 16 || (few_per_die <= 32 && !short_stages) || (L <= 32 && few_per_die >= 48 && S >= 256);
+  const bool few = L <= 16 || rvq_few_is_faster(G, L, N, S);
   if (few && S <= rvq_few_max_entries(nv) && reinterpret_cast<uintptr_t>(norms) % 16 == 0) {
     const unsigned n = (unsigned)((L + 16 * nv - 1) / (16 * nv) * (8 * (((int64_t)G + 7) / 8)));
     auto kern = nv == 1 ? rvq_few_kernel<1> : rvq_few_kernel<2>;
