@@ -369,8 +369,7 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
   c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
   c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
   c.slice = t.slice; c.slices = t.slices;
-  typename Epi::Pre pre;
-  if constexpr (PRE > 1) pre = epi.template preload<L>(c, d);
+  const typename Epi::Pre pre = epi.template preload<L>(c, d);
   if (nk > 0) {
 #pragma unroll
     for (int i = 0; i < PRE; ++i)
@@ -424,7 +423,6 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
 #pragma unroll
     for (int g = 1; g < KG; ++g) acc[0][0] += part[(g - 1) * NT + tid];
   }
-  if constexpr (PRE == 1) pre = epi.template preload<L>(c, d);
   epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
 }
 template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG = 1>
