@@ -449,9 +449,12 @@ typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 // bytes: no vector operation goes into the address.  Written as inline assembly because the compiler, given base + offset,
 // folds the offset into a per-lane 64-bit pointer outside the loop and adds the slab's stride to it with a vector add per
 // load.  It keeps no count of such a load: the waits that cover it are the ones written out in the main loop.
+// NT: non-temporal.
+template <bool NT = false>
 __device__ __attribute__((always_inline)) inline void load16_to_lds_uniform(const void* base, unsigned lane_bytes, void* l) {
   const unsigned lds = (unsigned)(size_t)(lds_ptr_t)l;      // uniform
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(lane_bytes), "s"(base), "s"(lds) : "memory");
+  if constexpr (NT) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" :: "v"(lane_bytes), "s"(base), "s"(lds) : "memory");
+  else asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(lane_bytes), "s"(base), "s"(lds) : "memory");
 }
 // ... and with a 64-bit address per lane, for rows that span 4 GiB or more and for the last slabs of an operand.  (Every load of the hot kernel's main loop is
 // one of these two, so that the compiler itself never sets M0 there.)

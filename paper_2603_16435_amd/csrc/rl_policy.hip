@@ -542,7 +542,7 @@ __device__ inline void local_rows(const SmallPrep& s, LocalRows<ROWS>& l) {
 }
 
 // Logits of a few tokens (bf16), see logits_few.h.  PREP: with the preparation.
-template <int BN, bool PREP>
+template <int BN, bool PREP, bool NT>
 __global__ __launch_bounds__(256, 1)
 void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, GemmDims d, EpiFwd<bf16_t> epi, SmallPrep s, RowFill f, AdvJob adv) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[few_lds_bytes<BN>()];
@@ -550,10 +550,10 @@ void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ 
     if (blockIdx.x == 0) { prep_small<256, kFewTokens>(s, f, adv); return; }
     __shared__ LocalRows<kFewTokens> l;
     local_rows<256>(s, l);
-    logits_few_tile<BN>(W, X, d, epi, (int)blockIdx.x - 1, l.n, l.rows, l.ids, smem);
+    logits_few_tile<BN, NT>(W, X, d, epi, (int)blockIdx.x - 1, l.n, l.rows, l.ids, smem);
   } else {
     const int left = *d.n_real;
-    logits_few_tile<BN>(W, X, d, epi, blockIdx.x, left < d.N ? left : d.N, d.b_rows, epi.ids_c, smem);
+    logits_few_tile<BN, NT>(W, X, d, epi, blockIdx.x, left < d.N ? left : d.N, d.b_rows, epi.ids_c, smem);
   }
 }
 
@@ -1492,6 +1492,12 @@ static bool few_tokens(const rl_batch* b, const Plan& p) {
   return p.dtype == RL_BF16 && !p.stash && !p.keep && p.R <= kFewTokens && (p.tiles_v + 127) / 128 % 2 && !small_k<EpiFwd<bf16_t>>(p.H) &&
          (reinterpret_cast<uintptr_t>(b->weight) | reinterpret_cast<uintptr_t>(b->hidden)) % 16 == 0;
 }
+// ... with W in non-temporal loads where it is larger than the 256 MB of the memory-side cache, so that a next call finds nothing of it in any case: 110 tokens, H 3584,
+// V 152064 263 -> 252 us, 40 at H 4096, V 151936 296 -> 274.  A W of 131 MB (H 2048, V 32000), scored again and again, 25 tokens 30.7 -> 37.8, 110 tokens 36.9 -> 40.2.
+static bool few_streams_w(const Plan& p) { return (int64_t)p.V * p.H * 2 > (int64_t)256 << 20; }
+template <bool NT> static auto few_kernel(int64_t rows, bool prep) {
+  return prep ? (rows <= 64 ? logits_few_kernel<64, true, NT> : logits_few_kernel<128, true, NT>) : rows <= 64 ? logits_few_kernel<64, false, NT> : logits_few_kernel<128, false, NT>;
+}
 static bool small_logits(const Plan& p) { return p.dtype == RL_F32 && p.n_chunks == 1 && p.R <= kLocalRows && few_forward_tiles(p.V, p.Tc, p.H); }
 
 // prep: row outputs cleared (rows that do not count read 0 / -1), advantages, counts, compaction, chunk records
@@ -1552,7 +1558,7 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
         few = few_tokens(b, p);
         if (few) {
           const EpiFwd<T> e{q.ids_c, q.zy, q.part, kFewTokens, p.V, p.inv_tau, q.ycol, nullptr};
-          auto kern = prep.on ? (p.R <= 64 ? logits_few_kernel<64, true> : logits_few_kernel<128, true>) : p.R <= 64 ? logits_few_kernel<64, false> : logits_few_kernel<128, false>;
+          auto kern = few_streams_w(p) ? few_kernel<true>(p.R, prep.on) : few_kernel<false>(p.R, prep.on);
           kern<<<2 * p.tiles_v + (prep.on ? 1 : 0), 256, 0, s>>>(W, X, d, e, prep.s, prep.f, prep.adv);
         }
       } else if (prep.on) {

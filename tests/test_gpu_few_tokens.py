@@ -49,3 +49,17 @@ def test_rows_scattered_and_none_counting():
     assert torch.equal(lp, full[0] * mask) and torch.equal(lse, full[1] * mask)
     lp, lse = binding.rl_token_logprob_tempered(b.hidden, b.weight, b.token_ids, torch.zeros_like(mask), 1.0, cu)
     assert not lp.any() and not lse.any()
+
+
+# a weight larger than the memory-side cache, with and without a K tail: non-temporal loads
+@pytest.mark.parametrize("H,V,T", [(4104, 32768, 3), (5120, 32000, 100)])
+def test_large_weight(H, V, T):
+    g = torch.Generator(device="cuda").manual_seed(97)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.bfloat16)
+    W, X = n(V, H) * H ** -0.5, n(300, H)
+    ids = torch.randint(0, V, (300,), generator=g, device="cuda", dtype=torch.int32)
+    mask = (torch.arange(300, device="cuda") < T).to(torch.uint8)
+    cu = lambda r: torch.tensor([0, r], dtype=torch.int32, device="cuda")
+    want = binding.rl_token_logprob_tempered(X, W, ids, mask, 1.0, cu(300))
+    got = binding.rl_token_logprob_tempered(X[:T], W, ids[:T], mask[:T], 1.0, cu(T))
+    assert torch.equal(got[0], want[0][:T]) and torch.equal(got[1], want[1][:T])
