@@ -626,18 +626,19 @@ __global__ void target_logit_kernel(const bf16_t* X, const bf16_t* W, int64_t R,
 }
 
 // Per-tile-row partial sums (s, u) of a chunk -> lse, logp, entropy and Z_t = sum_v exp(z - ref_t).
-// A workgroup handles 64 rows x 16 slices of the tile range (1024 threads: the sums are chains of dependent f64 adds,
-// so it takes many short chains to keep the memory system busy), merged through LDS in a fixed order.
-constexpr int kSumSlices = 16;
-__global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* part, int ldp, int tiles_v, const float* zy_c, const float* ref_l2e,
+// A workgroup handles 16 rows (a line of 128 bytes) x 64 slices of the tile range (1024 threads: the sums are chains of dependent f64 adds,
+// so it takes many short chains to keep the memory system busy), merged through LDS in a fixed order.  (64 rows x 16 slices: few workgroups, which a CU's 28 bytes a ns held up, 747
+// tokens, 594 tiles 22 us instead of 10, 67 k 101 instead of 83.)
+constexpr int kSumRows = 16, kSumSlices = 64;
+__global__ __launch_bounds__(kSumRows * kSumSlices) void lse_sum_kernel(const float2* part, int ldp, int tiles_v, const float* zy_c, const float* ref_l2e,
                                const int32_t* row_map, const ChunkDesc* desc, const int32_t* ycol_c, Ctrl* ctrl, rl_stats* stats,
                                float* lse_c, float* logp_c, float* zsum_c, float* lse_out, float* logp_out, float* ent_out,
                                float* zy_out, int32_t* ycol_out) {
-  __shared__ double ss[kSumSlices][64], su[kSumSlices][64];
+  __shared__ double ss[kSumSlices][kSumRows], su[kSumSlices][kSumRows];
   const int left = desc->rows, chunk_start = desc->row_start;
-  if ((int)blockIdx.x * 64 >= left) return;
-  const int col = threadIdx.x & 63, slice = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + col;
+  if ((int)blockIdx.x * kSumRows >= left) return;
+  const int col = threadIdx.x % kSumRows, slice = threadIdx.x / kSumRows;
+  const int n = blockIdx.x * kSumRows + col;
   double s = 0.0, u = 0.0;
   if (n < left)
     for (int t0 = slice; t0 < tiles_v; t0 += 8 * kSumSlices) {       // eight loads in flight, added in order
@@ -649,9 +650,13 @@ __global__ __launch_bounds__(64 * kSumSlices) void lse_sum_kernel(const float2* 
     }
   ss[slice][col] = s; su[slice][col] = u;
   __syncthreads();
+  if (threadIdx.x >= 64) return;
+  double S = 0.0, U = 0.0;                                           // four lanes per row, sixteen slices each
+#pragma unroll
+  for (int k = 0; k < kSumSlices / 4; ++k) { S += ss[slice * (kSumSlices / 4) + k][col]; U += su[slice * (kSumSlices / 4) + k][col]; }
+#pragma unroll
+  for (int o = kSumRows; o < 64; o <<= 1) { S += __shfl_xor(S, o); U += __shfl_xor(U, o); }
   if (slice == 0 && n < left) {
-    double S = 0.0, U = 0.0;
-    for (int k = 0; k < kSumSlices; ++k) { S += ss[k][col]; U += su[k][col]; }
     const int g = chunk_start + n;
     const double lse_d = (double)ref_l2e[g] * 0.6931471805599453 + log(S);
     const float lse = (float)lse_d;
@@ -689,26 +694,30 @@ __global__ void stash_patch_kernel(const ChunkDesc* desc, const int32_t* ids_c, 
 }
 
 // ------------------------------------------------------------------ forward combine
-// Fold the per-vocab-tile partials (max, sumexp) of a chunk into lse, logp.  A workgroup handles 64
+// Fold the per-vocab-tile partials (max, sumexp) of a chunk into lse, logp.  A workgroup handles 16 or 64
 // compact rows x SLICES slices of the tile range: one online (rescaling) pass per thread, coalesced
 // along the rows, sums in f64, then the slices are scaled to the row's maximum, one exponential per thread, and added through LDS in order.
 // Few rows are all latency and want many slices, many rows of few tiles pay for the exponential of every slice.  32768 rows, 4, 8, 16 slices, us: 4 tiles
 // 4.3 - 4.6, 16 tiles 4.8 4.7 5.9, 63 tiles 9.0 8.3 11.3; 96 rows: 4 tiles 3.0 - 3.6, 16 tiles 3.8 3.5 4.2, 63 tiles 8.4 5.6 5.2, 125 tiles 8.8 - 6.7.  (By the
 // vocabulary alone: a token's bits must not depend on the batch.)
 constexpr int combine_slices(int tiles_v) { return tiles_v <= 8 ? 4 : tiles_v <= 64 ? 8 : 16; }
+// Rows of a workgroup: 64 (above), 16 where the partials of a row are many and few workgroups would wait for what a CU takes in (28 bytes a ns): scoring of 99 tokens, V 32000
+// 36.6 -> 35.7 us, of 25 30.6 -> 29.4; with four slices and many rows 64 are the better ones (48 k rows, V 1000 79.0 against 80.7).  Same bits.
+constexpr int combine_rows(int slices) { return slices == 16 ? 16 : 64; }
 // HALVES: the partials are those of half tiles (logits_few_kernel), two of which make one.
 template <bool HALVES, int SLICES>
-__global__ __launch_bounds__(64 * SLICES) void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
+__global__ __launch_bounds__(combine_rows(SLICES) * SLICES) void lse_combine_kernel(const float4* part, int ldp, int tiles_v, const float* zy_c,
                                    const int32_t* row_map, const Ctrl* ctrl, int chunk_start, int chunk_rows, const int32_t* ycol_c,
                                    float* lse_c, float* logp_c, float* lse_out, float* logp_out, float* ent_out,
                                    float* zy_out, int32_t* ycol_out) {
-  __shared__ float sm[SLICES][64];
-  __shared__ double ss[SLICES][64], su[SLICES][64];
+  constexpr int ROWS = combine_rows(SLICES);
+  __shared__ float sm[SLICES][ROWS];
+  __shared__ double ss[SLICES][ROWS], su[SLICES][ROWS];
   int left = ctrl->n_real - chunk_start;
   if (left > chunk_rows) left = chunk_rows;
-  if ((int)blockIdx.x * 64 >= left) return;
-  const int col = threadIdx.x & 63, slice = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + col;
+  if ((int)blockIdx.x * ROWS >= left) return;
+  const int col = threadIdx.x % ROWS, slice = threadIdx.x / ROWS;
+  const int n = blockIdx.x * ROWS + col;
   const float NEG = -__builtin_inff();
   float m = NEG;
   double s = 0.0, u = 0.0;
@@ -1576,7 +1585,8 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
     const int slices = combine_slices(p.tiles_v);
     auto kern = slices == 4 ? (few ? lse_combine_kernel<true, 4> : lse_combine_kernel<false, 4>)
                 : slices == 8 ? (few ? lse_combine_kernel<true, 8> : lse_combine_kernel<false, 8>) : few ? lse_combine_kernel<true, 16> : lse_combine_kernel<false, 16>;
-    kern<<<few ? kFewTokens / 64 : (p.Tc + 63) / 64, 64 * slices, 0, s>>>(q.part, few ? kFewTokens : p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc,
+    const int rows = combine_rows(slices);
+    kern<<<((few ? kFewTokens : p.Tc) + rows - 1) / rows, rows * slices, 0, s>>>(q.part, few ? kFewTokens : p.Tc, p.tiles_v, q.zy, q.row_map, q.ctrl, c0, p.Tc,
                                                                                q.ycol, q.lse_c, q.logp_c, lse_out, logp_out, ent_out, zy_out, ycol_out);
   }
 }
@@ -1734,7 +1744,7 @@ static void run_fused(const rl_batch* b, const rl_params* prm, int objective, co
     }
     {
       ProfScope ps(RL_PROF_COMBINE, s);
-      lse_sum_kernel<<<(p.Tc + 63) / 64, 64 * kSumSlices, 0, s>>>(part, p.Tc, p.tiles_v, q.zy, q.ref, q.row_map, dk, q.ycol, q.ctrl, out->stats,
+      lse_sum_kernel<<<(p.Tc + kSumRows - 1) / kSumRows, kSumRows * kSumSlices, 0, s>>>(part, p.Tc, p.tiles_v, q.zy, q.ref, q.row_map, dk, q.ycol, q.ctrl, out->stats,
                                                       q.lse_c, q.logp_c, q.zsum, out->lse, out->logprob, out->entropy,
                                                       out->target_logit, out->target_col);
     }
