@@ -1204,6 +1204,8 @@ struct Plan {
   bool bwd;
   bool tiled;            // bf16: the work buffers dS/E, W^T, X^T are slab-tiled (hot kernel operands)
   bool k_major_w;        // dX reads W as it is stored: no W^T is made (f32: dS^T too, no dS)
+  bool small_pair;       // f32: dX and dW in tiles of 64 x 16, in one launch, out of dS, W^T, dS^T and X^T
+  bool small_grads;      // f32: the whole backward in one launch, out of the kept logits, W and X (grads_small.h)
   bool stash;            // single-pass backward (forward keeps each chunk's unnormalised probabilities)
   bool keep;             // recompute mode, one chunk: the forward keeps the logits, dS is formed from them
   int n_desc, max_len;   // stash: number of chunk records, promised bound on rows per sequence
@@ -1232,6 +1234,11 @@ static int64_t split_tile_rows(int tm, int tn, int steps, int slots) {
 }
 static size_t split_bytes(int M, int N, int K, int bn, int step, int slots) {
   return (size_t)split_tile_rows((M + kBM - 1) / kBM, (N + bn - 1) / bn, (K + step - 1) / step, slots) * kBM * (size_t)N * 4;
+}
+
+// dX (and dW beside it) in tiles of 64 x 16 with four K groups: one round of them at most.
+static bool small_dx(int M, int N, int K) {
+  return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
 static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Plan& p) {
@@ -1268,8 +1275,9 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.bwd = bwd;
   p.tiled = (b->dtype == RL_BF16);
   p.k_major_w = p.tiled && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
-  if (b->dtype == RL_F32)          // (256 x 64 tiles of gemm_f32.h: their dX reads dS^T and W K-major)
-    p.k_major_w = bwd && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && tc < (1 << 22) && b->H < (1 << 22) && f32_tile_n(tc, b->H, p.Vp, true) == kF32BN;
+  p.small_pair = b->dtype == RL_F32 && bwd && small_dx(tc, b->H, p.Vp) && small_dx(b->V, b->H, tc);
+  if (b->dtype == RL_F32)          // (256 x 64 tiles of gemm_f32.h: their dX reads dS^T and W K-major.  A dX cut along K may count as so many tiles and still be small_pair's.)
+    p.k_major_w = bwd && !p.small_pair && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && tc < (1 << 22) && b->H < (1 << 22) && f32_tile_n(tc, b->H, p.Vp, true) == kF32BN;
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len
@@ -1283,6 +1291,10 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   const bool keep_room = bwd && p.n_chunks == 1 && (b->dtype == RL_F32 || (mode == RL_BWD_AUTO && b->R <= kKeepRows && b->H >= kKeepH && b->R * b->H * 2 < kFarBytes &&
                                                                            !(stash_asked && b->H % 128 == 0)));
   p.keep = keep_room && (b->dtype == RL_F32 || (reinterpret_cast<uintptr_t>(b->hidden) | reinterpret_cast<uintptr_t>(b->weight)) % 16 == 0);
+  // The whole backward of a small f32 batch in one launch, see grads_small.h.  What it gains is launches; a workgroup of dX walks the whole vocabulary by itself, so a
+  // large one takes longer than they did.  us of the call, former launches / this one, 16, 400, 2000 rows: H 16, V 1000 43 46 73 / 28 31 51, V 2000 40 48 84 / 34 39 61,
+  // V 4000 41 54 99 / 48 56 78, V 16000 47 87 212 / 120 143 185; H 128, V 300 42 47 77 / 28 31 57, V 2000 45 59 113 / 40 47 88; H 512, V 500 55 68 - / 40 50 -.
+  p.small_grads = p.small_pair && p.keep && b->V <= 2048;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
   const size_t Rp = (size_t)rp + 256;
@@ -1441,19 +1453,8 @@ static void launch_dx_dw(const bf16_t* E, const bf16_t* W, const bf16_t* WT, Gem
   splitk_reduce_kernel<bf16_t><<<512, 256, 0, s>>>(dx, ex, kBM, kBN, kHotStep);
 }
 
-// dX (and dW beside it) in tiles of 64 x 16 with four K groups: one round of them at most.
-static bool small_dx(int M, int N, int K) {
-  return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
-}
-
-// The whole backward of a small f32 batch in one launch, see grads_small.h.  What it gains is launches; a workgroup of dX walks the whole vocabulary by itself, so a
-// large one takes longer than they did.  us of the call, former launches / this one, 16, 400, 2000 rows: H 16, V 1000 43 46 73 / 28 31 51, V 2000 40 48 84 / 34 39 61,
-// V 4000 41 54 99 / 48 56 78, V 16000 47 87 212 / 120 143 185; H 128, V 300 42 47 77 / 28 31 57, V 2000 45 59 113 / 40 47 88; H 512, V 500 55 68 - / 40 50 -.
-static bool small_grads(const Plan& p) {
-  return p.dtype == RL_F32 && p.bwd && p.keep && p.V <= 2048 && small_dx(p.Tc, p.H, p.Vp) && small_dx(p.V, p.H, p.Tc);
-}
-// ... and its combine inside the loss launch, also that of a loss without gradients: up to 1024 rows, which are four tokens of a thread at most.
-static bool fold_combine(const Plan& p) { return p.dtype == RL_F32 && p.n_chunks == 1 && p.tiles_v <= kFoldTiles && p.Tc <= kFoldRows && (!p.bwd || small_grads(p)); }
+// The combine of a small f32 batch inside its loss launch, also where no gradients are asked for: up to 1024 rows, which are four tokens of a thread at most.
+static bool fold_combine(const Plan& p) { return p.dtype == RL_F32 && p.n_chunks == 1 && p.tiles_v <= kFoldTiles && p.Tc <= kFoldRows && (!p.bwd || p.small_grads); }
 
 struct Ptrs {
   Ctrl* ctrl; int32_t *seq_len, *cstart, *row_map, *ids_c, *cpos;
@@ -1607,7 +1608,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
     if (!p.k_major_w) launch_transpose<T>(gw, s, W, p.H, p.V, p.H, nullptr, q.ctrl, 0, 0, nullptr, nullptr, WT, p.Vp, p.Vp, p.tiled);
   }
   if constexpr (sizeof(T) == 4)
-    if (small_grads(p)) {
+    if (p.small_grads) {
       ProfScope ps(RL_PROF_GEMM_BWD, s);
       // (blocks of 32 columns where those of dX are one round of the CUs at most, else of 64)
       const int rows = p.Tc / 16, nbx = rows * ((p.H + 31) / 32) <= kHotSlots ? 2 : 4, xc = (p.H + 16 * nbx - 1) / (16 * nbx), nx = rows * xc;
@@ -1655,7 +1656,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
       launch_dx_dw(dS, W, p.k_major_w ? nullptr : WT, dx, ex, XT, dw, ew, s);
     } else {
       dx.split_slots = kF32Slots;
-      if (small_dx(dx.M, dx.N, dx.K) && small_dx(dw.M, dw.N, dw.K)) {         // both in tiles of 64 x 16, in one launch
+      if (p.small_pair) {
         ProfScope ps(RL_PROF_GEMM_BWD, s);
         const int n1 = split_launch((dx.M + 63) / 64, (dx.N + kF32SmallBN - 1) / kF32SmallBN, kF32Slots);
         gemm_nt_small_pair_kernel<<<n1 + launch_tiles((dw.M + 63) / 64, (dw.N + kF32SmallBN - 1) / kF32SmallBN), 1024, 0, s>>>(dS, WT, dx, ex, n1, dST, XT, dw, ew);
@@ -1679,7 +1680,7 @@ static bool run_loss_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const
   const float *X = static_cast<const float*>(b->hidden), *W = static_cast<const float*>(b->weight);
   float *WT = static_cast<float*>(q.wt), *XT = static_cast<float*>(q.xt);
   const int wx = (p.Vp + 63) / 64, xx = (p.Tc + 63) / 64, hy = (p.H + 63) / 64;
-  const bool small = small_grads(p);                    // (reads W and X as they are)
+  const bool small = p.small_grads;                     // (reads W and X as they are)
   const int64_t nw = small || p.k_major_w ? 0 : (int64_t)wx * hy, nx = small ? 0 : (int64_t)xx * hy, n = p.B + nw + nx + (p.R + 3) / 4;
   if (p.dtype != RL_F32 || p.n_chunks != 1 || n >= (1 << 24)) return false;        // (2^32 threads a launch)
   loss_prep_kernel<<<(unsigned)n, kLossThreads, 0, s>>>(
@@ -1958,7 +1959,7 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   LossJob j = loss_job(b, prm, objective, p, q, out, nullptr);
   {
     ProfScope ps(RL_PROF_LOSS, s);
-    j.finish_later = small_grads(p) && p.B <= kFinishSeqs;
+    j.finish_later = p.small_grads && p.B <= kFinishSeqs;
     if (fold) {
       j.comb = CombineJob{q.part, p.Tc, p.tiles_v, q.zy, q.row_map, q.ycol, q.lse_c, q.logp_c, out->lse, out->logprob, out->entropy, out->target_logit, out->target_col};
       loss_fold_kernel<<<p.B + (bwd ? (p.R + 3) / 4 : 0), kLossThreads, 0, s>>>(j, q.cpos, static_cast<float*>(out->d_hidden), p.R, p.H);

@@ -3,7 +3,7 @@ the oracle."""
 import pytest
 import torch
 
-from paper_2603_16435_amd import synth
+from paper_2603_16435_amd import binding, synth
 from parity_util import compare_all, run_gpu, run_oracle
 from test_gpu_f32_tiles import F32_TOL, off_grid
 
@@ -24,3 +24,17 @@ def test_dx_reads_its_operands_k_major(H, V, lengths, chunk):
     b.weight = off_grid(b.weight)
     want = run_gpu(b, "grpo", chunk_rows=chunk)
     assert torch.equal(got.d_hidden, want.d_hidden) and torch.equal(got.d_weight, want.d_weight)
+
+
+# shapes whose dX makes as many tiles of 256 x 64 as K-major operands take only when it is cut along K, and whose dX and dW are small enough for the pair in one launch,
+# which contracts W^T and dS: as one chunk, and as chunks of a larger batch; a workspace of NaN shows an operand that the call did not make
+@pytest.mark.parametrize("H,V,lengths,chunk", [(72, 3000, [1500, 700, 3, 860], 0), (16, 8192, [1000, 0, 1000, 48], 0), (64, 4096, [1024, 1024, 1500, 500], 0),
+                                               (32, 5400, [2100, 1, 1999, 300], 3072)])
+def test_the_pair_of_small_contractions_finds_what_it_reads(H, V, lengths, chunk):
+    b = synth.make_rollouts(synth.RolloutConfig("kmajor", 2, 2, 1, 64, H, V, "f32", 0.5, seed=76), "cuda", "packed", lengths=lengths)
+    batch = binding.make_batch(b.hidden, b.weight, b.token_ids, b.mask, b.cu_seqlens, b.group_idx, b.rewards, b.old_logprob, b.ref_logprob, b.log_z, 2)
+    plan = binding.PolicyLossPlan(batch, binding.make_params(chunk_rows=chunk), "cuda", torch.float32)
+    plan.ws.view(torch.float32).fill_(float("nan"))
+    got = plan.run(binding.RL_OBJ_GRPO)
+    torch.cuda.synchronize()
+    print(compare_all(b, got, run_oracle(b, "grpo"), **F32_TOL), flush=True)
