@@ -1241,7 +1241,14 @@ static bool small_dx(int M, int N, int K) {
   return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
-static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Plan& p) {
+// whether two arrays of so many bytes share memory
+static bool meets(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + b_bytes && y < x + a_bytes;
+}
+
+// out: where the call's outputs go, nullptr where only the size of the workspace is asked for (which no choice that depends on them changes)
+static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Plan& p, const rl_outputs* out = nullptr) {
   if (!b) return RL_ERR_NULL;
   if (b->R < 1 || b->R >= ((int64_t)1 << 31) - (1 << 16) || b->H < 1 || b->V < 1 || b->B < 1 || b->P < 1) return RL_ERR_SHAPE;
   if (b->dtype != RL_F32 && b->dtype != RL_BF16) return RL_ERR_DTYPE;
@@ -1276,8 +1283,13 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   p.tiled = (b->dtype == RL_BF16);
   p.k_major_w = p.tiled && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && b->R <= kKMajorRows;
   p.small_pair = b->dtype == RL_F32 && bwd && small_dx(tc, b->H, p.Vp) && small_dx(b->V, b->H, tc);
+  // A gradient may take the place of an input.  dX, then dW are contracted from copies, in that order; a launch that writes one while it reads the inputs themselves is
+  // not taken where they share memory.
+  const size_t x_bytes = p.esz * (size_t)b->R * b->H, w_bytes = p.esz * (size_t)b->V * b->H;
+  auto on_gradients = [&](const void* in, size_t bytes) { return out && (meets(out->d_hidden, x_bytes, in, bytes) || meets(out->d_weight, 4 * (size_t)b->V * b->H, in, bytes)); };
   if (b->dtype == RL_F32)          // (256 x 64 tiles of gemm_f32.h: their dX reads dS^T and W K-major.  A dX cut along K may count as so many tiles and still be small_pair's.)
-    p.k_major_w = bwd && !p.small_pair && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && tc < (1 << 22) && b->H < (1 << 22) && f32_tile_n(tc, b->H, p.Vp, true) == kF32BN;
+    p.k_major_w = bwd && !p.small_pair && reinterpret_cast<uintptr_t>(b->weight) % 16 == 0 && tc < (1 << 22) && b->H < (1 << 22) && f32_tile_n(tc, b->H, p.Vp, true) == kF32BN &&
+                  !(out && meets(out->d_hidden, x_bytes, b->weight, w_bytes));
   p.stash = can_stash;
   p.max_len = p.stash ? prm->max_seq_len : 0;
   // chunk records: two consecutive chunks hold more than Tc rows, and every chunk but the last more than Tc - max_len
@@ -1294,7 +1306,8 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   // The whole backward of a small f32 batch in one launch, see grads_small.h.  What it gains is launches; a workgroup of dX walks the whole vocabulary by itself, so a
   // large one takes longer than they did.  us of the call, former launches / this one, 16, 400, 2000 rows: H 16, V 1000 43 46 73 / 28 31 51, V 2000 40 48 84 / 34 39 61,
   // V 4000 41 54 99 / 48 56 78, V 16000 47 87 212 / 120 143 185; H 128, V 300 42 47 77 / 28 31 57, V 2000 45 59 113 / 40 47 88; H 512, V 500 55 68 - / 40 50 -.
-  p.small_grads = p.small_pair && p.keep && b->V <= 2048;
+  // (It adds up the loss as well, out of group_idx.)
+  p.small_grads = p.small_pair && p.keep && b->V <= 2048 && !on_gradients(b->hidden, x_bytes) && !on_gradients(b->weight, w_bytes) && !on_gradients(b->group_idx, 4 * (size_t)b->B);
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
   const size_t Rp = (size_t)rp + 256;
@@ -1484,11 +1497,8 @@ static Ptrs carve(void* ws, const Plan& p) {
 
 // whether an output (of `size` bytes) shares memory with what the preparation reads
 static bool on_prep_inputs(const rl_batch* b, const Plan& p, const void* out, size_t size) {
-  auto meets = [&](const void* in, size_t bytes) {
-    const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(in);
-    return out && in && o < i + bytes && i < o + size;
-  };
-  return meets(b->token_ids, 4 * (size_t)p.R) || meets(b->mask, (size_t)p.R) || meets(b->cu_seqlens, 4 * ((size_t)p.B + 1)) || meets(b->group_idx, 4 * (size_t)p.B);
+  auto on = [&](const void* in, size_t bytes) { return meets(out, size, in, bytes); };
+  return on(b->token_ids, 4 * (size_t)p.R) || on(b->mask, (size_t)p.R) || on(b->cu_seqlens, 4 * ((size_t)p.B + 1)) || on(b->group_idx, 4 * (size_t)p.B);
 }
 
 // The preparation as the launch of the logits does it, if it does (on).
@@ -1935,7 +1945,7 @@ rl_status rl_policy_loss_fwd_bwd(const rl_batch* b, const rl_params* prm, int32_
   const bool bwd = out->d_hidden || out->d_weight;
   if (bwd && (!out->d_hidden || !out->d_weight)) return RL_ERR_NULL;
   Plan p;
-  rl_status st = make_plan(b, prm, bwd, p);
+  rl_status st = make_plan(b, prm, bwd, p, out);
   if (st != RL_OK) return st;
   st = check_ws(ws, ws_bytes, p);
   if (st != RL_OK) return st;

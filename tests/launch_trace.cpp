@@ -1,6 +1,6 @@
 // launch_trace.cpp - walks the host side of librl_policy.so without a GPU: the HIP runtime's entry points are defined here, ahead of the real
 // ones, and a launch is a line in a list.  For every call of the grid below each operand of a backward contraction has to be an input or an array that
-// an earlier launch of the same call wrote.
+// an earlier launch of the same call wrote, and a contraction that reads an input itself must not write a gradient that shares memory with it.
 //   launch_trace LIBRARY     prints the kinds of contraction it met, how often, and every operand that nothing wrote; 0 if there is none
 #include <dlfcn.h>
 
@@ -22,6 +22,7 @@ static std::map<std::string, long> g_met;
 static std::string g_case;
 static long g_bad = 0;
 static const void *g_x, *g_w;
+static bool g_no_small, g_no_k_major;      // gradients meet what these launches read while they write them
 
 template <class T> static T arg(void** args, int i, size_t offset = 0) {
   T v;
@@ -54,10 +55,14 @@ static void launch(const std::string& n, void** a) {
   if (!is("splitk_reduce") && (pair || is("EpiDXIf") || is("EpiDWE"))) {
     const char* kind = is("small_pair") ? "small pair" : pair ? "bf16 pair" : is("EpiDWE") ? "dW" : is("gemm_nt_f32_kernelINS_5EpiDXIfEELb0ELb1E") ? "dX K-major" : "dX";
     ++g_met[kind];
+    if (g_no_k_major && !strcmp(kind, "dX K-major")) bad("dX is written over W, which its launch reads");
     reads(kind, "A", ptr(a, 0)); reads(kind, "B", ptr(a, 1));
     if (pair) { reads(kind, "the second A", ptr(a, 5)); reads(kind, "the second B", ptr(a, 6)); }
   }
-  if (is("small_grads_kernel")) ++g_met["small grads"];
+  if (is("small_grads_kernel")) {
+    ++g_met["small grads"];
+    if (g_no_small) bad("gradients are written over what their launch reads");
+  }
 }
 
 extern "C" {
@@ -81,16 +86,18 @@ int main(int argc, char** argv) {
   if (g_names.empty()) { fprintf(stderr, "the library registered no kernel here\n"); return 2; }
   // addresses that nothing follows, far apart
   auto at = [](int i, int off = 0) { return reinterpret_cast<void*>(((uintptr_t)(i + 1) << 40) + off); };
-  long calls = 0;
+  long calls = 0, before = 0, apart = 0;
   for (int dtype : {RL_F32, RL_BF16})
     for (int64_t R : {1, 200, 356, 1000, 1025, 2048, 2600, 3072, 4096, 5400, 8192, 16384, 33000})
       for (int H : {4, 8, 16, 32, 40, 64, 72, 80, 128, 264, 512, 712, 1024})
         for (int V : {5, 300, 1000, 2048, 2064, 3000, 3199, 4096, 5400, 8000, 8192, 16384, 33024, 50257})
           for (int chunk : {0, 256, 2048, 3072, 5120})
             for (int off : {0, 4})
-              for (int promise : {0, 100}) {
+              for (int promise : {0, 100})
+              for (int place = 0; place < 8; ++place) {
                 if (dtype == RL_BF16 && H % 8) continue;
                 if (dtype == RL_F32 && promise) continue;
+                if (place && (dtype != RL_F32 || off || R > 5400)) continue;
                 rl_batch b{};
                 b.R = R; b.H = H; b.V = V; b.B = 4; b.P = 2; b.dtype = dtype;
                 b.hidden = g_x = at(0); b.weight = g_w = at(1, off); b.token_ids = (const int32_t*)at(2); b.mask = (const uint8_t*)at(3);
@@ -100,13 +107,27 @@ int main(int argc, char** argv) {
                 p.clip_eps = 0.2f; p.adv_eps = 1e-6f; p.chunk_rows = chunk; p.max_seq_len = promise;
                 rl_outputs o{};
                 o.loss = (float*)at(10); o.d_hidden = at(11); o.d_weight = (float*)at(12);
+                // gradients beside the inputs, in their place, over their first or last bytes
+                const size_t xb = 4 * (size_t)R * H, wb = 4 * (size_t)V * H;
+                char *X = (char*)at(0), *W = (char*)at(1, off);
+                if (place == 1) { o.d_hidden = X + xb; o.d_weight = (float*)(W - wb); }
+                if (place == 2) o.d_hidden = X;
+                if (place == 3) o.d_weight = (float*)W;
+                if (place == 4) o.d_hidden = W + wb - 4;
+                if (place == 5) o.d_weight = (float*)(X - wb + 4);
+                if (place == 6) o.d_hidden = (char*)at(5) + 12;
+                if (place == 7) o.d_hidden = W - xb + 4;
+                g_no_small = place > 1; g_no_k_major = place == 4 || place == 7;
                 size_t n = 0;
-                char text[128];
-                snprintf(text, sizeof text, "%s, %ld rows, H %d, V %d, chunks of %d, weight + %d, lengths up to %d", dtype == RL_F32 ? "f32" : "bf16", (long)R, H, V, chunk, off, promise);
+                char text[160];
+                snprintf(text, sizeof text, "%s, %ld rows, H %d, V %d, chunks of %d, weight + %d, lengths up to %d, place %d", dtype == RL_F32 ? "f32" : "bf16", (long)R, H, V, chunk, off, promise, place);
                 g_case = text;
                 g_written.clear();
                 if (bytes(&b, &p, 1, &n) != RL_OK || call(&b, &p, RL_OBJ_FLOW, &o, at(20), n, nullptr) != RL_OK) bad("refused");
                 ++calls;
+                if (place == 0) apart = g_met["small grads"] + g_met["dX K-major"] - before;
+                if (place == 1 && g_met["small grads"] + g_met["dX K-major"] - before != apart) bad("gradients beside the inputs take another path");
+                before = g_met["small grads"] + g_met["dX K-major"];
               }
   printf("%ld calls\n", calls);
   for (auto& m : g_met) printf("%s: %ld\n", m.first.c_str(), m.second);

@@ -3,6 +3,8 @@ import pytest
 import torch
 
 from paper_2603_16435_amd import binding, synth
+from parity_util import compare_all, run_oracle
+from test_gpu_f32_tiles import F32_TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +84,27 @@ def test_outputs_in_the_place_of_inputs(P, G, dtype, mode, objective):
             assert n == field or torch.equal(getattr(plan.res, n), want[n]), (field, n)
         getattr(b, inp).copy_(keep)
         setattr(plan.out, field, own)
+
+
+# a small batch, whose one launch for both gradients reads the inputs themselves and steps aside; K-major operands of dX; rows that do not count become zero in place
+@pytest.mark.parametrize("H,V,lengths,layout", [(128, 1024, [100, 99, 1, 156], "packed"), (64, 300, [30, 0, 1, 12], "padded"), (68, 33024, [130, 1, 0, 126], "packed")])
+def test_gradients_in_the_place_of_inputs(H, V, lengths, layout):
+    b = synth.make_rollouts(synth.RolloutConfig("views", 2, 2, 1, 64, H, V, "f32", 0.5, seed=74), "cuda", layout, lengths=lengths)
+    ref = run_oracle(b, "flow")
+    # the flow weight is exp of a sum of n <= 156 f32 log-probs below 16, each rounded by up to 2^-21: at random signs 4 sqrt(n / 3) 2^-21 = 1.4e-5 of a term, and the
+    # terms of d_log_z, whose differences remain, are up to 2 x 1.2 x 16 / B = 9.6: 1.4e-4
+    tol = dict(F32_TOL, loss_tol=1.4e-4)
+    hidden, weight = b.hidden.clone(), b.weight.clone()
+    got = {}
+    for name, inp in (("d_hidden", "hidden"), ("d_weight", "weight")):
+        plan = _plan(b, "auto", 0)
+        setattr(plan.out, name, getattr(b, inp).data_ptr())
+        setattr(plan.res, name, getattr(b, inp))
+        res = plan.run(binding.RL_OBJ_FLOW)
+        torch.cuda.synchronize()
+        got[name] = (res.d_hidden.clone(), res.d_weight.clone())
+        b.hidden.copy_(hidden), b.weight.copy_(weight)
+        res.d_hidden, res.d_weight = got[name]
+        print(name, compare_all(b, res, ref, **tol), flush=True)
+    for a, c in zip(*got.values()):
+        assert torch.equal(a, c)

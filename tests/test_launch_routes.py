@@ -1,5 +1,5 @@
 """The host's choice of kernels, on the CPU: over a grid of shapes, chunk sizes, alignments and length promises, every operand of a backward contraction is an
-input or an array that an earlier launch of the same call wrote (launch_trace.cpp)."""
+input or an array that an earlier launch of the same call wrote, and none that reads an input writes a gradient in its place (launch_trace.cpp)."""
 import os
 import shutil
 import subprocess
