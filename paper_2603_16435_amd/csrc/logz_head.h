@@ -101,9 +101,10 @@ __global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows
 // through LDS.  (Sixteen accumulators leave one workgroup per CU: 64 prompts at H = M = 5120 took 1.2 % longer.)  VEC: rows are
 // 16-byte aligned (else element loads).  (The vector-FMA form with the pooled states in LDS was bound by its LDS reads: 94 us against
 // 18 us on the shape above.)
-// part_z != nullptr: log Z too.  A workgroup adds up its units' w2 g and the one that is last of its 16 prompts the workgroups'.  These sums go past the
-// L2s (agent-scope accesses), each waited for before the count that announces it: with a release fence, which writes back all that the L2 holds, the call took
-// 61.8 us instead of 60.8.  A launch is saved: forward + backward of one prompt of 20 rows, H 100, M 64 13.6 -> 11.3 us, 4 of 800, H = M = 1024 15.7 -> 15.2.  Many
+// part_z != nullptr: log Z too.  A workgroup adds up its units' w2 g and the one that is last of its 16 prompts the workgroups', which it may read because the
+// count that announces a sum is a release and an acquire at device scope, behind a barrier of the workgroup that wrote it.  That writes back what the L2 holds: forward + backward of 16 prompts, H 3584,
+// M 1024 32.5 us, 32.2 with sums that go past the L2s and no more than a wait ahead of the count, 34.2 with the launch that this saves; one prompt of 20 rows,
+// H 100, M 64 25.2 of 27.6 us, 4 of 800, H = M = 1024 24.8 of 27.2 (called from Python).  Many
 // workgroups count one after the other: 40 prompts, H 300, M 3000 14.3 -> 17.6 (the forward), on the shape above no gain.  So up to kLogzSumUnits units and 16 prompts (33 prompts, M 500
 // 30.1 -> 30.5).
 constexpr int kLogzSumUnits = 1024;
@@ -167,21 +168,20 @@ __global__ __launch_bounds__(kLogzWaves * 64, 4) void logz_hidden_kernel(const f
     if (part_z) {
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) z += __shfl_xor(z, o);
-      if (u == 0 && q < np) __hip_atomic_store(part_z + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * np + q, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (u == 0 && q < np) part_z[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * np + q] = z;
     }
   }
   if (!part_z) return;
   __shared__ int last;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) last = __hip_atomic_fetch_add(done + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  if (threadIdx.x == 0) last = __hip_atomic_fetch_add(done + blockIdx.y, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
   __syncthreads();
   if (!last) return;
   const int q = threadIdx.x & 15, t = threadIdx.x >> 4;                                     // prompt; workgroups t, t + 4 WAVES, ...
   const float* z = part_z + (int64_t)blockIdx.y * gridDim.x * np + (q < np ? q : 0);
   float s = 0.f;
 #pragma unroll 4
-  for (int k = t; k < (int)gridDim.x; k += 4 * WAVES) s += __hip_atomic_load(z + (int64_t)k * np, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int k = t; k < (int)gridDim.x; k += 4 * WAVES) s += z[(int64_t)k * np];
   s += __shfl_xor(s, 16); s += __shfl_xor(s, 32);
   if (lane < 16) part[wave][0][lane] = s;
   __syncthreads();
