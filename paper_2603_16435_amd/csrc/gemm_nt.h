@@ -345,7 +345,13 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
       for (int p = 0; p < PB; ++p) rb[i][p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
     }
   };
-  auto stored = [](const uint4& v) __attribute__((always_inline)) { return SMALL ? make_uint4(v.x, v.z, v.y, v.w) : v; };
+  // Held behind the MFMAs: by itself the compiler exchanges the middle elements where the two kinds of load meet, ahead of the MFMAs, and waits for the loads there.  Scoring in f32,
+  // us: 2630 tokens, H 1024, V 1000 112.3 -> 96.6; 1872, H 600, V 657 69.0 -> 63.9; 1752, H 1200, V 4000 274.5 -> 238.3; loss of 15.5 k tokens, H 64, V 2000 334.7 -> 299.7.
+  auto stored = [](uint4 v) __attribute__((always_inline)) {
+    if (!SMALL) return v;
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    return make_uint4(v.x, v.z, v.y, v.w);
+  };
   auto lstore = [&](int buf, int i) __attribute__((always_inline)) {
     unsigned char* as = smem + buf * (A_BYTES + B_BYTES);
     unsigned char* bs = as + A_BYTES;
@@ -378,11 +384,8 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
   }
   __syncthreads();
   const int frow = lane & (L::kBlk - 1), fq = lane / L::kBlk;
-  for (int kt0 = 0; kt0 < nk; kt0 += PRE)
-#pragma unroll
-  for (int i = 0; i < PRE; ++i) {
-    const int kt = kt0 + i, cur = kt & 1;
-    if (PRE > 1 && kt >= nk) break;
+  auto slab = [&](int kt, int i) __attribute__((always_inline)) {
+    const int cur = kt & 1;
     if (kt + PRE < nk) gload((k_begin + (kt + PRE) * KG) * BK, i);
     const unsigned char* as = smem + cur * (A_BYTES + B_BYTES);
     const unsigned char* bs = as + A_BYTES;
@@ -412,6 +415,16 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
     }
     if (kt + 1 < nk) lstore(cur ^ 1, (i + 1) % PRE);
     __syncthreads();
+  };
+  if constexpr (PRE == 1) {
+    for (int kt = 0; kt < nk; ++kt) slab(kt, 0);
+  } else {
+    for (int kt0 = 0; kt0 < nk; kt0 += PRE)
+#pragma unroll
+      for (int i = 0; i < PRE; ++i) {
+        if (kt0 + i >= nk) break;
+        slab(kt0 + i, i);
+      }
   }
 
   if constexpr (KG > 1) {                            // (the epilogues used with it need no barrier)

@@ -30,3 +30,24 @@ def test_the_prefetch_is_the_last_load_before_each_wait_that_leaves_one_in_fligh
             waits += 1
             assert last.startswith("global_load_dword "), last
     assert waits >= 2 * 8                                # two slabs per turn of the loop, eight kernels at the least
+
+
+@pytest.mark.skipif(not os.path.exists(binding.LIB_PATH) or not all(map(os.path.exists, TOOLS)), reason="library or LLVM tools not there")
+def test_the_narrow_f32_tiles_wait_for_their_loads_where_they_store_them(tmp_path):
+    """The general kernel exchanges the middle elements of what it loads on the way to LDS.  Where the compiler does that ahead of the MFMAs, each wait for a load with a
+    copy behind it is hundreds of instructions ahead of the store, and the loads are in flight for nothing."""
+    copy, unbundle, dump = TOOLS
+    fat, dev = str(tmp_path / "fat"), str(tmp_path / "dev.o")
+    subprocess.run([copy, f"--dump-section=.hip_fatbin={fat}", binding.LIB_PATH, os.devnull], check=True)
+    subprocess.run([unbundle, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}", f"--output={dev}"], check=True)
+    text = subprocess.run([dump, "-d", "--no-show-raw-insn", dev], check=True, capture_output=True, text=True).stdout
+    met = 0
+    for f in re.split(r"\n(?=[0-9a-f]+ <)", text):
+        if not re.match(r"[0-9a-f]+ <\S*(gemm_nt_kernelIf\S*ELi16ELi\d+ELi1E|gemm_nt_small_pair_kernel)", f):
+            continue
+        ins = [line.split("//")[0].strip() for line in f.splitlines()[1:]]
+        for i, (this, following) in enumerate(zip(ins, ins[1:])):
+            if this.startswith("s_waitcnt vmcnt") and re.match(r"v_mov_b32_e32 v\d+, v\d+", following):
+                met += 1
+                assert any(s.startswith("ds_write_b128") for s in ins[i:i + 20]), (f.splitlines()[0], ins[i:i + 20])
+    assert met >= 20
