@@ -2114,17 +2114,23 @@ static rl_status rvq_check(int32_t G, int64_t L, int32_t D, int32_t N, int32_t S
   return RL_OK;
 }
 
-// Whether more than 16 vectors of a group are encoded faster by the kernel that takes 32 of them per workgroup than by the one that takes 256 or 512.  Both keep
-// one workgroup on a CU (the other at most two, which slow each other down), 32 on an accelerator die, which the workgroups of a group share: rounds of workgroups times what one
-// takes, us fitted to calls of 8 to 512 groups.  The other kernel now and then looks at a whole stage again, about once in 100 thousand
-// decisions, which takes 130 us: 37 groups of 253 vectors, 16 stages of 512 entries, 325 us with it and 205 without, here 228.  Other kernel and this one, us, 16 stages of 512 entries: 256 groups of 33 to 64 vectors (two rounds) 325 to 332 and 234 to 245, of 96 (three) 332 and 360,
-// 40 of 300 424 and 231, 4 of 1100 310 and 226; 56 of 1024: 160 groups of 50 1265 and 1365, 64 of 140 1234 and 1352, 4 of 1100 1719 and 1345; 40 of 1024, 264 groups of
-// 32 1157 and 1076; 10 of 256, 256 groups of 40 213 and 98; 8 groups of 17, 16 stages of 64 entries 69 and 53, of 128 86 and 54.
+// Whether more than 16 vectors of a group are encoded faster by the kernel that takes 32 of them per workgroup (few) than by the one that takes 256 or 512 (many).  Both keep
+// one workgroup on a CU (the second kind of `many` at most two, which slow each other down), 32 on an accelerator die, which the workgroups of a group share: what a launch takes is
+// its rounds of workgroups times what one takes to start and per stage.  Now and then `many` looks at a whole stage again, some 50 us each time; that depends on the vectors,
+// is rarer in the first two stages, for which nothing is added, and is counted by its mean over N(0, 1) vectors: past 20 thousand decisions more than half of the calls have one.
+// Fitted to 1800 calls of 1 to 4096 groups of 17 to 4096 vectors, 1 to 64 stages of 64 to 1024 entries, of which it takes 0.9 % more than the faster kernel would; of 1600 others
+// 1.1 %, at worst 2.0 times as long where the inputs need a second look, 1.6 times where they need none.  (Without the cost of a start 3.3 % and 6.0 times.)
+// us, few and many (without such a stage / mean of eight inputs):
+//   2 stages of 64:   512 groups of 256 172, 31 / 32;  264 of 512 179, 53 / 53        1 of 512: 100 groups of 512 86, 33 / 34
+//   4 of 1024:  37 of 512 163, 135 / 136      8 of 64:  128 of 256 124, 54 / 55;  8 of 1024 36, 77 / 78      10 of 256:  12 of 17 47, 75 / 86
+//   16 of 512:  264 of 64 356, 292 / 342;  40 of 300 231, - / 424;  256 of 96 360, - / 332      40 of 256:  37 of 17 166, 367 / 395      56 of 1024:  160 of 50 1365, - / 1265
 static bool rvq_few_is_faster(int64_t G, int64_t L, int N, int S) {
-  const int64_t die = (G + 7) / 8, big = L > 256 ? 512 : 256;
-  const double rounds = (double)(((L + 31) / 32 * die + 31) / 32), n = (double)((L + big - 1) / big * die);       // of this kernel; workgroups of the other
-  const double d = (double)G * L * N, share = n <= 32 ? 1.0 : n <= 64 ? 1.15 + 0.6 * (n - 33) / 32 : 0.87 * n / 32;
-  return rounds * N * (1.9 + 0.0103 * S) <= share * N * (3.2 + (big == 256 ? 0.017 : 0.024) * S) + 130.0 * d / (d + 1e5);
+  const int64_t die = (G + 7) / 8, rows = L > 256 ? 512 : 256;
+  const double rounds = (double)(((L + 31) / 32 * die + 31) / 32), n = (double)((L + rows - 1) / rows * die);       // few; workgroups of `many` on a die
+  const double few = 4.0 + rounds * (4.5 + N * (2.2 + 0.0094 * S));
+  const double share = n <= 32 ? 1.0 : rows == 512 ? 1.08 * (double)(((int64_t)n + 31) / 32) : n <= 64 ? 1.5 + 0.5 * (n - 32) / 32 : 0.85 * n / 32;
+  const double d = N > 2 ? (double)G * L * (N - 2) : 0.0;
+  return few <= 6.0 + share * (13.0 + N * (rows == 512 ? 5.5 + 0.0255 * S : 3.8 + 0.0177 * S)) + 36.0 * d / (d + 2e4);
 }
 
 rl_status rl_rvq_codebook_norms(const void* codebooks, int32_t G, int32_t N, int32_t S, int32_t D, float* norms, void* stream) {

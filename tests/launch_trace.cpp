@@ -1,11 +1,13 @@
 // launch_trace.cpp - walks the host side of librl_policy.so without a GPU: the HIP runtime's entry points are defined here, ahead of the real
 // ones, and a launch is a line in a list.  For every call of the grid below each operand of a backward contraction has to be an input or an array that
 // an earlier launch of the same call wrote, and a contraction that reads an input itself must not write a gradient that shares memory with it.
+//   launch_trace LIBRARY G L N S ..     prints which kernel encodes L vectors of each of G groups in N stages of S entries, "few" or "many", a line for each four
 //   launch_trace LIBRARY     prints the kinds of contraction it met, how often, and every operand that nothing wrote; 0 if there is none
 #include <dlfcn.h>
 
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <set>
@@ -40,6 +42,8 @@ static void reads(const char* kind, const char* which, const void* p) {
 
 static void launch(const std::string& n, void** a) {
   auto is = [&](const char* s) { return n.find(s) != std::string::npos; };
+  if (is("rvq_few_kernel")) printf("few\n");
+  if (is("rvq_encode_kernel")) printf("many\n");
   auto writes = [&](const void* p) { if (p) g_written.insert(p); };
   // epilogues that store an operand: EpiDS {ids, lse, c, dS, stride, dS^T, ..}, EpiFwdStash {ref, part, stride, E, ..}
   if (is("EpiDSI")) { writes(ptr(a, 3, 24)); if (is("EpiDSIf")) writes(ptr(a, 3, 40)); }
@@ -79,13 +83,19 @@ int hipGetLastError() { return 0; }
 }
 
 int main(int argc, char** argv) {
-  void* lib = argc == 2 ? dlopen(argv[1], RTLD_NOW | RTLD_LOCAL) : nullptr;
-  if (!lib) { fprintf(stderr, "%s\n", argc == 2 ? dlerror() : "usage: launch_trace LIBRARY"); return 2; }
+  void* lib = argc >= 2 && argc % 4 == 2 ? dlopen(argv[1], RTLD_NOW | RTLD_LOCAL) : nullptr;
+  if (!lib) { fprintf(stderr, "%s\n", argc >= 2 && argc % 4 == 2 ? dlerror() : "usage: launch_trace LIBRARY [G L N S ..]"); return 2; }
   const auto bytes = reinterpret_cast<decltype(&rl_workspace_bytes)>(dlsym(lib, "rl_workspace_bytes"));
   const auto call = reinterpret_cast<decltype(&rl_policy_loss_fwd_bwd)>(dlsym(lib, "rl_policy_loss_fwd_bwd"));
   if (g_names.empty()) { fprintf(stderr, "the library registered no kernel here\n"); return 2; }
   // addresses that nothing follows, far apart
   auto at = [](int i, int off = 0) { return reinterpret_cast<void*>(((uintptr_t)(i + 1) << 40) + off); };
+  if (argc > 2) {
+    const auto encode = reinterpret_cast<decltype(&rl_rvq_encode)>(dlsym(lib, "rl_rvq_encode"));
+    for (int i = 2; i + 3 < argc; i += 4)
+      if (encode(at(0), at(1), (const float*)at(2), atoi(argv[i]), atoi(argv[i + 1]), 128, atoi(argv[i + 2]), atoi(argv[i + 3]), (int32_t*)at(3), at(4), nullptr) != RL_OK) printf("refused\n");
+    return 0;
+  }
   long calls = 0, before = 0, apart = 0;
   for (int dtype : {RL_F32, RL_BF16})
     for (int64_t R : {1, 200, 356, 1000, 1025, 2048, 2600, 3072, 4096, 5400, 8192, 16384, 33000})
