@@ -312,7 +312,6 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
     float m4 = 0.f;
     bool gt = false;
     auto fold = [&](int rb, int u, const floatx4& v, int blk) __attribute__((always_inline)) {
-#ifndef RVQ_PROBE_NO_UPDATE
       if (u == 0) {
         float m3, mx;
         asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m3) : "v"(v[0]), "v"(v[1]), "v"(v[2]));
@@ -330,9 +329,6 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
         second[rb] = __builtin_amdgcn_fmed3f(best[rb], second[rb], m4);
         asm("v_max_f32 %0, %0, %1" : "+v"(best[rb]) : "v"(m4));
       }
-#else
-      if (u == 0) asm("v_max_f32 %0, %0, %1" : "+v"(best[rb]) : "v"(v[0]));
-#endif
     };
 #pragma unroll
     for (int j = 0; j < 5; ++j) read1(0, j, fa[0], nqr[0]);
@@ -357,18 +353,10 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int ks = i >> 2, rb = i & 3;
-#ifdef RVQ_PROBE_NO_MFMA
-        acc[c & 1][rb] = h;
-#else
         acc[c & 1][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[c & 1][ks]), __builtin_bit_cast(bf16x8, ra[rb][ks]),
                                                               ks == 0 ? h : acc[c & 1][rb], 0, 0, 0);
-#endif
-#ifndef RVQ_PROBE_NO_LDSREAD
         if (c < 3 && i < 5) read1(c + 1, i, fa[(c + 1) & 1], nqr[(c + 1) & 1]);
-#endif
-#ifndef RVQ_PROBE_NO_DMA
         if (i == 6 && (kW == 4 || (c & 1) == 0)) stage_in1(tn, kW == 4 ? c : c >> 1, loff, (unsigned)lq, nxt, nnxt);
-#endif
         // part i % 4 of folding in the previous block's scores for vector block i / 4 (region 0: the previous chunk's last block)
         fold(i >> 2, i & 3, c == 0 ? tail[i >> 2] : acc[(c - 1) & 1][i >> 2], blkv);
         __builtin_amdgcn_sched_barrier(0);
@@ -381,9 +369,7 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
     // the wavefront's fragment reads are done (the stage may be overwritten).  Written out instead of __syncthreads(), whose
     // fence would wait for the loads of the chunk after next as well; nothing but LDS is shared here.
     __builtin_amdgcn_s_waitcnt(kW == 4 ? 0x0075 : 0x0073);   // vmcnt(5 or 3) lgkmcnt(0)
-#ifndef RVQ_PROBE_NO_SYNC
     __builtin_amdgcn_s_barrier();
-#endif
     asm volatile("" ::: "memory");                // (the compiler keeps LDS accesses on their side of the barrier)
    }
     {
@@ -457,9 +443,6 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
         }
         amb_any[rb] = unk != 0;
         amb_known[rb] = unk == 0 && cnt != 1;
-#ifdef RVQ_MEASURE_WITHOUT_EXACT_PATH                       // timing probes only: never defined in the library build
-        amb_any[rb] = false; amb_known[rb] = false;
-#endif
       }
       unsigned long long todo = 0, mine = 0;
 #pragma unroll
@@ -564,7 +547,6 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
           float lmax = live ? rq.best[e16] - mg : NEG;
           const int nblk = S / 16, per = (nblk + kW - 1) / kW;
           const int blk_end = (wave + 1) * per < nblk ? (wave + 1) * per : nblk;
-#ifndef RVQ_PROBE_NO_PASS
 #pragma unroll 1
           for (int blk0 = wave * per; blk0 < blk_end; blk0 += 4) {
             u32x4_t a[4][4];
@@ -597,12 +579,10 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
               }
             }
           }
-#endif
           rq.top[e16][wave * 4 + kq] = lmax;            // (a wavefront without entries writes its floor: the main pass's best minus the margin, or -inf)
         }
         __syncthreads();
         // 3.: wavefront w decides slots w, w + 4, ...
-#ifndef RVQ_PROBE_NO_DECIDE
         for (int j = wave; j < nslot; j += kW) {
           float top = rq.top[j][lane & (4 * kW - 1)];
 #pragma unroll
@@ -628,9 +608,6 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
           }
           if (lane == 0) rq.result[j] = imin;
         }
-#else
-        if (tid < kRvqSlots) rq.result[tid] = 0;
-#endif
         __syncthreads();
         for (int j = 0; j < nslot; ++j) {                  // the owners collect their answers
           const int o = rq.owner[j];
