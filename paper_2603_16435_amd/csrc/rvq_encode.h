@@ -106,6 +106,8 @@ __device__ __attribute__((always_inline)) inline float rvq_max4(float v) {
   rvq_pair<32>(__float_as_uint(v), a, b); return fmaxf(__uint_as_float(a), __uint_as_float(b));
 }
 
+typedef float rvq_norms4 __attribute__((ext_vector_type(4), aligned(4)));      // (the norms may start at any element)
+
 // ---- exact decisions by the whole workgroup, for the vectors with a near score whose entry nobody can name (rare: three
 // block maxima of one lane within the margin).  At the end of a stage, up to 16 such vectors at a time:
 //  1. The vectors become the 16 columns of an MFMA B operand and the float32 scores r . c - |c|^2 / 2 of all S entries
@@ -557,7 +559,7 @@ void rvq_encode_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ 
               const bf16_t* ent = stage_cb + (int64_t)(blk * 16 + e16) * kRvqD + kq * 8;
 #pragma unroll
               for (int ks = 0; ks < 4; ++ks) a[u][ks] = *reinterpret_cast<const u32x4_t*>(ent + ks * 32);
-              h[u] = *reinterpret_cast<const floatx4*>(stage_cn + blk * 16 + 4 * kq);
+              h[u] = *reinterpret_cast<const rvq_norms4*>(stage_cn + blk * 16 + 4 * kq);
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {

@@ -45,6 +45,14 @@ def _compare(x, cb, codes, res):
     return n_same, n_rows, n_diff_dec
 
 
+def _many(cb):
+    """Norms off the 16-byte grid, which the kernel for few vectors does not take: the one for many encodes, whatever the sizes."""
+    norms = binding.rl_rvq_codebook_norms(cb)
+    buf = torch.empty(norms.numel() + 1, device=norms.device)
+    buf[1:] = norms.flatten()
+    return buf[1:].view(norms.shape)
+
+
 @pytest.mark.parametrize("G,L,N,S", [(2, 300, 6, 128),      # ragged tail (L % 256 != 0), two groups
                                       (1, 1, 3, 64),         # a single vector, a single chunk per stage
                                       (3, 513, 16, 512),     # the value-cache shape of the paper's 8B setting (N=16, S=512)
@@ -63,7 +71,7 @@ def test_rvq_encode_key_cache_shape_sampled():
     # the key-cache shape of the paper's 8B setting, N = 56 stages of S = 1024 entries, L = 1024 vectors (one local window):
     # the oracle checks a seeded sample of 96 vectors in full (rows are independent)
     x, cb = synth.make_rvq_case(2, 1024, 56, 1024, device="cuda")
-    codes, res = binding.rl_rvq_encode(x, cb)
+    codes, res = binding.rl_rvq_encode(x, cb, _many(cb))          # (as with the groups of a whole model)
     torch.cuda.synchronize()
     pick = torch.from_numpy(np.random.default_rng(1).choice(1024, 96, replace=False)).cuda()
     for g in range(2):
@@ -86,12 +94,13 @@ def test_rvq_encode_ties_and_exact_recovery():
     picks = torch.randint(0, S, (L, N), generator=g)
     picks[picks == 40] = 7
     xx = sum(cb[0, i, picks[:, i]].float() for i in range(N)).to(torch.bfloat16).unsqueeze(0)
-    codes, res = binding.rl_rvq_encode(xx.cuda(), cb.cuda())
-    torch.cuda.synchronize()
     want, want_res = rvq.rvq_encode(_bits(xx[0]), _bits(cb[0]))
-    np.testing.assert_array_equal(codes[0].cpu().numpy(), want)
-    assert not bool((codes == 40).any())
-    assert float(res.float().abs().max()) == 0.0
+    for norms in (_many(cb.cuda()), None):
+        codes, res = binding.rl_rvq_encode(xx.cuda(), cb.cuda(), norms)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(codes[0].cpu().numpy(), want)
+        assert not bool((codes == 40).any())
+        assert float(res.float().abs().max()) == 0.0
 
 
 def test_rvq_encode_near_ties_are_decided_exactly():
@@ -106,28 +115,30 @@ def test_rvq_encode_near_ties_are_decided_exactly():
     cb[:, :, 0::2, 0] = 0
     cb[:, :, 1::2, :] = cb[:, :, 0::2, :]
     cb[:, :, 1::2, 0] = (sign * 2.0 ** -20).view(1, 1, -1)
-    n_exact = torch.zeros(1, dtype=torch.int32, device="cuda")
-    codes, res = binding.rl_rvq_encode(x, cb, count_exact=n_exact)
-    torch.cuda.synchronize()
     want, want_res = rvq.rvq_encode(_bits(x[0]), _bits(cb[0]))
-    got = codes[0].cpu().numpy()
-    assert (got % 2 == 1).any() and (got % 2 == 0).any()            # both members of pairs win somewhere
-    np.testing.assert_array_equal(got, want)
-    np.testing.assert_array_equal(_bits(res[0]), want_res)
-    n = int(n_exact.item())
-    print("decisions re-evaluated exactly:", n, "of", L * N)
-    assert n >= L * N
+    for norms in (_many(cb), None):
+        n_exact = torch.zeros(1, dtype=torch.int32, device="cuda")
+        codes, res = binding.rl_rvq_encode(x, cb, norms, count_exact=n_exact)
+        torch.cuda.synchronize()
+        got = codes[0].cpu().numpy()
+        assert (got % 2 == 1).any() and (got % 2 == 0).any()        # both members of pairs win somewhere
+        np.testing.assert_array_equal(got, want)
+        np.testing.assert_array_equal(_bits(res[0]), want_res)
+        n = int(n_exact.item())
+        print("decisions re-evaluated exactly:", n, "of", L * N)
+        assert n >= L * N
 
 
 def test_rvq_encode_exact_path_is_rare_on_ordinary_inputs():
     G, L, N, S = 2, 1024, 16, 1024
     x, cb = synth.make_rvq_case(G, L, N, S, device="cuda")
-    n_exact = torch.zeros(1, dtype=torch.int32, device="cuda")
-    binding.rl_rvq_encode(x, cb, count_exact=n_exact)
-    torch.cuda.synchronize()
-    n = int(n_exact.item())
-    print("decisions re-evaluated exactly:", n, "of", G * L * N)
-    assert n <= 0.01 * G * L * N
+    for norms in (_many(cb), None):
+        n_exact = torch.zeros(1, dtype=torch.int32, device="cuda")
+        binding.rl_rvq_encode(x, cb, norms, count_exact=n_exact)
+        torch.cuda.synchronize()
+        n = int(n_exact.item())
+        print("decisions re-evaluated exactly:", n, "of", G * L * N)
+        assert n <= 0.01 * G * L * N
 
 
 @pytest.mark.parametrize("G,L,N,S", [
@@ -140,18 +151,19 @@ def test_rvq_encode_exact_path_is_rare_on_ordinary_inputs():
     (1, 64, 2, 1024),         # two workgroups of a group, the largest codebook of that form
     (1, 33, 2, 1088),         # ... and one beyond it
     (2, 65, 2, 128),          # three workgroups of each of two groups
-    (130, 33, 1, 64),         # two workgroups of each of seventeen groups per die: more than fit the chip, the other kernel
+    (130, 33, 1, 64),         # two workgroups of each of seventeen groups per die: two more than fit the chip
     (88, 65, 1, 64),          # three of each of eleven: one more than fit
     (80, 65, 2, 128),         # three of each of ten
     (300, 16, 1, 64),         # up to 16 vectors: more workgroups than fit the chip
-    (376, 17, 2, 256),        # 47 workgroups a die ...
-    (384, 17, 2, 256),        # ... and 48, in two rounds
-    (384, 32, 2, 192),        # ... of a codebook too small for that
-    (8, 47, 2, 128),          # short stages, few decisions
-    (8, 48, 2, 128),          # enough vectors of a group
-    (241, 17, 4, 64),         # 16388 decisions
+    (376, 17, 2, 256),        # 47 workgroups a die, in two rounds
+    (384, 17, 2, 256),        # ... and 48
+    (384, 32, 2, 192),        # every one of them full
+    (8, 47, 2, 128),          # one vector short of three blocks
+    (8, 48, 2, 128),          # ... and three whole ones
+    (241, 17, 4, 64),         # one group on the last die
     (1, 1024, 2, 64),         # 32 workgroups on one die ...
     (1, 1025, 2, 64),         # ... and one more
+    (264, 96, 1, 64),         # so many that the sizes choose the kernel for many vectors
 ])
 def test_rvq_encode_of_few_vectors(G, L, N, S):
     x, cb = synth.make_rvq_case(G, L, N, S, device="cuda", seed=0x5EED0300)
@@ -160,7 +172,8 @@ def test_rvq_encode_of_few_vectors(G, L, N, S):
         torch.cuda.synchronize()
         if want_residual:
             print(_compare(x, cb, codes, res))
-            first = codes
+            first, many = codes, binding.rl_rvq_encode(x, cb, _many(cb))
+            assert torch.equal(many[0], codes) and np.array_equal(_bits(many[1]), _bits(res))
     np.testing.assert_array_equal(codes.cpu().numpy(), first.cpu().numpy())
 
 
@@ -187,7 +200,7 @@ def test_rvq_encode_of_few_vectors_settles_near_and_equal_entries_exactly(L):
 @pytest.mark.parametrize("L", [12, 30])
 @pytest.mark.parametrize("S", [512, 192])
 def test_rvq_codes_do_not_depend_on_how_many_vectors_are_encoded(L, S):
-    """Few vectors and the same ones in front of 1100 others (two kernels), among them vectors and entries that are not finite, for
+    """Few vectors and the same ones in front of 1100 others (three kernels: 16 or 32 vectors a workgroup, 512), among them vectors and entries that are not finite, for
     which the definition names no code: it is settled all the same, by the scores and not by the order the wavefronts finish in."""
     inf, nan = float("inf"), float("nan")
     x, cb = synth.make_rvq_case(2, 1100 + L, 3, S, seed=0x5EED0500, device="cuda")
@@ -197,7 +210,9 @@ def test_rvq_codes_do_not_depend_on_how_many_vectors_are_encoded(L, S):
     cb[1, 0, 5, 9], cb[1, 0, 6], cb[1, 0, S - 1, 127] = nan, inf, -inf          # some entries of a stage ...
     cb[1, 2, :, 1] = inf                                                        # ... all of them
     x[1, 3, 2] = inf
-    want, want_res = binding.rl_rvq_encode(x, cb)
+    want, want_res = binding.rl_rvq_encode(x, cb, _many(cb))
+    mid, mid_res = binding.rl_rvq_encode(x, cb)
+    assert torch.equal(mid, want) and np.array_equal(_bits(mid_res), _bits(want_res))
     for _ in range(4):
         codes, res = binding.rl_rvq_encode(x[:, :L].contiguous(), cb)
         np.testing.assert_array_equal(codes.cpu().numpy(), want[:, :L].cpu().numpy())
