@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-from paper_2603_16435_amd import synth
+from paper_2603_16435_amd import binding, synth
 from parity_util import compare_all, run_gpu, run_oracle
 
 pytestmark = pytest.mark.gpu
@@ -19,14 +19,19 @@ def off_grid(t):
 # wide tiles in the logits from 512 tiles of 256 x 64 on; one, two, three, five slabs of K, whole or with a tail
 @pytest.mark.parametrize("H,V,lengths", [(4, 33001, [130, 1, 0, 99]), (32, 33001, [64, 64, 64, 64]), (36, 33001, [129, 0, 3, 61]),
                                          (96, 40000, [193, 1, 1, 1]), (132, 33001, [200, 1, 0, 99])])
-def test_aligned_and_unaligned_operands_give_the_same_bits(H, V, lengths):
+@pytest.mark.parametrize("chunk", [0, 256])                  # the logits kept, or (more than 256 tokens) formed again for dS; in scoring neither
+def test_aligned_and_unaligned_operands_give_the_same_bits(H, V, lengths, chunk):
     cfg = synth.RolloutConfig("edge", 2, 2, 1, 64, H, V, "f32", 0.5, seed=71)
     b = synth.make_rollouts(cfg, "cuda", "packed", lengths=lengths)
-    want = run_gpu(b, "flow")
+    want = run_gpu(b, "flow", chunk_rows=chunk)
+    scored = binding.rl_token_logprob_tempered(b.hidden, b.weight, b.token_ids, b.mask, 1.0, b.cu_seqlens)
     b.weight, b.hidden = off_grid(b.weight), off_grid(b.hidden)
-    got = run_gpu(b, "flow")
+    got = run_gpu(b, "flow", chunk_rows=chunk)
     for name in OUT:
         assert torch.equal(getattr(got, name), getattr(want, name)), name
+    again = binding.rl_token_logprob_tempered(b.hidden, b.weight, b.token_ids, b.mask, 1.0, b.cu_seqlens)
+    for lp, lse in (scored, again):
+        assert torch.equal(lp, want.logprob) and torch.equal(lse, want.lse)
 
 
 @pytest.mark.parametrize("chunk", [0, 1024])

@@ -7,11 +7,16 @@ from paper_2603_16435_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 
-def score(b, hidden, ids, tau, static=False):
+def offsets(R, seqs=1):
+    """One sequence of R rows behind empty ones; of more than 64 sequences the preparation is in launches of its own."""
+    return torch.tensor([0] * seqs + [R], dtype=torch.int32, device="cuda")
+
+
+def score(b, hidden, ids, tau, static=False, seqs=1):
     R = hidden.shape[0]
     mask = torch.ones(R, dtype=torch.uint8, device="cuda")
     mask[b.T:] = 0
-    cu = torch.tensor([0, R], dtype=torch.int32, device="cuda")
+    cu = offsets(R, seqs)
     if static:
         out = tuple(torch.empty(R, device="cuda") for _ in range(2))
         binding.rl_token_logprob_static(hidden, b.weight, ids, mask, cu, *out, tau)
@@ -31,7 +36,8 @@ def test_few_tokens(H, V, T):
     ids = torch.cat([b.token_ids, torch.zeros(pad, dtype=torch.int32, device="cuda")])
     for tau in (1.0, 0.7):
         want = score(b, hidden, ids, tau)
-        for got in (score(b, b.hidden, b.token_ids, tau), score(b, b.hidden, b.token_ids, tau, static=True)):
+        for got in (score(b, b.hidden, b.token_ids, tau), score(b, b.hidden, b.token_ids, tau, static=True),
+                    score(b, b.hidden, b.token_ids, tau, seqs=70)):
             assert torch.equal(got[0], want[0][:T]) and torch.equal(got[1], want[1][:T])
         assert not want[0][T:].any()
     z = b.hidden.double().cpu() @ b.weight.double().cpu().t()
@@ -59,7 +65,7 @@ def test_large_weight(H, V, T):
     W, X = n(V, H) * H ** -0.5, n(300, H)
     ids = torch.randint(0, V, (300,), generator=g, device="cuda", dtype=torch.int32)
     mask = (torch.arange(300, device="cuda") < T).to(torch.uint8)
-    cu = lambda r: torch.tensor([0, r], dtype=torch.int32, device="cuda")
-    want = binding.rl_token_logprob_tempered(X, W, ids, mask, 1.0, cu(300))
-    got = binding.rl_token_logprob_tempered(X[:T], W, ids[:T], mask[:T], 1.0, cu(T))
-    assert torch.equal(got[0], want[0][:T]) and torch.equal(got[1], want[1][:T])
+    want = binding.rl_token_logprob_tempered(X, W, ids, mask, 1.0, offsets(300))
+    for seqs in (1, 70):
+        got = binding.rl_token_logprob_tempered(X[:T], W, ids[:T], mask[:T], 1.0, offsets(T, seqs))
+        assert torch.equal(got[0], want[0][:T]) and torch.equal(got[1], want[1][:T])
