@@ -256,9 +256,10 @@ __device__ inline GeneralTile general_tile(GemmDims& d, int pid) {
   GeneralTile t{};
   if (!resolve_dims(d, t.M, t.N, t.K)) return t;
   t.nk = (t.K + BK - 1) / BK; t.slices = 1;
-  // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs over the static grid
+  // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs, with dynamic N (logits) over the tiles that exist: dealt over the static grid, which
+  // is rounded up to 256 rows, they came two to a CU of one XCD while others had none (f32 scoring, us: 125 tokens, H 3816, V 4792 202 -> 154, 600, H 3072, V 3000 302 -> 175)
   const bool by_share = d.dyn == 1;
-  const int tiles_m = ((by_share ? t.M : d.M) + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
+  const int tiles_m = ((by_share ? t.M : d.M) + BM - 1) / BM, tiles_n = ((d.dyn == 2 ? t.N : d.N) + BN - 1) / BN;
   if (d.split_slots > 0) {
     const SplitK sk = split_k(tiles_m * tiles_n, t.nk, d.split_slots, 0);
     t.slices = sk.slices;
@@ -283,12 +284,14 @@ __device__ inline GeneralTile general_tile(GemmDims& d, int pid) {
 //
 // KG > 1: KG groups of such wavefronts share a tile, each taking every KG-th slab through LDS stages of its own; their accumulators are added in
 // order at the end (for tiles that are few and have a long K; a step of a K cut is then KG slabs).
-template <class T, int BM, int BN, int KG> constexpr int general_lds_bytes() { return KG * 2 * (BM + BN) * kSlabBytes; }
 //
-// PRE: slabs that are on their way in registers ahead of the one computed on.
-template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG, int PRE = 1>
-__device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, const Epi& epi,
-                                                                           int pid, unsigned char* smem_all) {
+// HOLD (16x16 blocks): a slab's loads are waited for where it is stored, behind the MFMAs of the one before.  By itself the compiler exchanges the middle elements where the two kinds of load
+// meet, ahead of the MFMAs, and waits for the loads there.  us without and with: scoring in f32, 2630 tokens, H 1024, V 1000 111 and 98; 13 tokens, H 3072, V 16 k 152 and 114; loss of 14 k tokens,
+// H 64, V 2000 318 and 285.  (More slabs on their way: no faster anywhere, 160 tokens and tiles of sixteen wavefronts, H 3072 101 with four against 97.)
+template <class T, int BM, int BN, int KG> constexpr int general_lds_bytes() { return KG * 2 * (BM + BN) * kSlabBytes; }
+template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG, bool HOLD>
+__device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const T* __restrict__ A, const T* __restrict__ B, const GemmDims& d, const GeneralTile& t,
+                                                                           const Epi& epi, unsigned char* smem_all) {
   constexpr int NT = WAVES_M * WAVES_N * 64;
   constexpr int BK = Elem<T>::kBK;
   constexpr int EPC = Elem<T>::kPerChunk;
@@ -302,8 +305,6 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
   static_assert(BM % ROWS_PER_PASS == 0 && (BN % ROWS_PER_PASS == 0 || BN < ROWS_PER_PASS), "tile vs threads");
   constexpr int A_BYTES = BM * kSlabBytes, B_BYTES = BN * kSlabBytes;
 
-  const GeneralTile t = general_tile<BM, BN, BK * KG>(d, pid);
-  if (!t.any) return;
   const int M = t.M, N = t.N, K = t.K, nk = t.nk, tm = t.tm, tn = t.tn;
 
   const int group = KG > 1 ? (int)threadIdx.x / NT : 0;
@@ -330,36 +331,34 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
     if (d.b_rows) r = d.b_rows[r];
     bp[p] = B + (int64_t)r * d.ldb + lchunk * EPC;
   }
-  uint4 ra[PRE][PA], rb[PRE][PB];
-  auto gload = [&](int k0, int i) __attribute__((always_inline)) {
+  uint4 ra[PA], rb[PB];
+  auto gload = [&](int k0) __attribute__((always_inline)) {
     if (k0 + BK <= K) {                              // a whole slab
 #pragma unroll
-      for (int p = 0; p < PA; ++p) ra[i][p] = *reinterpret_cast<const uint4*>(ap[p] + k0);
+      for (int p = 0; p < PA; ++p) ra[p] = *reinterpret_cast<const uint4*>(ap[p] + k0);
 #pragma unroll
-      for (int p = 0; p < PB; ++p) rb[i][p] = *reinterpret_cast<const uint4*>(bp[p] + k0);
+      for (int p = 0; p < PB; ++p) rb[p] = *reinterpret_cast<const uint4*>(bp[p] + k0);
     } else {
       const bool ok = (k0 + lchunk * EPC) < K;
 #pragma unroll
-      for (int p = 0; p < PA; ++p) ra[i][p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
+      for (int p = 0; p < PA; ++p) ra[p] = ok ? *reinterpret_cast<const uint4*>(ap[p] + k0) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-      for (int p = 0; p < PB; ++p) rb[i][p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
+      for (int p = 0; p < PB; ++p) rb[p] = ok ? *reinterpret_cast<const uint4*>(bp[p] + k0) : make_uint4(0, 0, 0, 0);
     }
   };
-  // Held behind the MFMAs: by itself the compiler exchanges the middle elements where the two kinds of load meet, ahead of the MFMAs, and waits for the loads there.  Scoring in f32,
-  // us: 2630 tokens, H 1024, V 1000 112.3 -> 96.6; 1872, H 600, V 657 69.0 -> 63.9; 1752, H 1200, V 4000 274.5 -> 238.3; loss of 15.5 k tokens, H 64, V 2000 334.7 -> 299.7.
   auto stored = [](uint4 v) __attribute__((always_inline)) {
     if (!SMALL) return v;
-    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    if constexpr (HOLD) asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
     return make_uint4(v.x, v.z, v.y, v.w);
   };
-  auto lstore = [&](int buf, int i) __attribute__((always_inline)) {
+  auto lstore = [&](int buf) __attribute__((always_inline)) {
     unsigned char* as = smem + buf * (A_BYTES + B_BYTES);
     unsigned char* bs = as + A_BYTES;
 #pragma unroll
-    for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(ra[i][p]);
+    for (int p = 0; p < PA; ++p) *reinterpret_cast<uint4*>(as + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(ra[p]);
 #pragma unroll
     for (int p = 0; p < PB; ++p)
-      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(rb[i][p]);
+      if (BN % ROWS_PER_PASS == 0 || lrow < BN) *reinterpret_cast<uint4*>(bs + lds_off(lrow + p * ROWS_PER_PASS, lchunk)) = stored(rb[p]);
   };
 
   typename L::acc_t acc[MB][NB];
@@ -370,23 +369,15 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
 #pragma unroll
       for (int e = 0; e < L::kRegs; ++e) acc[i][j][e] = 0.f;
 
-  static_assert(PRE == 1 || PRE % 2 == 0, "stage of a slab");
-  TileCtx c;
-  c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
-  c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
-  c.slice = t.slice; c.slices = t.slices;
-  const typename Epi::Pre pre = epi.template preload<L>(c, d);
   if (nk > 0) {
-#pragma unroll
-    for (int i = 0; i < PRE; ++i)
-      if (i < nk) gload((k_begin + i * KG) * BK, i);
-    lstore(0, 0);
+    gload(k_begin * BK);
+    lstore(0);
   }
   __syncthreads();
   const int frow = lane & (L::kBlk - 1), fq = lane / L::kBlk;
-  auto slab = [&](int kt, int i) __attribute__((always_inline)) {
+  for (int kt = 0; kt < nk; ++kt) {
     const int cur = kt & 1;
-    if (kt + PRE < nk) gload((k_begin + (kt + PRE) * KG) * BK, i);
+    if (kt + 1 < nk) gload((k_begin + (kt + 1) * KG) * BK);
     const unsigned char* as = smem + cur * (A_BYTES + B_BYTES);
     const unsigned char* bs = as + A_BYTES;
     typedef typename GeneralLayout<SMALL>::F F;
@@ -413,18 +404,8 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
               acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
           }
     }
-    if (kt + 1 < nk) lstore(cur ^ 1, (i + 1) % PRE);
+    if (kt + 1 < nk) lstore(cur ^ 1);
     __syncthreads();
-  };
-  if constexpr (PRE == 1) {
-    for (int kt = 0; kt < nk; ++kt) slab(kt, 0);
-  } else {
-    for (int kt0 = 0; kt0 < nk; kt0 += PRE)
-#pragma unroll
-      for (int i = 0; i < PRE; ++i) {
-        if (kt0 + i >= nk) break;
-        slab(kt0 + i, i);
-      }
   }
 
   if constexpr (KG > 1) {                            // (the epilogues used with it need no barrier)
@@ -436,13 +417,34 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
 #pragma unroll
     for (int g = 1; g < KG; ++g) acc[0][0] += part[(g - 1) * NT + tid];
   }
+  TileCtx c;
+  c.m0 = tm * BM + wm * WM; c.n0 = tn * BN + wn * WN;
+  c.Mv = M; c.Nv = N; c.lane = lane; c.wm = wm; c.wn = wn; c.tile_m = tm; c.tile_n = tn; c.tid = tid;
+  c.slice = t.slice; c.slices = t.slices;
+  const typename Epi::Pre pre = epi.template preload<L>(c, d);
   epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
+}
+template <class Epi> constexpr bool kIsForward = false;      // (f32 logits)
+// Whether an f32 forward in narrow tiles has two workgroups on some CUs and no more on any, all of whole bands: these start together and stay in step, and do better when each waits for its
+// loads as soon as they are out (HOLD = false) and the other computes meanwhile.  Scoring in f32, us, held and not: 4 rows of tiles x 70 at H 3072 169 and 162, 8 x 35 at H 3916 231
+// and 214, 16 x 17 228 and 215.  Others: one workgroup a CU, 8 x 32 98 and 127 (H 3072); several rounds, 8 x 65 259 and 302; broken or more bands, 40 x 7 170 and 180.
+__device__ inline bool two_a_cu(const GeneralTile& t, const GemmDims& d, int bm, int bn) {
+  constexpr int kCus = 256;
+  const int tiles_m = (t.M + bm - 1) / bm, n = tiles_m * ((t.N + bn - 1) / bn);
+  return n > kCus && n <= 2 * kCus && (tiles_m <= d.group_m || tiles_m == 2 * d.group_m);
 }
 template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG = 1>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * KG * 64, WAVES_M * WAVES_N * KG > 8 ? 1 : 2)
 void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, Epi epi) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[general_lds_bytes<T, BM, BN, KG>()];
-  gemm_nt_general_tile<T, Epi, BM, BN, WAVES_M, WAVES_N, KG>(A, B, d, epi, blockIdx.x, smem);
+  const GeneralTile t = general_tile<BM, BN, Elem<T>::kBK * KG>(d, blockIdx.x);
+  if (!t.any) return;
+  if constexpr (kIsForward<Epi> && BN / WAVES_N < 32 && WAVES_M * WAVES_N == 4)
+    if (two_a_cu(t, d, BM, BN)) {
+      gemm_nt_general_tile<T, Epi, BM, BN, WAVES_M, WAVES_N, KG, false>(A, B, d, t, epi, smem);
+      return;
+    }
+  gemm_nt_general_tile<T, Epi, BM, BN, WAVES_M, WAVES_N, KG, true>(A, B, d, t, epi, smem);
 }
 // Two f32 contractions in tiles of 64 x 16 with four K groups in one launch: workgroups [0, n1) work on the first, the rest on the second.
 template <class Epi1, class Epi2>
@@ -450,8 +452,13 @@ __global__ __launch_bounds__(1024)
 void gemm_nt_small_pair_kernel(const float* __restrict__ A1, const float* __restrict__ B1, GemmDims d1, Epi1 epi1, int n1,
                                const float* __restrict__ A2, const float* __restrict__ B2, GemmDims d2, Epi2 epi2) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[general_lds_bytes<float, 64, 16, 4>()];
-  if ((int)blockIdx.x < n1) gemm_nt_general_tile<float, Epi1, 64, 16, 4, 1, 4>(A1, B1, d1, epi1, blockIdx.x, smem);
-  else gemm_nt_general_tile<float, Epi2, 64, 16, 4, 1, 4>(A2, B2, d2, epi2, (int)blockIdx.x - n1, smem);
+  if ((int)blockIdx.x < n1) {
+    const GeneralTile t = general_tile<64, 16, Elem<float>::kBK * 4>(d1, blockIdx.x);
+    if (t.any) gemm_nt_general_tile<float, Epi1, 64, 16, 4, 1, 4, true>(A1, B1, d1, t, epi1, smem);
+  } else {
+    const GeneralTile t = general_tile<64, 16, Elem<float>::kBK * 4>(d2, (int)blockIdx.x - n1);
+    if (t.any) gemm_nt_general_tile<float, Epi2, 64, 16, 4, 1, 4, true>(A2, B2, d2, t, epi2, smem);
+  }
 }
 
 // ------------------------------------------------------------------ bf16 hot kernel

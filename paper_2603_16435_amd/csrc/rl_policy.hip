@@ -557,7 +557,7 @@ void logits_few_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ 
   }
 }
 
-// Logits of a small f32 batch with the preparation: the general kernel's narrow tiles by sixteen wavefronts, four slabs on their way.  (A's loads ahead of local_rows
+// Logits of a small f32 batch with the preparation: the general kernel's narrow tiles by sixteen wavefronts.  (A's loads ahead of local_rows
 // as well: 29.0 us of that call instead of 27.9.)
 constexpr int kLocalRows = 1024;
 template <class Epi>
@@ -568,7 +568,8 @@ void logits_small_kernel(const float* __restrict__ W, const float* __restrict__ 
   __shared__ LocalRows<kLocalRows> l;
   local_rows<1024>(s, l);
   d.n_real = &l.n; d.b_rows = l.rows; epi.ids_c = l.ids;
-  gemm_nt_general_tile<float, Epi, kBM, kF32SmallBN, 16, 1, 1, 4>(W, X, d, epi, (int)blockIdx.x - 1, smem);
+  const GeneralTile t = general_tile<kBM, kF32SmallBN, Elem<float>::kBK>(d, (int)blockIdx.x - 1);
+  if (t.any) gemm_nt_general_tile<float, Epi, kBM, kF32SmallBN, 16, 1, 1, true>(W, X, d, t, epi, smem);
 }
 
 // one wavefront per row; rows that count are left alone (the dX epilogue writes them)
@@ -1398,8 +1399,6 @@ static bool few_forward_tiles(int M, int N, int K) {
   return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + kBM - 1) / kBM) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
-template <class Epi> constexpr bool kIsForward = false;
-template <bool KEEP> constexpr bool kIsForward<EpiFwd<float, KEEP>> = true;
 template <class Tune, class Epi>
 static void launch_gemm(const float* A, const float* B, const GemmDims& d, const Epi& epi, hipStream_t s) {
   const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);

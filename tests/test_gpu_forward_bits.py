@@ -22,6 +22,18 @@ def test_f32_log_probs_do_not_depend_on_the_chunk(V, rows, tau):
             assert torch.equal(getattr(got, name), getattr(want, name)), (chunk, name)
 
 
+# narrow tiles one short of and at a CU each, one past it (two on some), at two each, one past that; one, two and broken bands of rows of tiles; a K tail.  The same
+# tokens among 9000 rows take wide tiles
+@pytest.mark.parametrize("V,tiles_n", [(2048, 31), (2048, 32), (2000, 33), (2048, 64), (2048, 65), (4096, 17), (4096, 32), (3000, 22), (10240, 7)])
+def test_f32_log_probs_do_not_depend_on_how_the_tiles_fill_the_chip(V, tiles_n):
+    cfg = synth.RolloutConfig("bits", 1, 1, 1, 8, 100, V, "f32", 0.5, seed=64)
+    b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[9000])
+    n = 16 * tiles_n - 5
+    score = lambda r: binding.rl_token_logprob_tempered(b.hidden[:r], b.weight, b.token_ids[:r], b.mask[:r], 0.9, torch.tensor([0, r], dtype=torch.int32, device="cuda"))
+    for got, want in zip(score(n), score(9000)):
+        assert torch.equal(got, want[:n])
+
+
 @pytest.mark.parametrize("backward", [False, True])                        # True: the logits are kept as well
 def test_f32_square_tiles_of_unaligned_operands_give_the_same_bits(backward):
     cfg = synth.RolloutConfig("bits", 2, 4, 1, 1000, 68, 30000, "f32", 0.5, seed=63)          # 118 x 32 square tiles: fifteen rounds

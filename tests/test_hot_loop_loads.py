@@ -41,13 +41,16 @@ def test_the_narrow_f32_tiles_wait_for_their_loads_where_they_store_them(tmp_pat
     subprocess.run([copy, f"--dump-section=.hip_fatbin={fat}", binding.LIB_PATH, os.devnull], check=True)
     subprocess.run([unbundle, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}", f"--output={dev}"], check=True)
     text = subprocess.run([dump, "-d", "--no-show-raw-insn", dev], check=True, capture_output=True, text=True).stdout
-    met = 0
+    met = held = 0
     for f in re.split(r"\n(?=[0-9a-f]+ <)", text):
         if not re.match(r"[0-9a-f]+ <\S*(gemm_nt_kernelIf\S*ELi16ELi\d+ELi1E|gemm_nt_small_pair_kernel)", f):
             continue
+        both = re.match(r"[0-9a-f]+ <\S*EpiFwd\S*ELi256ELi16ELi4E", f)           # has a form that waits at once as well
         ins = [line.split("//")[0].strip() for line in f.splitlines()[1:]]
         for i, (this, following) in enumerate(zip(ins, ins[1:])):
             if this.startswith("s_waitcnt vmcnt") and re.match(r"v_mov_b32_e32 v\d+, v\d+", following):
                 met += 1
-                assert any(s.startswith("ds_write_b128") for s in ins[i:i + 20]), (f.splitlines()[0], ins[i:i + 20])
-    assert met >= 20
+                ok = any(s.startswith("ds_write_b128") for s in ins[i:i + 20])
+                held += bool(both) and ok
+                assert ok or both, (f.splitlines()[0], ins[i:i + 20])
+    assert met >= 20 and held >= 2 * 4
