@@ -493,10 +493,7 @@ __global__ __launch_bounds__(1024) void prep_small_kernel(SmallPrep s, RowFill f
 // The preparation inside the launch of the logits (logits_small_kernel, logits_few_kernel), for batches of so few rows that every workgroup can work out for itself
 // which ones count: workgroup 0 does the above, for the launches that follow, the others go by their own list in LDS (2 us, about what the two
 // dependent loads of the row map took).  A launch is saved: scoring of 99 tokens, H 2048, V 32000 46.7 -> 42.4 us; f32 loss of 356 tokens, H 128, V 1024 35.1 -> 30.3.
-template <int ROWS> struct LocalRows {
-  int n, rows[ROWS], ids[ROWS];
-  int a[kSmallSeqs], b[kSmallSeqs], count[ROWS / 64];
-};
+template <int ROWS> struct LocalRows { int n, rows[ROWS], ids[ROWS], count[ROWS / 64]; };
 template <int NT, int ROWS>
 __device__ inline void local_rows(const SmallPrep& s, LocalRows<ROWS>& l) {
   constexpr int kPer = (ROWS + NT - 1) / NT;
@@ -509,21 +506,20 @@ __device__ inline void local_rows(const SmallPrep& s, LocalRows<ROWS>& l) {
     on[k] = false; y[k] = -1;
     if (r < s.R) { on[k] = s.mask[r]; y[k] = s.ids[r]; }
   }
-  if (t < 64) {                                                // (as there: a valid range at or behind every earlier offset, of a valid prompt)
-    int a = INT32_MIN, b = 0, g = 0;
-    if (t < s.B) { a = s.cu[t]; b = s.cu[t + 1]; if (s.group_idx) g = s.group_idx[t]; }
-    const int hi = wave_scan_max(a, s.B);
-    const bool ok = a >= 0 && a <= b && b <= s.R && a >= hi && (!s.group_idx || (g >= 0 && g < s.P));
-    l.a[t] = ok ? a : 0; l.b[t] = ok ? b : 0;
-  }
-  __syncthreads();
+  // A lane of every wavefront has a sequence (as there: a valid range at or behind every earlier offset, of a valid prompt), and the lanes put together which of
+  // the wavefront's 64 rows are in one: no barrier, and no walk over the sequences (60 of them, 947 rows, V 114 in f32 25.6 us that way).
+  int a = INT32_MIN, b = 0, g = 0;
+  if (lane < s.B) { a = s.cu[lane]; b = s.cu[lane + 1]; if (s.group_idx) g = s.group_idx[lane]; }
+  const int hi = wave_scan_max(a, s.B);
+  if (!(lane < s.B && a >= 0 && a <= b && b <= s.R && a >= hi && (!s.group_idx || (g >= 0 && g < s.P)))) a = b = 0;
   unsigned long long m[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int r = k * NT + t;
-    bool in = false;
-    for (int i = 0; i < s.B; ++i) in |= r >= l.a[i] && r < l.b[i];
-    m[k] = __ballot(in && on[k] && y[k] >= 0 && y[k] < s.V);
+    const int r = k * NT + t, r0 = r - lane, lo = min(max(a - r0, 0), 64), up = min(max(b - r0, 0), 64);
+    unsigned long long in = up > lo ? ~0ull >> (64 - (up - lo)) << lo : 0ull;
+    for (int o = 1; o < 64 && o < s.B; o <<= 1) in |= __shfl_xor(in, o);
+    in = __shfl(in, 0);
+    m[k] = __ballot((in >> lane & 1) && on[k] && y[k] >= 0 && y[k] < s.V);
     if (lane == 0 && r < ROWS) l.count[r >> 6] = __popcll(m[k]);
   }
   __syncthreads();
@@ -1511,9 +1507,14 @@ static bool few_tokens(const rl_batch* b, const Plan& p) {
   return p.dtype == RL_BF16 && !p.stash && !p.keep && p.R <= kFewTokens && (p.tiles_v + 127) / 128 % 2 && !small_k<EpiFwd<bf16_t>>(p.H) &&
          (reinterpret_cast<uintptr_t>(b->weight) | reinterpret_cast<uintptr_t>(b->hidden)) % 16 == 0;
 }
-// ... with W in non-temporal loads where it is larger than the 256 MB of the memory-side cache, so that a next call finds nothing of it in any case: 110 tokens, H 3584,
-// V 152064 263 -> 252 us, 40 at H 4096, V 151936 296 -> 274.  A W of 131 MB (H 2048, V 32000), scored again and again, 25 tokens 30.7 -> 37.8, 110 tokens 36.9 -> 40.2.
-static bool few_streams_w(const Plan& p) { return (int64_t)p.V * p.H * 2 > (int64_t)256 << 20; }
+// ... with W in non-temporal loads where it is larger than the 256 MB of the memory-side cache, so that a next call finds nothing of it in any case, and its rows lie on lines of 128
+// bytes.  us without and with, scored again and again: 5 tokens, H 3584, V 83705 (600 MB) 128 and 118; 60 tokens, H 2048, V 80566 (330 MB) 99 and 93; 40 at H 4096, V 151936 291 and 266;
+// behind 1 GB of other stores 30 to 80 us less.  A W of 131 MB (H 2048, V 32000) 25 tokens 30.7 and 37.8, 110 tokens 36.9 and 40.2; rows off the lines, each of which is then taken
+// twice: 5 tokens, H 2040, V 142262 152 and 169, H 3592, V 152064 241 and 259.
+static bool few_streams_w(const rl_batch* b, const Plan& p) { return (int64_t)p.V * p.H * 2 > (int64_t)256 << 20 && p.H % 64 == 0 && reinterpret_cast<uintptr_t>(b->weight) % 128 == 0; }
+// ... and the preparation in the same launch where it is one to three rounds of workgroups, each of which works out the rows: us in the launch and ahead of it, 99 tokens, V 32000
+// 35.5 and 38.1, 120 tokens, H 512, V 68000 40.4 and 42.2; five rounds, 38 tokens in as many sequences, H 128, V 153761 41.7 and 39.6, 110 tokens at the 7B head 246 and 241.
+static bool few_prepare(const Plan& p) { return p.tiles_v <= 3 * 128; }
 template <bool NT> static auto few_kernel(int64_t rows, bool prep) {
   return prep ? (rows <= 64 ? logits_few_kernel<64, true, NT> : logits_few_kernel<128, true, NT>) : rows <= 64 ? logits_few_kernel<64, false, NT> : logits_few_kernel<128, false, NT>;
 }
@@ -1535,7 +1536,7 @@ static void run_prep(const rl_batch* b, const Plan& p, const Ptrs& q, const int3
   clear(out.logprob, 0); clear(out.lse, 0); clear(out.coeff, 0);
   if (!late) clear_last();
   if (!late && p.R <= kSmallRows && p.B <= kSmallSeqs && (!adv.blocks || p.P <= kSmallPrompts)) {
-    job = PrepJob{small_logits(p) || few_tokens(b, p),
+    job = PrepJob{small_logits(p) || (few_tokens(b, p) && few_prepare(p)),
                   SmallPrep{b->mask, b->token_ids, b->cu_seqlens, group_idx, (int)p.R, p.V, p.P, p.B, q.seq_len, q.cstart, q.row_map, q.ids_c, q.cpos, out.row_map, q.ctrl,
                             ChunkJob{p.stash ? q.desc : nullptr, p.n_desc, p.Tc, p.max_len}, out.stats}, f, adv};
     // (there, outputs are cleared while other workgroups still read the inputs: with one in the place of another the preparation goes first)
@@ -1577,7 +1578,7 @@ static void run_forward(const rl_batch* b, const Plan& p, const Ptrs& q, float* 
         few = few_tokens(b, p);
         if (few) {
           const EpiFwd<T> e{q.ids_c, q.zy, q.part, kFewTokens, p.V, p.inv_tau, q.ycol, nullptr};
-          auto kern = few_streams_w(p) ? few_kernel<true>(p.R, prep.on) : few_kernel<false>(p.R, prep.on);
+          auto kern = few_streams_w(b, p) ? few_kernel<true>(p.R, prep.on) : few_kernel<false>(p.R, prep.on);
           kern<<<2 * p.tiles_v + (prep.on ? 1 : 0), 256, 0, s>>>(W, X, d, e, prep.s, prep.f, prep.adv);
         }
       } else if (prep.on) {

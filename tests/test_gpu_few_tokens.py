@@ -57,8 +57,8 @@ def test_rows_scattered_and_none_counting():
     assert not lp.any() and not lse.any()
 
 
-# a weight larger than the memory-side cache, with and without a K tail: non-temporal loads
-@pytest.mark.parametrize("H,V,T", [(4104, 32768, 3), (5120, 32000, 100)])
+# a weight larger than the memory-side cache: non-temporal loads, but where its rows are off the lines; more rounds of workgroups than prepare for themselves
+@pytest.mark.parametrize("H,V,T", [(4104, 32768, 3), (4160, 32768, 3), (5120, 32000, 100), (1024, 140000, 64), (960, 140000, 65)])
 def test_large_weight(H, V, T):
     g = torch.Generator(device="cuda").manual_seed(97)
     n = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.bfloat16)
