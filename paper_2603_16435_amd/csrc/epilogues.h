@@ -297,7 +297,6 @@ struct EpiFwd {
     }
   }
 };
-template <bool KEEP> constexpr bool kIsForward<EpiFwd<float, KEEP>> = true;
 
 // ---- forward that also keeps the chunk's unnormalised probabilities for a single-pass backward.
 //      Every token has a reference ref_t close to its logsumexp, known before the contraction

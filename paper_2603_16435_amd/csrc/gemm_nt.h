@@ -249,17 +249,36 @@ __device__ inline float acc_read(const V& v, int i) {
   }
 }
 
+// Narrow tiles of logits (`there` columns of the tiles_n of the static bounds exist): whether equal runs over the static grid put two on some CUs and three on none.  Workgroups that
+// start together like this stay in step; they do best with the static runs and when each waits for its loads as soon as they are out (HOLD = false, below) and the other
+// computes meanwhile.  In a run there are whole bands and part of one.  (Static grids of more than four workgroups a CU: those that do not exist make room, and the rest are not in step.)
+// Scoring in f32, us, so and with held loads over the tiles that exist: 12 rows of tiles x 23, H 3916 213 and 230, 4 x 70, H 3072 161 and 168.  Others: one tile a CU at the most,
+// 8 x 32, H 3072 127 and 98, 40 x 5 165 and 115; several on some, 12 x 33 302 and 180, 8 x 65 302 and 259; 100 x 4 206 and 177.  (The host asks for both forms where the bounds and K
+// leave it open, may_be_two_a_cu: the second one costs short tiles 0.7 of 28 us.)
+__device__ inline bool two_a_cu(int tiles_m, int tiles_n, int there, int group_m) {
+  const int n = tiles_m * there, run = (tiles_m * tiles_n + kXcds - 1) / kXcds;
+  if (n <= 32 * kXcds || n > 64 * kXcds || run > 128) return false;         // (ahead of the divisions)
+  const int rows = tiles_m < group_m ? tiles_m : group_m, band = rows * tiles_n, part = run % band;
+  return run / band * rows * there + (part < rows * there ? part : rows * there) <= 64;
+}
+
 // Tile, and slice of K, of a workgroup of the general and the f32 kernel.
-struct GeneralTile { bool any; int M, N, K, nk, tm, tn, k_begin, slice, slices; };       // nk slabs of BK from slab k_begin on
-template <int BM, int BN, int BK>
+struct GeneralTile { bool any, two; int M, N, K, nk, tm, tn, k_begin, slice, slices; };       // nk slabs of BK from slab k_begin on; two: two_a_cu
+template <int BM, int BN, int BK, bool TWO = false>      // TWO: ask two_a_cu
 __device__ inline GeneralTile general_tile(GemmDims& d, int pid) {
   GeneralTile t{};
   if (!resolve_dims(d, t.M, t.N, t.K)) return t;
   t.nk = (t.K + BK - 1) / BK; t.slices = 1;
-  // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs, with dynamic N (logits) over the tiles that exist: dealt over the static grid, which
-  // is rounded up to 256 rows, they came two to a CU of one XCD while others had none (f32 scoring, us: 125 tokens, H 3816, V 4792 202 -> 154, 600, H 3072, V 3000 302 -> 175)
+  // dynamic M (dX): XCD shares of the M-tiles that exist; otherwise equal runs, of narrow tiles with dynamic N (logits) over those that exist: dealt over the static grid, which
+  // is rounded up to 256 rows, they came two to a CU of one XCD while others had none (f32 scoring, us: 125 tokens, H 3816, V 4792 202 -> 154, 600, H 3072, V 3000 302 -> 181)
   const bool by_share = d.dyn == 1;
-  const int tiles_m = ((by_share ? t.M : d.M) + BM - 1) / BM, tiles_n = ((d.dyn == 2 ? t.N : d.N) + BN - 1) / BN;
+  const int tiles_m = ((by_share ? t.M : d.M) + BM - 1) / BM;
+  int tiles_n = (d.N + BN - 1) / BN;
+  if (d.dyn == 2 && BN == 16) {
+    const int there = (t.N + BN - 1) / BN;
+    t.two = TWO && two_a_cu(tiles_m, tiles_n, there, d.group_m);
+    if (!t.two) tiles_n = there;
+  }
   if (d.split_slots > 0) {
     const SplitK sk = split_k(tiles_m * tiles_n, t.nk, d.split_slots, 0);
     t.slices = sk.slices;
@@ -424,23 +443,14 @@ __device__ __attribute__((always_inline)) inline void gemm_nt_general_tile(const
   const typename Epi::Pre pre = epi.template preload<L>(c, d);
   epi.template run<L, MB, NB, BM, BN, WAVES_M, WAVES_N, false>(acc, c, smem, d, pre);
 }
-template <class Epi> constexpr bool kIsForward = false;      // (f32 logits)
-// Whether an f32 forward in narrow tiles has two workgroups on some CUs and no more on any, all of whole bands: these start together and stay in step, and do better when each waits for its
-// loads as soon as they are out (HOLD = false) and the other computes meanwhile.  Scoring in f32, us, held and not: 4 rows of tiles x 70 at H 3072 169 and 162, 8 x 35 at H 3916 231
-// and 214, 16 x 17 228 and 215.  Others: one workgroup a CU, 8 x 32 98 and 127 (H 3072); several rounds, 8 x 65 259 and 302; broken or more bands, 40 x 7 170 and 180.
-__device__ inline bool two_a_cu(const GeneralTile& t, const GemmDims& d, int bm, int bn) {
-  constexpr int kCus = 256;
-  const int tiles_m = (t.M + bm - 1) / bm, n = tiles_m * ((t.N + bn - 1) / bn);
-  return n > kCus && n <= 2 * kCus && (tiles_m <= d.group_m || tiles_m == 2 * d.group_m);
-}
-template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG = 1>
+template <class T, class Epi, int BM, int BN, int WAVES_M, int WAVES_N, int KG = 1, bool TWO = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * KG * 64, WAVES_M * WAVES_N * KG > 8 ? 1 : 2)
 void gemm_nt_kernel(const T* __restrict__ A, const T* __restrict__ B, GemmDims d, Epi epi) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[general_lds_bytes<T, BM, BN, KG>()];
-  const GeneralTile t = general_tile<BM, BN, Elem<T>::kBK * KG>(d, blockIdx.x);
+  const GeneralTile t = general_tile<BM, BN, Elem<T>::kBK * KG, TWO>(d, blockIdx.x);
   if (!t.any) return;
-  if constexpr (kIsForward<Epi> && BN / WAVES_N < 32 && WAVES_M * WAVES_N == 4)
-    if (two_a_cu(t, d, BM, BN)) {
+  if constexpr (TWO)
+    if (t.two) {
       gemm_nt_general_tile<T, Epi, BM, BN, WAVES_M, WAVES_N, KG, false>(A, B, d, t, epi, smem);
       return;
     }

@@ -1238,6 +1238,11 @@ static bool small_dx(int M, int N, int K) {
   return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + 63) / 64) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
+// The launch of grads_small.h: blocks of 16 columns of a dX workgroup (two where those of dX are one round of the CUs at most, else four), workgroups of dX and of dX and dW.
+static int small_dx_cols(int tc, int H) { return tc / 16 * ((H + 31) / 32) <= kHotSlots ? 2 : 4; }
+static int small_dx_blocks(int tc, int H) { const int w = 16 * small_dx_cols(tc, H); return tc / 16 * ((H + w - 1) / w); }
+static int small_grads_blocks(int tc, int H, int V) { return small_dx_blocks(tc, H) + (V + 15) / 16 * ((H + 16 * kGradNBW - 1) / (16 * kGradNBW)); }
+
 // whether two arrays of so many bytes share memory
 static bool meets(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
   const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
@@ -1303,8 +1308,9 @@ static rl_status make_plan(const rl_batch* b, const rl_params* prm, bool bwd, Pl
   // The whole backward of a small f32 batch in one launch, see grads_small.h.  What it gains is launches; a workgroup of dX walks the whole vocabulary by itself, so a
   // large one takes longer than they did.  us of the call, former launches / this one, 16, 400, 2000 rows: H 16, V 1000 43 46 73 / 28 31 51, V 2000 40 48 84 / 34 39 61,
   // V 4000 41 54 99 / 48 56 78, V 16000 47 87 212 / 120 143 185; H 128, V 300 42 47 77 / 28 31 57, V 2000 45 59 113 / 40 47 88; H 512, V 500 55 68 - / 40 50 -.
+  // It is to be one round of two workgroups a CU, or of a small vocabulary: us likewise, H 4, V 1000 6000, 8000, 16000 rows 135 149 283 / 116 173 337; V 700 8000, 16000 rows 140 270 / 133 267.
   // (It adds up the loss as well, out of group_idx.)
-  p.small_grads = p.small_pair && p.keep && b->V <= 2048 && !on_gradients(b->hidden, x_bytes) && !on_gradients(b->weight, w_bytes) && !on_gradients(b->group_idx, 4 * (size_t)b->B);
+  p.small_grads = p.small_pair && p.keep && b->V <= 2048 && (b->V <= 3 * kBM || small_grads_blocks(tc, b->H, b->V) <= 2 * kHotSlots) && !on_gradients(b->hidden, x_bytes) && !on_gradients(b->weight, w_bytes) && !on_gradients(b->group_idx, 4 * (size_t)b->B);
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up256(bytes); return at; };
   const size_t Rp = (size_t)rp + 256;
@@ -1395,6 +1401,10 @@ static bool few_forward_tiles(int M, int N, int K) {
   return f32_tile_n(M, N, K, false) == kF32SmallBN && (int64_t)((M + kBM - 1) / kBM) * ((N + kF32SmallBN - 1) / kF32SmallBN) <= kHotSlots;
 }
 
+template <class Epi> constexpr bool kIsForward = false;
+template <bool KEEP> constexpr bool kIsForward<EpiFwd<float, KEEP>> = true;
+// f32 logits in narrow tiles of which two may come to share a CU (two_a_cu), over more than eight slabs
+static bool may_be_two_a_cu(int tiles, int K) { return tiles > kHotSlots && tiles <= 4 * kHotSlots && K > 256; }
 template <class Tune, class Epi>
 static void launch_gemm(const float* A, const float* B, const GemmDims& d, const Epi& epi, hipStream_t s) {
   const int bn = f32_tile_n(d.M, d.N, d.K, d.split_slots > 0);
@@ -1427,6 +1437,10 @@ static void launch_gemm(const float* A, const float* B, const GemmDims& d, const
   if constexpr (kIsForward<Epi>) {
     if (few_forward_tiles(d.M, d.N, d.K)) {
       gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 16, 1><<<tiles, 1024, 0, s>>>(A, B, d, epi);
+      return;
+    }
+    if (bn == kF32SmallBN && may_be_two_a_cu(tm * tn, d.K)) {
+      gemm_nt_kernel<float, Epi, kBM, kF32SmallBN, 4, 1, 1, true><<<tiles, 256, 0, s>>>(A, B, d, epi);
       return;
     }
   }
@@ -1620,9 +1634,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
   if constexpr (sizeof(T) == 4)
     if (p.small_grads) {
       ProfScope ps(RL_PROF_GEMM_BWD, s);
-      // (blocks of 32 columns where those of dX are one round of the CUs at most, else of 64)
-      const int rows = p.Tc / 16, nbx = rows * ((p.H + 31) / 32) <= kHotSlots ? 2 : 4, xc = (p.H + 16 * nbx - 1) / (16 * nbx), nx = rows * xc;
-      const int n = nx + (p.V + 15) / 16 * ((p.H + 16 * kGradNBW - 1) / (16 * kGradNBW));
+      const int nbx = small_dx_cols(p.Tc, p.H), xc = (p.H + 16 * nbx - 1) / (16 * nbx), nx = small_dx_blocks(p.Tc, p.H), n = small_grads_blocks(p.Tc, p.H, p.V);
       auto kern = nbx == 4 ? small_grads_kernel<4, 1> : n <= kHotSlots ? small_grads_kernel<2, 2> : small_grads_kernel<2, 1>;
       kern<<<n + 1, kGradWaves * 64, 0, s>>>(
           SmallGrads{{q.ids_c, q.lse_c, q.c_c, &q.ctrl->n_real, p.V, p.inv_tau}, q.kept, p.Tc, X, W, q.row_map, p.H, dX, d_weight, xc, nx}, loss);

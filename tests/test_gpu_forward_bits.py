@@ -26,7 +26,7 @@ def test_f32_log_probs_do_not_depend_on_the_chunk(V, rows, tau):
 # tokens among 9000 rows take wide tiles
 @pytest.mark.parametrize("V,tiles_n", [(2048, 31), (2048, 32), (2000, 33), (2048, 64), (2048, 65), (4096, 17), (4096, 32), (3000, 22), (10240, 7)])
 def test_f32_log_probs_do_not_depend_on_how_the_tiles_fill_the_chip(V, tiles_n):
-    cfg = synth.RolloutConfig("bits", 1, 1, 1, 8, 100, V, "f32", 0.5, seed=64)
+    cfg = synth.RolloutConfig("bits", 1, 1, 1, 8, 292, V, "f32", 0.5, seed=64)
     b = synth.make_rollouts(cfg, "cuda", "packed", lengths=[9000])
     n = 16 * tiles_n - 5
     score = lambda r: binding.rl_token_logprob_tempered(b.hidden[:r], b.weight, b.token_ids[:r], b.mask[:r], 0.9, torch.tensor([0, r], dtype=torch.int32, device="cuda"))

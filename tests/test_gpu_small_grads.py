@@ -37,3 +37,10 @@ def test_no_row_counts():
     b.mask.zero_()
     r = run_gpu(b, "grpo")
     assert not r.d_hidden.any() and not r.d_weight.any() and r.loss.item() == 0.0
+
+
+# two workgroups a CU at the most, one launch; more, of a small vocabulary; more, of a larger one: the pair of contractions
+@pytest.mark.parametrize("V,rows", [(1000, 1700), (700, 2000), (1000, 2000)])
+def test_many_rows(V, rows):
+    b = synth.make_rollouts(synth.RolloutConfig("small", 2, 2, 1, 8, 4, V, "f32", 0.5, seed=93), "cuda", "packed", lengths=[rows, rows, rows - 3, rows])
+    print(compare_all(b, run_gpu(b, "grpo"), run_oracle(b, "grpo"), **F32_TOL), flush=True)

@@ -45,7 +45,7 @@ def test_the_narrow_f32_tiles_wait_for_their_loads_where_they_store_them(tmp_pat
     for f in re.split(r"\n(?=[0-9a-f]+ <)", text):
         if not re.match(r"[0-9a-f]+ <\S*(gemm_nt_kernelIf\S*ELi16ELi\d+ELi1E|gemm_nt_small_pair_kernel)", f):
             continue
-        both = re.match(r"[0-9a-f]+ <\S*EpiFwd\S*ELi256ELi16ELi4E", f)           # has a form that waits at once as well
+        both = re.match(r"[0-9a-f]+ <\S*EpiFwd\S*ELi256ELi16ELi4ELi1ELi1ELb1E", f)           # has a form that waits at once as well
         ins = [line.split("//")[0].strip() for line in f.splitlines()[1:]]
         for i, (this, following) in enumerate(zip(ins, ins[1:])):
             if this.startswith("s_waitcnt vmcnt") and re.match(r"v_mov_b32_e32 v\d+, v\d+", following):
