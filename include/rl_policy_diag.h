@@ -25,7 +25,7 @@ extern "C" {
 enum { RL_PROF_PREP = 0,       /* counts, scan, compaction, zero-fill (not in a forward) */
        RL_PROF_GEMM_FWD = 1,   /* forward logits contraction + online partial softmax   */
        RL_PROF_COMBINE = 2,    /* partials -> lse, logp (small f32 batches: in the loss)  */
-       RL_PROF_LOSS = 3,       /* per-sequence loss, final reduce; f32 batches of one chunk: W^T, X^T and zeroing too */
+       RL_PROF_LOSS = 3,       /* per-sequence loss, final reduce; f32 batches of one chunk: zeroing, and X^T and W^T where they are made, too */
        RL_PROF_TRANSPOSE = 4,  /* W^T, X^T chunks, zeroing masked dX rows               */
        RL_PROF_GEMM_DS = 5,    /* recomputed or kept logits -> dS                       */
        RL_PROF_GEMM_DX = 6,    /* dX = dS W (f32 inputs)                                */

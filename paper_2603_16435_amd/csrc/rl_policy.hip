@@ -41,7 +41,7 @@ constexpr int kBM = 256, kBN = 256;
 // kernel), or 256 x 16 where the large ones would leave CUs without work.  MFMA-bound: 128-141 TFLOP/s, 102-109 in the general kernel, whose
 // loads and addresses take a tenth of the issue slots.  Loss and gradients of 2175 tokens, H 768, V 50257, with dX cut along K and the logits
 // recomputed: 5.25 ms, 6.2 in the general kernel; with its 256 x 256 tiles 17.9 (27 dX
-// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us (28 since small batches have a backward of their own, grads_small.h), 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
+// tiles of K = 50432: 12.5).  356 tokens, H 128, V 1024: 51 us (27 since small batches have a backward of their own, grads_small.h), 557 with 256 x 256 tiles (32-wide narrow ones took 7 % longer).
 constexpr int kF32BN = 64, kF32SmallBN = 16, kF32Slots = 512;
 
 // Batches of up to this many rows contract dX with W as it is stored (K-major operand of the hot kernel) instead of a transposed copy.
@@ -1624,7 +1624,7 @@ static void run_backward(const rl_batch* b, const Plan& p, const Ptrs& q, void* 
   T* dS = static_cast<T*>(q.ds); T* dST = static_cast<T*>(q.dst);
   T* dX = static_cast<T*>(d_hidden);
   // masked rows of dX are zero; rows that count are written by the dX epilogue.  W^T [H][Vp] with zero padding columns, once per
-  // call (bf16: unless dX reads W as it is).  xt_done: both, and X^T of the only chunk, are there (loss_prep_kernel).
+  // call unless dX reads W as it is (k_major_w).  xt_done: those that are needed, and X^T of the only chunk, are there (loss_prep_kernel; a batch whose gradients come in one launch needs none).
   const dim3 gw((p.Vp + 63) / 64, (p.H + 63) / 64), gx((p.Tc + 63) / 64, (p.H + 63) / 64);
   if (!xt_done) {
     ProfScope ps(RL_PROF_TRANSPOSE, s);
