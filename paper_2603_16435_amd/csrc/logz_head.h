@@ -32,11 +32,8 @@ template <class T, int VEC> __device__ inline void logz_load(const T* p, float (
   }
 }
 
-template <class T, int VEC> struct LogzPiece { typedef uint4 type; };
-template <class T> struct LogzPiece<T, 1> { typedef T type; };
-
 // grid (P, ceil(H / (LANES VEC))): a workgroup of eight wavefronts pools LANES VEC columns of one prompt, 512 / LANES rows at a
-// time, four pieces in flight per lane (f32: eight; 8 prompts of 200 to 1100 rows, H 4096: the forward 43.1 -> 41.2 us, bf16 no better); f32 sums, merged through LDS in a fixed order.
+// time, four pieces in flight per lane (eight: no faster, f32 at H 3584 64 prompts of 40 rows 10.6 us instead of 9.9); f32 sums, merged through LDS in a fixed order.
 // (One element per lane, 64 columns per workgroup: 22 us on the shape above, 16 bytes per lane: 14 us.)
 template <int VEC> constexpr int logz_pool_lanes() { return VEC == 1 ? 64 : 16; }
 template <class T, int VEC>
@@ -57,22 +54,15 @@ __global__ __launch_bounds__(512) void logz_pool_kernel(const T* X, int64_t rows
   if (h < H) {
     const T* x = X + h;
     int64_t r = a + slice;
-    auto rows_at = [&](auto n) __attribute__((always_inline)) {
-      constexpr int N = decltype(n)::value;
-      typename LogzPiece<T, VEC>::type v[N];
+    for (; r + 3 * SLICES < b; r += 4 * SLICES) {
+      float v[4][VEC];
 #pragma unroll
-      for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const typename LogzPiece<T, VEC>::type*>(x + (r + SLICES * u) * H);
+      for (int u = 0; u < 4; ++u) logz_load<T, VEC>(x + (r + SLICES * u) * H, v[u]);
 #pragma unroll
-      for (int u = 0; u < N; ++u) {
-        float f[VEC];
-        logz_load<T, VEC>(reinterpret_cast<const T*>(&v[u]), f);
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) s[u & 3][i] += f[i];
-      }
-      r += N * SLICES;
-    };
-    if constexpr (sizeof(T) == 4) while (r + 7 * SLICES < b) rows_at(std::integral_constant<int, 8>());
-    while (r + 3 * SLICES < b) rows_at(std::integral_constant<int, 4>());
+        for (int i = 0; i < VEC; ++i) s[u][i] += v[u][i];
+    }
     for (; r < b; r += SLICES) {
       float v[VEC];
       logz_load<T, VEC>(x + r * H, v);
